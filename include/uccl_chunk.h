@@ -93,7 +93,10 @@ typedef struct uccl_extents {
  *   chunk_bytes  the transport's chunk size (the control path chooses it per connection: 32 KB by
  *                default, Section 3.3 "control coalescing"; Appendix A onChunkSize), 0 = unknown.
  *                Sets how many records a workgroup takes: about 32 KiB of payload per workgroup (calls of
- *                at most 128 records take one workgroup per record, sized to the chunk).
+ *                at most 128 records take one workgroup per record, sized to the chunk).  Calls of much payload
+ *                (records x chunk_bytes: 96 MiB for a reduction, 192 MiB or chunks of 64 KiB for a copy; chunks
+ *                of 16 KiB and more) are streamed in destination order, by two launches (see "Scratch
+ *                memory" below).
  *   parts        workgroups per record for calls of few, large records (Appendix C.4: small
  *                messages are where the kernel's fixed costs show): 0 = the library decides,
  *                1 = never cut a record, 2..16 = that many.  Honoured only when a workgroup takes
@@ -408,6 +411,9 @@ int uccl_feed_destroy(uccl_feed* feed);
  * `gather` != 0: uccl_chunk_reduce_gather, else the apply / scatter family; `reads_acc` != 0: the
  * op combines with the accumulator (anything but UCCL_COPY).  `parts` > 1 assumes that claim words
  * are to be had (see "Scratch memory"); a call that finds none is launched with parts = 1.
+ * `ordered` > 0: where scratch memory is to be had, uccl_chunk_apply_opts and uccl_chunk_scatter_opts
+ * decide the records first and stream them in destination order, in that many pairs of launches
+ * (chunk_order_kernel, chunk_ordered_kernel); the other fields say what the call is launched as otherwise.
  * UCCL_EINVAL for a NULL `plan` or options the data-path calls would refuse.  Utility, no passage
  * of the paper. */
 enum { UCCL_KERNEL_FLAT = 0, UCCL_KERNEL_FEW = 1, UCCL_KERNEL_GATHER = 2, UCCL_KERNEL_GATHER_PARTS = 3 };
@@ -418,7 +424,8 @@ typedef struct uccl_plan {
   uint32_t threads;           /* workgroup size */
   uint32_t groups;            /* workgroups in the launch */
   uint32_t unit_bytes;        /* bytes per stream a wavefront moves per trip */
-  uint32_t reserved[2];       /* 0 */
+  uint32_t ordered;           /* pairs of launches of the ordered form, 0 = not ordered */
+  uint32_t reserved;          /* 0 */
 } uccl_plan;
 int uccl_launch_plan(uint32_t n_descs, const uccl_launch_opts* opts, int gather, int reads_acc, uccl_plan* plan);
 
@@ -426,7 +433,8 @@ int uccl_launch_plan(uint32_t n_descs, const uccl_launch_opts* opts, int gather,
  * two hipEvent_t (either may be NULL) to its kernel dispatch, so that
  * hipEventElapsedTime(start, stop) is that kernel's own execution time on the device,
  * without the queueing and launch gaps an event pair recorded around the call would
- * include.  One-shot: cleared by the launch (also by a launch that fails). */
+ * include.  A call of several launches (`ordered` above) has its start on the first and its stop on the
+ * last.  One-shot: cleared by the launch (also by a launch that fails). */
 int uccl_time_next_launch(void* start_event, void* stop_event);
 
 /* Diagnostics: parts of split records that gave up waiting for their record's decision since the

@@ -36,7 +36,8 @@ class uccl_launch_opts(C.Structure):
 
 class uccl_plan(C.Structure):
     _fields_ = [("kernel", C.c_uint32), ("records_per_group", C.c_uint32), ("parts", C.c_uint32),
-                ("threads", C.c_uint32), ("groups", C.c_uint32), ("unit_bytes", C.c_uint32), ("reserved", C.c_uint32 * 2)]
+                ("threads", C.c_uint32), ("groups", C.c_uint32), ("unit_bytes", C.c_uint32),
+                ("ordered", C.c_uint32), ("reserved", C.c_uint32)]
 
 
 KERNEL_NAMES = ("chunk_flat_kernel", "chunk_few_kernel", "chunk_gather_kernel", "chunk_gather_parts_kernel")
@@ -380,9 +381,16 @@ def uccl_launch_plan(n_descs, opts=None, gather=False, reads_acc=True) -> dict:
     """What a call of ``n_descs`` records with these options is launched as (host arithmetic only)."""
     p = uccl_plan()
     _call("uccl_launch_plan", int(n_descs), _opts(opts), int(bool(gather)), int(bool(reads_acc)), C.byref(p))
-    d = {k: getattr(p, k) for k, _ in uccl_plan._fields_ if k != "reserved"}
+    d = {k: getattr(p, k) for k, _ in uccl_plan._fields_ if k not in ("ordered", "reserved")}
     d["kernel"] = KERNEL_NAMES[p.kernel]
     return d
+
+
+def uccl_launch_ordered(n_descs, opts=None, gather=False, reads_acc=True) -> int:
+    """``uccl_plan.ordered``: in how many pairs of launches the call is streamed in destination order, 0 = it is not."""
+    p = uccl_plan()
+    _call("uccl_launch_plan", int(n_descs), _opts(opts), int(bool(gather)), int(bool(reads_acc)), C.byref(p))
+    return p.ordered
 
 
 def uccl_time_next_launch(start_event, stop_event):

@@ -21,6 +21,10 @@
 // the same seq each issue their own atomic, so the hardware serialises them and exactly one
 // sees the bit clear.
 //
+// Calls of much payload are bound by how well the memory system takes their mix of reads and
+// writes, which depends on the order of the accesses: they decide all sequence numbers in a small
+// launch of its own and stream the winners in destination order in a second one.
+//
 // Calls of few records (Appendix C.4: small messages are where fixed costs show) take another
 // kernel, which shortens the chain of latencies instead: one record per workgroup, payload
 // loads issued before the sequence number is decided, and, when the records alone would leave
@@ -71,22 +75,28 @@ int launch_failed(hipError_t e) {
 // reading it would clear the caller's).  The one-shot timing events, if any, are attached to
 // this very dispatch.
 template <class... Params, size_t... I>
-hipError_t launch_raw(void (*kernel)(Params...), dim3 grid, dim3 block, hipStream_t s,
+hipError_t launch_raw(void (*kernel)(Params...), dim3 grid, dim3 block, uint32_t lds, hipStream_t s,
                       std::tuple<Params...>& params, std::index_sequence<I...>) {
   void* ptrs[] = {static_cast<void*>(&std::get<I>(params))...};
   hipEvent_t t0 = t_start, t1 = t_stop;
   t_start = t_stop = nullptr;
   if (t0 != nullptr || t1 != nullptr)
-    return hipExtLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, ptrs, 0, s, t0, t1, 0);
-  return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, ptrs, 0, s);
+    return hipExtLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, ptrs, lds, s, t0, t1, 0);
+  return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, ptrs, lds, s);
+}
+
+// `lds`: dynamic LDS per workgroup.
+template <class... Params, class... KernelArgs>
+int launch_kernel_lds(void (*kernel)(Params...), uint32_t tiles, uint32_t threads, uint32_t lds, hipStream_t s, KernelArgs... a) {
+  static_assert(sizeof...(Params) == sizeof...(KernelArgs), "one argument per kernel parameter");
+  std::tuple<Params...> params(static_cast<Params>(a)...);  // objects of the kernel's own parameter types
+  const hipError_t e = launch_raw(kernel, dim3(tiles), dim3(threads), lds, s, params, std::index_sequence_for<Params...>{});
+  return e == hipSuccess ? UCCL_OK : launch_failed(e);
 }
 
 template <class... Params, class... KernelArgs>
 int launch_kernel(void (*kernel)(Params...), uint32_t tiles, uint32_t threads, hipStream_t s, KernelArgs... a) {
-  static_assert(sizeof...(Params) == sizeof...(KernelArgs), "one argument per kernel parameter");
-  std::tuple<Params...> params(static_cast<Params>(a)...);  // objects of the kernel's own parameter types
-  const hipError_t e = launch_raw(kernel, dim3(tiles), dim3(threads), s, params, std::index_sequence_for<Params...>{});
-  return e == hipSuccess ? UCCL_OK : launch_failed(e);
+  return launch_kernel_lds(kernel, tiles, threads, 0u, s, a...);
 }
 
 uint32_t tiles_for(uint32_t n_descs, uint32_t tile) {
@@ -210,6 +220,7 @@ struct Tuning {
   uint32_t chunk_bytes;
   uint32_t parts;
   unsigned long long* static_claims = nullptr;
+  bool host_records = false;  // the records are in host memory: read them as seldom as possible
 };
 
 template <int T, int U, class Op>
@@ -300,6 +311,33 @@ struct Plan {
   uint32_t tile, parts, threads, unroll;
 };
 
+// Calls of much payload decide all sequence numbers first and stream the winners in destination order
+// (chunk_order_kernel, chunk_ordered_kernel).  The extra launch costs about 5 us, the order gains more the
+// more streams the call has and the larger its chunks are.  Measured on the two kinds of board of this
+// machine (the second mixes reads and writes better), us, this form / the other; ring steps, bf16, the
+// reduce phase ordered alone: 56 MiB of payload in 32 KiB chunks 73.0 / 70.2 (second kind); 112 MiB 134 / 139
+// and 132 / 135; 168 MiB in 16 KiB chunks 194 / 204 and 195 / 191, in 128 KiB chunks 198 / 225 and 194 / 203;
+// 896 MiB in 128 KiB chunks 563 / 689; 224 MiB in 9 KB chunks 279 / 265 (second kind).  The copy phase too, against
+// the reduce phase alone: 112 MiB in 32 KiB chunks 136 / 134 and 134 / 132, 168 MiB in 128 KiB chunks 191 / 198
+// and 191 / 194, 240 MiB in 32 KiB chunks 268 / 270, 224 MiB in 20 KB chunks 258 / 261 and 252 / 260.
+// Returns the number of launches of each kernel (the table holds kOrderRecords entries; more records are
+// taken in equal shares, each of which has to be worth it), 0 = not this form.  Needs a claim region and
+// records in device memory; a stated number of parts asks for the other form.
+constexpr uint32_t kOrderRecords = kRegionRecords * UCCL_CLAIM_STRIDE / 2 - 1;   // two words each, and the spill count
+static_assert(kOrderRecords <= 0xFFFFu, "a table entry has 16 bits for the record");
+constexpr uint32_t kOrderChunk = 16u << 10;
+constexpr uint64_t kOrderBytes = 96ull << 20;
+constexpr uint32_t kOrderCopyChunk = 64u << 10;        // copies: chunks of this size from kOrderBytes on,
+constexpr uint64_t kOrderCopyBytes = 192ull << 20;     // smaller ones from here on
+constexpr uint32_t kOrderMaxParts = 64;   // longer records are walked: keeps the grid far below a launch's limit
+
+uint32_t ordered_launches(uint32_t n_descs, const Tuning& tune, bool reads_acc) {
+  if (tune.parts != 0u || tune.chunk_bytes < kOrderChunk || n_descs == 0u) return 0u;
+  const uint32_t launches = (n_descs - 1u) / kOrderRecords + 1u;
+  const uint64_t least = reads_acc || tune.chunk_bytes >= kOrderCopyChunk ? kOrderBytes : kOrderCopyBytes;
+  return static_cast<uint64_t>(n_descs / launches) * tune.chunk_bytes >= least ? launches : 0u;
+}
+
 Plan plan_apply(uint32_t n_descs, const Tuning& tune, bool reads_acc) {
   const uint32_t t = flat_tile(n_descs, tune.chunk_bytes);
   if (t >= 2 && tune.chunk_bytes > 8192u && n_descs < kHalfTileRecords) return {kRouteHalf, 1u, 1u, 1024u, 1u};
@@ -320,8 +358,46 @@ Plan plan_apply(uint32_t n_descs, const Tuning& tune, bool reads_acc) {
   return {kRouteOne, 1u, 1u, UCCL_FLAT_THREADS, unroll};
 }
 
+// `region`: the stream's claim words; called with the pool's launch lock held.  HIP has no reason of its
+// own to refuse a later launch of a call after it took the first: all are in one code object and their
+// grids stay within 16383 * 64 workgroups of 256 threads.  The timing events span the whole call.
+template <class Op>
+int launch_ordered(Args a, hipStream_t s, const Tuning& tune, uint32_t launches, unsigned long long* region) {
+  const hipEvent_t begin = t_start, end = t_stop;
+  const uint32_t n = a.n_descs, parts = (tune.chunk_bytes - 1u) / kOrderPartBytes + 1u;
+  const uccl_chunk_desc* const descs = a.descs;
+  a.parts = parts < kOrderMaxParts ? parts : kOrderMaxParts;
+  int rc = UCCL_OK;
+  for (uint32_t i = 0; i < launches && rc == UCCL_OK; ++i) {
+    const uint32_t from = static_cast<uint32_t>(static_cast<uint64_t>(n) * i / launches);
+    a.descs = descs + from;
+    a.n_descs = static_cast<uint32_t>(static_cast<uint64_t>(n) * (i + 1u) / launches) - from;
+    OrderArgs t;
+    t.words = region;
+    t.spilled = region + kRegionWords - 1u;
+    t.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
+    t_start = i == 0u ? begin : nullptr;
+    t_stop = nullptr;
+    rc = launch_kernel(chunk_order_kernel<Op::kEs>, (a.n_descs + 255u) / 256u, 256, s, a, t);
+    if (rc != UCCL_OK) break;
+    t_stop = i + 1u == launches ? end : nullptr;
+    rc = launch_kernel_lds(chunk_ordered_kernel<Op>, a.n_descs * a.parts, kOrderThreads, Op::kReadsAcc ? kOrderReduceLds : 0u, s, a, t);
+  }
+  t_start = t_stop = nullptr;
+  return rc;
+}
+
 template <class Op>
 int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
+  const uint32_t ordered = a.n_ptr == nullptr && tune.static_claims == nullptr && !tune.host_records ? ordered_launches(a.n_descs, tune, Op::kReadsAcc) : 0u;
+  if (ordered != 0u) {
+    ClaimPool* pool = nullptr;
+    unsigned long long* const region = claim_region(s, &a.faults, &pool);
+    if (region != nullptr) {
+      std::lock_guard<std::mutex> in_order(pool->launch_lock);
+      return launch_ordered<Op>(a, s, tune, ordered, region);
+    }
+  }
   Plan p = plan_apply(a.n_descs, tune, Op::kReadsAcc);
   if (p.route == kRouteParts) {
     if (tune.static_claims != nullptr) {
@@ -563,15 +639,16 @@ int feed_flush(uccl_feed* f) {
     // workgroup, no copy to enqueue); a large one is copied to device memory first, so that
     // thousands of workgroups do not each wait on the host bus.
     const uccl_chunk_desc* records = sl.host[l];
+    Tuning tune{sl.max_len[l], 0u, nullptr, true};
     if (sl.count[l] > UCCL_FEED_DIRECT_RECORDS) {
       const hipError_t e = hipMemcpyAsync(sl.dev[l], sl.host[l], sizeof(uccl_chunk_desc) * sl.count[l],
                                           hipMemcpyHostToDevice, f->stream);
       if (e != hipSuccess) return launch_failed(e);
       records = sl.dev[l];
+      tune.host_records = false;
     }
     const int rc = apply_common(f->acc, f->out_stage, f->recv_stage, records, sl.count[l], f->bitmap,
-                                f->dtype, f->op[l], true, nullptr, nullptr, Tuning{sl.max_len[l], 0u, nullptr},
-                                f->stream);
+                                f->dtype, f->op[l], true, nullptr, nullptr, tune, f->stream);
     if (rc != UCCL_OK) return rc;
   }
   const hipError_t e = hipEventRecord(sl.done, f->stream);
@@ -960,7 +1037,8 @@ int uccl_launch_plan(uint32_t n_descs, const uccl_launch_opts* opts, int gather,
   plan->unit_bytes = 64u * 16u * p.unroll;
   const uint64_t groups = p.route == kRouteTile ? tiles_for(n_descs, p.tile) : static_cast<uint64_t>(n_descs) * p.parts;
   plan->groups = static_cast<uint32_t>(groups);
-  plan->reserved[0] = plan->reserved[1] = 0u;
+  plan->ordered = gather ? 0u : ordered_launches(n_descs, tune, reads_acc != 0);
+  plan->reserved = 0u;
   return UCCL_OK;
 }
 

@@ -76,17 +76,17 @@ struct Args {
 // per record, and the record's units are dealt over the wavefronts of all of them.  The sequence
 // number must still be decided exactly once, by one atomic OR on the bitmap, and every part that
 // has units must learn the outcome.  Record k of the call has a 64-bit claim word in scratch
-// memory, holding `tag * 4 + state`: the tag of the last call that used the word, and 0 = a part
+// memory, holding `tag << 16 | state`: the tag of the last call that used the word, and 0 = a part
 // is deciding, 1 = applied, 2 = not applied.
 //
-//   enter    every part issues one atomic max of `tag * 4` on the word, after the payload loads of
+//   enter    every part issues one atomic max of `tag << 16` on the word, after the payload loads of
 //            its first unit (memory operations return in order, so entering earlier would hold up
 //            the record itself).  Tags grow from call to call in the order the calls run (the host
 //            draws the tag and enqueues the launch under one lock, and calls that share a word run
 //            on one stream), so exactly one part of the call -- the first to get there -- finds an
 //            older tag in the word: it decides.
 //   decide   the deciding part issues the bitmap atomic (or rejects the record) and stores
-//            `tag * 4 + outcome`.  It waits for nothing.
+//            `tag << 16 | outcome`.  It waits for nothing.
 //   await    the other parts poll the word until it carries the call's tag and an outcome.
 //
 // A part only ever waits for a part that is already running and never waits itself, so the wait
@@ -96,23 +96,25 @@ struct Args {
 // each record's word has a 128-byte line to itself (UCCL_CLAIM_STRIDE), because device-scope atomics
 // on one line are served one after the other and a call's parts all arrive at about the same time
 // (57 records x 8 parts: 6.2 us per call with the words packed, 5.4 us with a line each).
-// Nothing is ever cleared between calls: a stale word is recognised by its older tag.
+// Nothing is ever cleared between calls: a stale word is recognised by its older tag.  The order table
+// of large calls (below) lives in the same words and carries its tag in the same bits, so either kind
+// of call finds the other's leftovers stale.
 __device__ __forceinline__ unsigned long long claim_enter(unsigned long long* claim, unsigned long long tag) {
-  return __hip_atomic_fetch_max(claim, tag << 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_fetch_max(claim, tag << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ bool claim_decides(unsigned long long entered, unsigned long long tag) {
-  return (entered >> 2) < tag;
+  return (entered >> 16) < tag;
 }
 
 __device__ __forceinline__ void claim_publish(unsigned long long* claim, unsigned long long tag, bool win) {
-  __hip_atomic_store(claim, (tag << 2) | (win ? 1ull : 2ull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(claim, (tag << 16) | (win ? 1ull : 2ull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // `seen`: what this part's claim_enter returned (the outcome may already be in it).
 __device__ __forceinline__ bool claim_await(unsigned long long* claim, unsigned long long seen,
                                             unsigned long long tag, uint32_t* faults) {
-  for (uint32_t polls = 0; (seen >> 2) != tag || (seen & 3ull) == 0ull; ++polls) {
+  for (uint32_t polls = 0; (seen >> 16) != tag || (seen & 3ull) == 0ull; ++polls) {
     if (polls >= UCCL_CLAIM_SPIN_LIMIT) {
       atomicAdd(faults, 1u);
       return false;
@@ -152,12 +154,12 @@ __device__ __forceinline__ void stream_tail(const char* r, char* a, char* o, uin
 
 // What a record must satisfy before its bit is touched (the unchecked entry points pass
 // unbounded extents, which leaves alignment, granularity and the forward rules).
-template <class Op>
+template <uint32_t kEs>
 __device__ __forceinline__ bool record_ok(const Args& g, uint64_t src, uint64_t dst, uint64_t out,
                                           uint32_t len, uint32_t seq) {
   const bool fwd = out != UCCL_NO_FORWARD;
   const uint64_t out_at = out & ~UCCL_FORWARD_ONLY;
-  bool ok = seq < g.ext.n_bits && ((src | dst) & 15u) == 0 && len % Op::kEs == 0 &&
+  bool ok = seq < g.ext.n_bits && ((src | dst) & 15u) == 0 && len % kEs == 0 &&
             src <= g.ext.recv_bytes && len <= g.ext.recv_bytes - src &&
             dst <= g.ext.acc_bytes && len <= g.ext.acc_bytes - dst;
   if (fwd)
@@ -195,7 +197,7 @@ __device__ __forceinline__ void dedup_tile(const Args& g, Tile<T>& s, uint32_t t
     out = hi.x | (static_cast<uint64_t>(hi.y) << 32);
     len = hi.z;
     const uint32_t seq = hi.w;
-    const bool ok = record_ok<Op>(g, src, dst, out, len, seq);
+    const bool ok = record_ok<Op::kEs>(g, src, dst, out, len, seq);
     if (k >= live) {
       // beyond the published count: not a record at all, neither applied nor rejected
     } else if (ok) {
@@ -325,6 +327,99 @@ __global__ void __launch_bounds__(NT) chunk_flat_kernel(const Args g) {
   }
 }
 
+// ---- large calls: decide first, then stream in destination order ------------------------------
+//
+// What bounds a call of hundreds of MiB is how well the memory system takes its mix of reads and
+// writes, and that depends on the order of the accesses.  Arrival order scatters two of the four
+// streams (accumulator and staging) over the reorder window.  Measured with dense kernels of two reads
+// and two writes, 240 MiB per stream: destinations scattered in 32 KiB blocks 5.4 TB/s, in order 5.8;
+// in order, one 4 KiB block per 256-thread workgroup, at most 24 wavefronts per compute unit, 6.3; the
+// read of the slots scattered instead of the destinations, 6.3 as well.  So such a call is two launches:
+//
+//   order    one lane per record validates it, decides its sequence number with one atomic OR and, if it
+//            is a first arrival, leaves its index in entry seq mod n of a table in scratch memory (an
+//            atomic exchange; n = records of the launch).  Sequence numbers ascend with the destination
+//            in a collective's stream and a call covers about one run of them, so the table lists the
+//            winners in destination order.  Two winners of one entry (sequence numbers that are no run)
+//            are both served: the one that was there goes to the spill list, in any order.
+//   stream   workgroup b takes 4 KiB part b mod `parts` of the record in entry b / parts: no atomic, no
+//            barrier, no LDS.  Consecutive workgroups run on different XCDs; runs of kOrderRun of them
+//            (128 KiB) are laid out so that each XCD works on one contiguous piece (1 GiB reduce-scatter
+//            590 us without, 562 us with it; 64 KiB 566, 256 KiB 565, 512 KiB 570).  A launch that
+//            combines is held to six workgroups per compute unit by asking for 24 KiB of LDS that it does
+//            not use (562 us; eight 609, seven 591, five 591); copies are not (the 256 MiB bf16 step: 269 us
+//            either way; five 283).
+//
+// Words of the table and the spill list carry the call's tag as claim words do, so nothing is cleared.
+// Entry i of the table is word 2 i and entry i of the spill list word 2 i + 1: one load serves both.
+constexpr uint32_t kOrderThreads = 256;            // 4 KiB per stream: one vector per lane
+constexpr uint32_t kOrderPartBytes = kOrderThreads * 16u;
+constexpr uint32_t kOrderRun = 32;
+constexpr uint32_t kOrderReduceLds = 24576;
+
+struct OrderArgs {
+  unsigned long long* words;    // 2 * n_descs words: tag << 16 | record
+  unsigned long long* spilled;  // tag << 16 | length of the spill list
+  unsigned long long tag;
+};
+
+template <uint32_t kEs>
+__global__ void __launch_bounds__(256) chunk_order_kernel(const Args g, const OrderArgs t) {
+  const uint32_t k = blockIdx.x * 256u + threadIdx.x;
+  if (k >= g.n_descs) return;
+  const u32x4* p = reinterpret_cast<const u32x4*>(g.descs + k);
+  const u32x4 lo = p[0], hi = p[1];
+  const uint64_t src = lo.x | (static_cast<uint64_t>(lo.y) << 32);
+  const uint64_t dst = lo.z | (static_cast<uint64_t>(lo.w) << 32);
+  const uint64_t out = hi.x | (static_cast<uint64_t>(hi.y) << 32);
+  const uint32_t seq = hi.w;
+  if (!record_ok<kEs>(g, src, dst, out, hi.z, seq)) {
+    if (g.rejected != nullptr) atomicAdd(g.rejected, 1u);
+    return;
+  }
+  const uint32_t bit = 1u << (seq & 31u);
+  if ((atomicOr(g.bitmap + (seq >> 5), bit) & bit) != 0u) return;
+  const unsigned long long was = __hip_atomic_exchange(t.words + 2u * static_cast<size_t>(seq % g.n_descs), (t.tag << 16) | k,
+                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if ((was >> 16) == t.tag) {
+    // the count starts at this call's tag whichever lane gets there first: an older call's is smaller
+    __hip_atomic_fetch_max(t.spilled, t.tag << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long at = __hip_atomic_fetch_add(t.spilled, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xFFFFu;
+    t.words[2u * at + 1u] = was;   // at < winners <= n_descs
+  }
+}
+
+// Part `part` of record k: units part * 4 + wavefront, then every parts * 4 units (a record longer than
+// the stated chunk size).
+template <class Op>
+__device__ __forceinline__ void ordered_part(const Args& g, uint32_t k, uint32_t part) {
+  constexpr uint32_t kUnit = 64u, kWaves = kOrderThreads / 64;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+  const uccl_chunk_desc d = g.descs[k];   // the same address in every lane
+  const uint32_t vecs = (d.len >> 4) + ((d.len & 15u) != 0u ? 1u : 0u);
+  const uint32_t total = (vecs + kUnit - 1u) / kUnit;
+  for (uint32_t u = part * kWaves + wave; u < total; u += g.parts * kWaves) {
+    if (d.out_off == UCCL_NO_FORWARD)
+      stream_unit<1, Op, false, true>(g.recv + d.src_off, g.acc + d.dst_off, nullptr, d.len, u, lane);
+    else if (d.out_off & UCCL_FORWARD_ONLY)
+      stream_unit<1, Op, true, false>(g.recv + d.src_off, g.acc + d.dst_off, g.out + (d.out_off & ~UCCL_FORWARD_ONLY), d.len, u, lane);
+    else
+      stream_unit<1, Op, true, true>(g.recv + d.src_off, g.acc + d.dst_off, g.out + d.out_off, d.len, u, lane);
+  }
+}
+
+template <class Op>
+__global__ void __launch_bounds__(kOrderThreads) chunk_ordered_kernel(const Args g, const OrderArgs t) {
+  uint32_t b = blockIdx.x;   // the launch has n_descs * parts workgroups; workgroup b runs on XCD b mod 8
+  const uint32_t group = b / (8u * kOrderRun), in = b % (8u * kOrderRun);
+  if ((group + 1u) * (8u * kOrderRun) <= gridDim.x) b = group * (8u * kOrderRun) + (in & 7u) * kOrderRun + (in >> 3);
+  const uint32_t entry = b / g.parts, part = b % g.parts;
+  const unsigned long long first = t.words[2u * static_cast<size_t>(entry)];
+  const unsigned long long spill = t.words[2u * static_cast<size_t>(entry) + 1u];
+  if ((first >> 16) == t.tag) ordered_part<Op>(g, static_cast<uint32_t>(first & 0xFFFFu), part);
+  if ((spill >> 16) == t.tag) ordered_part<Op>(g, static_cast<uint32_t>(spill & 0xFFFFu), part);
+}
+
 // ---- calls of few records --------------------------------------------------------------------
 //
 // A call of a few dozen records (a 4 MiB message in 64 KiB chunks is 57 of them per phase) cannot
@@ -373,7 +468,7 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
   const uint32_t len = __builtin_amdgcn_readfirstlane(hi.z);
   const uint32_t seq = __builtin_amdgcn_readfirstlane(hi.w);
   const bool is_record = k < live;
-  const bool ok = is_record && record_ok<Op>(g, src, dst, out, len, seq);
+  const bool ok = is_record && record_ok<Op::kEs>(g, src, dst, out, len, seq);
 
   const uint32_t nvec = len >> 4;
   const uint32_t vecs = nvec + ((len & 15u) != 0u ? 1u : 0u);

@@ -1,0 +1,125 @@
+"""Calls that are streamed in destination order (chunk_order_kernel, chunk_ordered_kernel): the rule that
+picks them (CPU), and parity at the edges of the table, its spill list, parts and launches (GPU).  The rule
+looks at the stated chunk size alone, and results never depend on it, so small records with a large stated
+size reach every branch."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2504_17307_amd as pkg
+from randstream import random_stream
+from synth.layout import DESC, NO_FORWARD, F32, BF16, F16, I32, SUM, MAX, MIN, COPY, PROD
+
+MiB = 1 << 20
+TABLE = 16383  # records one launch orders
+
+
+def test_rule():
+    ordered = pkg.uccl_launch_ordered
+    KiB = 1024
+    copy = lambda n, c: ordered(n, (c, 0), reads_acc=False)
+    assert ordered(3072, (32 * KiB, 0)) == 1 and ordered(3071, (32 * KiB, 0)) == 0       # from 96 MiB of payload on
+    assert ordered(8963, (128 * KiB, 0)) == 1 and ordered(1, (96 * MiB, 0)) == 1
+    assert ordered(TABLE, (16 * KiB, 0)) == 1 and ordered(TABLE, (16 * KiB - 16, 0)) == 0  # chunks of 16 KiB and more
+    assert ordered(TABLE + 1, (32 * KiB, 0)) == 2 and ordered(TABLE + 1, (16 * KiB, 0)) == 2   # equal shares of a longer call
+    assert copy(TABLE, 16 * KiB) == 1 and copy(TABLE + 1, 16 * KiB) == 0                 # whose shares have to be worth it
+    assert copy(6144, 32 * KiB) == 1 and copy(6143, 32 * KiB) == 0 and copy(1536, 64 * KiB) == 1 and copy(1535, 64 * KiB) == 0
+    assert ordered(1 << 20, None) == 0 and ordered(1 << 20, (32 * KiB, 1)) == 0           # no size given; parts stated
+    assert ordered(0, (32 * KiB, 0)) == 0 and ordered(2 ** 32 - 1, (32 * KiB, 0)) == -(-(2 ** 32 - 1) // TABLE)
+    assert ordered(8963, (128 * KiB, 0), gather=True) == 0
+
+
+def run(w, opts, streams=1):
+    import torch
+    from gpuhelp import to_dev
+    acc, recv, descs = to_dev(w["acc"]), to_dev(w["recv"]), to_dev(w["descs"])
+    out = torch.full((max(w["out_bytes"], 16),), 0xA5, dtype=torch.uint8, device="cuda")
+    bitmap = torch.zeros((w["n_bits"] + 31) // 32, dtype=torch.int32, device="cuda")
+    rejected = torch.zeros(1, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    for s in [torch.cuda.Stream() for _ in range(streams)]:
+        pkg.uccl_chunk_apply_opts(acc, out, recv, descs, len(w["descs"]), bitmap, w["dtype"], w["op"], n_rejected=rejected,
+                                  n_bits=w["n_bits"], opts=opts, stream=s)
+    torch.cuda.synchronize()
+    return [t.cpu().numpy() for t in (acc, out, bitmap, rejected)]
+
+
+def check(w, opts, rejected=0, streams=1):
+    """The ordered form against the oracle, and against the form it replaces, over the same records."""
+    assert pkg.uccl_launch_ordered(len(w["descs"]), opts, reads_acc=w["op"] != COPY) > 0 and pkg.uccl_launch_ordered(len(w["descs"]), (opts[0], 1)) == 0
+    acc, out, seen = w["acc"].copy(), np.full(max(w["out_bytes"], 16), 0xA5, dtype=np.uint8), oracle.new_seen(w["n_bits"])
+    good = w["descs"][w["descs"]["seq"] < w["n_bits"]]
+    oracle.apply(acc, out, w["recv"], good, seen, w["dtype"], w["op"])
+    exp = [acc.view(np.uint8), out, oracle.pack_bitmap(seen).view(np.int32), np.array([rejected * streams], dtype=np.int32)]
+    for how in (opts, (opts[0], 1)):
+        for name, g, e in zip(("acc", "out", "bitmap", "rejected"), run(w, how, streams), exp):
+            assert np.array_equal(g, e), (name, how)
+
+
+def hint_for(n):
+    """A stated chunk size with which a call of n records is ordered."""
+    launches = -(-n // TABLE)
+    return max(16384, -(-192 * MiB // (n // launches)) + 15 & ~15)
+
+
+# how the sequence numbers meet the table: one run; all of them in one entry (the rest spills); a few per entry
+SPREAD = {"run": lambda n, seq: seq, "one entry": lambda n, seq: seq * n, "pairs": lambda n, seq: (seq // 2) + (seq % 2) * (3 * n)}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("spread", sorted(SPREAD))
+@pytest.mark.parametrize("dtype,op", [(F32, SUM), (BF16, SUM), (F16, MAX), (I32, PROD), (F32, MIN), (BF16, COPY), (F32, COPY)])
+def test_random_streams(gpu_lib, spread, dtype, op):
+    for seed in range(6):
+        w = random_stream(700 + seed, dtype, op, max_chunks=(1, 2, 40, 200, 300, 90)[seed], max_len=(5000, 300, 9000, 5000, 64, 20000)[seed])
+        n = len(w["descs"])
+        w["descs"]["seq"] = SPREAD[spread](n, w["descs"]["seq"])
+        w["n_bits"] = int(w["descs"]["seq"].max()) + 1
+        print(spread, dtype, op, seed, n, flush=True)
+        check(w, (hint_for(n), 0), streams=1 + seed % 2)   # the second stream finds every bit set, or takes its share
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [TABLE - 1, TABLE, TABLE + 1, 2 * TABLE + 1, 40001])
+def test_table_and_launch_edges(gpu_lib, n):
+    """Calls around one and two launches' worth of records, in shuffled order with repeats and some
+    out-of-range sequence numbers; records of 0..48 bytes, and a few that are longer than all parts of one."""
+    g = np.random.default_rng(n)
+    unique = n - n // 16
+    seq = np.concatenate([np.arange(unique), g.integers(0, unique, n - unique)])[g.permutation(n)]
+    d = np.zeros(n, dtype=DESC)
+    lens = g.integers(0, 13, unique) * 4
+    lens[g.integers(0, unique, 3)] = 64 * 4096 + 20
+    pitch = (lens + 15) // 16 * 16
+    at = np.concatenate([[0], np.cumsum(pitch)])
+    d["src_off"], d["dst_off"], d["out_off"], d["len"], d["seq"] = at[seq], at[seq], at[seq], lens[seq], seq
+    d["out_off"][seq % 3 == 0] = NO_FORWARD
+    bad = g.random(n) < 0.01
+    d["seq"][bad] = unique + 7
+    total = int(at[-1])
+    w = dict(descs=d, recv=g.random(total // 4, dtype=np.float32), acc=g.random(total // 4, dtype=np.float32), out_bytes=total,
+             n_bits=unique, dtype=F32, op=SUM)
+    print(n, flush=True)
+    check(w, (hint_for(n), 0), rejected=int(bad.sum()))
+
+
+@pytest.mark.gpu
+def test_calls_in_turn_share_a_region(gpu_lib):
+    """Ordered calls and calls cut into parts in turn on one stream: they share its scratch words, and each
+    recognises what the other left there as stale."""
+    import torch
+    from gpuhelp import to_dev
+    s = torch.cuda.Stream()
+    for k in range(8):
+        w = random_stream(900 + k, F32, SUM, max_chunks=60, max_len=9000)
+        n = len(w["descs"])
+        acc, recv, descs = to_dev(w["acc"]), to_dev(w["recv"]), to_dev(w["descs"])
+        out = torch.zeros(w["out_bytes"], dtype=torch.uint8, device="cuda")
+        bitmap = torch.zeros((w["n_bits"] + 31) // 32, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        pkg.uccl_chunk_apply_opts(acc, out, recv, descs, n, bitmap, F32, SUM, opts=(hint_for(n), 0) if k % 2 else (65536, 8), stream=s)
+        s.synchronize()
+        e, o, seen = w["acc"].copy(), np.zeros(w["out_bytes"], dtype=np.uint8), oracle.new_seen(w["n_bits"])
+        oracle.apply(e, o, w["recv"], w["descs"], seen, F32, SUM)
+        assert np.array_equal(acc.cpu().numpy(), e.view(np.uint8)) and np.array_equal(out.cpu().numpy(), o), k
+    assert pkg.uccl_claim_timeouts() == 0
