@@ -236,7 +236,8 @@ int uccl_chunk_apply_indirect(void* acc, void* out_stage, const void* recv_stage
  * `seq` dedups the record as a whole: the control path issues it when all its sources are
  * in, and may issue it again.  `extents` / `n_rejected` as in uccl_chunk_apply_checked, both
  * may be NULL; `opts` may be NULL.  A call of few records of 32 KiB or more is cut into parts like
- * uccl_chunk_apply's (same claim pool, same fallback under graph capture).  Records: 160 bytes, 16-byte
+ * uccl_chunk_apply's, one of much payload is streamed in destination order (same claim pool, same
+ * fallback under graph capture).  Records: 160 bytes, 16-byte
  * aligned array.
  */
 #define UCCL_MAX_SOURCES 16
@@ -411,9 +412,9 @@ int uccl_feed_destroy(uccl_feed* feed);
  * `gather` != 0: uccl_chunk_reduce_gather, else the apply / scatter family; `reads_acc` != 0: the
  * op combines with the accumulator (anything but UCCL_COPY).  `parts` > 1 assumes that claim words
  * are to be had (see "Scratch memory"); a call that finds none is launched with parts = 1.
- * `ordered` > 0: where scratch memory is to be had, uccl_chunk_apply_opts and uccl_chunk_scatter_opts
- * decide the records first and stream them in destination order, in that many pairs of launches
- * (chunk_order_kernel, chunk_ordered_kernel); the other fields say what the call is launched as otherwise.
+ * `ordered` > 0: where scratch memory is to be had, uccl_chunk_apply_opts, uccl_chunk_scatter_opts and
+ * uccl_chunk_reduce_gather decide the records first and stream them in destination order, in that many
+ * pairs of launches (chunk_order_kernel and chunk_ordered_kernel, or their gather_ forms); the other fields say what the call is launched as otherwise.
  * UCCL_EINVAL for a NULL `plan` or options the data-path calls would refuse.  Utility, no passage
  * of the paper. */
 enum { UCCL_KERNEL_FLAT = 0, UCCL_KERNEL_FEW = 1, UCCL_KERNEL_GATHER = 2, UCCL_KERNEL_GATHER_PARTS = 3 };

@@ -320,6 +320,8 @@ struct Plan {
 // 896 MiB in 128 KiB chunks 563 / 689; 224 MiB in 9 KB chunks 279 / 265 (second kind).  The copy phase too, against
 // the reduce phase alone: 112 MiB in 32 KiB chunks 136 / 134 and 134 / 132, 168 MiB in 128 KiB chunks 191 / 198
 // and 191 / 194, 240 MiB in 32 KiB chunks 268 / 270, 224 MiB in 20 KB chunks 258 / 261 and 252 / 260.
+// Several sources per record (how many, the host does not know), 128 KiB chunks: 48 MiB of destination from one
+// source 35.3 / 32.4, from seven 82.7 / 90.0; 96 MiB 64.1 / 65.7 and 164 / 197; in 32 KiB chunks 66.0 / 69.8 and 172 / 190.
 // Returns the number of launches of each kernel (the table holds kOrderRecords entries; more records are
 // taken in equal shares, each of which has to be worth it), 0 = not this form.  Needs a claim region and
 // records in device memory; a stated number of parts asks for the other form.
@@ -361,11 +363,12 @@ Plan plan_apply(uint32_t n_descs, const Tuning& tune, bool reads_acc) {
 // `region`: the stream's claim words; called with the pool's launch lock held.  HIP has no reason of its
 // own to refuse a later launch of a call after it took the first: all are in one code object and their
 // grids stay within 16383 * 64 workgroups of 256 threads.  The timing events span the whole call.
-template <class Op>
-int launch_ordered(Args a, hipStream_t s, const Tuning& tune, uint32_t launches, unsigned long long* region) {
+template <class KernelArgs>
+int launch_ordered(void (*order)(KernelArgs, OrderArgs), void (*stream)(KernelArgs, OrderArgs), uint32_t lds, KernelArgs a, hipStream_t s,
+                   const Tuning& tune, uint32_t launches, unsigned long long* region) {
   const hipEvent_t begin = t_start, end = t_stop;
   const uint32_t n = a.n_descs, parts = (tune.chunk_bytes - 1u) / kOrderPartBytes + 1u;
-  const uccl_chunk_desc* const descs = a.descs;
+  const auto* const descs = a.descs;
   a.parts = parts < kOrderMaxParts ? parts : kOrderMaxParts;
   int rc = UCCL_OK;
   for (uint32_t i = 0; i < launches && rc == UCCL_OK; ++i) {
@@ -378,10 +381,10 @@ int launch_ordered(Args a, hipStream_t s, const Tuning& tune, uint32_t launches,
     t.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
     t_start = i == 0u ? begin : nullptr;
     t_stop = nullptr;
-    rc = launch_kernel(chunk_order_kernel<Op::kEs>, (a.n_descs + 255u) / 256u, 256, s, a, t);
+    rc = launch_kernel(order, (a.n_descs + 255u) / 256u, 256, s, a, t);
     if (rc != UCCL_OK) break;
     t_stop = i + 1u == launches ? end : nullptr;
-    rc = launch_kernel_lds(chunk_ordered_kernel<Op>, a.n_descs * a.parts, kOrderThreads, Op::kReadsAcc ? kOrderReduceLds : 0u, s, a, t);
+    rc = launch_kernel_lds(stream, a.n_descs * a.parts, kOrderThreads, lds, s, a, t);
   }
   t_start = t_stop = nullptr;
   return rc;
@@ -395,7 +398,8 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
     unsigned long long* const region = claim_region(s, &a.faults, &pool);
     if (region != nullptr) {
       std::lock_guard<std::mutex> in_order(pool->launch_lock);
-      return launch_ordered<Op>(a, s, tune, ordered, region);
+      return launch_ordered<Args>(chunk_order_kernel<Op::kEs>, chunk_ordered_kernel<Op>, Op::kReadsAcc ? kOrderReduceLds : 0u, a, s, tune,
+                                  ordered, region);
     }
   }
   Plan p = plan_apply(a.n_descs, tune, Op::kReadsAcc);
@@ -478,6 +482,15 @@ Plan plan_gather(uint32_t n_descs, const Tuning& tune) {
 
 template <class Op>
 int launch_gather_tile(GatherArgs& a, hipStream_t s, const Tuning& tune) {
+  const uint32_t ordered = ordered_launches(a.n_descs, tune, true);
+  if (ordered != 0u) {
+    ClaimPool* pool = nullptr;
+    unsigned long long* const region = claim_region(s, &a.faults, &pool);
+    if (region != nullptr) {
+      std::lock_guard<std::mutex> in_order(pool->launch_lock);
+      return launch_ordered<GatherArgs>(gather_order_kernel<Op::kEs>, gather_ordered_kernel<Op>, 0u, a, s, tune, ordered, region);
+    }
+  }
   const Plan p = plan_gather(a.n_descs, tune);
   if (p.route == kRouteTile) {
     if (p.tile >= 16) return launch_gather<16, Op>(a, s);
@@ -1037,7 +1050,7 @@ int uccl_launch_plan(uint32_t n_descs, const uccl_launch_opts* opts, int gather,
   plan->unit_bytes = 64u * 16u * p.unroll;
   const uint64_t groups = p.route == kRouteTile ? tiles_for(n_descs, p.tile) : static_cast<uint64_t>(n_descs) * p.parts;
   plan->groups = static_cast<uint32_t>(groups);
-  plan->ordered = gather ? 0u : ordered_launches(n_descs, tune, reads_acc != 0);
+  plan->ordered = ordered_launches(n_descs, tune, gather || reads_acc);
   plan->reserved = 0u;
   return UCCL_OK;
 }

@@ -363,6 +363,24 @@ struct OrderArgs {
   unsigned long long tag;
 };
 
+// Record k, a first arrival, into the table of a launch of n records.
+__device__ __forceinline__ void order_put(const OrderArgs& t, uint32_t n, uint32_t seq, uint32_t k) {
+  const unsigned long long was = __hip_atomic_exchange(t.words + 2u * static_cast<size_t>(seq % n), (t.tag << 16) | k,
+                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if ((was >> 16) == t.tag) {
+    // the count starts at this call's tag whichever lane gets there first: an older call's is smaller
+    __hip_atomic_fetch_max(t.spilled, t.tag << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long at = __hip_atomic_fetch_add(t.spilled, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xFFFFu;
+    t.words[2u * at + 1u] = was;   // at < winners <= n
+  }
+}
+
+// The n_descs * parts workgroups of a launch in the order of their work: workgroup b runs on XCD b mod 8.
+__device__ __forceinline__ uint32_t order_position() {
+  const uint32_t b = blockIdx.x, group = b / (8u * kOrderRun), in = b % (8u * kOrderRun);
+  return (group + 1u) * (8u * kOrderRun) <= gridDim.x ? group * (8u * kOrderRun) + (in & 7u) * kOrderRun + (in >> 3) : b;
+}
+
 template <uint32_t kEs>
 __global__ void __launch_bounds__(256) chunk_order_kernel(const Args g, const OrderArgs t) {
   const uint32_t k = blockIdx.x * 256u + threadIdx.x;
@@ -379,14 +397,7 @@ __global__ void __launch_bounds__(256) chunk_order_kernel(const Args g, const Or
   }
   const uint32_t bit = 1u << (seq & 31u);
   if ((atomicOr(g.bitmap + (seq >> 5), bit) & bit) != 0u) return;
-  const unsigned long long was = __hip_atomic_exchange(t.words + 2u * static_cast<size_t>(seq % g.n_descs), (t.tag << 16) | k,
-                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if ((was >> 16) == t.tag) {
-    // the count starts at this call's tag whichever lane gets there first: an older call's is smaller
-    __hip_atomic_fetch_max(t.spilled, t.tag << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned long long at = __hip_atomic_fetch_add(t.spilled, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xFFFFu;
-    t.words[2u * at + 1u] = was;   // at < winners <= n_descs
-  }
+  order_put(t, g.n_descs, seq, k);
 }
 
 // Part `part` of record k: units part * 4 + wavefront, then every parts * 4 units (a record longer than
@@ -410,10 +421,7 @@ __device__ __forceinline__ void ordered_part(const Args& g, uint32_t k, uint32_t
 
 template <class Op>
 __global__ void __launch_bounds__(kOrderThreads) chunk_ordered_kernel(const Args g, const OrderArgs t) {
-  uint32_t b = blockIdx.x;   // the launch has n_descs * parts workgroups; workgroup b runs on XCD b mod 8
-  const uint32_t group = b / (8u * kOrderRun), in = b % (8u * kOrderRun);
-  if ((group + 1u) * (8u * kOrderRun) <= gridDim.x) b = group * (8u * kOrderRun) + (in & 7u) * kOrderRun + (in >> 3);
-  const uint32_t entry = b / g.parts, part = b % g.parts;
+  const uint32_t b = order_position(), entry = b / g.parts, part = b % g.parts;
   const unsigned long long first = t.words[2u * static_cast<size_t>(entry)];
   const unsigned long long spill = t.words[2u * static_cast<size_t>(entry) + 1u];
   if ((first >> 16) == t.tag) ordered_part<Op>(g, static_cast<uint32_t>(first & 0xFFFFu), part);
@@ -560,8 +568,22 @@ struct GatherArgs {
   uint32_t parts;
 };
 
+// What a record must satisfy but for its sources, and what each of them must.
+template <uint32_t kEs>
+__device__ __forceinline__ bool gather_ok(const GatherArgs& g, uint64_t dst, uint64_t out, uint32_t len, uint32_t seq, uint32_t n_src) {
+  const uint64_t out_at = out & ~UCCL_FORWARD_ONLY;
+  bool ok = seq < g.ext.n_bits && (dst & 15u) == 0 && len % kEs == 0 && n_src >= 1 && n_src <= UCCL_MAX_SOURCES &&
+            dst <= g.ext.acc_bytes && len <= g.ext.acc_bytes - dst;
+  if (out != UCCL_NO_FORWARD)
+    ok = ok && g.out != nullptr && (out_at & 15u) == 0 && out_at <= g.ext.out_bytes && len <= g.ext.out_bytes - out_at;
+  return ok;
+}
+__device__ __forceinline__ bool gather_source_ok(const GatherArgs& g, uint64_t src, uint32_t len) {
+  return (src & 15u) == 0 && src <= g.ext.recv_bytes && len <= g.ext.recv_bytes - src;
+}
+
 // One unit (64 * U vectors from vector v0 on) of one destination chunk: the accumulator's value,
-// the sources folded into it in the listed order (src[] in LDS), the result written back and / or
+// the sources folded into it in the listed order (src[], the same address in every lane), the result written back and / or
 // forwarded.  Sources are loaded in batches, all loads of a batch issued before the folds.
 template <int U, class Op>
 __device__ __forceinline__ void gather_unit(const GatherArgs& g, uint64_t dst, uint64_t out, uint32_t len,
@@ -669,19 +691,8 @@ __global__ void __launch_bounds__(NT) chunk_gather_kernel(const GatherArgs g) {
       len = hi.x;
       const uint32_t seq = hi.y;
       n_src = hi.z;
-      const bool fwd = out != UCCL_NO_FORWARD;
-      const uint64_t out_at = out & ~UCCL_FORWARD_ONLY;
-      bool ok = seq < g.ext.n_bits && (dst & 15u) == 0 && len % Op::kEs == 0 && n_src >= 1 &&
-                n_src <= UCCL_MAX_SOURCES && dst <= g.ext.acc_bytes && len <= g.ext.acc_bytes - dst;
-      if (fwd)
-        ok = ok && g.out != nullptr && (out_at & 15u) == 0 && out_at <= g.ext.out_bytes &&
-             len <= g.ext.out_bytes - out_at;
-      if (ok) {
-        for (uint32_t j = 0; j < n_src; ++j) {
-          const uint64_t so = d->src_off[j];
-          ok = ok && (so & 15u) == 0 && so <= g.ext.recv_bytes && len <= g.ext.recv_bytes - so;
-        }
-      }
+      bool ok = gather_ok<Op::kEs>(g, dst, out, len, seq, n_src);
+      for (uint32_t j = 0; ok && j < n_src; ++j) ok = gather_source_ok(g, d->src_off[j], len);
       if (ok) {
         const uint32_t bit = 1u << (seq & 31u);
         const uint32_t old = atomicOr(g.bitmap + (seq >> 5), bit);
@@ -753,17 +764,12 @@ __global__ void __launch_bounds__(NT) chunk_gather_parts_kernel(const GatherArgs
   const uint32_t vecs = (len >> 4) + ((len & 15u) != 0u ? 1u : 0u);
   const uint32_t total = (vecs + kUnit - 1u) / kUnit;
   if (wave == 0) {
-    const bool fwd = out != UCCL_NO_FORWARD;
-    const uint64_t out_at = out & ~UCCL_FORWARD_ONLY;
-    bool ok = seq < g.ext.n_bits && (dst & 15u) == 0 && len % Op::kEs == 0 && n_src >= 1 &&
-              n_src <= UCCL_MAX_SOURCES && dst <= g.ext.acc_bytes && len <= g.ext.acc_bytes - dst;
-    if (fwd)
-      ok = ok && g.out != nullptr && (out_at & 15u) == 0 && out_at <= g.ext.out_bytes && len <= g.ext.out_bytes - out_at;
+    bool ok = gather_ok<Op::kEs>(g, dst, out, len, seq, n_src);
     bool src_ok = true;
     if (lane < UCCL_MAX_SOURCES && lane < n_src) {  // lane j checks and stages source j
       const uint64_t so = d->src_off[lane];
       s_src[lane] = so;
-      src_ok = (so & 15u) == 0 && so <= g.ext.recv_bytes && len <= g.ext.recv_bytes - so;
+      src_ok = gather_source_ok(g, so, len);
     }
     ok = ok && __all(src_ok);
     if (lane == 0) {
@@ -788,6 +794,49 @@ __global__ void __launch_bounds__(NT) chunk_gather_parts_kernel(const GatherArgs
   if (s_win == 0u) return;   // uniform over the workgroup
   for (uint32_t u = part * kWaves + wave; u < total; u += kWaves * g.parts)
     gather_unit<U, Op>(g, dst, out, len, n_src, s_src, u * kUnit, lane);
+}
+
+// A call of much payload: order and stream, as above.  What bounds it is the same, and a workgroup of 4 KiB
+// of the destination keeps its n + 1 loads of one vector per lane in flight at once where the tile kernel
+// walks 32 KiB and more (seven senders, fp32, 128 MiB in 128 KiB chunks: 256.5 us in the tile kernel, 208 here;
+// 2 KiB parts 209, 8 KiB 211, two vectors per lane 217, without the contiguous runs 215, with six workgroups
+// per compute unit 223, so the launch is not held back).
+template <uint32_t kEs>
+__global__ void __launch_bounds__(256) gather_order_kernel(const GatherArgs g, const OrderArgs t) {
+  const uint32_t k = blockIdx.x * 256u + threadIdx.x;
+  if (k >= g.n_descs) return;
+  const uccl_gather_desc* d = g.descs + k;
+  const uint32_t len = d->len, seq = d->seq, n_src = d->n_src;
+  bool ok = gather_ok<kEs>(g, d->dst_off, d->out_off, len, seq, n_src);
+  for (uint32_t j = 0; ok && j < n_src; ++j) ok = gather_source_ok(g, d->src_off[j], len);
+  if (!ok) {
+    if (g.rejected != nullptr) atomicAdd(g.rejected, 1u);
+    return;
+  }
+  const uint32_t bit = 1u << (seq & 31u);
+  if ((atomicOr(g.bitmap + (seq >> 5), bit) & bit) != 0u) return;
+  order_put(t, g.n_descs, seq, k);
+}
+
+template <class Op>
+__device__ __forceinline__ void ordered_gather_part(const GatherArgs& g, uint32_t k, uint32_t part) {
+  constexpr uint32_t kUnit = 64u, kWaves = kOrderThreads / 64;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+  const uccl_gather_desc* d = g.descs + k;   // the same address in every lane
+  const uint32_t len = d->len;
+  const uint32_t vecs = (len >> 4) + ((len & 15u) != 0u ? 1u : 0u);
+  const uint32_t total = (vecs + kUnit - 1u) / kUnit;
+  for (uint32_t u = part * kWaves + wave; u < total; u += g.parts * kWaves)
+    gather_unit<1, Op>(g, d->dst_off, d->out_off, len, d->n_src, d->src_off, u * kUnit, lane);
+}
+
+template <class Op>
+__global__ void __launch_bounds__(kOrderThreads) gather_ordered_kernel(const GatherArgs g, const OrderArgs t) {
+  const uint32_t b = order_position(), entry = b / g.parts, part = b % g.parts;
+  const unsigned long long first = t.words[2u * static_cast<size_t>(entry)];
+  const unsigned long long spill = t.words[2u * static_cast<size_t>(entry) + 1u];
+  if ((first >> 16) == t.tag) ordered_gather_part<Op>(g, static_cast<uint32_t>(first & 0xFFFFu), part);
+  if ((spill >> 16) == t.tag) ordered_gather_part<Op>(g, static_cast<uint32_t>(spill & 0xFFFFu), part);
 }
 
 // ---- sender side: tensor buffer -> staged chunks + send records --------------------------------

@@ -8,7 +8,7 @@ import pytest
 import oracle
 import paper_2504_17307_amd as pkg
 from randstream import random_stream
-from synth.layout import DESC, NO_FORWARD, F32, BF16, F16, I32, SUM, MAX, MIN, COPY, PROD
+from synth.layout import DESC, GATHER_DESC, NO_FORWARD, F32, BF16, F16, I32, SUM, MAX, MIN, COPY, PROD
 
 MiB = 1 << 20
 TABLE = 16383  # records one launch orders
@@ -26,7 +26,7 @@ def test_rule():
     assert copy(6144, 32 * KiB) == 1 and copy(6143, 32 * KiB) == 0 and copy(1536, 64 * KiB) == 1 and copy(1535, 64 * KiB) == 0
     assert ordered(1 << 20, None) == 0 and ordered(1 << 20, (32 * KiB, 1)) == 0           # no size given; parts stated
     assert ordered(0, (32 * KiB, 0)) == 0 and ordered(2 ** 32 - 1, (32 * KiB, 0)) == -(-(2 ** 32 - 1) // TABLE)
-    assert ordered(8963, (128 * KiB, 0), gather=True) == 0
+    assert ordered(3072, (32 * KiB, 0), gather=True) == 1 and ordered(3071, (32 * KiB, 0), gather=True, reads_acc=False) == 0
 
 
 def run(w, opts, streams=1):
@@ -123,3 +123,40 @@ def test_calls_in_turn_share_a_region(gpu_lib):
         oracle.apply(e, o, w["recv"], w["descs"], seen, F32, SUM)
         assert np.array_equal(acc.cpu().numpy(), e.view(np.uint8)) and np.array_equal(out.cpu().numpy(), o), k
     assert pkg.uccl_claim_timeouts() == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("spread", sorted(SPREAD))
+@pytest.mark.parametrize("dtype,op,n_src", [(F32, SUM, 16), (BF16, SUM, 7), (F16, MIN, 1), (I32, PROD, 3), (BF16, MAX, 5)])
+def test_gather_random(gpu_lib, spread, dtype, op, n_src):
+    """The multi-source fold in destination order: ragged and empty chunks, repeats, forwarding, relays and
+    records with a bad source, against the oracle and against the form it replaces."""
+    import torch
+    from gpuhelp import to_dev
+    for seed in range(4):
+        w = random_stream(800 + seed, dtype, op, max_chunks=(1, 60, 300, 20)[seed], max_len=(700, 9000, 900, 20000)[seed])
+        g, src = np.random.default_rng(seed), w["descs"]
+        n = len(src)
+        d = np.zeros(n, dtype=GATHER_DESC)
+        for f in ("dst_off", "out_off", "len", "seq"):
+            d[f] = src[f]
+        d["seq"] = SPREAD[spread](n, d["seq"])
+        bits = int(d["seq"].max()) + 1
+        # sources: any slots, the same for every copy of a record
+        slots = g.integers(0, n, (w["n_bits"], n_src))
+        d["src_off"][:, :n_src] = (slots * (int(src["src_off"][1]) if n > 1 else 0))[src["seq"]]
+        d["n_src"] = g.integers(1, n_src + 1, w["n_bits"])[src["seq"]]
+        bad = g.random(w["n_bits"])[src["seq"]] < 0.1
+        d["src_off"][bad, 0] += 8
+        good = d[~bad]
+        acc, out, seen = w["acc"].copy(), np.full(max(w["out_bytes"], 16), 0xA5, dtype=np.uint8), oracle.new_seen(bits)
+        oracle.reduce_gather(acc, out, w["recv"], good, seen, dtype, op)
+        for opts in ((hint_for(n), 0), (hint_for(n), 1)):
+            print(spread, dtype, op, seed, n, opts, flush=True)
+            assert (pkg.uccl_launch_ordered(n, opts, gather=True) > 0) == (opts[1] == 0)
+            da, do, dr, dd = to_dev(w["acc"]), torch.full((len(out),), 0xA5, dtype=torch.uint8, device="cuda"), to_dev(w["recv"]), to_dev(d)
+            bitmap, rejected = torch.zeros((bits + 31) // 32, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+            pkg.uccl_chunk_reduce_gather(da, do, dr, dd, n, bitmap, dtype, op, n_rejected=rejected, n_bits=bits, opts=opts)
+            torch.cuda.synchronize()
+            assert np.array_equal(da.cpu().numpy(), acc.view(np.uint8)) and np.array_equal(do.cpu().numpy(), out)
+            assert np.array_equal(bitmap.cpu().numpy(), oracle.pack_bitmap(seen).view(np.int32)) and int(rejected) == int(bad.sum())
