@@ -889,7 +889,7 @@ def main():
         "stream_ceiling": stream_ceiling,
         "device": device_info(torch),
         "dedup_report": {"n_bits": w.n_bits, "median_us": round(report_us, 2),
-                         "what": "ack_report_kernel: cumulative ack, applied count, selective ranges",
+                         "what": "ack_segments_kernel: cumulative ack, applied count, selective ranges",
                          "every_97th_chunk_missing": lossy_report},
         "message_status": {"slots": 128, "bits_per_slot": 256, "median_us": round(status_us, 2),
                            "what": "message_status_kernel: per-slot cumulative point, applied count, completion"},

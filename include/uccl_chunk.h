@@ -328,6 +328,8 @@ int uccl_dedup_reset(uint32_t* dedup_bitmap, uint64_t n_bits, void* stream);
  *   complete   1 if n_applied == n_bits
  * followed by the runs in ascending order as pairs {start, end} of uint64_t, end exclusive.
  * Bits at and above n_bits in the last word are ignored.  n_bits < 2^40.  Stream ordered.
+ * Up to 2^28 bits the work is spread over workgroups that add up their counts in the stream's region of
+ * the claim pool ("Scratch memory" above; without a region, and under graph capture, one workgroup does it).
  */
 typedef struct uccl_ack_report {
   uint64_t cum_ack;

@@ -1020,8 +1020,25 @@ int uccl_dedup_report(const uint32_t* dedup_bitmap, uint64_t n_bits, void* repor
   if (misaligned(dedup_bitmap, 4) || misaligned(report, 8)) return UCCL_EALIGN;
   AckHeader* hdr = static_cast<AckHeader*>(report);
   uint64_t* ranges = reinterpret_cast<uint64_t*>(hdr + 1);
-  return launch_kernel(ack_report_kernel, 1, 1024, static_cast<hipStream_t>(stream), dedup_bitmap,
-                       n_bits, hdr, ranges, max_ranges);
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  // One workgroup per segment; several need scratch words to add up.  A bitmap of more than kAckMaxSegments
+  // (each looks at all before it), or a stream without a region or being captured, gets the kernel of one workgroup.
+  const uint64_t segments = n_bits == 0 ? 1 : (n_bits - 1) / kAckSegBits + 1;
+  if (segments == 1)
+    return launch_kernel(ack_segments_kernel, 1, 256, s, dedup_bitmap, n_bits, hdr, ranges, max_ranges, nullptr, 0ull);
+  static_assert(kAckMaxSegments * 4 <= kRegionWords, "four words a segment");
+  if (segments <= kAckMaxSegments) {
+    uint32_t* faults = nullptr;
+    ClaimPool* pool = nullptr;
+    unsigned long long* const region = claim_region(s, &faults, &pool);
+    if (region != nullptr) {
+      std::lock_guard<std::mutex> in_order(pool->launch_lock);
+      const unsigned long long tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
+      return launch_kernel(ack_segments_kernel, static_cast<uint32_t>(segments), 256, s, dedup_bitmap, n_bits, hdr, ranges, max_ranges,
+                           region, tag);
+    }
+  }
+  return launch_kernel(ack_report_kernel, 1, 1024, s, dedup_bitmap, n_bits, hdr, ranges, max_ranges);
 }
 
 int uccl_message_status(uint32_t* dedup_bitmap, const uint32_t* n_chunks, uint32_t n_slots,
