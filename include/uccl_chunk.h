@@ -96,7 +96,7 @@ typedef struct uccl_extents {
  *                at most 128 records take one workgroup per record, sized to the chunk).  Calls of much payload
  *                (records x chunk_bytes: 96 MiB for a reduction, 192 MiB or chunks of 64 KiB for a copy; chunks
  *                of 16 KiB and more) are streamed in destination order, by two launches (see "Scratch
- *                memory" below).
+ *                memory" below); so are calls of 3072 to 16383 records of unknown size.
  *   parts        workgroups per record for calls of few, large records (Appendix C.4: small
  *                messages are where the kernel's fixed costs show): 0 = the library decides,
  *                1 = never cut a record, 2..16 = that many.  Honoured only when a workgroup takes
@@ -414,8 +414,8 @@ int uccl_feed_destroy(uccl_feed* feed);
  * `gather` != 0: uccl_chunk_reduce_gather, else the apply / scatter family; `reads_acc` != 0: the
  * op combines with the accumulator (anything but UCCL_COPY).  `parts` > 1 assumes that claim words
  * are to be had (see "Scratch memory"); a call that finds none is launched with parts = 1.
- * `ordered` > 0: where scratch memory is to be had, uccl_chunk_apply_opts, uccl_chunk_scatter_opts and
- * uccl_chunk_reduce_gather decide the records first and stream them in destination order, in that many
+ * `ordered` > 0: where scratch memory is to be had, apply and scatter calls (not the indirect and
+ * no-allocation ones) and uccl_chunk_reduce_gather decide the records first and stream them in destination order, in that many
  * pairs of launches (chunk_order_kernel and chunk_ordered_kernel, or their gather_ forms); the other fields say what the call is launched as otherwise.
  * UCCL_EINVAL for a NULL `plan` or options the data-path calls would refuse.  Utility, no passage
  * of the paper. */

@@ -322,18 +322,32 @@ struct Plan {
 // and 191 / 194, 240 MiB in 32 KiB chunks 268 / 270, 224 MiB in 20 KB chunks 258 / 261 and 252 / 260.
 // Several sources per record (how many, the host does not know), 128 KiB chunks: 48 MiB of destination from one
 // source 35.3 / 32.4, from seven 82.7 / 90.0; 96 MiB 64.1 / 65.7 and 164 / 197; in 32 KiB chunks 66.0 / 69.8 and 172 / 190.
+//
+// With the chunk size unknown the same form is taken for another reason.  A workgroup per record decides
+// its sequence number with an atomic of its own, atomics of neighbouring records meet on one 128-byte line of
+// the bitmap, and such atomics are served one after the other, about 6.5 ns each: 5000 records take 30 us whatever
+// their size, while the order kernel's wavefronts issue 64 at a time.  Four parts an entry suit records of any
+// size (ring steps, bf16, us, this form / one workgroup per record): 3000 records of 4 KiB 37 / 51, 9 KB 48 / 59,
+// 16 KiB 67 / 70, 32 KiB 116 / 116, 64 KiB 240 / 246; 5000 of 4 KiB 47 / 74, 9 KB 66 / 86, 32 KiB 189 / 196, 64 KiB 437 / 444;
+// 2000 of 32 KiB 84 / 83; against tiles of four from 8192 records on, 12 000 of 4 KiB 75.6 / 76.1, 9 KB 130 / 134,
+// 16 KiB 219 / 240, 32 KiB 489 / 538; in two launches it does not pay (20 000 of 4 KiB 135 / 112).  (Three parts are
+// better for small records and lose 2 % on 64 KiB ones, eight the other way round.)
+//
 // Returns the number of launches of each kernel (the table holds kOrderRecords entries; more records are
 // taken in equal shares, each of which has to be worth it), 0 = not this form.  Needs a claim region and
 // records in device memory; a stated number of parts asks for the other form.
 constexpr uint32_t kOrderRecords = kRegionRecords * UCCL_CLAIM_STRIDE / 2 - 1;   // two words each, and the spill count
-static_assert(kOrderRecords <= 0xFFFFu, "a table entry has 16 bits for the record");
+static_assert(kOrderRecords <= 0x3FFFu, "a table entry has 14 bits for the record");
 constexpr uint32_t kOrderChunk = 16u << 10;
 constexpr uint64_t kOrderBytes = 96ull << 20;
 constexpr uint32_t kOrderCopyChunk = 64u << 10;        // copies: chunks of this size from kOrderBytes on,
 constexpr uint64_t kOrderCopyBytes = 192ull << 20;     // smaller ones from here on
+constexpr uint32_t kOrderUnknownRecords = 3072;        // chunk size unknown: from this many records to one table full
+constexpr uint32_t kOrderUnknownParts = 4;
 constexpr uint32_t kOrderMaxParts = 64;   // longer records are walked: keeps the grid far below a launch's limit
 
-uint32_t ordered_launches(uint32_t n_descs, const Tuning& tune, bool reads_acc) {
+uint32_t ordered_launches(uint32_t n_descs, const Tuning& tune, bool reads_acc, bool gather) {
+  if (tune.parts == 0u && tune.chunk_bytes == 0u && !gather) return n_descs >= kOrderUnknownRecords && n_descs <= kOrderRecords ? 1u : 0u;
   if (tune.parts != 0u || tune.chunk_bytes < kOrderChunk || n_descs == 0u) return 0u;
   const uint32_t launches = (n_descs - 1u) / kOrderRecords + 1u;
   const uint64_t least = reads_acc || tune.chunk_bytes >= kOrderCopyChunk ? kOrderBytes : kOrderCopyBytes;
@@ -367,7 +381,7 @@ template <class KernelArgs>
 int launch_ordered(void (*order)(KernelArgs, OrderArgs), void (*stream)(KernelArgs, OrderArgs), uint32_t lds, KernelArgs a, hipStream_t s,
                    const Tuning& tune, uint32_t launches, unsigned long long* region) {
   const hipEvent_t begin = t_start, end = t_stop;
-  const uint32_t n = a.n_descs, parts = (tune.chunk_bytes - 1u) / kOrderPartBytes + 1u;
+  const uint32_t n = a.n_descs, parts = tune.chunk_bytes == 0u ? kOrderUnknownParts : (tune.chunk_bytes - 1u) / kOrderPartBytes + 1u;
   const auto* const descs = a.descs;
   a.parts = parts < kOrderMaxParts ? parts : kOrderMaxParts;
   int rc = UCCL_OK;
@@ -392,14 +406,15 @@ int launch_ordered(void (*order)(KernelArgs, OrderArgs), void (*stream)(KernelAr
 
 template <class Op>
 int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
-  const uint32_t ordered = a.n_ptr == nullptr && tune.static_claims == nullptr && !tune.host_records ? ordered_launches(a.n_descs, tune, Op::kReadsAcc) : 0u;
+  const uint32_t ordered = a.n_ptr == nullptr && tune.static_claims == nullptr && !tune.host_records ? ordered_launches(a.n_descs, tune, Op::kReadsAcc, false) : 0u;
   if (ordered != 0u) {
     ClaimPool* pool = nullptr;
     unsigned long long* const region = claim_region(s, &a.faults, &pool);
     if (region != nullptr) {
       std::lock_guard<std::mutex> in_order(pool->launch_lock);
-      return launch_ordered<Args>(chunk_order_kernel<Op::kEs>, chunk_ordered_kernel<Op>, Op::kReadsAcc ? kOrderReduceLds : 0u, a, s, tune,
-                                  ordered, region);
+      // held back only where the records are known to be large: empty parts want as many workgroups as there can be
+      const uint32_t lds = Op::kReadsAcc && tune.chunk_bytes != 0u ? kOrderReduceLds : 0u;
+      return launch_ordered<Args>(chunk_order_kernel<Op::kEs>, chunk_ordered_kernel<Op>, lds, a, s, tune, ordered, region);
     }
   }
   Plan p = plan_apply(a.n_descs, tune, Op::kReadsAcc);
@@ -482,7 +497,7 @@ Plan plan_gather(uint32_t n_descs, const Tuning& tune) {
 
 template <class Op>
 int launch_gather_tile(GatherArgs& a, hipStream_t s, const Tuning& tune) {
-  const uint32_t ordered = ordered_launches(a.n_descs, tune, true);
+  const uint32_t ordered = ordered_launches(a.n_descs, tune, true, true);
   if (ordered != 0u) {
     ClaimPool* pool = nullptr;
     unsigned long long* const region = claim_region(s, &a.faults, &pool);
@@ -1067,7 +1082,7 @@ int uccl_launch_plan(uint32_t n_descs, const uccl_launch_opts* opts, int gather,
   plan->unit_bytes = 64u * 16u * p.unroll;
   const uint64_t groups = p.route == kRouteTile ? tiles_for(n_descs, p.tile) : static_cast<uint64_t>(n_descs) * p.parts;
   plan->groups = static_cast<uint32_t>(groups);
-  plan->ordered = ordered_launches(n_descs, tune, gather || reads_acc);
+  plan->ordered = ordered_launches(n_descs, tune, gather || reads_acc, gather != 0);
   plan->reserved = 0u;
   return UCCL_OK;
 }

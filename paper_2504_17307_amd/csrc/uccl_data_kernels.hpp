@@ -351,20 +351,27 @@ __global__ void __launch_bounds__(NT) chunk_flat_kernel(const Args g) {
 //            either way; five 283).
 //
 // Words of the table and the spill list carry the call's tag as claim words do, so nothing is cleared.
-// Entry i of the table is word 2 i and entry i of the spill list word 2 i + 1: one load serves both.
+// Entry i of the table is word 2 i and entry i of the spill list word 2 i + 1: one load serves both.  An entry
+// also says whether its record is shorter than 2, 4 or 8 KiB parts would be, so that a workgroup whose part
+// does not exist leaves without reading the record.  Which of an entry's workgroups takes which part turns
+// with the entry: records shorter than `parts` parts would otherwise leave the same workgroups idle every time,
+// and as workgroups are dealt to the shader engines in turn, the same engines (5000 records of 4 KiB each
+// in four parts: 73 us the two phases without, 47 with it).
 constexpr uint32_t kOrderThreads = 256;            // 4 KiB per stream: one vector per lane
 constexpr uint32_t kOrderPartBytes = kOrderThreads * 16u;
 constexpr uint32_t kOrderRun = 32;
 constexpr uint32_t kOrderReduceLds = 24576;
 
 struct OrderArgs {
-  unsigned long long* words;    // 2 * n_descs words: tag << 16 | record
+  unsigned long long* words;    // 2 * n_descs words: tag << 16 | size class << 14 | record
   unsigned long long* spilled;  // tag << 16 | length of the spill list
   unsigned long long tag;
 };
 
-// Record k, a first arrival, into the table of a launch of n records.
-__device__ __forceinline__ void order_put(const OrderArgs& t, uint32_t n, uint32_t seq, uint32_t k) {
+// Record k (below 2^14), a first arrival, into the table of a launch of n records.
+__device__ __forceinline__ void order_put(const OrderArgs& t, uint32_t n, uint32_t seq, uint32_t k, uint32_t len) {
+  const uint32_t size = len <= kOrderPartBytes ? 0u : len <= 2u * kOrderPartBytes ? 1u : len <= 4u * kOrderPartBytes ? 2u : 3u;
+  k |= size << 14;
   const unsigned long long was = __hip_atomic_exchange(t.words + 2u * static_cast<size_t>(seq % n), (t.tag << 16) | k,
                                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if ((was >> 16) == t.tag) {
@@ -374,6 +381,13 @@ __device__ __forceinline__ void order_put(const OrderArgs& t, uint32_t n, uint32
     t.words[2u * at + 1u] = was;   // at < winners <= n
   }
 }
+
+// Whether `entry` is of this call and its record has a part `part` (size class 3: any number of parts).
+__device__ __forceinline__ bool order_has(const OrderArgs& t, unsigned long long entry, uint32_t part) {
+  const uint32_t size = (static_cast<uint32_t>(entry) >> 14) & 3u;
+  return (entry >> 16) == t.tag && (size == 3u || part < (1u << size));
+}
+__device__ __forceinline__ uint32_t order_record(unsigned long long entry) { return static_cast<uint32_t>(entry) & 0x3FFFu; }
 
 // The n_descs * parts workgroups of a launch in the order of their work: workgroup b runs on XCD b mod 8.
 __device__ __forceinline__ uint32_t order_position() {
@@ -397,7 +411,7 @@ __global__ void __launch_bounds__(256) chunk_order_kernel(const Args g, const Or
   }
   const uint32_t bit = 1u << (seq & 31u);
   if ((atomicOr(g.bitmap + (seq >> 5), bit) & bit) != 0u) return;
-  order_put(t, g.n_descs, seq, k);
+  order_put(t, g.n_descs, seq, k, hi.z);
 }
 
 // Part `part` of record k: units part * 4 + wavefront, then every parts * 4 units (a record longer than
@@ -421,11 +435,11 @@ __device__ __forceinline__ void ordered_part(const Args& g, uint32_t k, uint32_t
 
 template <class Op>
 __global__ void __launch_bounds__(kOrderThreads) chunk_ordered_kernel(const Args g, const OrderArgs t) {
-  const uint32_t b = order_position(), entry = b / g.parts, part = b % g.parts;
+  const uint32_t b = order_position(), entry = b / g.parts, part = (b + entry) % g.parts;
   const unsigned long long first = t.words[2u * static_cast<size_t>(entry)];
   const unsigned long long spill = t.words[2u * static_cast<size_t>(entry) + 1u];
-  if ((first >> 16) == t.tag) ordered_part<Op>(g, static_cast<uint32_t>(first & 0xFFFFu), part);
-  if ((spill >> 16) == t.tag) ordered_part<Op>(g, static_cast<uint32_t>(spill & 0xFFFFu), part);
+  if (order_has(t, first, part)) ordered_part<Op>(g, order_record(first), part);
+  if (order_has(t, spill, part)) ordered_part<Op>(g, order_record(spill), part);
 }
 
 // ---- calls of few records --------------------------------------------------------------------
@@ -815,7 +829,7 @@ __global__ void __launch_bounds__(256) gather_order_kernel(const GatherArgs g, c
   }
   const uint32_t bit = 1u << (seq & 31u);
   if ((atomicOr(g.bitmap + (seq >> 5), bit) & bit) != 0u) return;
-  order_put(t, g.n_descs, seq, k);
+  order_put(t, g.n_descs, seq, k, len);
 }
 
 template <class Op>
@@ -832,11 +846,11 @@ __device__ __forceinline__ void ordered_gather_part(const GatherArgs& g, uint32_
 
 template <class Op>
 __global__ void __launch_bounds__(kOrderThreads) gather_ordered_kernel(const GatherArgs g, const OrderArgs t) {
-  const uint32_t b = order_position(), entry = b / g.parts, part = b % g.parts;
+  const uint32_t b = order_position(), entry = b / g.parts, part = (b + entry) % g.parts;
   const unsigned long long first = t.words[2u * static_cast<size_t>(entry)];
   const unsigned long long spill = t.words[2u * static_cast<size_t>(entry) + 1u];
-  if ((first >> 16) == t.tag) ordered_gather_part<Op>(g, static_cast<uint32_t>(first & 0xFFFFu), part);
-  if ((spill >> 16) == t.tag) ordered_gather_part<Op>(g, static_cast<uint32_t>(spill & 0xFFFFu), part);
+  if (order_has(t, first, part)) ordered_gather_part<Op>(g, order_record(first), part);
+  if (order_has(t, spill, part)) ordered_gather_part<Op>(g, order_record(spill), part);
 }
 
 // ---- sender side: tensor buffer -> staged chunks + send records --------------------------------

@@ -24,7 +24,9 @@ def test_rule():
     assert ordered(TABLE + 1, (32 * KiB, 0)) == 2 and ordered(TABLE + 1, (16 * KiB, 0)) == 2   # equal shares of a longer call
     assert copy(TABLE, 16 * KiB) == 1 and copy(TABLE + 1, 16 * KiB) == 0                 # whose shares have to be worth it
     assert copy(6144, 32 * KiB) == 1 and copy(6143, 32 * KiB) == 0 and copy(1536, 64 * KiB) == 1 and copy(1535, 64 * KiB) == 0
-    assert ordered(1 << 20, None) == 0 and ordered(1 << 20, (32 * KiB, 1)) == 0           # no size given; parts stated
+    assert ordered(1 << 20, (32 * KiB, 1)) == 0                                          # parts stated
+    assert [ordered(n, None) for n in (3071, 3072, TABLE, TABLE + 1)] == [0, 1, 1, 0]    # no size given
+    assert ordered(5000, (0, 0), gather=True) == 0 and ordered(5000, (0, 1)) == 0
     assert ordered(0, (32 * KiB, 0)) == 0 and ordered(2 ** 32 - 1, (32 * KiB, 0)) == -(-(2 ** 32 - 1) // TABLE)
     assert ordered(3072, (32 * KiB, 0), gather=True) == 1 and ordered(3071, (32 * KiB, 0), gather=True, reads_acc=False) == 0
 
@@ -80,8 +82,8 @@ def test_random_streams(gpu_lib, spread, dtype, op):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n", [TABLE - 1, TABLE, TABLE + 1, 2 * TABLE + 1, 40001])
-def test_table_and_launch_edges(gpu_lib, n):
+@pytest.mark.parametrize("n,stated", [(TABLE - 1, True), (TABLE, True), (TABLE + 1, True), (2 * TABLE + 1, True), (40001, True), (3072, False), (TABLE, False)])
+def test_table_and_launch_edges(gpu_lib, n, stated):
     """Calls around one and two launches' worth of records, in shuffled order with repeats and some
     out-of-range sequence numbers; records of 0..48 bytes, and a few that are longer than all parts of one."""
     g = np.random.default_rng(n)
@@ -90,6 +92,8 @@ def test_table_and_launch_edges(gpu_lib, n):
     d = np.zeros(n, dtype=DESC)
     lens = g.integers(0, 13, unique) * 4
     lens[g.integers(0, unique, 3)] = 64 * 4096 + 20
+    for at_edge in (4096, 8192, 16384):                                      # the size classes of a table entry
+        lens[g.integers(0, unique, 12)] = at_edge + np.array([-4, 0, 4] * 4)
     pitch = (lens + 15) // 16 * 16
     at = np.concatenate([[0], np.cumsum(pitch)])
     d["src_off"], d["dst_off"], d["out_off"], d["len"], d["seq"] = at[seq], at[seq], at[seq], lens[seq], seq
@@ -99,8 +103,8 @@ def test_table_and_launch_edges(gpu_lib, n):
     total = int(at[-1])
     w = dict(descs=d, recv=g.random(total // 4, dtype=np.float32), acc=g.random(total // 4, dtype=np.float32), out_bytes=total,
              n_bits=unique, dtype=F32, op=SUM)
-    print(n, flush=True)
-    check(w, (hint_for(n), 0), rejected=int(bad.sum()))
+    print(n, stated, flush=True)
+    check(w, (hint_for(n) if stated else 0, 0), rejected=int(bad.sum()))
 
 
 @pytest.mark.gpu
