@@ -167,10 +167,10 @@ int uccl_init(void);
  * (or uccl_init) looks the array's device address up.
  *   - n_descs > UCCL_NOALLOC_MAX_DESCS returns UCCL_ETOOBIG and enqueues nothing.  (Calls that
  *     large are never cut into parts, so uccl_chunk_apply serves them without any scratch memory.)
- *   - Every call on a GPU shares that GPU's array, whatever the stream: a split call first clears
- *     its own words with a small fill kernel, then runs; the pair may be captured and replayed.
+ *   - Every call on a GPU shares that GPU's array, whatever the stream.  A split call may be captured and
+ *     replayed: a captured one first clears its own words with a small fill kernel, then runs.
  *     Calls (or replays) that overlap in time on one GPU race on the array: keep them on one
- *     stream, or order them with events.
+ *     stream, or order them with events (so that they also run in the order in which they were made).
  */
 #define UCCL_NOALLOC_MAX_DESCS 2048
 int uccl_chunk_apply_noalloc(void* acc, void* out_stage, const void* recv_stage,

@@ -1,0 +1,44 @@
+"""Eager and captured calls of the no-allocation entry point in turn: they share one array of claim words,
+the eager ones with tags that grow, the captured ones with words they clear."""
+import pytest
+import torch
+
+from synth import workloads as wl
+from synth.layout import BF16
+
+from gpuhelp import DeviceRun, oracle_results, assert_same
+
+pytestmark = pytest.mark.gpu
+
+
+def test_eager_calls_between_replays(gpu_lib):
+    captured, eager = wl.config1(seed=17), wl.ring_share("eager", 18, R=4, M=4 * (9 * 40960 + 528), C=40960, dtype=BF16, paths=3,
+                                                         window=None, dup=0.2, dist="normal")
+    want = {w.name: oracle_results(w) for w in (captured, eager)}
+
+    def issue(run, w):
+        gpu_lib.uccl_dedup_reset(run.bitmap, w.n_bits)
+        for ph, d in zip(w.phases, run.descs):
+            gpu_lib.uccl_chunk_apply_noalloc(run.acc, run.out, run.recv, d, len(ph.descs), run.bitmap, w.dtype, ph.op)
+
+    def check(run, w, what):
+        torch.cuda.synchronize()
+        for got, exp, name in zip(run.results(), want[w.name], ("acc", "out_stage", "bitmap")):
+            assert_same(got, exp, f"{w.name}, {what}: {name}")
+
+    gpu_lib.uccl_init()
+    run = DeviceRun(captured)
+    acc0 = run.acc.clone()
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=side):
+        issue(run, captured)
+    for turn in range(4):
+        for _ in range(turn):                      # none, then several eager calls between two replays
+            mine = DeviceRun(eager)
+            issue(mine, eager)
+            check(mine, eager, f"turn {turn}")
+        run.acc.copy_(acc0)
+        graph.replay()
+        check(run, captured, f"replay {turn}")
+    assert gpu_lib.uccl_claim_timeouts() == 0
