@@ -489,7 +489,11 @@ int launch_gather(const GatherArgs& a, hipStream_t s) {
 // 6.7 us in 8; 128 x 32 KiB 12.3 -> 10.1 us in 4; 128 x 128 KiB 35.4 -> 28.1 us in 16; 512 x 32 KiB
 // 32.2 -> 32.0 us in 4): parts of about 8 KiB, at most 16, while the call has at most 16 MiB of
 // destination payload and the launch stays within 2048 workgroups; with the chunk size unknown, by
-// record count alone.
+// record count alone.  Smaller chunks are cut into parts of 4 KiB, one vector per lane, in calls of up to 288
+// records, which as tiles leave most compute units idle (event pairs, bf16, tiles -> parts; seven sources:
+// 8 x 4 KiB 9.2 -> 5.5 us, 65 x 16 KiB 11.4 -> 6.4, 256 x 9 KB 14.6 -> 8.8; one source: 65 x 4 KiB 6.0 -> 4.8,
+// 256 x 4 KiB 6.7 -> 6.6, but 400 x 4 KiB 7.1 -> 7.9, hence the limit).
+constexpr uint32_t kGatherSmallRecords = 288;
 uint32_t gather_parts(uint32_t n_descs, uint32_t chunk_bytes) {
   if (chunk_bytes == 0u) return n_descs <= 64u ? 8u : n_descs <= 128u ? 4u : 1u;
   if (static_cast<uint64_t>(n_descs) * chunk_bytes > (16ull << 20)) return 1u;
@@ -499,12 +503,21 @@ uint32_t gather_parts(uint32_t n_descs, uint32_t chunk_bytes) {
   return parts;
 }
 
-Plan plan_gather(uint32_t n_descs, const Tuning& tune) {
+Plan plan_gather_uncut(uint32_t n_descs, const Tuning& tune) {
   const uint32_t t = flat_tile(n_descs, tune.chunk_bytes);
   if (t >= 2) return {kRouteTile, t >= 16 ? 16u : t >= 8 ? 8u : t >= 4 ? 4u : 2u, 1u, 1024u, UCCL_GATHER_UNROLL};
-  const uint32_t parts = tune.parts ? tune.parts : gather_parts(n_descs, tune.chunk_bytes);
-  if (parts > 1u && n_descs <= kRegionRecords) return {kRouteParts, 1u, parts, UCCL_PART_THREADS, UCCL_GATHER_UNROLL};
   return {kRouteOne, 1u, 1u, 1024u, UCCL_GATHER_UNROLL};
+}
+
+Plan plan_gather(uint32_t n_descs, const Tuning& tune) {
+  if (flat_tile(n_descs, tune.chunk_bytes) >= 2) {
+    if (tune.chunk_bytes != 0u && tune.parts == 0u && n_descs <= kGatherSmallRecords)
+      return {kRouteParts, 1u, (tune.chunk_bytes - 1u) / (UCCL_PART_THREADS * 16u) + 1u, UCCL_PART_THREADS, 1u};
+  } else {
+    const uint32_t parts = tune.parts ? tune.parts : gather_parts(n_descs, tune.chunk_bytes);
+    if (parts > 1u && n_descs <= kRegionRecords) return {kRouteParts, 1u, parts, UCCL_PART_THREADS, UCCL_GATHER_UNROLL};
+  }
+  return plan_gather_uncut(n_descs, tune);
 }
 
 template <class Op>
@@ -518,13 +531,7 @@ int launch_gather_tile(GatherArgs& a, hipStream_t s, const Tuning& tune) {
       return launch_ordered<GatherArgs>(gather_order_kernel<Op::kEs>, gather_ordered_kernel<Op>, 0u, a, s, tune, ordered, region);
     }
   }
-  const Plan p = plan_gather(a.n_descs, tune);
-  if (p.route == kRouteTile) {
-    if (p.tile >= 16) return launch_gather<16, Op>(a, s);
-    if (p.tile >= 8) return launch_gather<8, Op>(a, s);
-    if (p.tile >= 4) return launch_gather<4, Op>(a, s);
-    return launch_gather<2, Op>(a, s);
-  }
+  Plan p = plan_gather(a.n_descs, tune);
   if (p.route == kRouteParts) {
     ClaimPool* pool = nullptr;
     a.claims = claim_region(s, &a.faults, &pool);
@@ -532,9 +539,17 @@ int launch_gather_tile(GatherArgs& a, hipStream_t s, const Tuning& tune) {
       std::lock_guard<std::mutex> in_order(pool->launch_lock);
       a.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
       a.parts = p.parts;
-      return launch_kernel(chunk_gather_parts_kernel<UCCL_PART_THREADS, UCCL_GATHER_UNROLL, Op>, a.n_descs * p.parts,
-                           UCCL_PART_THREADS, s, a);
+      return p.unroll == 1u ? launch_kernel(chunk_gather_parts_kernel<UCCL_PART_THREADS, 1, Op>, a.n_descs * p.parts, UCCL_PART_THREADS, s, a)
+                            : launch_kernel(chunk_gather_parts_kernel<UCCL_PART_THREADS, UCCL_GATHER_UNROLL, Op>, a.n_descs * p.parts,
+                                            UCCL_PART_THREADS, s, a);
     }
+    p = plan_gather_uncut(a.n_descs, tune);   // no claim words to be had
+  }
+  if (p.route == kRouteTile) {
+    if (p.tile >= 16) return launch_gather<16, Op>(a, s);
+    if (p.tile >= 8) return launch_gather<8, Op>(a, s);
+    if (p.tile >= 4) return launch_gather<4, Op>(a, s);
+    return launch_gather<2, Op>(a, s);
   }
   return launch_gather<1, Op>(a, s);
 }

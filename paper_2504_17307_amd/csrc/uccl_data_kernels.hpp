@@ -596,57 +596,68 @@ __device__ __forceinline__ bool gather_source_ok(const GatherArgs& g, uint64_t s
   return (src & 15u) == 0 && src <= g.ext.recv_bytes && len <= g.ext.recv_bytes - src;
 }
 
-// One unit (64 * U vectors from vector v0 on) of one destination chunk: the accumulator's value,
-// the sources folded into it in the listed order (src[], the same address in every lane), the result written back and / or
-// forwarded.  Sources are loaded in batches, all loads of a batch issued before the folds.
+// One unit (64 * U vectors from vector v0 on) of one destination chunk: the accumulator's value and the
+// sources folded into it in the listed order (fold), the result written back and / or forwarded (store).
+// Sources are loaded in batches of B, all loads of a batch issued before the folds.  src(j): offset of
+// source j, the same in every lane.
 template <int U, class Op>
-__device__ __forceinline__ void gather_unit(const GatherArgs& g, uint64_t dst, uint64_t out, uint32_t len,
-                                            uint32_t n_src, const uint64_t* src, uint32_t v0, uint32_t lane) {
+struct GatherUnit {
+  bool live[U];
+  typename Op::State st[U][4];
+};
+
+template <int U, int B, class Op, class Src>
+__device__ __forceinline__ void gather_fold(const GatherArgs& g, GatherUnit<U, Op>& t, uint64_t dst, uint32_t len, uint32_t n_src, Src src,
+                                            uint32_t v0, uint32_t lane) {
+  const uint32_t nvec = len >> 4;
+  const u32x4* ap = reinterpret_cast<const u32x4*>(g.acc + dst) + v0 + lane;
+#pragma unroll
+  for (int i = 0; i < U; ++i) {
+    t.live[i] = v0 + lane + i * 64 < nvec;
+    u32x4 a = {0u, 0u, 0u, 0u};
+    if (t.live[i]) a = ap[i * 64];
+    t.st[i][0] = Op::open(a.x); t.st[i][1] = Op::open(a.y); t.st[i][2] = Op::open(a.z); t.st[i][3] = Op::open(a.w);
+  }
+  for (uint32_t j0 = 0; j0 < n_src; j0 += B) {
+    u32x4 rv[B][U];
+#pragma unroll
+    for (uint32_t b = 0; b < B; ++b) {
+      if (j0 + b < n_src) {
+        const u32x4* rp = reinterpret_cast<const u32x4*>(g.recv + src(j0 + b)) + v0 + lane;
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+          rv[b][i] = u32x4{0u, 0u, 0u, 0u};
+          if (t.live[i]) rv[b][i] = __builtin_nontemporal_load(rp + i * 64);
+        }
+      }
+    }
+#pragma unroll
+    for (uint32_t b = 0; b < B; ++b) {
+      if (j0 + b < n_src) {
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+          Op::fold(t.st[i][0], rv[b][i].x); Op::fold(t.st[i][1], rv[b][i].y);
+          Op::fold(t.st[i][2], rv[b][i].z); Op::fold(t.st[i][3], rv[b][i].w);
+        }
+      }
+    }
+  }
+}
+
+template <int U, class Op, class Src>
+__device__ __forceinline__ void gather_store(const GatherArgs& g, const GatherUnit<U, Op>& u, uint64_t dst, uint64_t out, uint32_t len,
+                                             uint32_t n_src, Src src, uint32_t v0, uint32_t lane) {
   constexpr uint32_t kUnit = 64u * U;
-  constexpr uint32_t kBatch = UCCL_GATHER_BATCH;
   const uint32_t nvec = len >> 4;
   const bool fwd = out != UCCL_NO_FORWARD;
   const bool keep = !(fwd && (out & UCCL_FORWARD_ONLY));
   u32x4* ap = reinterpret_cast<u32x4*>(g.acc + dst) + v0 + lane;
   u32x4* op = reinterpret_cast<u32x4*>(g.out + (out & ~UCCL_FORWARD_ONLY)) + v0 + lane;
-  bool live[U];
-  typename Op::State st[U][4];
 #pragma unroll
   for (int i = 0; i < U; ++i) {
-    live[i] = v0 + lane + i * 64 < nvec;
-    u32x4 a = {0u, 0u, 0u, 0u};
-    if (live[i]) a = ap[i * 64];
-    st[i][0] = Op::open(a.x); st[i][1] = Op::open(a.y); st[i][2] = Op::open(a.z); st[i][3] = Op::open(a.w);
-  }
-  for (uint32_t j0 = 0; j0 < n_src; j0 += kBatch) {
-    u32x4 rv[kBatch][U];
-#pragma unroll
-    for (uint32_t b = 0; b < kBatch; ++b) {
-      if (j0 + b < n_src) {
-        const u32x4* rp = reinterpret_cast<const u32x4*>(g.recv + wave_uniform(src[j0 + b])) + v0 + lane;
-#pragma unroll
-        for (int i = 0; i < U; ++i) {
-          rv[b][i] = u32x4{0u, 0u, 0u, 0u};
-          if (live[i]) rv[b][i] = __builtin_nontemporal_load(rp + i * 64);
-        }
-      }
-    }
-#pragma unroll
-    for (uint32_t b = 0; b < kBatch; ++b) {
-      if (j0 + b < n_src) {
-#pragma unroll
-        for (int i = 0; i < U; ++i) {
-          Op::fold(st[i][0], rv[b][i].x); Op::fold(st[i][1], rv[b][i].y);
-          Op::fold(st[i][2], rv[b][i].z); Op::fold(st[i][3], rv[b][i].w);
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < U; ++i) {
-    if (!live[i]) continue;
+    if (!u.live[i]) continue;
     u32x4 t;
-    t.x = Op::close(st[i][0]); t.y = Op::close(st[i][1]); t.z = Op::close(st[i][2]); t.w = Op::close(st[i][3]);
+    t.x = Op::close(u.st[i][0]); t.y = Op::close(u.st[i][1]); t.z = Op::close(u.st[i][2]); t.w = Op::close(u.st[i][3]);
     if (keep) ap[i * 64] = t;
     if (fwd) __builtin_nontemporal_store(t, op + i * 64);
   }
@@ -659,7 +670,7 @@ __device__ __forceinline__ void gather_unit(const GatherArgs& g, uint64_t dst, u
     else a_el = *reinterpret_cast<const uint16_t*>(g.acc + dst + off);
     typename Op::State t = Op::open(a_el);
     for (uint32_t j = 0; j < n_src; ++j) {
-      const char* rp = g.recv + wave_uniform(src[j]) + off;
+      const char* rp = g.recv + src(j) + off;
       uint32_t r_el;
       if constexpr (Op::kEs == 4) r_el = *reinterpret_cast<const uint32_t*>(rp);
       else r_el = *reinterpret_cast<const uint16_t*>(rp);
@@ -674,6 +685,16 @@ __device__ __forceinline__ void gather_unit(const GatherArgs& g, uint64_t dst, u
       if (fwd) *reinterpret_cast<uint16_t*>(g.out + (out & ~UCCL_FORWARD_ONLY) + off) = static_cast<uint16_t>(res);
     }
   }
+}
+
+// Both, with the sources' offsets in memory (src[], the same address in every lane).
+template <int U, class Op>
+__device__ __forceinline__ void gather_unit(const GatherArgs& g, uint64_t dst, uint64_t out, uint32_t len,
+                                            uint32_t n_src, const uint64_t* src, uint32_t v0, uint32_t lane) {
+  const auto at = [src](uint32_t j) { return wave_uniform(src[j]); };
+  GatherUnit<U, Op> t;
+  gather_fold<U, UCCL_GATHER_BATCH, Op>(g, t, dst, len, n_src, at, v0, lane);
+  gather_store<U, Op>(g, t, dst, out, len, n_src, at, v0, lane);
 }
 
 template <int T>
@@ -758,18 +779,22 @@ __global__ void __launch_bounds__(NT) chunk_gather_kernel(const GatherArgs g) {
 // A call of few multi-source records: `parts` workgroups per record share its units (one compute
 // unit reads a record's n + 1 streams far below its share of the memory system's rate: eight
 // records of 128 KiB from seven senders take 25 us uncut).  The record's fate is decided once, by
-// the first part to arrive (see claim_enter); blockIdx.x = record * parts + part.
+// the first part to arrive (see claim_enter); blockIdx.x = record * parts + part.  As in
+// chunk_few_kernel every wavefront reads the record for itself and folds its first unit before the fate is
+// known, so that the loads and the decision overlap (event pairs, seven sources, decided first -> folded first:
+// 8 x 32 KiB 7.3 -> 6.7 us, 65 x 32 KiB 8.7 -> 8.0, 65 x 128 KiB 17.5 -> 16.1; three, 128 x 32 KiB 8.4 -> 7.6).
 template <int NT, int U, class Op>
 __global__ void __launch_bounds__(NT) chunk_gather_parts_kernel(const GatherArgs g) {
   constexpr uint32_t kUnit = 64u * U;
   constexpr uint32_t kWaves = NT / 64;
-  __shared__ uint64_t s_src[UCCL_MAX_SOURCES];
+  constexpr int kBatch = 8 / U;
   __shared__ uint32_t s_win;
   const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63u;
   const uint32_t k = blockIdx.x / g.parts, part = blockIdx.x % g.parts;   // the launch has n_descs * parts workgroups
   const uccl_gather_desc* d = g.descs + k;
   const u32x4* p = reinterpret_cast<const u32x4*>(d);
   const u32x4 lo = p[0], hi = p[1];   // every lane reads the same 32 bytes
+  const uint64_t so = d->src_off[lane & (UCCL_MAX_SOURCES - 1u)];   // lane j holds source j, named or not
   const uint64_t dst = wave_uniform(lo.x | (static_cast<uint64_t>(lo.y) << 32));
   const uint64_t out = wave_uniform(lo.z | (static_cast<uint64_t>(lo.w) << 32));
   const uint32_t len = __builtin_amdgcn_readfirstlane(hi.x);
@@ -777,37 +802,39 @@ __global__ void __launch_bounds__(NT) chunk_gather_parts_kernel(const GatherArgs
   const uint32_t n_src = __builtin_amdgcn_readfirstlane(hi.z);
   const uint32_t vecs = (len >> 4) + ((len & 15u) != 0u ? 1u : 0u);
   const uint32_t total = (vecs + kUnit - 1u) / kUnit;
-  if (wave == 0) {
-    bool ok = gather_ok<Op::kEs>(g, dst, out, len, seq, n_src);
-    bool src_ok = true;
-    if (lane < UCCL_MAX_SOURCES && lane < n_src) {  // lane j checks and stages source j
-      const uint64_t so = d->src_off[lane];
-      s_src[lane] = so;
-      src_ok = gather_source_ok(g, so, len);
-    }
-    ok = ok && __all(src_ok);
-    if (lane == 0) {
-      uint32_t win = 0u;
-      unsigned long long* const claim = g.claims + static_cast<size_t>(k) * UCCL_CLAIM_STRIDE;
-      const unsigned long long entered = claim_enter(claim, g.tag);
-      if (claim_decides(entered, g.tag)) {
-        if (ok) {
-          const uint32_t bit = 1u << (seq & 31u);
-          win = (atomicOr(g.bitmap + (seq >> 5), bit) & bit) == 0u ? 1u : 0u;
-        } else if (g.rejected != nullptr) {
-          atomicAdd(g.rejected, 1u);
-        }
-        claim_publish(claim, g.tag, win != 0u);
-      } else if (ok && part * kWaves < total) {  // a part without units has nothing to wait for
-        win = claim_await(claim, entered, g.tag, g.faults) ? 1u : 0u;
+  const bool ok = gather_ok<Op::kEs>(g, dst, out, len, seq, n_src) && __all(lane >= n_src || gather_source_ok(g, so, len));
+  const auto src = [so](uint32_t j) {
+    const uint32_t a = __builtin_amdgcn_readlane(static_cast<uint32_t>(so), j), b = __builtin_amdgcn_readlane(static_cast<uint32_t>(so >> 32), j);
+    return a | (static_cast<uint64_t>(b) << 32);
+  };
+  const uint32_t u0 = part * kWaves + wave;
+  const bool have = ok && u0 < total;
+  GatherUnit<U, Op> t;
+  if (have) gather_fold<U, kBatch, Op>(g, t, dst, len, n_src, src, u0 * kUnit, lane);   // in bounds whatever the record's fate
+  if (tid == 0) {
+    uint32_t win = 0u;
+    unsigned long long* const claim = g.claims + static_cast<size_t>(k) * UCCL_CLAIM_STRIDE;
+    const unsigned long long entered = claim_enter(claim, g.tag);
+    if (claim_decides(entered, g.tag)) {
+      if (ok) {
+        const uint32_t bit = 1u << (seq & 31u);
+        win = (atomicOr(g.bitmap + (seq >> 5), bit) & bit) == 0u ? 1u : 0u;
+      } else if (g.rejected != nullptr) {
+        atomicAdd(g.rejected, 1u);
       }
-      s_win = win;
+      claim_publish(claim, g.tag, win != 0u);
+    } else if (ok && part * kWaves < total) {  // a part without units has nothing to wait for
+      win = claim_await(claim, entered, g.tag, g.faults) ? 1u : 0u;
     }
+    s_win = win;
   }
   __syncthreads();
   if (s_win == 0u) return;   // uniform over the workgroup
-  for (uint32_t u = part * kWaves + wave; u < total; u += kWaves * g.parts)
-    gather_unit<U, Op>(g, dst, out, len, n_src, s_src, u * kUnit, lane);
+  if (have) gather_store<U, Op>(g, t, dst, out, len, n_src, src, u0 * kUnit, lane);
+  for (uint32_t u = u0 + kWaves * g.parts; u < total; u += kWaves * g.parts) {
+    gather_fold<U, kBatch, Op>(g, t, dst, len, n_src, src, u * kUnit, lane);
+    gather_store<U, Op>(g, t, dst, out, len, n_src, src, u * kUnit, lane);
+  }
 }
 
 // A call of much payload: order and stream, as above.  What bounds it is the same, and a workgroup of 4 KiB

@@ -133,7 +133,7 @@ def test_calls_in_turn_share_a_region(gpu_lib):
 @pytest.mark.parametrize("spread", sorted(SPREAD))
 @pytest.mark.parametrize("dtype,op,n_src", [(F32, SUM, 16), (BF16, SUM, 7), (F16, MIN, 1), (I32, PROD, 3), (BF16, MAX, 5)])
 def test_gather_random(gpu_lib, spread, dtype, op, n_src):
-    """The multi-source fold in destination order: ragged and empty chunks, repeats, forwarding, relays and
+    """The multi-source fold in destination order, and cut into small parts: ragged and empty chunks, repeats, forwarding, relays and
     records with a bad source, against the oracle and against the form it replaces."""
     import torch
     from gpuhelp import to_dev
@@ -155,9 +155,13 @@ def test_gather_random(gpu_lib, spread, dtype, op, n_src):
         good = d[~bad]
         acc, out, seen = w["acc"].copy(), np.full(max(w["out_bytes"], 16), 0xA5, dtype=np.uint8), oracle.new_seen(bits)
         oracle.reduce_gather(acc, out, w["recv"], good, seen, dtype, op)
-        for opts in ((hint_for(n), 0), (hint_for(n), 1)):
+        # ordered; uncut; and small chunks in parts of 4 KiB (records longer than stated are walked)
+        for opts in ((hint_for(n), 0), (hint_for(n), 1), (4096, 0), (9008, 0), (20000, 0)):
             print(spread, dtype, op, seed, n, opts, flush=True)
-            assert (pkg.uccl_launch_ordered(n, opts, gather=True) > 0) == (opts[1] == 0)
+            assert (pkg.uccl_launch_ordered(n, opts, gather=True) > 0) == (opts == (hint_for(n), 0))
+            if opts[0] <= 20000:
+                plan = pkg.uccl_launch_plan(n, opts, gather=True)
+                assert (plan["kernel"] == "chunk_gather_parts_kernel") == (n <= 288) and (n > 288 or plan["parts"] == -(-opts[0] // 4096))
             da, do, dr, dd = to_dev(w["acc"]), torch.full((len(out),), 0xA5, dtype=torch.uint8, device="cuda"), to_dev(w["recv"]), to_dev(d)
             bitmap, rejected = torch.zeros((bits + 31) // 32, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
             pkg.uccl_chunk_reduce_gather(da, do, dr, dd, n, bitmap, dtype, op, n_rejected=rejected, n_bits=bits, opts=opts)
