@@ -106,16 +106,19 @@ uint32_t tiles_for(uint32_t n_descs, uint32_t tile) {
 // ---- claim words for records cut into parts ---------------------------------------------------
 //
 // Scratch memory of the split launch (see claim_enter): one 64-bit word per record of the call,
-// on a 128-byte line of its own.  The library owns one pool per device (16 MiB), made at the first
+// on a 128-byte line of its own.  Ordered calls keep their table in the same words
+// (chunk_order_kernel), the acknowledgement report its segments' counts (ack_segments_kernel); every
+// word carries the tag of the call that wrote it in bits 16 and up, whatever the call, so each kind
+// finds the others' words stale.  The library owns one pool per device (16 MiB), made at the first
 // call that needs it (or by uccl_init) and kept until the process ends: kRegions regions for
-// kRegionRecords records each, one region per stream
-// handle that has issued a split call.  Calls on one stream run in order, so they can share a
-// region; calls on different streams may overlap, so they never do.  A call whose stream finds
-// no free region, or that is being captured into a graph (a replay would carry the captured tag
-// again, and could overlap with anything), is launched with one workgroup per record.
+// kRegionRecords records each, one region per stream handle that has issued such a call.  Calls on
+// one stream run in order, so they can share a region; calls on different streams may overlap, so
+// they never do.  A call whose stream finds no free region, or that is being captured into a graph
+// (a replay would carry the captured tag again, and could overlap with anything), is launched in the
+// form that needs none.
 //
 // Tags must grow in the order in which the calls that share a word run.  They come from one
-// process-wide counter, and a split call draws its tag and enqueues its launch while holding the
+// process-wide counter, and such a call draws its tag and enqueues its launches while holding the
 // device's launch lock, so on any one stream the later launch always carries the larger tag, also
 // when several host threads issue calls on that stream.
 constexpr uint32_t kRegionRecords = 2048;  // most records a split call can have
