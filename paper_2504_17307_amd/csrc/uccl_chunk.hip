@@ -137,6 +137,26 @@ struct ClaimPool {
 ClaimPool g_pools[kMaxDevices];
 std::atomic<unsigned long long> g_next_tag{2};  // tags are unique across streams, devices and threads; 1 is for captured calls
 
+// Zeroed device memory, ready for every stream when this returns.  Cleared on a stream of its own, which waits
+// for nobody and which nobody waits for, and with the thread's capture checks relaxed: another stream of the
+// program may be under capture, and neither the allocation nor the wait concerns it.
+void* zeroed_memory(size_t bytes) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  void* mem = nullptr;
+  hipStream_t own = nullptr;
+  bool ok = hipMalloc(&mem, bytes) == hipSuccess;
+  if (ok) {
+    ok = hipStreamCreateWithFlags(&own, hipStreamNonBlocking) == hipSuccess && hipMemsetAsync(mem, 0, bytes, own) == hipSuccess &&
+         hipStreamSynchronize(own) == hipSuccess;
+    if (own != nullptr) (void)hipStreamDestroy(own);
+    if (!ok) (void)hipFree(mem);
+  }
+  if (!ok) (void)hipGetLastError();
+  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return ok ? mem : nullptr;
+}
+
 unsigned long long* pool_base(int dev, bool may_allocate) {
   ClaimPool& p = g_pools[dev];
   unsigned long long* b = p.base.load(std::memory_order_acquire);
@@ -144,15 +164,9 @@ unsigned long long* pool_base(int dev, bool may_allocate) {
   std::lock_guard<std::mutex> hold(p.lock);
   b = p.base.load(std::memory_order_acquire);
   if (b != nullptr) return b;
-  void* mem = nullptr;
-  if (hipMalloc(&mem, kPoolBytes) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
-  if (hipMemset(mem, 0, kPoolBytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
-    (void)hipGetLastError();
-    (void)hipFree(mem);
-    return nullptr;
-  }
-  p.base.store(static_cast<unsigned long long*>(mem), std::memory_order_release);
-  return static_cast<unsigned long long*>(mem);
+  b = static_cast<unsigned long long*>(zeroed_memory(kPoolBytes));
+  if (b != nullptr) p.base.store(b, std::memory_order_release);
+  return b;
 }
 
 uint32_t* pool_faults(unsigned long long* base) {
