@@ -36,11 +36,11 @@ METRIC = "reduced payload GB/s (dedup+place+reduce+forward of one rank's chunk s
 # kernel source it was measured on, identified by the hash of the HIP source files.
 MEASURED_TRAFFIC = {
     # (workload, source_hash() of the files under csrc/): bytes per launch
-    ("config1", "f7b813b2d90af113"): 14888152,
-    ("config2", "f7b813b2d90af113"): 1008563096,
-    ("config3", "f7b813b2d90af113"): 3626326858,
-    ("config4", "f7b813b2d90af113"): 108179920,
-    ("direct-rs", "f7b813b2d90af113"): 1208717772,
+    ("config1", "e3cdccda022a1ee5"): 14888152,
+    ("config2", "e3cdccda022a1ee5"): 1008563096,
+    ("config3", "e3cdccda022a1ee5"): 3626326858,
+    ("config4", "e3cdccda022a1ee5"): 108179920,
+    ("direct-rs", "e3cdccda022a1ee5"): 1208717772,
 }
 
 WORKLOADS = {

@@ -183,7 +183,10 @@ unsigned long long* claim_region(hipStream_t stream, uint32_t** faults, ClaimPoo
   unsigned long long* base = pool_base(dev, true);
   if (base == nullptr) return nullptr;
   ClaimPool& p = g_pools[dev];
-  const uintptr_t key = reinterpret_cast<uintptr_t>(stream) + 1;  // 0 marks a free entry; the null stream is 1
+  // 0 marks a free entry; the null stream is 1.  hipStreamPerThread is one handle for a stream of each thread, and
+  // those may overlap: each thread has a region of its own for it.
+  static thread_local char t_this_thread;
+  const uintptr_t key = 1 + (stream == hipStreamPerThread ? reinterpret_cast<uintptr_t>(&t_this_thread) : reinterpret_cast<uintptr_t>(stream));
   uint32_t n = p.n_streams.load(std::memory_order_acquire);
   uint32_t at = kRegions;
   for (uint32_t i = 0; i < n; ++i)

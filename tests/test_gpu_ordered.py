@@ -168,3 +168,41 @@ def test_gather_random(gpu_lib, spread, dtype, op, n_src):
             torch.cuda.synchronize()
             assert np.array_equal(da.cpu().numpy(), acc.view(np.uint8)) and np.array_equal(do.cpu().numpy(), out)
             assert np.array_equal(bitmap.cpu().numpy(), oracle.pack_bitmap(seen).view(np.int32)) and int(rejected) == int(bad.sum())
+
+
+@pytest.mark.gpu
+def test_per_thread_streams_do_not_share_scratch_words(gpu_lib):
+    """hipStreamPerThread is one handle for as many streams as there are threads: ordered calls of several
+    threads on it run side by side, each with a table of its own."""
+    import threading
+    import torch
+    from gpuhelp import to_dev
+    per_thread, rounds, failed = 2, 12, []
+    work = []
+    for k in range(4):
+        w = random_stream(950 + k, F32, SUM, max_chunks=300, max_len=20000)
+        e, seen = w["acc"].copy(), oracle.new_seen(w["n_bits"])
+        o = np.zeros(w["out_bytes"], dtype=np.uint8)
+        oracle.apply(e, o, w["recv"], w["descs"], seen, F32, SUM)
+        work.append((w, e, [(to_dev(w["acc"]), torch.zeros(w["out_bytes"], dtype=torch.uint8, device="cuda"),
+                             torch.zeros((w["n_bits"] + 31) // 32, dtype=torch.int32, device="cuda")) for _ in range(rounds)], to_dev(w["recv"]), to_dev(w["descs"])))
+    torch.cuda.synchronize()
+
+    def issue(w, sets, recv, descs):
+        try:
+            torch.cuda.set_device(0)
+            n = len(w["descs"])
+            for acc, out, bitmap in sets:
+                pkg.uccl_chunk_apply_opts(acc, out, recv, descs, n, bitmap, F32, SUM, opts=(hint_for(n), 0), stream=per_thread)
+        except Exception as e:  # noqa: BLE001 - reported by the main thread
+            failed.append(e)
+    threads = [threading.Thread(target=issue, args=(w, sets, recv, descs)) for w, _, sets, recv, descs in work]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not failed, failed
+    for k, (w, e, sets, _, _) in enumerate(work):
+        for r, (acc, _, _) in enumerate(sets):
+            assert np.array_equal(acc.cpu().numpy(), e.view(np.uint8)), (k, r)
