@@ -132,7 +132,8 @@ typedef struct uccl_launch_opts {
  *
  * Returns UCCL_OK (also for n_descs == 0, which enqueues nothing) or a negative code;
  * on error nothing has been enqueued.  One launch covers the whole call with one workgroup
- * per 1..32 records; a record count whose workgroup count exceeds what the device accepts
+ * per 1..32 records (or several per record, or a pair of launches for every 16383 records; see
+ * "Scratch memory"); a record count whose workgroup count exceeds what the device accepts
  * in one launch comes back as UCCL_ELAUNCH (split the call).
  *
  * Scratch memory.  A call of few large records (at most 16 MiB of payload in chunks above 32 KiB, or at
@@ -142,11 +143,13 @@ typedef struct uccl_launch_opts {
  * own) in a pool the library allocates once per device (16 MiB + 8 bytes, hipMalloc at the first
  * such call or in uccl_init, kept until the process ends).  The pool has one region per stream
  * handle (hipStreamPerThread: per thread), for the first 64 that issue such a call on the device; a
- * region is never given back, so do not destroy a stream while such a call is still running on it (a stream created
- * next may be given the same handle, and with it the region).  If the pool cannot be had, the
- * stream is the 65th or later, or the stream is being
- * captured into a graph, the call is launched with one workgroup per record instead: slower,
- * same result.  Apart from that one-time allocation no data-path call allocates.
+ * region is never given back, so do not destroy a stream while such a call is still running on it
+ * (a stream created next may be given the same handle, and with it the region).  A call that is
+ * streamed in destination order (uccl_launch_opts) keeps that order in the same region, and
+ * uccl_dedup_report its counts.  If the pool cannot be had, the stream is the 65th or later, or the
+ * stream is being captured into a graph, the call is launched in the form that needs no scratch
+ * memory instead (one workgroup per record or per tile of records): slower, same result.  Apart from
+ * that one-time allocation no data-path call allocates.
  */
 int uccl_chunk_apply(void* acc, void* out_stage, const void* recv_stage,
                      const uccl_chunk_desc* descs, uint32_t n_descs, uint32_t* dedup_bitmap,
