@@ -364,11 +364,15 @@ constexpr uint32_t kOrderCopyChunk = 64u << 10;        // copies: chunks of this
 constexpr uint64_t kOrderCopyBytes = 192ull << 20;     // smaller ones from here on
 constexpr uint32_t kOrderUnknownRecords = 3072;        // chunk size unknown: from this many records to one table full
 constexpr uint32_t kOrderUnknownParts = 4;
+constexpr uint32_t kMaxLaunchThreads = 0xFFFFFFFFu;    // HIP counts a launch's threads in 32 bits
 constexpr uint32_t kOrderMaxParts = 64;   // longer records are walked: keeps the grid far below a launch's limit
 
 uint32_t ordered_launches(uint32_t n_descs, const Tuning& tune, bool reads_acc, bool gather) {
   if (tune.parts == 0u && tune.chunk_bytes == 0u && !gather) return n_descs >= kOrderUnknownRecords && n_descs <= kOrderRecords ? 1u : 0u;
   if (tune.parts != 0u || tune.chunk_bytes < kOrderChunk || n_descs == 0u) return 0u;
+  // A count that is too large for the form of one launch is refused there, before anything is enqueued: a count that
+  // is none (-1) must not become a quarter of a million launches.
+  if (tiles_for(n_descs, flat_tile(n_descs, tune.chunk_bytes)) > kMaxLaunchThreads / UCCL_FLAT_THREADS) return 0u;
   const uint32_t launches = (n_descs - 1u) / kOrderRecords + 1u;
   const uint64_t least = reads_acc || tune.chunk_bytes >= kOrderCopyChunk ? kOrderBytes : kOrderCopyBytes;
   return static_cast<uint64_t>(n_descs / launches) * tune.chunk_bytes >= least ? launches : 0u;

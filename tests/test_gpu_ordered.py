@@ -27,7 +27,12 @@ def test_rule():
     assert ordered(1 << 20, (32 * KiB, 1)) == 0                                          # parts stated
     assert [ordered(n, None) for n in (3071, 3072, TABLE, TABLE + 1)] == [0, 1, 1, 0]    # no size given
     assert ordered(5000, (0, 0), gather=True) == 0 and ordered(5000, (0, 1)) == 0
-    assert ordered(0, (32 * KiB, 0)) == 0 and ordered(2 ** 32 - 1, (32 * KiB, 0)) == -(-(2 ** 32 - 1) // TABLE)
+    assert ordered(0, (32 * KiB, 0)) == 0
+    # counts that one workgroup per record (two records of 16 KiB) could not be launched for are refused, not split
+    most = 2 ** 22 - 1
+    assert ordered(most, (32 * KiB, 0)) == -(-most // TABLE) and ordered(most + 1, (32 * KiB, 0)) == 0 and ordered(2 ** 32 - 1, (32 * KiB, 0)) == 0
+    assert ordered(2 * most, (16 * KiB, 0)) == -(-2 * most // TABLE) and ordered(2 * most + 1, (16 * KiB, 0)) == 0
+    assert ordered(most, (32 * KiB, 0), gather=True) > 0 and ordered(most + 1, (128 * KiB, 0), gather=True) == 0
     assert ordered(3072, (32 * KiB, 0), gather=True) == 1 and ordered(3071, (32 * KiB, 0), gather=True, reads_acc=False) == 0
 
 

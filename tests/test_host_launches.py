@@ -1,0 +1,97 @@
+"""What the library asks of the HIP runtime, call by call: launches, allocations, scratch words.  The runtime is
+tests/hip_stub.c, so nothing runs and no GPU is needed; each test's body runs in a process of its own, where
+the stub is loaded first and serves the library by its soname."""
+import ctypes as C
+import os
+import subprocess
+import sys
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, ROOT)
+import paper_2504_17307_amd as pkg  # noqa: E402
+
+KiB, MiB = 1 << 10, 1 << 20
+A, OUT, RECV, DESCS, BITS, REPORT = (0x100000 * k for k in range(1, 7))   # addresses; nothing is read from them
+
+
+class Runtime:
+    """The stub and the library on it.  `launches`: (kernel, grid, block, lds, stream, scratch), one per accepted
+    launch; `calls`: the other runtime calls by name.  `answer[name]`: what a call returns (a number or a function
+    of its subject); `refuse(kernel, start, stop)`: the launches to turn down."""
+
+    def __init__(self, stub):
+        self.stub = C.CDLL(stub, mode=C.RTLD_GLOBAL)
+        self.lib = C.CDLL(pkg.LIB_PATH)
+        for name, (res, args) in pkg._SIGNATURES.items():
+            fn = getattr(self.lib, name)
+            fn.restype, fn.argtypes = res, args
+        self.launches, self.calls, self.answer, self.refuse = [], [], {}, lambda *a: False
+        on_launch = C.CFUNCTYPE(C.c_int, C.c_char_p, C.c_uint, C.c_uint, C.c_uint, C.c_void_p, C.POINTER(C.c_void_p), C.c_void_p, C.c_void_p)
+        on_call = C.CFUNCTYPE(C.c_int, C.c_char_p, C.c_void_p)
+        self.keep = on_launch(self._launch), on_call(self._call)
+        self.stub.stub_callbacks(*self.keep)
+
+    def _launch(self, kernel, grid, block, lds, stream, args, start, stop):
+        name = next((k for k in KERNELS if k.encode() in kernel), kernel.decode())
+        if self.refuse(name, start, stop):
+            return 1
+        scratch = None
+        if name in ("chunk_order_kernel", "chunk_ordered_kernel", "gather_order_kernel", "gather_ordered_kernel"):
+            words = C.cast(args[1], C.POINTER(C.c_uint64))           # OrderArgs: words, spilled, tag
+            scratch = words[0], words[2]
+        elif name == "ack_segments_kernel":
+            scratch = C.cast(args[5], C.POINTER(C.c_uint64))[0], C.cast(args[6], C.POINTER(C.c_uint64))[0]
+        self.launches.append((name, grid, block, lds, stream or 0, scratch))
+        return 0
+
+    def _call(self, name, subject):
+        name = name.decode()
+        self.calls.append(name)
+        a = self.answer.get(name, 0)
+        return a(subject or 0) if callable(a) else a
+
+    def apply(self, n, chunk=None, stream=0, op=0, parts=0):
+        if chunk is None:
+            return self.lib.uccl_chunk_apply(A, OUT, RECV, DESCS, n, BITS, 0, op, stream)
+        return self.lib.uccl_chunk_apply_opts(A, OUT, RECV, DESCS, n, BITS, 0, op, None, None, C.byref(pkg.uccl_launch_opts(chunk, parts)), stream)
+
+    def fold(self, n, chunk, stream=0):
+        return self.lib.uccl_chunk_reduce_gather(A, OUT, RECV, DESCS, n, BITS, 0, 0, None, None, C.byref(pkg.uccl_launch_opts(chunk, 0)), stream)
+
+    def report(self, bits, stream=0):
+        return self.lib.uccl_dedup_report(BITS, bits, REPORT, 4, stream)
+
+    def kernels(self):
+        return [l[0] for l in self.launches]
+
+
+KERNELS = ("chunk_order_kernel", "chunk_ordered_kernel", "gather_order_kernel", "gather_ordered_kernel", "chunk_flat_kernel", "chunk_few_kernel",
+           "chunk_gather_parts_kernel", "chunk_gather_kernel", "ack_segments_kernel", "ack_report_kernel", "fill_words_kernel")
+
+
+def in_process(scenario, tmp_path):
+    stub = str(tmp_path / "libamdhip64.so.7")
+    subprocess.check_call(["gcc", "-O1", "-shared", "-fPIC", "-w", "-I/opt/rocm/include", "-Wl,-soname,libamdhip64.so.7",
+                           os.path.join(ROOT, "tests", "hip_stub.c"), "-o", stub])
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), scenario, stub], cwd=ROOT, capture_output=True, text=True, timeout=110)
+    assert r.returncode == 0 and "SCENARIO DONE" in r.stdout, r.stdout[-2000:] + r.stderr[-4000:]
+
+
+def refused_counts(rt):
+    for n, chunk in ((2 ** 32 - 1, 32 * KiB), (2 ** 32 - 1, 16 * KiB), (2 ** 32 - 1, 128 * KiB), (1 << 23, 128 * KiB), ((1 << 22) + 1, 32 * KiB)):
+        assert rt.apply(n, chunk) == pkg.UCCL_ELAUNCH and rt.fold(n, chunk) == pkg.UCCL_ELAUNCH, (n, chunk)
+        assert not rt.launches
+    assert rt.apply(2 ** 32 - 1) == pkg.UCCL_ELAUNCH and not rt.launches
+    # the largest counts that one workgroup per record (or per two) can be launched for are still taken
+    assert rt.apply((1 << 22) - 1, 32 * KiB) == pkg.UCCL_OK and set(rt.kernels()) == {"chunk_order_kernel", "chunk_ordered_kernel"}
+
+
+def test_record_counts_beyond_one_launch_are_refused_and_nothing_is_enqueued(tmp_path):
+    """A count that is no count of records (-1, say) comes back as an error also where the call would be streamed in
+    destination order, whose launches of 16383 records each would all be accepted."""
+    in_process("refused_counts", tmp_path)
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[1]](Runtime(sys.argv[2]))
+    print("SCENARIO DONE")
