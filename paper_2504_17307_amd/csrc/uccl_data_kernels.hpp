@@ -661,28 +661,36 @@ __device__ __forceinline__ void gather_store(const GatherArgs& g, const GatherUn
     if (keep) ap[i * 64] = t;
     if (fwd) __builtin_nontemporal_store(t, op + i * 64);
   }
-  // the last len % 16 bytes, element by element, by the unit that holds vector index nvec
+  // the last len % 16 bytes, element by element, by the unit that holds vector index nvec.  The whole wavefront walks
+  // the sources (src may read another lane's register); only the loads and stores are the lanes' that have an element.
   const uint32_t rem = len & 15u;
-  if (rem && nvec >= v0 && nvec < v0 + kUnit && lane < rem / Op::kEs) {
+  if (rem && nvec >= v0 && nvec < v0 + kUnit) {
+    const bool mine = lane < rem / Op::kEs;
     const uint64_t off = (static_cast<uint64_t>(nvec) << 4) + lane * Op::kEs;
-    uint32_t a_el;
-    if constexpr (Op::kEs == 4) a_el = *reinterpret_cast<const uint32_t*>(g.acc + dst + off);
-    else a_el = *reinterpret_cast<const uint16_t*>(g.acc + dst + off);
+    uint32_t a_el = 0u;
+    if (mine) {
+      if constexpr (Op::kEs == 4) a_el = *reinterpret_cast<const uint32_t*>(g.acc + dst + off);
+      else a_el = *reinterpret_cast<const uint16_t*>(g.acc + dst + off);
+    }
     typename Op::State t = Op::open(a_el);
     for (uint32_t j = 0; j < n_src; ++j) {
       const char* rp = g.recv + src(j) + off;
-      uint32_t r_el;
-      if constexpr (Op::kEs == 4) r_el = *reinterpret_cast<const uint32_t*>(rp);
-      else r_el = *reinterpret_cast<const uint16_t*>(rp);
+      uint32_t r_el = 0u;
+      if (mine) {
+        if constexpr (Op::kEs == 4) r_el = *reinterpret_cast<const uint32_t*>(rp);
+        else r_el = *reinterpret_cast<const uint16_t*>(rp);
+      }
       Op::fold(t, r_el);
     }
     const uint32_t res = Op::close(t);
-    if constexpr (Op::kEs == 4) {
-      if (keep) *reinterpret_cast<uint32_t*>(g.acc + dst + off) = res;
-      if (fwd) *reinterpret_cast<uint32_t*>(g.out + (out & ~UCCL_FORWARD_ONLY) + off) = res;
-    } else {
-      if (keep) *reinterpret_cast<uint16_t*>(g.acc + dst + off) = static_cast<uint16_t>(res);
-      if (fwd) *reinterpret_cast<uint16_t*>(g.out + (out & ~UCCL_FORWARD_ONLY) + off) = static_cast<uint16_t>(res);
+    if (mine) {
+      if constexpr (Op::kEs == 4) {
+        if (keep) *reinterpret_cast<uint32_t*>(g.acc + dst + off) = res;
+        if (fwd) *reinterpret_cast<uint32_t*>(g.out + (out & ~UCCL_FORWARD_ONLY) + off) = res;
+      } else {
+        if (keep) *reinterpret_cast<uint16_t*>(g.acc + dst + off) = static_cast<uint16_t>(res);
+        if (fwd) *reinterpret_cast<uint16_t*>(g.out + (out & ~UCCL_FORWARD_ONLY) + off) = static_cast<uint16_t>(res);
+      }
     }
   }
 }

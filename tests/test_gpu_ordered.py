@@ -176,6 +176,32 @@ def test_gather_random(gpu_lib, spread, dtype, op, n_src):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("dtype,es", [(F32, 4), (BF16, 2)])
+def test_gather_tails(gpu_lib, dtype, es):
+    """The last len % 16 bytes of a fold of 16 sources, for every such remainder, where fewer lanes have an element than
+    there are sources: cut into parts (the sources' offsets are held one per lane), and uncut."""
+    import torch
+    from gpuhelp import to_dev
+    g, lens = np.random.default_rng(es), [v * 16 + r for v in (0, 1, 63, 64, 65, 255, 256, 300) for r in range(es, 16, es)]
+    n, pitch = len(lens), 4832
+    kind = {F32: np.float32, BF16: np.uint16}[dtype]
+    draw = lambda m: g.random(m, dtype=np.float32).view(np.uint32) if dtype == F32 else (g.random(m, dtype=np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    acc, recv = draw(n * pitch // es).view(kind), draw(3 * n * pitch // es).view(kind)
+    d = np.zeros(n, dtype=GATHER_DESC)
+    d["seq"], d["len"], d["n_src"] = np.arange(n), lens, 16
+    d["dst_off"] = d["out_off"] = np.arange(n, dtype=np.uint64) * pitch
+    d["src_off"] = g.integers(0, 3 * n, (n, 16)) * np.uint64(pitch)
+    e, o, seen = acc.copy(), np.full(n * pitch, 0xA5, dtype=np.uint8), oracle.new_seen(n)
+    oracle.reduce_gather(e, o, recv, d, seen, dtype, SUM)
+    for opts in ((4096, 0), (4832, 0), (65536, 4), (65536, 1)):
+        print(dtype, opts, flush=True)
+        da, do, bitmap = to_dev(acc), torch.full((n * pitch,), 0xA5, dtype=torch.uint8, device="cuda"), torch.zeros((n + 31) // 32, dtype=torch.int32, device="cuda")
+        pkg.uccl_chunk_reduce_gather(da, do, to_dev(recv), to_dev(d), n, bitmap, dtype, SUM, opts=opts)
+        torch.cuda.synchronize()
+        assert np.array_equal(da.cpu().numpy(), e.view(np.uint8)) and np.array_equal(do.cpu().numpy(), o), opts
+
+
+@pytest.mark.gpu
 def test_per_thread_streams_do_not_share_scratch_words(gpu_lib):
     """hipStreamPerThread is one handle for as many streams as there are threads: ordered calls of several
     threads on it run side by side, each with a table of its own."""
