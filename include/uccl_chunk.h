@@ -139,7 +139,7 @@ typedef struct uccl_launch_opts {
  * Scratch memory.  A call of few large records (at most 16 MiB of payload in chunks above 32 KiB, or at
  * most 32 chunks of 32 KiB; at most 128 records when no chunk size is given) is launched with several
  * workgroups per record so that it fills the machine; those workgroups
- * agree on the record's fate through one 64-bit claim word per record (on a 128-byte line of its
+ * agree on the record's fate through two 64-bit claim words per record (on a 128-byte line of their
  * own) in a pool the library allocates once per device (16 MiB + 8 bytes, hipMalloc at the first
  * such call or in uccl_init, kept until the process ends).  The pool has one region per stream
  * handle (hipStreamPerThread: per thread), for the first 64 that issue such a call on the device; a
@@ -173,7 +173,7 @@ int uccl_init(void);
  *   - Every call on a GPU shares that GPU's array, whatever the stream.  A split call may be captured and
  *     replayed: a captured one first clears its own words with a small fill kernel, then runs.
  *     Calls (or replays) that overlap in time on one GPU race on the array: keep them on one
- *     stream, or order them with events (so that they also run in the order in which they were made).
+ *     stream, or order them.  Calls that do not overlap may run in any order.
  */
 #define UCCL_NOALLOC_MAX_DESCS 2048
 int uccl_chunk_apply_noalloc(void* acc, void* out_stage, const void* recv_stage,

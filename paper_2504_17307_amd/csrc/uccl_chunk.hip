@@ -29,7 +29,7 @@
 // kernel, which shortens the chain of latencies instead: one record per workgroup, payload
 // loads issued before the sequence number is decided, and, when the records alone would leave
 // most compute units idle, each record cut into parts over several workgroups that agree on
-// its fate through a claim word in scratch memory (uccl_data_kernels.hpp).  The sender side
+// its fate through claim words in scratch memory (uccl_data_kernels.hpp).  The sender side
 // (tensor range -> staged chunks + send records) and the feedback kernels (acknowledgement
 // report, per-message status) are dense, small kernels of their own.
 #include <hip/hip_runtime.h>
@@ -51,8 +51,8 @@
 #include "uccl_data_kernels.hpp"
 #include "uccl_feedback_kernels.hpp"
 
-// Claim words for uccl_chunk_apply_noalloc (see claim_enter): one per record of a call, each on a
-// 128-byte line of its own, UCCL_NOALLOC_MAX_DESCS of them, then the word that counts parts that
+// Claim words for uccl_chunk_apply_noalloc (see claim_enter): a record's two on a
+// 128-byte line of their own, UCCL_NOALLOC_MAX_DESCS of them, then the word that counts parts that
 // gave up waiting: 256.25 KiB.  Every GPU the
 // library runs on holds its own copy at its own address until the process ends.  In host code
 // this name only stands for the symbol: the device address is looked up per device (static_claims).
@@ -105,8 +105,8 @@ uint32_t tiles_for(uint32_t n_descs, uint32_t tile) {
 
 // ---- claim words for records cut into parts ---------------------------------------------------
 //
-// Scratch memory of the split launch (see claim_enter): one 64-bit word per record of the call,
-// on a 128-byte line of its own.  Ordered calls keep their table in the same words
+// Scratch memory of the split launch (see claim_enter): two 64-bit words per record of the call,
+// on a 128-byte line of their own.  Ordered calls keep their table in the same words
 // (chunk_order_kernel), the acknowledgement report its segments' counts (ack_segments_kernel); every
 // word carries the tag of the call that wrote it in bits 16 and up, whatever the call, so each kind
 // finds the others' words stale.  The library owns one pool per device (16 MiB), made at the first
@@ -117,9 +117,9 @@ uint32_t tiles_for(uint32_t n_descs, uint32_t tile) {
 // (a replay would carry the captured tag again, and could overlap with anything), is launched in the
 // form that needs none.
 //
-// Tags must grow in the order in which the calls that share a word run.  They come from one
-// process-wide counter, and such a call draws its tag and enqueues its launches while holding the
-// device's launch lock, so on any one stream the later launch always carries the larger tag, also
+// Tags come from one process-wide counter.  A call draws its tag and enqueues its launches while holding the
+// device's launch lock: the spill count of an ordered call needs tags that grow in the order in which the calls of a
+// stream run, and the launches of two ordered calls on one stream must not come between each other, also
 // when several host threads issue calls on that stream.
 constexpr uint32_t kRegionRecords = 2048;  // most records a split call can have
 constexpr uint32_t kRegionWords = kRegionRecords * UCCL_CLAIM_STRIDE;
@@ -444,23 +444,20 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
   Plan p = plan_apply(a.n_descs, tune, Op::kReadsAcc);
   if (p.route == kRouteParts) {
     if (tune.static_claims != nullptr) {
-      // Every call shares the device's one array, in the order the calls run: a call draws its tag and is
-      // enqueued under one lock, as with the pool, and finds what earlier ones left stale.
+      // Every call shares the device's one array and finds what other calls left there stale by their tags.
       a.claims = tune.static_claims;
       a.faults = reinterpret_cast<uint32_t*>(tune.static_claims + UCCL_NOALLOC_MAX_DESCS * UCCL_CLAIM_STRIDE);
       a.parts = p.parts;
       hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
       const bool eager = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
       if (eager) {
-        std::lock_guard<std::mutex> in_order(g_static_lock);
         a.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
         return launch_kernel(chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, true>, a.n_descs * p.parts,
                              UCCL_PART_THREADS, s, a);
       }
       (void)hipGetLastError();
       // A captured call carries the same tag in every replay, so it clears its words first, with a fill
-      // kernel (no memset node), and its tag is the one that is larger than a cleared word's and smaller than
-      // any that an eager call draws.  (An eager call without the fill and its gap: 28 + 28 records of 32 KiB,
+      // kernel (no memset node); no eager call draws that tag.  (An eager call without the fill and its gap: 28 + 28 records of 32 KiB,
       // reset included, 15.9 us with it, 11.2 without.)
       a.tag = 1ull;
       const hipEvent_t keep0 = t_start, keep1 = t_stop;  // the timing events belong to the data kernel

@@ -38,10 +38,10 @@
 #define UCCL_XCD_CONTIGUOUS 0   // 1: chunk_flat_kernel gives each of the 8 XCDs one contiguous eighth of the tiles
 #endif
 #ifndef UCCL_CLAIM_STRIDE
-#define UCCL_CLAIM_STRIDE 16    // 64-bit words from one record's claim word to the next: one 128-byte line each
+#define UCCL_CLAIM_STRIDE 16    // 64-bit words from one record's claim words to the next: one 128-byte line each
 #endif
 #ifndef UCCL_CLAIM_SPIN_LIMIT
-#define UCCL_CLAIM_SPIN_LIMIT (1u << 16)  // polls of a claim word before a part gives up (see claim_await)
+#define UCCL_CLAIM_SPIN_LIMIT (1u << 16)  // polls of a claim's outcome before a part gives up (see claim_await)
 #endif
 namespace {
 
@@ -60,7 +60,7 @@ struct Args {
   const uint32_t* n_ptr;  // optional: the record count is read from here (capped by n_descs)
   uint32_t n_descs;
   uint32_t allow_forward;
-  // one record cut into `parts` workgroups (see claim_enter): claims[k] is record k's claim word,
+  // one record cut into `parts` workgroups (see claim_enter): record k's claim words begin at claims[k * UCCL_CLAIM_STRIDE],
   // tag is this call's own value, faults counts parts that gave up waiting for a decision
   unsigned long long* claims;
   uint32_t* faults;
@@ -75,52 +75,54 @@ struct Args {
 // below its share of the memory system's rate.  Such a call is launched with `parts` workgroups
 // per record, and the record's units are dealt over the wavefronts of all of them.  The sequence
 // number must still be decided exactly once, by one atomic OR on the bitmap, and every part that
-// has units must learn the outcome.  Record k of the call has a 64-bit claim word in scratch
-// memory, holding `tag << 16 | state`: the tag of the last call that used the word, and 0 = a part
-// is deciding, 1 = applied, 2 = not applied.
+// has units must learn the outcome.  Record k of the call has two 64-bit claim words in scratch
+// memory: the first holds `tag << 16` of the last call that used it, the second that call's outcome
+// for its record, `tag << 16 | 1` = applied, `| 2` = not applied.  No two calls have the same tag.
 //
-//   enter    every part issues one atomic max of `tag << 16` on the word, after the payload loads of
+//   enter    every part exchanges the first word for `tag << 16`, after the payload loads of
 //            its first unit (memory operations return in order, so entering earlier would hold up
-//            the record itself).  Tags grow from call to call in the order the calls run (the host
-//            draws the tag and enqueues the launch under one lock, and calls that share a word run
-//            on one stream), so exactly one part of the call -- the first to get there -- finds an
-//            older tag in the word: it decides.
+//            the record itself).  Exactly one part of the call -- the first to get there -- finds another
+//            call's tag in the word: it decides.  Which of two calls that share a word was made first
+//            does not matter, only that they do not overlap.
 //   decide   the deciding part issues the bitmap atomic (or rejects the record) and stores
-//            `tag << 16 | outcome`.  It waits for nothing.
-//   await    the other parts poll the word until it carries the call's tag and an outcome.
+//            the outcome in the second word.  It waits for nothing.
+//   await    the other parts poll the second word until it carries the call's tag.
 //
 // A part only ever waits for a part that is already running and never waits itself, so the wait
 // ends whatever order the hardware starts workgroups in.  It is bounded all the same: a part that
 // gives up counts itself in `faults` and streams nothing.  Claim words are read and written with
 // device-scope atomics only, so every part sees the one coherent copy whichever XCD it runs on;
-// each record's word has a 128-byte line to itself (UCCL_CLAIM_STRIDE), because device-scope atomics
+// each record's words have a 128-byte line to themselves (UCCL_CLAIM_STRIDE), because device-scope atomics
 // on one line are served one after the other and a call's parts all arrive at about the same time
 // (57 records x 8 parts: 6.2 us per call with the words packed, 5.4 us with a line each).
-// Nothing is ever cleared between calls: a stale word is recognised by its older tag.  The order table
+// Nothing is ever cleared between calls: a stale word is recognised by its other tag.  The order table
 // of large calls (below) lives in the same words and carries its tag in the same bits, so either kind
 // of call finds the other's leftovers stale.
-__device__ __forceinline__ unsigned long long claim_enter(unsigned long long* claim, unsigned long long tag) {
-  return __hip_atomic_fetch_max(claim, tag << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+struct Claim {
+  bool decides;
+  unsigned long long outcome;   // the second word as it was on entry: the outcome may already be in it
+};
 
-__device__ __forceinline__ bool claim_decides(unsigned long long entered, unsigned long long tag) {
-  return (entered >> 16) < tag;
+__device__ __forceinline__ Claim claim_enter(unsigned long long* claim, unsigned long long tag) {
+  const unsigned long long was = __hip_atomic_exchange(claim, tag << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const unsigned long long outcome = __hip_atomic_load(claim + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return {(was >> 16) != tag, outcome};
 }
 
 __device__ __forceinline__ void claim_publish(unsigned long long* claim, unsigned long long tag, bool win) {
-  __hip_atomic_store(claim, (tag << 16) | (win ? 1ull : 2ull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(claim + 1, (tag << 16) | (win ? 1ull : 2ull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// `seen`: what this part's claim_enter returned (the outcome may already be in it).
+// `seen`: the outcome word as this part's claim_enter found it.
 __device__ __forceinline__ bool claim_await(unsigned long long* claim, unsigned long long seen,
                                             unsigned long long tag, uint32_t* faults) {
-  for (uint32_t polls = 0; (seen >> 16) != tag || (seen & 3ull) == 0ull; ++polls) {
+  for (uint32_t polls = 0; (seen >> 16) != tag; ++polls) {
     if (polls >= UCCL_CLAIM_SPIN_LIMIT) {
       atomicAdd(faults, 1u);
       return false;
     }
     __builtin_amdgcn_s_sleep(1);
-    seen = __hip_atomic_load(claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    seen = __hip_atomic_load(claim + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   return (seen & 3ull) == 1ull;
 }
@@ -515,9 +517,9 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
   }
   if (tid == 0) {
     uint32_t win = 0u;
-    unsigned long long entered = 0ull;
+    Claim entered = {true, 0ull};
     if constexpr (PARTS) entered = claim_enter(claim, g.tag);
-    if (!PARTS || claim_decides(entered, g.tag)) {
+    if (entered.decides) {
       if (ok) {
         const uint32_t bit = 1u << (seq & 31u);
         win = (atomicOr(g.bitmap + (seq >> 5), bit) & bit) == 0u ? 1u : 0u;
@@ -526,7 +528,7 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
       }
       if constexpr (PARTS) claim_publish(claim, g.tag, win != 0u);
     } else if (part_has_units) {  // a part without units has nothing to wait for
-      win = claim_await(claim, entered, g.tag, g.faults) ? 1u : 0u;
+      win = claim_await(claim, entered.outcome, g.tag, g.faults) ? 1u : 0u;
     }
     s_win = win;
   }
@@ -822,8 +824,8 @@ __global__ void __launch_bounds__(NT) chunk_gather_parts_kernel(const GatherArgs
   if (tid == 0) {
     uint32_t win = 0u;
     unsigned long long* const claim = g.claims + static_cast<size_t>(k) * UCCL_CLAIM_STRIDE;
-    const unsigned long long entered = claim_enter(claim, g.tag);
-    if (claim_decides(entered, g.tag)) {
+    const Claim entered = claim_enter(claim, g.tag);
+    if (entered.decides) {
       if (ok) {
         const uint32_t bit = 1u << (seq & 31u);
         win = (atomicOr(g.bitmap + (seq >> 5), bit) & bit) == 0u ? 1u : 0u;
@@ -832,7 +834,7 @@ __global__ void __launch_bounds__(NT) chunk_gather_parts_kernel(const GatherArgs
       }
       claim_publish(claim, g.tag, win != 0u);
     } else if (ok && part * kWaves < total) {  // a part without units has nothing to wait for
-      win = claim_await(claim, entered, g.tag, g.faults) ? 1u : 0u;
+      win = claim_await(claim, entered.outcome, g.tag, g.faults) ? 1u : 0u;
     }
     s_win = win;
   }

@@ -1,5 +1,5 @@
-"""Eager and captured calls of the no-allocation entry point in turn: they share one array of claim words,
-the eager ones with tags that grow, the captured ones with words they clear."""
+"""Calls of the no-allocation entry point share one array of claim words: eager and captured calls in turn (the
+captured ones clear their words first), and calls that run in another order than they were made."""
 import pytest
 import torch
 
@@ -41,4 +41,37 @@ def test_eager_calls_between_replays(gpu_lib):
         run.acc.copy_(acc0)
         graph.replay()
         check(run, captured, f"replay {turn}")
+    assert gpu_lib.uccl_claim_timeouts() == 0
+
+
+def test_calls_that_run_in_another_order_than_they_were_made(gpu_lib):
+    """A call held back on its stream is overtaken by one that was made after it on another stream: both are applied
+    whole, whichever of them the array's words remember."""
+    held_back, overtaking = wl.config1(seed=19), wl.config1(seed=20)
+    want = [oracle_results(w) for w in (held_back, overtaking)]
+    runs = [DeviceRun(w) for w in (held_back, overtaking)]
+    gate, first, second = (torch.cuda.Stream() for _ in range(3))
+    a = torch.randn(8192, 8192, device="cuda")
+    opened = torch.cuda.Event()
+
+    def issue(run, w, stream):
+        for ph, d in zip(w.phases, run.descs):
+            gpu_lib.uccl_chunk_apply_noalloc(run.acc, run.out, run.recv, d, len(ph.descs), run.bitmap, w.dtype, ph.op, stream=stream)
+
+    torch.mm(a, a)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(gate):
+        for _ in range(40):                         # some hundred milliseconds of other work
+            torch.mm(a, a)
+        opened.record()
+    first.wait_event(opened)
+    issue(runs[0], held_back, first)
+    issue(runs[1], overtaking, second)
+    second.synchronize()
+    overtaken = not opened.query()
+    torch.cuda.synchronize()
+    assert overtaken, "the first call was not held back long enough: nothing shown"
+    for run, w, expected in zip(runs, (held_back, overtaking), want):
+        for got, exp, name in zip(run.results(), expected, ("acc", "out_stage", "bitmap")):
+            assert_same(got, exp, f"{w.name}: {name}")
     assert gpu_lib.uccl_claim_timeouts() == 0
