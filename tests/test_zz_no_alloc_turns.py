@@ -1,5 +1,7 @@
 """Calls of the no-allocation entry point share one array of claim words: eager and captured calls in turn (the
 captured ones clear their words first), and calls that run in another order than they were made."""
+import time
+
 import pytest
 import torch
 
@@ -50,22 +52,31 @@ def test_calls_that_run_in_another_order_than_they_were_made(gpu_lib):
     held_back, overtaking = wl.config1(seed=19), wl.config1(seed=20)
     want = [oracle_results(w) for w in (held_back, overtaking)]
     runs = [DeviceRun(w) for w in (held_back, overtaking)]
-    gate, first, second = (torch.cuda.Stream() for _ in range(3))
-    a = torch.randn(8192, 8192, device="cuda")
-    opened = torch.cuda.Event()
+    first, opened = torch.cuda.Stream(), torch.cuda.Event()
+    a, x = torch.randn(8192, 8192, device="cuda"), torch.zeros(64, device="cuda")
 
     def issue(run, w, stream):
         for ph, d in zip(w.phases, run.descs):
             gpu_lib.uccl_chunk_apply_noalloc(run.acc, run.out, run.recv, d, len(ph.descs), run.bitmap, w.dtype, ph.op, stream=stream)
 
+    def overtakes(stream):                          # streams share hardware queues: one that does not wait behind `first`
+        done = torch.cuda.Event()
+        with torch.cuda.stream(stream):
+            x.add_(1.0)
+            done.record()
+        end = time.monotonic() + 0.02
+        while not done.query() and time.monotonic() < end:
+            pass
+        return done.query()
+
     torch.mm(a, a)
     torch.cuda.synchronize()
-    with torch.cuda.stream(gate):
-        for _ in range(40):                         # some hundred milliseconds of other work
+    with torch.cuda.stream(first):
+        for _ in range(60):                         # some hundred milliseconds of other work
             torch.mm(a, a)
         opened.record()
-    first.wait_event(opened)
     issue(runs[0], held_back, first)
+    second = next(s for s in (torch.cuda.Stream() for _ in range(8)) if overtakes(s))
     issue(runs[1], overtaking, second)
     second.synchronize()
     overtaken = not opened.query()
