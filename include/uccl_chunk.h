@@ -76,7 +76,7 @@ enum {
   UCCL_EINVAL = -1,  /* null pointer with n_descs > 0, unknown dtype/op, bad launch options, aliasing buffers */
   UCCL_EALIGN = -2,  /* a base pointer is not 16-byte aligned (bitmap / counter: 4-byte) */
   UCCL_ELAUNCH = -3, /* HIP refused the launch; uccl_last_error_detail() has HIP's message */
-  UCCL_ENOMEM = -4,  /* uccl_feed_create / uccl_init could not get host, pinned or device memory */
+  UCCL_ENOMEM = -4,  /* uccl_feed_create could not get host, pinned or device memory */
   UCCL_ETOOBIG = -5  /* more records than the entry point's stated maximum: split the call */
 };
 
@@ -140,36 +140,34 @@ typedef struct uccl_launch_opts {
  * most 32 chunks of 32 KiB; at most 128 records when no chunk size is given) is launched with several
  * workgroups per record so that it fills the machine; those workgroups
  * agree on the record's fate through two 64-bit claim words per record (on a 128-byte line of their
- * own) in a pool the library allocates once per device (16 MiB + 8 bytes, hipMalloc at the first
- * such call or in uccl_init, kept until the process ends).  The pool has one region per stream
+ * own) in an array inside the library's code object (16 MiB on every GPU the library runs on, until the process
+ * ends).  It has one region per stream
  * handle (hipStreamPerThread: per thread), for the first 64 that issue such a call on the device; a
  * region is never given back, so do not destroy a stream while such a call is still running on it
  * (a stream created next may be given the same handle, and with it the region).  A call that is
  * streamed in destination order (uccl_launch_opts) keeps that order in the same region, and
- * uccl_dedup_report its counts.  If the pool cannot be had, the stream is the 65th or later, or the
- * stream is being captured into a graph, the call is launched in the form that needs no scratch
- * memory instead (one workgroup per record or per tile of records): slower, same result.  Apart from
- * that one-time allocation no data-path call allocates.
+ * uccl_dedup_report its counts.  If the stream is the 65th or later, or is being captured into a graph, the
+ * call is launched in the form that needs no scratch
+ * memory instead (one workgroup per record or per tile of records): slower, same result.  No
+ * data-path call allocates; the first call on a device loads the library's code object.
  */
 int uccl_chunk_apply(void* acc, void* out_stage, const void* recv_stage,
                      const uccl_chunk_desc* descs, uint32_t n_descs, uint32_t* dedup_bitmap,
                      uccl_dtype dtype, uccl_op op, void* stream);
 
-/* Eagerly make the current device's claim pool (see "Scratch memory" above) and look up the
- * address of the array uccl_chunk_apply_noalloc uses, so that no later call allocates or loads
- * anything.  Idempotent; UCCL_OK or a negative code.  Utility, no passage of the paper. */
+/* Load the library's code object on the current device and look up the addresses of its scratch memory
+ * (see above), so that no later call has to.  Idempotent; UCCL_OK or a negative code.  Utility, no passage
+ * of the paper. */
 int uccl_init(void);
 
 /*
  * uccl_chunk_apply_noalloc -- uccl_chunk_apply for callers that cannot allocate device memory:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
  * operation and result; the claim words of records cut into parts (see "Scratch memory" above)
- * live in an array inside the library's code object instead of the pool: UCCL_NOALLOC_MAX_DESCS
- * lines of 128 bytes + 256 bytes = 256.25 KiB, held by every GPU the library runs on until the
- * process ends.  The call makes no hipMalloc / hipFree and creates no pool; the first call on a device
- * (or uccl_init) looks the array's device address up.
+ * live in an array that needs no region: UCCL_NOALLOC_MAX_DESCS
+ * lines of 128 bytes + 256 bytes = 256.25 KiB, held like the regions.  Calls are cut under capture too.
  *   - n_descs > UCCL_NOALLOC_MAX_DESCS returns UCCL_ETOOBIG and enqueues nothing.  (Calls that
- *     large are never cut into parts, so uccl_chunk_apply serves them without any scratch memory.)
+ *     large are never cut into parts; uccl_chunk_apply serves them, and allocates nothing either.)
  *   - Every call on a GPU shares that GPU's array, whatever the stream.  A split call may be captured and
  *     replayed: a captured one first clears its own words with a small fill kernel, then runs.
  *     Calls (or replays) that overlap in time on one GPU race on the array: keep them on one
@@ -239,7 +237,7 @@ int uccl_chunk_apply_indirect(void* acc, void* out_stage, const void* recv_stage
  * `seq` dedups the record as a whole: the control path issues it when all its sources are
  * in, and may issue it again.  `extents` / `n_rejected` as in uccl_chunk_apply_checked, both
  * may be NULL; `opts` may be NULL.  A call of few records is cut into parts like
- * uccl_chunk_apply's, one of much payload is streamed in destination order (same claim pool, same
+ * uccl_chunk_apply's, one of much payload is streamed in destination order (same scratch memory, same
  * fallback under graph capture).  Records: 160 bytes, 16-byte
  * aligned array.
  */
@@ -331,8 +329,8 @@ int uccl_dedup_reset(uint32_t* dedup_bitmap, uint64_t n_bits, void* stream);
  *   complete   1 if n_applied == n_bits
  * followed by the runs in ascending order as pairs {start, end} of uint64_t, end exclusive.
  * Bits at and above n_bits in the last word are ignored.  n_bits < 2^40.  Stream ordered.
- * Up to 2^28 bits the work is spread over workgroups that add up their counts in the stream's region of
- * the claim pool ("Scratch memory" above; without a region, and under graph capture, one workgroup does it).
+ * Up to 2^28 bits the work is spread over workgroups that add up their counts in the stream's region
+ * ("Scratch memory" above; without a region, and under graph capture, one workgroup does it).
  */
 typedef struct uccl_ack_report {
   uint64_t cum_ack;

@@ -51,12 +51,20 @@
 #include "uccl_data_kernels.hpp"
 #include "uccl_feedback_kernels.hpp"
 
+// Scratch memory: arrays inside the library's code object, so that no call allocates.  Every GPU the
+// library runs on holds its own copy, zero at first, at its own address until the process ends.  In host code
+// the names only stand for the symbols: the device addresses are looked up per device (device_array).
+
 // Claim words for uccl_chunk_apply_noalloc (see claim_enter): a record's two on a
 // 128-byte line of their own, UCCL_NOALLOC_MAX_DESCS of them, then the word that counts parts that
-// gave up waiting: 256.25 KiB.  Every GPU the
-// library runs on holds its own copy at its own address until the process ends.  In host code
-// this name only stands for the symbol: the device address is looked up per device (static_claims).
+// gave up waiting: 256.25 KiB.
 static __device__ __align__(256) unsigned long long scratch[UCCL_NOALLOC_MAX_DESCS * UCCL_CLAIM_STRIDE + 32];
+
+// The regions that streams own (see claim_region), then the same counter: 16 MiB.
+constexpr uint32_t kRegionRecords = 2048;  // most records a split call can have
+constexpr uint32_t kRegionWords = kRegionRecords * UCCL_CLAIM_STRIDE;
+constexpr uint32_t kRegions = 64;
+static __device__ __align__(256) unsigned long long regions[kRegions * kRegionWords + 32];
 
 namespace {
 
@@ -109,9 +117,8 @@ uint32_t tiles_for(uint32_t n_descs, uint32_t tile) {
 // on a 128-byte line of their own.  Ordered calls keep their table in the same words
 // (chunk_order_kernel), the acknowledgement report its segments' counts (ack_segments_kernel); every
 // word carries the tag of the call that wrote it in bits 16 and up, whatever the call, so each kind
-// finds the others' words stale.  The library owns one pool per device (16 MiB), made at the first
-// call that needs it (or by uccl_init) and kept until the process ends: kRegions regions for
-// kRegionRecords records each, one region per stream handle that has issued such a call.  Calls on
+// finds the others' words stale.  Every device has kRegions regions for
+// kRegionRecords records each, one per stream handle that has issued such a call.  Calls on
 // one stream run in order, so they can share a region; calls on different streams may overlap, so
 // they never do.  A call whose stream finds no free region, or that is being captured into a graph
 // (a replay would carry the captured tag again, and could overlap with anything), is launched in the
@@ -121,15 +128,10 @@ uint32_t tiles_for(uint32_t n_descs, uint32_t tile) {
 // device's launch lock: the spill count of an ordered call needs tags that grow in the order in which the calls of a
 // stream run, and the launches of two ordered calls on one stream must not come between each other, also
 // when several host threads issue calls on that stream.
-constexpr uint32_t kRegionRecords = 2048;  // most records a split call can have
-constexpr uint32_t kRegionWords = kRegionRecords * UCCL_CLAIM_STRIDE;
-constexpr uint32_t kRegions = 64;
 constexpr int kMaxDevices = 64;
-constexpr size_t kPoolBytes = sizeof(unsigned long long) * kRegions * kRegionWords + 8;  // + fault counter
 
 struct ClaimPool {
-  std::atomic<unsigned long long*> base{nullptr};
-  std::mutex lock;                       // guards creation and the stream table's growth
+  std::mutex lock;                       // guards the stream table's growth
   std::mutex launch_lock;                // held from drawing a tag until its launch is enqueued
   std::atomic<uint32_t> n_streams{0};
   std::atomic<uintptr_t> stream_of[kRegions];
@@ -137,39 +139,38 @@ struct ClaimPool {
 ClaimPool g_pools[kMaxDevices];
 std::atomic<unsigned long long> g_next_tag{2};  // tags are unique across streams, devices and threads; 1 is for captured calls
 
-// Zeroed device memory, ready for every stream when this returns.  Cleared on a stream of its own, which waits
-// for nobody and which nobody waits for, and with the thread's capture checks relaxed: another stream of the
-// program may be under capture, and neither the allocation nor the wait concerns it.
-void* zeroed_memory(size_t bytes) {
-  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-  void* mem = nullptr;
-  hipStream_t own = nullptr;
-  bool ok = hipMalloc(&mem, bytes) == hipSuccess;
-  if (ok) {
-    ok = hipStreamCreateWithFlags(&own, hipStreamNonBlocking) == hipSuccess && hipMemsetAsync(mem, 0, bytes, own) == hipSuccess &&
-         hipStreamSynchronize(own) == hipSuccess;
-    if (own != nullptr) (void)hipStreamDestroy(own);
-    if (!ok) (void)hipFree(mem);
+// One of the arrays above, by device: its address once it has been looked up with that device current.
+struct DeviceArray {
+  std::atomic<unsigned long long*> at[kMaxDevices];
+};
+DeviceArray g_scratch, g_regions;
+
+// The look-up loads the library's code object if nothing has yet; the thread's capture checks are relaxed
+// meanwhile, for another stream of the program may be under capture, which that does not concern.
+int device_array(DeviceArray& array, const void* symbol, int dev, unsigned long long** out) {
+  unsigned long long* p = array.at[dev].load(std::memory_order_acquire);
+  if (p == nullptr) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    void* at = nullptr;
+    const hipError_t e = hipGetSymbolAddress(&at, symbol);
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) return launch_failed(e);
+    if (at == nullptr) return UCCL_ELAUNCH;
+    p = static_cast<unsigned long long*>(at);
+    array.at[dev].store(p, std::memory_order_release);   // whoever else looks it up finds the same
   }
-  if (!ok) (void)hipGetLastError();
-  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
-  return ok ? mem : nullptr;
+  *out = p;
+  return UCCL_OK;
 }
 
-unsigned long long* pool_base(int dev, bool may_allocate) {
-  ClaimPool& p = g_pools[dev];
-  unsigned long long* b = p.base.load(std::memory_order_acquire);
-  if (b != nullptr || !may_allocate) return b;
-  std::lock_guard<std::mutex> hold(p.lock);
-  b = p.base.load(std::memory_order_acquire);
-  if (b != nullptr) return b;
-  b = static_cast<unsigned long long*>(zeroed_memory(kPoolBytes));
-  if (b != nullptr) p.base.store(b, std::memory_order_release);
-  return b;
+int current_device(int* dev) {
+  const hipError_t e = hipGetDevice(dev);
+  if (e != hipSuccess) return launch_failed(e);
+  return *dev < 0 || *dev >= kMaxDevices ? UCCL_EINVAL : UCCL_OK;
 }
 
-uint32_t* pool_faults(unsigned long long* base) {
+uint32_t* region_faults(unsigned long long* base) {
   return reinterpret_cast<uint32_t*>(base + static_cast<size_t>(kRegions) * kRegionWords);
 }
 
@@ -180,8 +181,8 @@ unsigned long long* claim_region(hipStream_t stream, uint32_t** faults, ClaimPoo
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &cap) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
   if (cap != hipStreamCaptureStatusNone) return nullptr;
-  unsigned long long* base = pool_base(dev, true);
-  if (base == nullptr) return nullptr;
+  unsigned long long* base = nullptr;
+  if (device_array(g_regions, HIP_SYMBOL(regions), dev, &base) != UCCL_OK) { (void)hipGetLastError(); return nullptr; }
   ClaimPool& p = g_pools[dev];
   // 0 marks a free entry; the null stream is 1.  hipStreamPerThread is one handle for a stream of each thread, and
   // those may overlap: each thread has a region of its own for it.
@@ -203,35 +204,9 @@ unsigned long long* claim_region(hipStream_t stream, uint32_t** faults, ClaimPoo
       at = n;
     }
   }
-  *faults = pool_faults(base);
+  *faults = region_faults(base);
   *pool = &p;
   return base + static_cast<size_t>(at) * kRegionWords;
-}
-
-// The current device's copy of `scratch`, looked up once per device with that device current.
-std::atomic<unsigned long long*> g_static_claims[kMaxDevices];
-std::mutex g_static_lock;
-
-int static_claims(unsigned long long** out) {
-  int dev = 0;
-  const hipError_t d = hipGetDevice(&dev);
-  if (d != hipSuccess) return launch_failed(d);
-  if (dev < 0 || dev >= kMaxDevices) return UCCL_EINVAL;
-  unsigned long long* p = g_static_claims[dev].load(std::memory_order_acquire);
-  if (p == nullptr) {
-    std::lock_guard<std::mutex> hold(g_static_lock);
-    p = g_static_claims[dev].load(std::memory_order_acquire);
-    if (p == nullptr) {
-      void* at = nullptr;
-      const hipError_t e = hipGetSymbolAddress(&at, HIP_SYMBOL(scratch));
-      if (e != hipSuccess) return launch_failed(e);
-      if (at == nullptr) return UCCL_ELAUNCH;
-      p = static_cast<unsigned long long*>(at);
-      g_static_claims[dev].store(p, std::memory_order_release);
-    }
-  }
-  *out = p;
-  return UCCL_OK;
 }
 
 // Per-call tuning (uccl_launch_opts); zero = let the library decide.  static_claims: the call
@@ -989,12 +964,11 @@ int uccl_chunk_scatter_opts(void* dst, const void* recv_stage, const uccl_chunk_
 
 int uccl_init(void) {
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return launch_failed(hipGetLastError());
-  if (dev < 0 || dev >= kMaxDevices) return UCCL_EINVAL;
-  unsigned long long* fixed = nullptr;
-  const int rc = static_claims(&fixed);
-  if (rc != UCCL_OK) return rc;
-  return pool_base(dev, true) != nullptr ? UCCL_OK : UCCL_ENOMEM;
+  int rc = current_device(&dev);
+  unsigned long long* at = nullptr;
+  if (rc == UCCL_OK) rc = device_array(g_scratch, HIP_SYMBOL(scratch), dev, &at);
+  if (rc == UCCL_OK) rc = device_array(g_regions, HIP_SYMBOL(regions), dev, &at);
+  return rc;
 }
 
 int uccl_chunk_apply_noalloc(void* acc, void* out_stage, const void* recv_stage,
@@ -1005,7 +979,9 @@ int uccl_chunk_apply_noalloc(void* acc, void* out_stage, const void* recv_stage,
   if (n_descs > UCCL_NOALLOC_MAX_DESCS) return UCCL_ETOOBIG;
   if (n_descs == 0) return UCCL_OK;
   Tuning tune{0u, 0u, nullptr};
-  const int rc = static_claims(&tune.static_claims);
+  int dev = 0;
+  int rc = current_device(&dev);
+  if (rc == UCCL_OK) rc = device_array(g_scratch, HIP_SYMBOL(scratch), dev, &tune.static_claims);
   if (rc != UCCL_OK) return rc;
   return apply_common(acc, out_stage, recv_stage, descs, n_descs, dedup_bitmap, dtype, op, true,
                       nullptr, nullptr, tune, stream);
@@ -1015,24 +991,19 @@ int uccl_claim_timeouts(uint64_t* count) {
   if (!count) return UCCL_EINVAL;
   *count = 0;
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return launch_failed(hipGetLastError());
-  if (dev < 0 || dev >= kMaxDevices) return UCCL_EINVAL;
-  uint64_t total = 0;
-  unsigned long long* base = pool_base(dev, false);
-  if (base != nullptr) {  // no pool: no split call through it so far
+  const int rc = current_device(&dev);
+  if (rc != UCCL_OK) return rc;
+  unsigned long long* const base = g_regions.at[dev].load(std::memory_order_acquire);
+  unsigned long long* const fixed = g_scratch.at[dev].load(std::memory_order_acquire);
+  const void* const counters[] = {base != nullptr ? region_faults(base) : nullptr,   // not looked up: no split call so far
+                                  fixed != nullptr ? fixed + UCCL_NOALLOC_MAX_DESCS * UCCL_CLAIM_STRIDE : nullptr};
+  for (const void* c : counters) {
+    if (c == nullptr) continue;
     uint32_t n = 0;
-    const hipError_t e = hipMemcpy(&n, pool_faults(base), sizeof(n), hipMemcpyDeviceToHost);
+    const hipError_t e = hipMemcpy(&n, c, sizeof(n), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return launch_failed(e);
-    total += n;
+    *count += n;
   }
-  unsigned long long* fixed = g_static_claims[dev].load(std::memory_order_acquire);
-  if (fixed != nullptr) {
-    uint32_t n = 0;
-    const hipError_t e = hipMemcpy(&n, fixed + UCCL_NOALLOC_MAX_DESCS * UCCL_CLAIM_STRIDE, sizeof(n), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return launch_failed(e);
-    total += n;
-  }
-  *count = total;
   return UCCL_OK;
 }
 

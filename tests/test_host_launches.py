@@ -92,6 +92,22 @@ def test_record_counts_beyond_one_launch_are_refused_and_nothing_is_enqueued(tmp
     in_process("refused_counts", tmp_path)
 
 
+def no_allocation(rt):
+    rt.apply(57, 64 * KiB), rt.apply(100), rt.apply(5000), rt.apply(8000, 32 * KiB), rt.apply(8000, 128 * KiB, op=pkg.UCCL_COPY)
+    rt.fold(8, 128 * KiB), rt.fold(65, 16 * KiB), rt.fold(1024, 128 * KiB)
+    rt.report(32768), rt.report(32769), rt.report(1572200)
+    rt.lib.uccl_chunk_apply_noalloc(A, OUT, RECV, DESCS, 57, BITS, 0, 0, 0)
+    rt.lib.uccl_chunk_scatter(A, RECV, DESCS, 5000, BITS, 0)
+    assert {"chunk_few_kernel", "chunk_order_kernel", "gather_order_kernel", "chunk_gather_parts_kernel", "ack_segments_kernel"} <= set(rt.kernels())
+    assert not {"hipMalloc", "hipFree", "hipHostMalloc", "hipMemsetAsync", "hipStreamCreateWithFlags", "hipStreamSynchronize"} & set(rt.calls), rt.calls
+
+
+def test_no_data_path_call_allocates_or_waits(tmp_path):
+    """Also not the first one on a device, and not the calls that a caller of the no-allocation entry point makes
+    beside it: calls of more records than that takes, and the acknowledgement report."""
+    in_process("no_allocation", tmp_path)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]](Runtime(sys.argv[2]))
     print("SCENARIO DONE")
