@@ -142,11 +142,11 @@ typedef struct uccl_launch_opts {
  * agree on the record's fate through two 64-bit claim words per record (on a 128-byte line of their
  * own) in an array inside the library's code object (16 MiB on every GPU the library runs on, until the process
  * ends).  It has one region per stream
- * handle (hipStreamPerThread: per thread), for the first 64 that issue such a call on the device; a
- * region is never given back, so do not destroy a stream while such a call is still running on it
- * (a stream created next may be given the same handle, and with it the region).  A call that is
+ * handle, for the first 64 that issue such a call on the device (hipStreamPerThread: one per thread, for the first 16
+ * threads).  A region is never given back; a stream created later under the handle of a destroyed one takes it over
+ * (hipStreamDestroy waits for the work on the stream).  A call that is
  * streamed in destination order (uccl_launch_opts) keeps that order in the same region, and
- * uccl_dedup_report its counts.  If the stream is the 65th or later, or is being captured into a graph, the
+ * uccl_dedup_report its counts.  If the stream has no region, or is being captured into a graph, the
  * call is launched in the form that needs no scratch
  * memory instead (one workgroup per record or per tile of records): slower, same result.  No
  * data-path call allocates; the first call on a device loads the library's code object.

@@ -132,6 +132,7 @@ constexpr int kMaxDevices = 64;
 
 struct ClaimPool {
   std::mutex lock;                       // guards the stream table's growth
+  uint32_t n_threads = 0;                // how many of its entries are threads (region_key)
   std::mutex launch_lock;                // held from drawing a tag until its launch is enqueued
   std::atomic<uint32_t> n_streams{0};
   std::atomic<uintptr_t> stream_of[kRegions];
@@ -174,6 +175,18 @@ uint32_t* region_faults(unsigned long long* base) {
   return reinterpret_cast<uint32_t*>(base + static_cast<size_t>(kRegions) * kRegionWords);
 }
 
+// Whose region it is: 0 marks a free entry, the null stream is 1.  hipStreamPerThread is one handle for a stream of each
+// thread, and those may overlap.  A thread goes by a number that no other thread ever has: its work may go on after it
+// has ended (the runtime does not wait there, as it does in hipStreamDestroy), when the next thread may have its
+// addresses.  Regions are not given back, so a program that keeps starting threads gets no more than kThreadRegions for them.
+constexpr uint32_t kThreadRegions = 16;
+uintptr_t region_key(hipStream_t stream) {
+  if (stream != hipStreamPerThread) return 1 + reinterpret_cast<uintptr_t>(stream);
+  static std::atomic<uintptr_t> threads{0};
+  static thread_local const uintptr_t mine = threads.fetch_add(1, std::memory_order_relaxed);
+  return ~mine;   // no address
+}
+
 // The claim region of `stream` on the current device, or nullptr (then the call is not split).
 unsigned long long* claim_region(hipStream_t stream, uint32_t** faults, ClaimPool** pool) {
   int dev = 0;
@@ -184,10 +197,7 @@ unsigned long long* claim_region(hipStream_t stream, uint32_t** faults, ClaimPoo
   unsigned long long* base = nullptr;
   if (device_array(g_regions, HIP_SYMBOL(regions), dev, &base) != UCCL_OK) { (void)hipGetLastError(); return nullptr; }
   ClaimPool& p = g_pools[dev];
-  // 0 marks a free entry; the null stream is 1.  hipStreamPerThread is one handle for a stream of each thread, and
-  // those may overlap: each thread has a region of its own for it.
-  static thread_local char t_this_thread;
-  const uintptr_t key = 1 + (stream == hipStreamPerThread ? reinterpret_cast<uintptr_t>(&t_this_thread) : reinterpret_cast<uintptr_t>(stream));
+  const uintptr_t key = region_key(stream);
   uint32_t n = p.n_streams.load(std::memory_order_acquire);
   uint32_t at = kRegions;
   for (uint32_t i = 0; i < n; ++i)
@@ -199,6 +209,10 @@ unsigned long long* claim_region(hipStream_t stream, uint32_t** faults, ClaimPoo
       if (p.stream_of[i].load(std::memory_order_relaxed) == key) { at = i; break; }
     if (at == kRegions) {
       if (n == kRegions) return nullptr;
+      if (stream == hipStreamPerThread) {
+        if (p.n_threads == kThreadRegions) return nullptr;
+        ++p.n_threads;
+      }
       p.stream_of[n].store(key, std::memory_order_relaxed);
       p.n_streams.store(n + 1, std::memory_order_release);
       at = n;

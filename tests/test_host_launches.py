@@ -108,6 +108,24 @@ def test_no_data_path_call_allocates_or_waits(tmp_path):
     in_process("no_allocation", tmp_path)
 
 
+def threads_one_after_another(rt):
+    import threading
+    per_thread = 2
+    for _ in range(24):
+        t = threading.Thread(target=rt.apply, args=(8000, 32 * KiB, per_thread))
+        t.start()
+        t.join()
+    ordered = [l for l in rt.launches if l[0] == "chunk_order_kernel"]
+    regions = [scratch[0] for *_, scratch in ordered]
+    assert len(regions) == len(set(regions)) == 16, regions     # the work of an ended thread may still be running
+    assert rt.kernels().count("chunk_flat_kernel") == 24 - 16   # the rest: the form that needs none
+    assert rt.apply(8000, 32 * KiB, stream=0x7000) == pkg.UCCL_OK and rt.kernels()[-1] == "chunk_ordered_kernel"
+
+
+def test_a_thread_never_gets_the_scratch_words_of_one_that_has_ended(tmp_path):
+    in_process("threads_one_after_another", tmp_path)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]](Runtime(sys.argv[2]))
     print("SCENARIO DONE")
