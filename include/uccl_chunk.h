@@ -140,13 +140,13 @@ typedef struct uccl_launch_opts {
  * most 32 chunks of 32 KiB; at most 128 records when no chunk size is given) is launched with several
  * workgroups per record so that it fills the machine; those workgroups
  * agree on the record's fate through two 64-bit claim words per record (on a 128-byte line of their
- * own) in an array inside the library's code object (16 MiB on every GPU the library runs on, until the process
+ * own) in an array inside the library's code object (36 MiB on every GPU the library runs on, until the process
  * ends).  It has one region per stream
  * handle, for the first 64 that issue such a call on the device (hipStreamPerThread: one per thread, for the first 16
  * threads).  A region is never given back; a stream created later under the handle of a destroyed one takes it over
- * (hipStreamDestroy waits for the work on the stream).  A call that is
- * streamed in destination order (uccl_launch_opts) keeps that order in the same region, and
- * uccl_dedup_report its counts.  If the stream has no region, or is being captured into a graph, the
+ * (hipStreamDestroy waits for the work on the stream).  Calls that are
+ * streamed in destination order (uccl_launch_opts) keep that order, folds of small chunks their claim words and
+ * uccl_dedup_report its counts in a second region of the stream, of which there are 64 too.  If the stream has no region, or is being captured into a graph, the
  * call is launched in the form that needs no scratch
  * memory instead (one workgroup per record or per tile of records): slower, same result.  No
  * data-path call allocates; the first call on a device loads the library's code object.

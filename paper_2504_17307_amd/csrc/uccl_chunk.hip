@@ -60,10 +60,12 @@
 // gave up waiting: 256.25 KiB.
 static __device__ __align__(256) unsigned long long scratch[UCCL_NOALLOC_MAX_DESCS * UCCL_CLAIM_STRIDE + 32];
 
-// The regions that streams own (see claim_region), then the same counter: 16 MiB.
+// The regions that streams own (see claim_region), then the same counter: 36 MiB.
 constexpr uint32_t kRegionRecords = 2048;  // most records a split call can have
 constexpr uint32_t kRegionWords = kRegionRecords * UCCL_CLAIM_STRIDE;
-constexpr uint32_t kRegions = 64;
+enum RegionUse : uint32_t { kCutCalls, kOtherCalls, kThreads, kRegionUses };
+constexpr uint32_t kGroupRegions = 64, kThreadRegions = 16;   // streams with regions: for either use; threads
+constexpr uint32_t kRegions = 2 * kGroupRegions + kThreadRegions;
 static __device__ __align__(256) unsigned long long regions[kRegions * kRegionWords + 32];
 
 namespace {
@@ -118,7 +120,9 @@ uint32_t tiles_for(uint32_t n_descs, uint32_t tile) {
 // (chunk_order_kernel), the acknowledgement report its segments' counts (ack_segments_kernel); every
 // word carries the tag of the call that wrote it in bits 16 and up, whatever the call, so each kind
 // finds the others' words stale.  Every device has kRegions regions for
-// kRegionRecords records each, one per stream handle that has issued such a call.  Calls on
+// kRegionRecords records each, one per stream handle that has issued such a call: one for its cut calls and another
+// for everything else, so that streams which only ask for reports, say, leave the cut calls theirs (these gain
+// most).  Calls on
 // one stream run in order, so they can share a region; calls on different streams may overlap, so
 // they never do.  A call whose stream finds no free region, or that is being captured into a graph
 // (a replay would carry the captured tag again, and could overlap with anything), is launched in the
@@ -130,12 +134,14 @@ uint32_t tiles_for(uint32_t n_descs, uint32_t tile) {
 // when several host threads issue calls on that stream.
 constexpr int kMaxDevices = 64;
 
+struct RegionOwners {
+  std::mutex lock;                       // guards the table's growth
+  std::atomic<uint32_t> n{0};
+  std::atomic<uintptr_t> key[kGroupRegions];
+};
 struct ClaimPool {
-  std::mutex lock;                       // guards the stream table's growth
-  uint32_t n_threads = 0;                // how many of its entries are threads (region_key)
+  RegionOwners owners[kRegionUses];
   std::mutex launch_lock;                // held from drawing a tag until its launch is enqueued
-  std::atomic<uint32_t> n_streams{0};
-  std::atomic<uintptr_t> stream_of[kRegions];
 };
 ClaimPool g_pools[kMaxDevices];
 std::atomic<unsigned long long> g_next_tag{2};  // tags are unique across streams, devices and threads; 1 is for captured calls
@@ -178,8 +184,8 @@ uint32_t* region_faults(unsigned long long* base) {
 // Whose region it is: 0 marks a free entry, the null stream is 1.  hipStreamPerThread is one handle for a stream of each
 // thread, and those may overlap.  A thread goes by a number that no other thread ever has: its work may go on after it
 // has ended (the runtime does not wait there, as it does in hipStreamDestroy), when the next thread may have its
-// addresses.  Regions are not given back, so a program that keeps starting threads gets no more than kThreadRegions for them.
-constexpr uint32_t kThreadRegions = 16;
+// addresses.  Regions are not given back, so threads have a few of their own, for any use, and a program that keeps starting them takes no
+// stream's away.
 uintptr_t region_key(hipStream_t stream) {
   if (stream != hipStreamPerThread) return 1 + reinterpret_cast<uintptr_t>(stream);
   static std::atomic<uintptr_t> threads{0};
@@ -187,40 +193,41 @@ uintptr_t region_key(hipStream_t stream) {
   return ~mine;   // no address
 }
 
-// The claim region of `stream` on the current device, or nullptr (then the call is not split).
-unsigned long long* claim_region(hipStream_t stream, uint32_t** faults, ClaimPool** pool) {
+// A region of `stream` on the current device; no words: there is none to be had, or the stream is being captured.
+struct Region {
+  unsigned long long* words = nullptr;
+  uint32_t* faults = nullptr;
+  std::mutex* launch_lock = nullptr;
+};
+
+Region claim_region(hipStream_t stream, RegionUse use) {
+  Region r;
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) { (void)hipGetLastError(); return nullptr; }
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) { (void)hipGetLastError(); return r; }
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &cap) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
-  if (cap != hipStreamCaptureStatusNone) return nullptr;
+  if (hipStreamIsCapturing(stream, &cap) != hipSuccess) { (void)hipGetLastError(); return r; }
+  if (cap != hipStreamCaptureStatusNone) return r;
   unsigned long long* base = nullptr;
-  if (device_array(g_regions, HIP_SYMBOL(regions), dev, &base) != UCCL_OK) { (void)hipGetLastError(); return nullptr; }
-  ClaimPool& p = g_pools[dev];
+  if (device_array(g_regions, HIP_SYMBOL(regions), dev, &base) != UCCL_OK) { (void)hipGetLastError(); return r; }
+  if (stream == hipStreamPerThread) use = kThreads;
+  RegionOwners& o = g_pools[dev].owners[use];
   const uintptr_t key = region_key(stream);
-  uint32_t n = p.n_streams.load(std::memory_order_acquire);
-  uint32_t at = kRegions;
-  for (uint32_t i = 0; i < n; ++i)
-    if (p.stream_of[i].load(std::memory_order_relaxed) == key) { at = i; break; }
-  if (at == kRegions) {
-    std::lock_guard<std::mutex> hold(p.lock);
-    n = p.n_streams.load(std::memory_order_acquire);
-    for (uint32_t i = 0; i < n; ++i)
-      if (p.stream_of[i].load(std::memory_order_relaxed) == key) { at = i; break; }
-    if (at == kRegions) {
-      if (n == kRegions) return nullptr;
-      if (stream == hipStreamPerThread) {
-        if (p.n_threads == kThreadRegions) return nullptr;
-        ++p.n_threads;
-      }
-      p.stream_of[n].store(key, std::memory_order_relaxed);
-      p.n_streams.store(n + 1, std::memory_order_release);
-      at = n;
+  uint32_t n = o.n.load(std::memory_order_acquire), at = 0;
+  while (at < n && o.key[at].load(std::memory_order_relaxed) != key) ++at;
+  if (at == n) {
+    std::lock_guard<std::mutex> hold(o.lock);
+    n = o.n.load(std::memory_order_acquire);
+    while (at < n && o.key[at].load(std::memory_order_relaxed) != key) ++at;   // only the new entries: old ones stay
+    if (at == n) {
+      if (n == (use == kThreads ? kThreadRegions : kGroupRegions)) return r;
+      o.key[n].store(key, std::memory_order_relaxed);
+      o.n.store(n + 1, std::memory_order_release);
     }
   }
-  *faults = region_faults(base);
-  *pool = &p;
-  return base + static_cast<size_t>(at) * kRegionWords;
+  r.words = base + (static_cast<size_t>(use) * kGroupRegions + at) * kRegionWords;
+  r.faults = region_faults(base);
+  r.launch_lock = &g_pools[dev].launch_lock;
+  return r;
 }
 
 // Per-call tuning (uccl_launch_opts); zero = let the library decide.  static_claims: the call
@@ -387,7 +394,7 @@ Plan plan_apply(uint32_t n_descs, const Tuning& tune, bool reads_acc) {
   return {kRouteOne, 1u, 1u, UCCL_FLAT_THREADS, unroll};
 }
 
-// `region`: the stream's claim words; called with the pool's launch lock held.  HIP has no reason of its
+// `region`: the stream's scratch words; called with the launch lock held.  HIP has no reason of its
 // own to refuse a later launch of a call after it took the first: all are in one code object and their
 // grids stay within 16383 * 64 workgroups of 256 threads.  The timing events span the whole call.
 template <class KernelArgs>
@@ -421,13 +428,12 @@ template <class Op>
 int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
   const uint32_t ordered = a.n_ptr == nullptr && tune.static_claims == nullptr && !tune.host_records ? ordered_launches(a.n_descs, tune, Op::kReadsAcc, false) : 0u;
   if (ordered != 0u) {
-    ClaimPool* pool = nullptr;
-    unsigned long long* const region = claim_region(s, &a.faults, &pool);
-    if (region != nullptr) {
-      std::lock_guard<std::mutex> in_order(pool->launch_lock);
+    const Region region = claim_region(s, kOtherCalls);
+    if (region.words != nullptr) {
+      std::lock_guard<std::mutex> in_order(*region.launch_lock);
       // held back only where the records are known to be large: empty parts want as many workgroups as there can be
       const uint32_t lds = Op::kReadsAcc && tune.chunk_bytes != 0u ? kOrderReduceLds : 0u;
-      return launch_ordered<Args>(chunk_order_kernel<Op::kEs>, chunk_ordered_kernel<Op>, lds, a, s, tune, ordered, region);
+      return launch_ordered<Args>(chunk_order_kernel<Op::kEs>, chunk_ordered_kernel<Op>, lds, a, s, tune, ordered, region.words);
     }
   }
   Plan p = plan_apply(a.n_descs, tune, Op::kReadsAcc);
@@ -460,10 +466,11 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
       return launch_kernel(chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, true>, a.n_descs * p.parts,
                            UCCL_PART_THREADS, s, a);
     }
-    ClaimPool* pool = nullptr;
-    a.claims = claim_region(s, &a.faults, &pool);
-    if (a.claims != nullptr) {
-      std::lock_guard<std::mutex> in_order(pool->launch_lock);
+    const Region region = claim_region(s, kCutCalls);
+    if (region.words != nullptr) {
+      std::lock_guard<std::mutex> in_order(*region.launch_lock);
+      a.claims = region.words;
+      a.faults = region.faults;
       a.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
       a.parts = p.parts;
       return launch_kernel(chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, true>, a.n_descs * p.parts,
@@ -534,19 +541,19 @@ template <class Op>
 int launch_gather_tile(GatherArgs& a, hipStream_t s, const Tuning& tune) {
   const uint32_t ordered = ordered_launches(a.n_descs, tune, true, true);
   if (ordered != 0u) {
-    ClaimPool* pool = nullptr;
-    unsigned long long* const region = claim_region(s, &a.faults, &pool);
-    if (region != nullptr) {
-      std::lock_guard<std::mutex> in_order(pool->launch_lock);
-      return launch_ordered<GatherArgs>(gather_order_kernel<Op::kEs>, gather_ordered_kernel<Op>, 0u, a, s, tune, ordered, region);
+    const Region region = claim_region(s, kOtherCalls);
+    if (region.words != nullptr) {
+      std::lock_guard<std::mutex> in_order(*region.launch_lock);
+      return launch_ordered<GatherArgs>(gather_order_kernel<Op::kEs>, gather_ordered_kernel<Op>, 0u, a, s, tune, ordered, region.words);
     }
   }
   Plan p = plan_gather(a.n_descs, tune);
   if (p.route == kRouteParts) {
-    ClaimPool* pool = nullptr;
-    a.claims = claim_region(s, &a.faults, &pool);
-    if (a.claims != nullptr) {
-      std::lock_guard<std::mutex> in_order(pool->launch_lock);
+    const Region region = claim_region(s, p.unroll == 1u ? kOtherCalls : kCutCalls);   // small chunks have another form that is nearly as good
+    if (region.words != nullptr) {
+      std::lock_guard<std::mutex> in_order(*region.launch_lock);
+      a.claims = region.words;
+      a.faults = region.faults;
       a.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
       a.parts = p.parts;
       return p.unroll == 1u ? launch_kernel(chunk_gather_parts_kernel<UCCL_PART_THREADS, 1, Op>, a.n_descs * p.parts, UCCL_PART_THREADS, s, a)
@@ -1076,14 +1083,12 @@ int uccl_dedup_report(const uint32_t* dedup_bitmap, uint64_t n_bits, void* repor
     return launch_kernel(ack_segments_kernel, 1, 256, s, dedup_bitmap, n_bits, hdr, ranges, max_ranges, nullptr, 0ull);
   static_assert(kAckMaxSegments * 4 <= kRegionWords, "four words a segment");
   if (segments <= kAckMaxSegments) {
-    uint32_t* faults = nullptr;
-    ClaimPool* pool = nullptr;
-    unsigned long long* const region = claim_region(s, &faults, &pool);
-    if (region != nullptr) {
-      std::lock_guard<std::mutex> in_order(pool->launch_lock);
+    const Region region = claim_region(s, kOtherCalls);
+    if (region.words != nullptr) {
+      std::lock_guard<std::mutex> in_order(*region.launch_lock);
       const unsigned long long tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
       return launch_kernel(ack_segments_kernel, static_cast<uint32_t>(segments), 256, s, dedup_bitmap, n_bits, hdr, ranges, max_ranges,
-                           region, tag);
+                           region.words, tag);
     }
   }
   return launch_kernel(ack_report_kernel, 1, 1024, s, dedup_bitmap, n_bits, hdr, ranges, max_ranges);

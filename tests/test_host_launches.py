@@ -126,6 +126,23 @@ def test_a_thread_never_gets_the_scratch_words_of_one_that_has_ended(tmp_path):
     in_process("threads_one_after_another", tmp_path)
 
 
+def reports_on_many_streams(rt):
+    for k in range(80):
+        assert rt.report(1572200, stream=0x1000 + 16 * k) == pkg.UCCL_OK
+    assert rt.kernels() == ["ack_segments_kernel"] * 64 + ["ack_report_kernel"] * 16
+    for k in range(80):   # the streams that move the payload come later
+        rt.launches.clear()
+        assert rt.apply(57, 64 * KiB, stream=0x9000 + 16 * k) == pkg.UCCL_OK
+        assert rt.launches[0][:3] == (("chunk_few_kernel", 57 * 8, 256) if k < 64 else ("chunk_few_kernel", 57, 1024)), k
+    rt.launches.clear()
+    assert rt.report(1572200, stream=0x1000) == pkg.UCCL_OK and rt.fold(8, 128 * KiB, stream=0x9000) == pkg.UCCL_OK
+    assert rt.kernels() == ["ack_segments_kernel", "chunk_gather_parts_kernel"]
+
+
+def test_streams_that_only_report_leave_cut_calls_their_regions(tmp_path):
+    in_process("reports_on_many_streams", tmp_path)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]](Runtime(sys.argv[2]))
     print("SCENARIO DONE")
