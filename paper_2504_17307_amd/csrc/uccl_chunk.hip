@@ -128,10 +128,11 @@ uint32_t tiles_for(uint32_t n_descs, uint32_t tile) {
 // (a replay would carry the captured tag again, and could overlap with anything), is launched in the
 // form that needs none.
 //
-// Tags come from one process-wide counter.  A call draws its tag and enqueues its launches while holding the
-// device's launch lock: the spill count of an ordered call needs tags that grow in the order in which the calls of a
-// stream run, and the launches of two ordered calls on one stream must not come between each other, also
-// when several host threads issue calls on that stream.
+// Tags come from one process-wide counter.  A call draws its tag and enqueues its launches while holding its
+// region's launch lock: the spill count of an ordered call needs tags that grow in the order in which the calls of a
+// region run, and the launches of two ordered calls on one stream must not come between each other, also
+// when several host threads issue calls on that stream.  A launch may wait for room in its stream's queue; calls on
+// other streams do not wait with it.
 constexpr int kMaxDevices = 64;
 
 struct RegionOwners {
@@ -141,7 +142,7 @@ struct RegionOwners {
 };
 struct ClaimPool {
   RegionOwners owners[kRegionUses];
-  std::mutex launch_lock;                // held from drawing a tag until its launch is enqueued
+  std::mutex launch_lock[kRegions];      // a region's: held from drawing a tag until its launches are enqueued
 };
 ClaimPool g_pools[kMaxDevices];
 std::atomic<unsigned long long> g_next_tag{2};  // tags are unique across streams, devices and threads; 1 is for captured calls
@@ -224,9 +225,10 @@ Region claim_region(hipStream_t stream, RegionUse use) {
       o.n.store(n + 1, std::memory_order_release);
     }
   }
-  r.words = base + (static_cast<size_t>(use) * kGroupRegions + at) * kRegionWords;
+  const uint32_t index = use * kGroupRegions + at;
+  r.words = base + static_cast<size_t>(index) * kRegionWords;
   r.faults = region_faults(base);
-  r.launch_lock = &g_pools[dev].launch_lock;
+  r.launch_lock = &g_pools[dev].launch_lock[index];
   return r;
 }
 
@@ -394,7 +396,7 @@ Plan plan_apply(uint32_t n_descs, const Tuning& tune, bool reads_acc) {
   return {kRouteOne, 1u, 1u, UCCL_FLAT_THREADS, unroll};
 }
 
-// `region`: the stream's scratch words; called with the launch lock held.  HIP has no reason of its
+// `region`: the stream's scratch words; called with its launch lock held.  HIP has no reason of its
 // own to refuse a later launch of a call after it took the first: all are in one code object and their
 // grids stay within 16383 * 64 workgroups of 256 threads.  The timing events span the whole call.
 template <class KernelArgs>

@@ -17,7 +17,7 @@ A, OUT, RECV, DESCS, BITS, REPORT = (0x100000 * k for k in range(1, 7))   # addr
 class Runtime:
     """The stub and the library on it.  `launches`: (kernel, grid, block, lds, stream, scratch), one per accepted
     launch; `calls`: the other runtime calls by name.  `answer[name]`: what a call returns (a number or a function
-    of its subject); `refuse(kernel, start, stop)`: the launches to turn down."""
+    of its subject); `refuse(kernel, stream, start, stop)`: the launches to turn down."""
 
     def __init__(self, stub):
         self.stub = C.CDLL(stub, mode=C.RTLD_GLOBAL)
@@ -26,6 +26,7 @@ class Runtime:
             fn = getattr(self.lib, name)
             fn.restype, fn.argtypes = res, args
         self.launches, self.calls, self.answer, self.refuse = [], [], {}, lambda *a: False
+        self.launching = False
         on_launch = C.CFUNCTYPE(C.c_int, C.c_char_p, C.c_uint, C.c_uint, C.c_uint, C.c_void_p, C.POINTER(C.c_void_p), C.c_void_p, C.c_void_p)
         on_call = C.CFUNCTYPE(C.c_int, C.c_char_p, C.c_void_p)
         self.keep = on_launch(self._launch), on_call(self._call)
@@ -33,7 +34,8 @@ class Runtime:
 
     def _launch(self, kernel, grid, block, lds, stream, args, start, stop):
         name = next((k for k in KERNELS if k.encode() in kernel), kernel.decode())
-        if self.refuse(name, start, stop):
+        self.launching = True
+        if self.refuse(name, stream or 0, start, stop):
             return 1
         scratch = None
         if name in ("chunk_order_kernel", "chunk_ordered_kernel", "gather_order_kernel", "gather_ordered_kernel"):
@@ -141,6 +143,25 @@ def reports_on_many_streams(rt):
 
 def test_streams_that_only_report_leave_cut_calls_their_regions(tmp_path):
     in_process("reports_on_many_streams", tmp_path)
+
+
+def a_full_queue(rt):
+    import threading
+    full, other, done = 0x1000, 0x2000, threading.Event()
+    waited = []
+    rt.refuse = lambda kernel, stream, *_: bool(stream == full and not waited and waited.append(done.wait(10)))
+    t = threading.Thread(target=rt.apply, args=(8000, 32 * KiB, full))
+    t.start()
+    while not rt.launching:
+        pass
+    assert rt.report(1572200, other) == 0 and rt.apply(8000, 128 * KiB, other) == 0 and rt.apply(57, 64 * KiB, other) == 0 and rt.fold(8, 128 * KiB, other) == 0
+    done.set()
+    t.join()
+    assert waited == [True], "calls on another stream waited for the launch on the first"
+
+
+def test_a_launch_that_waits_for_its_stream_does_not_hold_up_other_streams(tmp_path):
+    in_process("a_full_queue", tmp_path)
 
 
 if __name__ == "__main__":
