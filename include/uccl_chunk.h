@@ -131,7 +131,9 @@ typedef struct uccl_launch_opts {
  * or which forwards although out_stage is NULL, is skipped (its bit stays clear).
  *
  * Returns UCCL_OK (also for n_descs == 0, which enqueues nothing) or a negative code;
- * on error nothing has been enqueued.  One launch covers the whole call with one workgroup
+ * on error nothing has been enqueued (but for a call of several launches, `ordered` in uccl_plan, of which HIP takes
+ * the first and refuses a later one, as it may when the device is lost: then sequence numbers may be marked whose payload
+ * has not moved, and their retransmissions are dropped until the bitmap is reset).  One launch covers the whole call with one workgroup
  * per 1..32 records (or several per record, or a pair of launches for every 16383 records; see
  * "Scratch memory"); a record count whose workgroup count exceeds what the device accepts
  * in one launch comes back as UCCL_ELAUNCH (split the call).
@@ -416,7 +418,7 @@ int uccl_feed_destroy(uccl_feed* feed);
  * op combines with the accumulator (anything but UCCL_COPY).  `parts` > 1 assumes that claim words
  * are to be had (see "Scratch memory"); a call that finds none is launched with parts = 1.
  * `ordered` > 0: where scratch memory is to be had, apply and scatter calls (not the indirect and
- * no-allocation ones) and uccl_chunk_reduce_gather decide the records first and stream them in destination order, in that many
+ * no-allocation ones, nor a feed's hand-overs) and uccl_chunk_reduce_gather decide the records first and stream them in destination order, in that many
  * pairs of launches (chunk_order_kernel and chunk_ordered_kernel, or their gather_ forms); the other fields say what the call is launched as otherwise.
  * UCCL_EINVAL for a NULL `plan` or options the data-path calls would refuse.  Utility, no passage
  * of the paper. */

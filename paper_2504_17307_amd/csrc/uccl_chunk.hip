@@ -238,7 +238,7 @@ struct Tuning {
   uint32_t chunk_bytes;
   uint32_t parts;
   unsigned long long* static_claims = nullptr;
-  bool host_records = false;  // the records are in host memory: read them as seldom as possible
+  bool one_launch = false;  // the call may be offered again after an error: all of it is enqueued, or nothing
 };
 
 template <int T, int U, class Op>
@@ -352,8 +352,10 @@ struct Plan {
 // better for small records and lose 2 % on 64 KiB ones, eight the other way round.)
 //
 // Returns the number of launches of each kernel (the table holds kOrderRecords entries; more records are
-// taken in equal shares, each of which has to be worth it), 0 = not this form.  Needs a claim region and
-// records in device memory; a stated number of parts asks for the other form.
+// taken in equal shares, each of which has to be worth it), 0 = not this form.  Needs a region;
+// a stated number of parts asks for the other form.  The batcher's hand-overs stay with the other form: a hand-over
+// that fails is offered again, so it must not leave sequence numbers decided whose payload has not moved, and its
+// chunk size is the largest length in it, which may be one record's.
 constexpr uint32_t kOrderRecords = kRegionRecords * UCCL_CLAIM_STRIDE / 2 - 1;   // two words each, and the spill count
 static_assert(kOrderRecords <= 0x3FFFu, "a table entry has 14 bits for the record");
 constexpr uint32_t kOrderChunk = 16u << 10;
@@ -397,8 +399,9 @@ Plan plan_apply(uint32_t n_descs, const Tuning& tune, bool reads_acc) {
 }
 
 // `region`: the stream's scratch words; called with its launch lock held.  HIP has no reason of its
-// own to refuse a later launch of a call after it took the first: all are in one code object and their
-// grids stay within 16383 * 64 workgroups of 256 threads.  The timing events span the whole call.
+// own to refuse a later launch of a call after it took the first: all are in one code object, their
+// grids stay within 16383 * 64 workgroups of 256 threads, and a stop event that it does not take is refused with the first
+// launch, which has it too.  The timing events span the whole call.
 template <class KernelArgs>
 int launch_ordered(void (*order)(KernelArgs, OrderArgs), void (*stream)(KernelArgs, OrderArgs), uint32_t lds, KernelArgs a, hipStream_t s,
                    const Tuning& tune, uint32_t launches, unsigned long long* region) {
@@ -416,7 +419,7 @@ int launch_ordered(void (*order)(KernelArgs, OrderArgs), void (*stream)(KernelAr
     t.spilled = region + kRegionWords - 1u;
     t.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
     t_start = i == 0u ? begin : nullptr;
-    t_stop = nullptr;
+    t_stop = i == 0u ? end : nullptr;
     rc = launch_kernel(order, (a.n_descs + 255u) / 256u, 256, s, a, t);
     if (rc != UCCL_OK) break;
     t_stop = i + 1u == launches ? end : nullptr;
@@ -428,7 +431,7 @@ int launch_ordered(void (*order)(KernelArgs, OrderArgs), void (*stream)(KernelAr
 
 template <class Op>
 int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
-  const uint32_t ordered = a.n_ptr == nullptr && tune.static_claims == nullptr && !tune.host_records ? ordered_launches(a.n_descs, tune, Op::kReadsAcc, false) : 0u;
+  const uint32_t ordered = a.n_ptr == nullptr && tune.static_claims == nullptr && !tune.one_launch ? ordered_launches(a.n_descs, tune, Op::kReadsAcc, false) : 0u;
   if (ordered != 0u) {
     const Region region = claim_region(s, kOtherCalls);
     if (region.words != nullptr) {
@@ -713,13 +716,12 @@ int feed_flush(uccl_feed* f) {
     // workgroup, no copy to enqueue); a large one is copied to device memory first, so that
     // thousands of workgroups do not each wait on the host bus.
     const uccl_chunk_desc* records = sl.host[l];
-    Tuning tune{sl.max_len[l], 0u, nullptr, true};
+    const Tuning tune{sl.max_len[l], 0u, nullptr, true};
     if (sl.count[l] > UCCL_FEED_DIRECT_RECORDS) {
       const hipError_t e = hipMemcpyAsync(sl.dev[l], sl.host[l], sizeof(uccl_chunk_desc) * sl.count[l],
                                           hipMemcpyHostToDevice, f->stream);
       if (e != hipSuccess) return launch_failed(e);
       records = sl.dev[l];
-      tune.host_records = false;
     }
     const int rc = apply_common(f->acc, f->out_stage, f->recv_stage, records, sl.count[l], f->bitmap,
                                 f->dtype, f->op[l], true, nullptr, nullptr, tune, f->stream);

@@ -202,6 +202,27 @@ def test_gather_tails(gpu_lib, dtype, es):
 
 
 @pytest.mark.gpu
+def test_timing_events_span_an_ordered_call(gpu_lib):
+    """Start on the first launch, stop on the last: 3200 records of 32 KiB are read twice and written twice (400 MiB, no
+    less than 52 us at 8 TB/s), the first of the two launches alone takes some 6 us."""
+    import torch
+    n, size = 3200, 32768
+    d = np.zeros(n, dtype=DESC)
+    d["seq"], d["len"] = np.arange(n), size
+    d["src_off"] = d["dst_off"] = d["out_off"] = np.arange(n, dtype=np.uint64) * size
+    acc, out, recv = (torch.zeros(n * size, dtype=torch.uint8, device="cuda") for _ in range(3))
+    recs, bitmap = torch.from_numpy(d.view(np.uint8)).cuda(), torch.zeros((n + 31) // 32, dtype=torch.int32, device="cuda")
+    start, stop = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    start.record(), stop.record()
+    for _ in range(3):
+        bitmap.zero_()
+        pkg.uccl_time_next_launch(start, stop)
+        pkg.uccl_chunk_apply_opts(acc, out, recv, recs, n, bitmap, F32, SUM, opts=(size, 0))
+        torch.cuda.synchronize()
+        assert pkg.uccl_launch_ordered(n, (size, 0)) == 1 and 0.052 < start.elapsed_time(stop) < 50.0
+
+
+@pytest.mark.gpu
 def test_per_thread_streams_do_not_share_scratch_words(gpu_lib):
     """hipStreamPerThread is one handle for as many streams as there are threads: ordered calls of several
     threads on it run side by side, each with a table of its own."""

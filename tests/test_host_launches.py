@@ -164,6 +164,42 @@ def test_a_launch_that_waits_for_its_stream_does_not_hold_up_other_streams(tmp_p
     in_process("a_full_queue", tmp_path)
 
 
+def feed_hand_over(rt):
+    import numpy as np
+    n = 20000                                        # large enough to be copied to device memory before the launch
+    d = np.zeros(n, dtype=[("off", "<u8", 3), ("len", "<u4"), ("seq", "<u4")])
+    d["seq"], d["len"], d["len"][17] = np.arange(n), 4096, 256 * KiB
+    feed = C.c_void_p()
+    assert rt.lib.uccl_feed_create(C.byref(feed), A, OUT, RECV, BITS, 0, 0, 3, n, 2, None) == 0
+    rt.refuse = lambda kernel, *_: len(rt.launches) > 0              # whatever comes after the first launch of the hand-over
+    assert rt.lib.uccl_feed_push(feed, 0, d.ctypes.data, n) == 0
+    assert rt.kernels() == ["chunk_flat_kernel"] and rt.launches[0][1] <= n
+
+
+def test_a_feed_hand_over_is_one_launch_per_lane(tmp_path):
+    """All of a hand-over is enqueued or nothing, whatever its size, since it is offered again after an error; and the one
+    long record in it, whose length is the hand-over's chunk size, does not multiply the others' workgroups."""
+    in_process("feed_hand_over", tmp_path)
+
+
+def unusable_event(rt):
+    bad = 0x5000
+    rt.refuse = lambda kernel, stream, start, stop: bad in (start, stop)
+    for start, stop in ((0x6000, bad), (bad, None), (None, bad)):
+        for call in (lambda: rt.apply(8000, 32 * KiB), lambda: rt.apply(40000, 32 * KiB), lambda: rt.fold(1024, 128 * KiB), lambda: rt.apply(5000)):
+            rt.lib.uccl_time_next_launch(start, stop)
+            assert call() == pkg.UCCL_ELAUNCH and not rt.launches
+    rt.lib.uccl_time_next_launch(0x6000, 0x7000)
+    events = []
+    rt.refuse = lambda kernel, stream, start, stop: events.append((start, stop))
+    assert rt.apply(40000, 32 * KiB) == 0 and len(events) == 6
+    assert events[0][0] == 0x6000 and events[-1][1] == 0x7000 and not any(start for start, _ in events[1:])
+
+
+def test_a_timing_event_that_hip_does_not_take_fails_the_call_before_anything_is_enqueued(tmp_path):
+    in_process("unusable_event", tmp_path)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]](Runtime(sys.argv[2]))
     print("SCENARIO DONE")
