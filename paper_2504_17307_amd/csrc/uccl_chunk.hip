@@ -443,44 +443,42 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
   }
   Plan p = plan_apply(a.n_descs, tune, Op::kReadsAcc);
   if (p.route == kRouteParts) {
+    a.parts = p.parts;
+    const auto launch_parts = [&](unsigned long long tag) {
+      a.tag = tag;
+      return launch_kernel(chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, true>, a.n_descs * p.parts, UCCL_PART_THREADS, s, a);
+    };
     if (tune.static_claims != nullptr) {
       // Every call shares the device's one array and finds what other calls left there stale by their tags.
       a.claims = tune.static_claims;
       a.faults = reinterpret_cast<uint32_t*>(tune.static_claims + UCCL_NOALLOC_MAX_DESCS * UCCL_CLAIM_STRIDE);
-      a.parts = p.parts;
       hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-      const bool eager = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
-      if (eager) {
-        a.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
-        return launch_kernel(chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, true>, a.n_descs * p.parts,
-                             UCCL_PART_THREADS, s, a);
+      if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        cap = hipStreamCaptureStatusActive;   // not known: the form that is right either way
       }
-      (void)hipGetLastError();
+      if (cap == hipStreamCaptureStatusNone) return launch_parts(g_next_tag.fetch_add(1, std::memory_order_relaxed));
       // A captured call carries the same tag in every replay, so it clears its words first, with a fill
-      // kernel (no memset node); no eager call draws that tag.  (An eager call without the fill and its gap: 28 + 28 records of 32 KiB,
-      // reset included, 15.9 us with it, 11.2 without.)
-      a.tag = 1ull;
+      // kernel (no memset node); no eager call draws that tag.  (An eager call without the fill and its gap: 28 + 28
+      // records of 32 KiB, reset included, 15.9 us with it, 11.2 without.)
       const hipEvent_t keep0 = t_start, keep1 = t_stop;  // the timing events belong to the data kernel
       t_start = t_stop = nullptr;
       const uint64_t words = 2ull * a.n_descs * UCCL_CLAIM_STRIDE;
       const int rc = launch_kernel(fill_words_kernel, static_cast<uint32_t>((words + 255) / 256), 256, s,
                                    reinterpret_cast<uint32_t*>(a.claims), words, 0u);
+      if (rc != UCCL_OK) return rc;
       t_start = keep0;
       t_stop = keep1;
-      if (rc != UCCL_OK) { t_start = t_stop = nullptr; return rc; }
-      return launch_kernel(chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, true>, a.n_descs * p.parts,
-                           UCCL_PART_THREADS, s, a);
+      return launch_parts(1ull);
     }
     const Region region = claim_region(s, kCutCalls);
     if (region.words != nullptr) {
       std::lock_guard<std::mutex> in_order(*region.launch_lock);
       a.claims = region.words;
       a.faults = region.faults;
-      a.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
-      a.parts = p.parts;
-      return launch_kernel(chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, true>, a.n_descs * p.parts,
-                           UCCL_PART_THREADS, s, a);
+      return launch_parts(g_next_tag.fetch_add(1, std::memory_order_relaxed));
     }
+    a.parts = 1u;
     p.route = a.n_descs < kFewRecords ? kRouteFew : kRouteOne;   // no claim words to be had: uncut
   }
   switch (p.route) {

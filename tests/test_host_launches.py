@@ -200,6 +200,24 @@ def test_a_timing_event_that_hip_does_not_take_fails_the_call_before_anything_is
     in_process("unusable_event", tmp_path)
 
 
+def callers_error(rt):
+    noalloc = lambda: rt.lib.uccl_chunk_apply_noalloc(A, OUT, RECV, DESCS, 57, BITS, 0, 0, 0)
+    rt.lib.uccl_init()
+    for capturing, kernels in ((1, ["fill_words_kernel", "chunk_few_kernel"]), (0, ["chunk_few_kernel"])):
+        rt.answer["hipStreamIsCapturing"] = capturing
+        rt.launches.clear(), rt.calls.clear()
+        assert noalloc() == 0 and rt.kernels() == kernels
+        assert rt.apply(57, 64 * KiB) == 0 and rt.apply(8000, 32 * KiB) == 0 and rt.fold(8, 128 * KiB) == 0 and rt.report(1572200) == 0
+        assert "hipGetLastError" not in rt.calls       # reading it clears it
+    rt.answer["hipStreamIsCapturing"] = -1             # the library's own failed query: nothing of that is left behind
+    rt.launches.clear(), rt.calls.clear()
+    assert noalloc() == 0 and rt.kernels() == ["fill_words_kernel", "chunk_few_kernel"] and rt.calls.count("hipGetLastError") == 1
+
+
+def test_an_error_that_the_caller_has_pending_is_left_alone(tmp_path):
+    in_process("callers_error", tmp_path)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]](Runtime(sys.argv[2]))
     print("SCENARIO DONE")
