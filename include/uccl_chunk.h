@@ -417,7 +417,7 @@ int uccl_feed_destroy(uccl_feed* feed);
  * `gather` != 0: uccl_chunk_reduce_gather, else the apply / scatter family; `reads_acc` != 0: the
  * op combines with the accumulator (anything but UCCL_COPY).  `parts` > 1 assumes that claim words
  * are to be had (see "Scratch memory"); a call that finds none is launched with parts = 1.
- * `ordered` > 0: where scratch memory is to be had, apply and scatter calls (not the indirect and
+ * `ordered` > 0: where scratch memory is to be had and the records are in device memory, apply and scatter calls (not the indirect and
  * no-allocation ones, nor a feed's hand-overs) and uccl_chunk_reduce_gather decide the records first and stream them in destination order, in that many
  * pairs of launches (chunk_order_kernel and chunk_ordered_kernel, or their gather_ forms); the other fields say what the call is launched as otherwise.
  * UCCL_EINVAL for a NULL `plan` or options the data-path calls would refuse.  Utility, no passage

@@ -37,6 +37,25 @@ def test_records_read_from_pinned_host_memory(gpu_lib):
     assert_same(acc, eacc, "acc"); assert_same(out, eout, "out"); assert_same(bm, ebm, "bitmap")
 
 
+@pytest.mark.parametrize("kind", ["stated", "unknown"])
+def test_many_records_read_from_pinned_host_memory(gpu_lib, kind):
+    """Calls that would be streamed in destination order, with their records in pinned memory."""
+    w = wl.ring_share("pinned", 23, R=4, M=4 * 1100 * 64, C=64, dtype=F32, paths=3, window=256, dup=0.05, dist="uniform")
+    opts = (64 << 10, 0) if kind == "stated" else (0, 0)
+    eacc, eout, ebm = oracle_results(w)
+    run, keep = DeviceRun(w, opts=opts), []
+    for ph in w.phases:
+        assert gpu_lib.uccl_launch_ordered(len(ph.descs), opts, reads_acc=ph.op != COPY) == 1
+        t, v = pinned(ph.descs.nbytes)
+        v[:] = ph.descs.view(np.uint8).reshape(-1)
+        keep.append(t)
+        run.apply(t, len(ph.descs), ph.op)
+    torch.cuda.synchronize()
+    acc, out, bm, rej = run.results()
+    assert rej == 0
+    assert_same(acc, eacc, "acc"); assert_same(out, eout, "out"); assert_same(bm, ebm, "bitmap")
+
+
 def test_indirect_count(gpu_lib):
     w = wl.config2(seed=4, M=8 << 20)
     ph = w.phases[0]

@@ -218,6 +218,25 @@ def test_an_error_that_the_caller_has_pending_is_left_alone(tmp_path):
     in_process("callers_error", tmp_path)
 
 
+def records_in_host_memory(rt):
+    for where in (1, -1):                              # pinned; not known to the runtime
+        rt.answer["hipPointerGetAttributes"] = where
+        rt.launches.clear()
+        rt.apply(8000, 32 * KiB), rt.apply(5000), rt.apply(8000, 128 * KiB, op=pkg.UCCL_COPY), rt.fold(1024, 128 * KiB)
+        assert rt.kernels() == ["chunk_flat_kernel"] * 3 + ["chunk_gather_kernel"]
+    rt.answer["hipPointerGetAttributes"] = 0
+    rt.launches.clear()
+    rt.apply(8000, 32 * KiB), rt.fold(1024, 128 * KiB)
+    assert rt.kernels() == ["chunk_order_kernel", "chunk_ordered_kernel", "gather_order_kernel", "gather_ordered_kernel"]
+    asked = rt.calls.count("hipPointerGetAttributes")
+    rt.apply(57, 64 * KiB), rt.apply(100), rt.fold(8, 128 * KiB)
+    assert rt.calls.count("hipPointerGetAttributes") == asked       # small calls do not pay for the question
+
+
+def test_records_outside_device_memory_are_read_once(tmp_path):
+    in_process("records_in_host_memory", tmp_path)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]](Runtime(sys.argv[2]))
     print("SCENARIO DONE")
