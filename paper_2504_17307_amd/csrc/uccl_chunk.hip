@@ -344,18 +344,23 @@ struct Plan {
 // With the chunk size unknown the same form is taken for another reason.  A workgroup per record decides
 // its sequence number with an atomic of its own, atomics of neighbouring records meet on one 128-byte line of
 // the bitmap, and such atomics are served one after the other, about 6.5 ns each: 5000 records take 30 us whatever
-// their size, while the order kernel's wavefronts issue 64 at a time.  Four parts an entry suit records of any
-// size (ring steps, bf16, us, this form / one workgroup per record): 3000 records of 4 KiB 37 / 51, 9 KB 48 / 59,
-// 16 KiB 67 / 70, 32 KiB 116 / 116, 64 KiB 240 / 246; 5000 of 4 KiB 47 / 74, 9 KB 66 / 86, 32 KiB 189 / 196, 64 KiB 437 / 444;
-// 2000 of 32 KiB 84 / 83; against tiles of four from 8192 records on, 12 000 of 4 KiB 75.6 / 76.1, 9 KB 130 / 134,
-// 16 KiB 219 / 240, 32 KiB 489 / 538; in two launches it does not pay (20 000 of 4 KiB 135 / 112).  (Three parts are
-// better for small records and lose 2 % on 64 KiB ones, eight the other way round.)
+// their size, while the order kernel's wavefronts issue 64 at a time.  Nothing is gained by the order itself, and with
+// windows of sequence numbers that are partly used most of them would share entries of the table, so a record's entry is its own index.
+// Four parts an entry suit records of any size as long as the alternative is a workgroup per record; where that is
+// tiles of four (8192 records and more), whose workgroups are few, one part of 8 KiB.  Copies have two vectors per
+// lane there too (they do better with larger units, see plan_apply).  Measured, fp32 with forward, bitmap reset
+// included, us, this form / the other; sums, sequence numbers in one run: 3072 records of 64 B 18 / 23, 4 KiB 20 / 26, 9 KB
+// 26 / 31, 32 KiB 59 / 64, 128 KiB 318 / 317; 8191 of 64 B 27 / 43, 9 KB 48 / 68, 64 KiB 413 / 414; in windows of 256 numbers of which 64
+// are used: 3072 of 64 B 16 / 17, 9 KB 25 / 28, 8191 of 9 KB 48 / 65 (entries by sequence number 32 / 29 and 60 / 50); copies: 3072 of
+// 9 KB 25 / 29, 32 KiB 49.5 / 48.5, 64 KiB 90 / 93, 8191 of 32 KiB 110.5 / 108.3.  From 8192 records on, sums: 8192 of 64 B 17 / 21, 9 KB 49 / 53,
+// 16 383 of 64 B 22 / 31, 4 KiB 44 / 51, 9 KB 85 / 93, 32 KiB 409 / 414; copies 16 383 of 4 KiB 36 / 44, 9 KB 71 / 73, 32 KiB 310 / 316; in
+// windows 16 383 of 64 B 21 / 24, copies of 16 KiB 114 / 114.  (In four parts by sequence number 16 383 of 64 B 44, copies of 4 KiB 49.)
 //
 // Records in pinned host memory are read across the bus once by the order kernel and again by every part of theirs;
 // the other form reads them once (same measures, records in pinned memory: 7856 of 32 KiB 160 / 149, copies 123 / 105; 16 383
 // of 4 KiB of unknown size 77 / 54).  Asking the runtime where they are takes 0.1 us of the host's time.
 //
-// Returns the number of launches of each kernel (the table holds kOrderRecords entries; more records are
+// `launches`: of each kernel (the table holds kOrderRecords entries; more records are
 // taken in equal shares, each of which has to be worth it), 0 = not this form.  Needs a region;
 // a stated number of parts asks for the other form.  The batcher's hand-overs stay with the other form: a hand-over
 // that fails is offered again, so it must not leave sequence numbers decided whose payload has not moved, and its
@@ -367,7 +372,7 @@ constexpr uint64_t kOrderBytes = 96ull << 20;
 constexpr uint32_t kOrderCopyChunk = 64u << 10;        // copies: chunks of this size from kOrderBytes on,
 constexpr uint64_t kOrderCopyBytes = 192ull << 20;     // smaller ones from here on
 constexpr uint32_t kOrderUnknownRecords = 3072;        // chunk size unknown: from this many records to one table full
-constexpr uint32_t kOrderUnknownParts = 4;
+constexpr uint32_t kOrderUnknownTiles = 8192;          // where its alternative is tiles of four records (flat_tile)
 constexpr uint32_t kMaxLaunchThreads = 0xFFFFFFFFu;    // HIP counts a launch's threads in 32 bits
 constexpr uint32_t kOrderMaxParts = 64;   // longer records are walked: keeps the grid far below a launch's limit
 
@@ -378,15 +383,27 @@ bool in_device_memory(const void* p) {
   return false;
 }
 
-uint32_t ordered_launches(uint32_t n_descs, const Tuning& tune, bool reads_acc, bool gather) {
-  if (tune.parts == 0u && tune.chunk_bytes == 0u && !gather) return n_descs >= kOrderUnknownRecords && n_descs <= kOrderRecords ? 1u : 0u;
-  if (tune.parts != 0u || tune.chunk_bytes < kOrderChunk || n_descs == 0u) return 0u;
+struct OrderPlan {
+  uint32_t launches, parts, unroll;
+  bool by_seq;
+};
+constexpr OrderPlan kNotOrdered = {0u, 1u, 1u, false};
+
+OrderPlan plan_ordered(uint32_t n_descs, const Tuning& tune, bool reads_acc, bool gather) {
+  if (tune.parts == 0u && tune.chunk_bytes == 0u && !gather) {
+    if (n_descs < kOrderUnknownRecords || n_descs > kOrderRecords) return kNotOrdered;
+    const bool tiles = n_descs >= kOrderUnknownTiles;
+    return {1u, tiles ? 1u : 4u, tiles || !reads_acc ? 2u : 1u, false};
+  }
+  if (tune.parts != 0u || tune.chunk_bytes < kOrderChunk || n_descs == 0u) return kNotOrdered;
   // A count that is too large for the form of one launch is refused there, before anything is enqueued: a count that
   // is none (-1) must not become a quarter of a million launches.
-  if (tiles_for(n_descs, flat_tile(n_descs, tune.chunk_bytes)) > kMaxLaunchThreads / UCCL_FLAT_THREADS) return 0u;
+  if (tiles_for(n_descs, flat_tile(n_descs, tune.chunk_bytes)) > kMaxLaunchThreads / UCCL_FLAT_THREADS) return kNotOrdered;
   const uint32_t launches = (n_descs - 1u) / kOrderRecords + 1u;
   const uint64_t least = reads_acc || tune.chunk_bytes >= kOrderCopyChunk ? kOrderBytes : kOrderCopyBytes;
-  return static_cast<uint64_t>(n_descs / launches) * tune.chunk_bytes >= least ? launches : 0u;
+  if (static_cast<uint64_t>(n_descs / launches) * tune.chunk_bytes < least) return kNotOrdered;
+  const uint32_t parts = (tune.chunk_bytes - 1u) / kOrderPartBytes + 1u;
+  return {launches, parts < kOrderMaxParts ? parts : kOrderMaxParts, 1u, true};
 }
 
 Plan plan_apply(uint32_t n_descs, const Tuning& tune, bool reads_acc) {
@@ -415,25 +432,27 @@ Plan plan_apply(uint32_t n_descs, const Tuning& tune, bool reads_acc) {
 // launch, which has it too.  The timing events span the whole call.
 template <class KernelArgs>
 int launch_ordered(void (*order)(KernelArgs, OrderArgs), void (*stream)(KernelArgs, OrderArgs), uint32_t lds, KernelArgs a, hipStream_t s,
-                   const Tuning& tune, uint32_t launches, unsigned long long* region) {
+                   const OrderPlan& o, unsigned long long* region) {
   const hipEvent_t begin = t_start, end = t_stop;
-  const uint32_t n = a.n_descs, parts = tune.chunk_bytes == 0u ? kOrderUnknownParts : (tune.chunk_bytes - 1u) / kOrderPartBytes + 1u;
+  const uint32_t n = a.n_descs;
   const auto* const descs = a.descs;
-  a.parts = parts < kOrderMaxParts ? parts : kOrderMaxParts;
+  a.parts = o.parts;
   int rc = UCCL_OK;
-  for (uint32_t i = 0; i < launches && rc == UCCL_OK; ++i) {
-    const uint32_t from = static_cast<uint32_t>(static_cast<uint64_t>(n) * i / launches);
+  for (uint32_t i = 0; i < o.launches && rc == UCCL_OK; ++i) {
+    const uint32_t from = static_cast<uint32_t>(static_cast<uint64_t>(n) * i / o.launches);
     a.descs = descs + from;
-    a.n_descs = static_cast<uint32_t>(static_cast<uint64_t>(n) * (i + 1u) / launches) - from;
+    a.n_descs = static_cast<uint32_t>(static_cast<uint64_t>(n) * (i + 1u) / o.launches) - from;
     OrderArgs t;
     t.words = region;
     t.spilled = region + kRegionWords - 1u;
     t.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
+    t.part_bytes = kOrderPartBytes * o.unroll;
+    t.entries = o.by_seq ? a.n_descs : 0u;
     t_start = i == 0u ? begin : nullptr;
     t_stop = i == 0u ? end : nullptr;
     rc = launch_kernel(order, (a.n_descs + 255u) / 256u, 256, s, a, t);
     if (rc != UCCL_OK) break;
-    t_stop = i + 1u == launches ? end : nullptr;
+    t_stop = i + 1u == o.launches ? end : nullptr;
     rc = launch_kernel_lds(stream, a.n_descs * a.parts, kOrderThreads, lds, s, a, t);
   }
   t_start = t_stop = nullptr;
@@ -442,14 +461,15 @@ int launch_ordered(void (*order)(KernelArgs, OrderArgs), void (*stream)(KernelAr
 
 template <class Op>
 int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
-  const uint32_t ordered = a.n_ptr == nullptr && tune.static_claims == nullptr && !tune.one_launch ? ordered_launches(a.n_descs, tune, Op::kReadsAcc, false) : 0u;
-  if (ordered != 0u && in_device_memory(a.descs)) {
+  const OrderPlan ordered = a.n_ptr == nullptr && tune.static_claims == nullptr && !tune.one_launch ? plan_ordered(a.n_descs, tune, Op::kReadsAcc, false) : kNotOrdered;
+  if (ordered.launches != 0u && in_device_memory(a.descs)) {
     const Region region = claim_region(s, kOtherCalls);
     if (region.words != nullptr) {
       std::lock_guard<std::mutex> in_order(*region.launch_lock);
       // held back only where the records are known to be large: empty parts want as many workgroups as there can be
       const uint32_t lds = Op::kReadsAcc && tune.chunk_bytes != 0u ? kOrderReduceLds : 0u;
-      return launch_ordered<Args>(chunk_order_kernel<Op::kEs>, chunk_ordered_kernel<Op>, lds, a, s, tune, ordered, region.words);
+      return launch_ordered<Args>(chunk_order_kernel<Op::kEs>, ordered.unroll == 1u ? chunk_ordered_kernel<1, Op> : chunk_ordered_kernel<2, Op>, lds, a, s,
+                                  ordered, region.words);
     }
   }
   Plan p = plan_apply(a.n_descs, tune, Op::kReadsAcc);
@@ -553,12 +573,12 @@ Plan plan_gather(uint32_t n_descs, const Tuning& tune) {
 
 template <class Op>
 int launch_gather_tile(GatherArgs& a, hipStream_t s, const Tuning& tune) {
-  const uint32_t ordered = ordered_launches(a.n_descs, tune, true, true);
-  if (ordered != 0u && in_device_memory(a.descs)) {
+  const OrderPlan ordered = plan_ordered(a.n_descs, tune, true, true);
+  if (ordered.launches != 0u && in_device_memory(a.descs)) {
     const Region region = claim_region(s, kOtherCalls);
     if (region.words != nullptr) {
       std::lock_guard<std::mutex> in_order(*region.launch_lock);
-      return launch_ordered<GatherArgs>(gather_order_kernel<Op::kEs>, gather_ordered_kernel<Op>, 0u, a, s, tune, ordered, region.words);
+      return launch_ordered<GatherArgs>(gather_order_kernel<Op::kEs>, gather_ordered_kernel<Op>, 0u, a, s, ordered, region.words);
     }
   }
   Plan p = plan_gather(a.n_descs, tune);
@@ -1133,7 +1153,7 @@ int uccl_launch_plan(uint32_t n_descs, const uccl_launch_opts* opts, int gather,
   plan->unit_bytes = 64u * 16u * p.unroll;
   const uint64_t groups = p.route == kRouteTile ? tiles_for(n_descs, p.tile) : static_cast<uint64_t>(n_descs) * p.parts;
   plan->groups = static_cast<uint32_t>(groups);
-  plan->ordered = ordered_launches(n_descs, tune, gather || reads_acc, gather != 0);
+  plan->ordered = plan_ordered(n_descs, tune, gather || reads_acc, gather != 0).launches;
   plan->reserved = 0u;
   return UCCL_OK;
 }

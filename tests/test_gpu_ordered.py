@@ -87,7 +87,7 @@ def test_random_streams(gpu_lib, spread, dtype, op):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n,stated", [(TABLE - 1, True), (TABLE, True), (TABLE + 1, True), (2 * TABLE + 1, True), (40001, True), (3072, False), (TABLE, False)])
+@pytest.mark.parametrize("n,stated", [(TABLE - 1, True), (TABLE, True), (TABLE + 1, True), (2 * TABLE + 1, True), (40001, True), (3072, False), (8191, False), (8192, False), (TABLE, False)])
 def test_table_and_launch_edges(gpu_lib, n, stated):
     """Calls around one and two launches' worth of records, in shuffled order with repeats and some
     out-of-range sequence numbers; records of 0..48 bytes, and a few that are longer than all parts of one."""
@@ -97,7 +97,7 @@ def test_table_and_launch_edges(gpu_lib, n, stated):
     d = np.zeros(n, dtype=DESC)
     lens = g.integers(0, 13, unique) * 4
     lens[g.integers(0, unique, 3)] = 64 * 4096 + 20
-    for at_edge in (4096, 8192, 16384):                                      # the size classes of a table entry
+    for at_edge in (4096, 8192, 16384, 32768):                                      # the size classes of a table entry
         lens[g.integers(0, unique, 12)] = at_edge + np.array([-4, 0, 4] * 4)
     pitch = (lens + 15) // 16 * 16
     at = np.concatenate([[0], np.cumsum(pitch)])
@@ -108,8 +108,10 @@ def test_table_and_launch_edges(gpu_lib, n, stated):
     total = int(at[-1])
     w = dict(descs=d, recv=g.random(total // 4, dtype=np.float32), acc=g.random(total // 4, dtype=np.float32), out_bytes=total,
              n_bits=unique, dtype=F32, op=SUM)
-    print(n, stated, flush=True)
-    check(w, (hint_for(n) if stated else 0, 0), rejected=int(bad.sum()))
+    for op in (SUM, COPY):
+        w["op"] = op
+        print(n, stated, op, flush=True)
+        check(w, (hint_for(n) if stated else 0, 0), rejected=int(bad.sum()))
 
 
 @pytest.mark.gpu

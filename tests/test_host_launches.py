@@ -40,7 +40,7 @@ class Runtime:
         scratch = None
         if name in ("chunk_order_kernel", "chunk_ordered_kernel", "gather_order_kernel", "gather_ordered_kernel"):
             words = C.cast(args[1], C.POINTER(C.c_uint64))           # OrderArgs: words, spilled, tag
-            scratch = words[0], words[2]
+            scratch = words[0], words[2], words[3] & 0xFFFFFFFF, words[3] >> 32   # and bytes of a part, entries
         elif name == "ack_segments_kernel":
             scratch = C.cast(args[5], C.POINTER(C.c_uint64))[0], C.cast(args[6], C.POINTER(C.c_uint64))[0]
         self.launches.append((name, grid, block, lds, stream or 0, scratch))
@@ -235,6 +235,22 @@ def records_in_host_memory(rt):
 
 def test_records_outside_device_memory_are_read_once(tmp_path):
     in_process("records_in_host_memory", tmp_path)
+
+
+def unknown_sizes(rt):
+    for n, op, parts, part_bytes in ((3072, 0, 4, 4096), (8191, 0, 4, 4096), (3072, pkg.UCCL_COPY, 4, 8192), (8191, pkg.UCCL_COPY, 4, 8192),
+                                     (8192, 0, 1, 8192), (16383, 0, 1, 8192), (8192, pkg.UCCL_COPY, 1, 8192), (16383, pkg.UCCL_COPY, 1, 8192)):
+        rt.launches.clear()
+        assert rt.apply(n, op=op) == 0
+        (order, _, _, _, _, scratch), (stream, grid, block, _, _, _) = rt.launches
+        # no entries by sequence number: windows of numbers that are partly used would meet in few of them
+        assert (order, stream, grid, block, scratch[2:]) == ("chunk_order_kernel", "chunk_ordered_kernel", n * parts, 256, (part_bytes, 0)), n
+    rt.launches.clear()
+    assert rt.apply(8000, 32 * KiB) == 0 and rt.launches[0][5][2:] == (4096, 8000) and rt.launches[1][1] == 8 * 8000
+
+
+def test_calls_of_unknown_size_take_few_workgroups_and_do_not_depend_on_the_sequence_numbers(tmp_path):
+    in_process("unknown_sizes", tmp_path)
 
 
 if __name__ == "__main__":
