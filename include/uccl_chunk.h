@@ -96,7 +96,8 @@ typedef struct uccl_extents {
  *                at most 128 records take one workgroup per record, sized to the chunk).  Calls of much payload
  *                (records x chunk_bytes: 96 MiB for a reduction, 192 MiB or chunks of 64 KiB for a copy; chunks
  *                of 16 KiB and more) are streamed in destination order, by two launches (see "Scratch
- *                memory" below); so are calls of 3072 to 16383 records of unknown size.
+ *                memory" below); so are calls of 3072 to 16383 records of unknown size.  State the size that
+ *                most records of the call have: records much shorter than stated leave workgroups without work.
  *   parts        workgroups per record for calls of few, large records (Appendix C.4: small
  *                messages are where the kernel's fixed costs show): 0 = the library decides,
  *                1 = never cut a record, 2..16 = that many.  Honoured only when a workgroup takes

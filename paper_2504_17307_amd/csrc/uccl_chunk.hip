@@ -356,6 +356,11 @@ struct Plan {
 // 16 383 of 64 B 22 / 31, 4 KiB 44 / 51, 9 KB 85 / 93, 32 KiB 409 / 414; copies 16 383 of 4 KiB 36 / 44, 9 KB 71 / 73, 32 KiB 310 / 316; in
 // windows 16 383 of 64 B 21 / 24, copies of 16 KiB 114 / 114.  (In four parts by sequence number 16 383 of 64 B 44, copies of 4 KiB 49.)
 //
+// A record shorter than stated leaves workgroups without work, at about 0.43 ns each, which the host cannot know: 8000
+// records of 4 KiB stated as 128 KiB 144 / 53, as 32 KiB 47 / 53.  So no record has more than kOrderMaxParts of them: 8000 of
+// 4 KiB stated as 1 MiB 144 instead of 260 with 64, for 7 - 10 % on chunks that are that large (3072 of 256 KiB 534 / 641, 496 with
+// 64 parts).
+//
 // Records in pinned host memory are read across the bus once by the order kernel and again by every part of theirs;
 // the other form reads them once (same measures, records in pinned memory: 7856 of 32 KiB 160 / 149, copies 123 / 105; 16 383
 // of 4 KiB of unknown size 77 / 54).  Asking the runtime where they are takes 0.1 us of the host's time.
@@ -374,7 +379,7 @@ constexpr uint64_t kOrderCopyBytes = 192ull << 20;     // smaller ones from here
 constexpr uint32_t kOrderUnknownRecords = 3072;        // chunk size unknown: from this many records to one table full
 constexpr uint32_t kOrderUnknownTiles = 8192;          // where its alternative is tiles of four records (flat_tile)
 constexpr uint32_t kMaxLaunchThreads = 0xFFFFFFFFu;    // HIP counts a launch's threads in 32 bits
-constexpr uint32_t kOrderMaxParts = 64;   // longer records are walked: keeps the grid far below a launch's limit
+constexpr uint32_t kOrderMaxParts = 32;   // longer records are walked
 
 bool in_device_memory(const void* p) {
   hipPointerAttribute_t a;
@@ -428,7 +433,7 @@ Plan plan_apply(uint32_t n_descs, const Tuning& tune, bool reads_acc) {
 
 // `region`: the stream's scratch words; called with its launch lock held.  HIP has no reason of its
 // own to refuse a later launch of a call after it took the first: all are in one code object, their
-// grids stay within 16383 * 64 workgroups of 256 threads, and a stop event that it does not take is refused with the first
+// grids stay within 16383 * 32 workgroups of 256 threads, and a stop event that it does not take is refused with the first
 // launch, which has it too.  The timing events span the whole call.
 template <class KernelArgs>
 int launch_ordered(void (*order)(KernelArgs, OrderArgs), void (*stream)(KernelArgs, OrderArgs), uint32_t lds, KernelArgs a, hipStream_t s,

@@ -249,6 +249,17 @@ def unknown_sizes(rt):
     assert rt.apply(8000, 32 * KiB) == 0 and rt.launches[0][5][2:] == (4096, 8000) and rt.launches[1][1] == 8 * 8000
 
 
+def stated_sizes(rt):
+    for chunk, parts in ((16 * KiB, 4), (20000, 5), (128 * KiB, 32), (256 * KiB, 32), (1 * MiB, 32), (2 ** 32 - 1, 32)):
+        rt.launches.clear()
+        assert rt.apply(7000, chunk) == 0 and rt.fold(7000, chunk) == 0
+        assert [l[1] for l in rt.launches] == [28, 7000 * parts] * 2, chunk
+
+
+def test_a_stated_size_far_above_the_records_does_not_multiply_workgroups_without_end(tmp_path):
+    in_process("stated_sizes", tmp_path)
+
+
 def test_calls_of_unknown_size_take_few_workgroups_and_do_not_depend_on_the_sequence_numbers(tmp_path):
     in_process("unknown_sizes", tmp_path)
 
