@@ -588,6 +588,7 @@ int launch_gather_tile(GatherArgs& a, hipStream_t s, const Tuning& tune) {
   }
   Plan p = plan_gather(a.n_descs, tune);
   if (p.route == kRouteParts) {
+    if (p.parts == 1u) return launch_kernel(chunk_gather_parts_kernel<UCCL_PART_THREADS, 1, Op>, a.n_descs, UCCL_PART_THREADS, s, a);
     const Region region = claim_region(s, p.unroll == 1u ? kOtherCalls : kCutCalls);   // small chunks have another form that is nearly as good
     if (region.words != nullptr) {
       std::lock_guard<std::mutex> in_order(*region.launch_lock);

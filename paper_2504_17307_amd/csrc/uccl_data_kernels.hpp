@@ -796,7 +796,7 @@ __global__ void __launch_bounds__(NT) chunk_gather_kernel(const GatherArgs g) {
 // A call of few multi-source records: `parts` workgroups per record share its units (one compute
 // unit reads a record's n + 1 streams far below its share of the memory system's rate: eight
 // records of 128 KiB from seven senders take 25 us uncut).  The record's fate is decided once, by
-// the first part to arrive (see claim_enter); blockIdx.x = record * parts + part.  As in
+// the first part to arrive (see claim_enter; a call of one part a record has no claim words); blockIdx.x = record * parts + part.  As in
 // chunk_few_kernel every wavefront reads the record for itself and folds its first unit before the fate is
 // known, so that the loads and the decision overlap (event pairs, seven sources, decided first -> folded first:
 // 8 x 32 KiB 7.3 -> 6.7 us, 65 x 32 KiB 8.7 -> 8.0, 65 x 128 KiB 17.5 -> 16.1; three, 128 x 32 KiB 8.4 -> 7.6).
@@ -831,7 +831,8 @@ __global__ void __launch_bounds__(NT) chunk_gather_parts_kernel(const GatherArgs
   if (tid == 0) {
     uint32_t win = 0u;
     unsigned long long* const claim = g.claims + static_cast<size_t>(k) * UCCL_CLAIM_STRIDE;
-    const Claim entered = claim_enter(claim, g.tag);
+    Claim entered = {true, 0ull};
+    if (g.parts > 1u) entered = claim_enter(claim, g.tag);   // the only part has nobody to agree with
     if (entered.decides) {
       if (ok) {
         const uint32_t bit = 1u << (seq & 31u);
@@ -839,7 +840,7 @@ __global__ void __launch_bounds__(NT) chunk_gather_parts_kernel(const GatherArgs
       } else if (g.rejected != nullptr) {
         atomicAdd(g.rejected, 1u);
       }
-      claim_publish(claim, g.tag, win != 0u);
+      if (g.parts > 1u) claim_publish(claim, g.tag, win != 0u);
     } else if (ok && part * kWaves < total) {  // a part without units has nothing to wait for
       win = claim_await(claim, entered.outcome, g.tag, g.faults) ? 1u : 0u;
     }

@@ -264,6 +264,20 @@ def test_calls_of_unknown_size_take_few_workgroups_and_do_not_depend_on_the_sequ
     in_process("unknown_sizes", tmp_path)
 
 
+def folds_of_one_part(rt):
+    for capturing in (0, 1):
+        rt.answer["hipStreamIsCapturing"] = capturing
+        rt.launches.clear(), rt.calls.clear()
+        assert rt.fold(1, 4096) == 0 and rt.fold(288, 64) == 0
+        assert [l[:3] for l in rt.launches] == [("chunk_gather_parts_kernel", 1, 256), ("chunk_gather_parts_kernel", 288, 256)]
+        assert not rt.calls                            # no region is asked for
+    assert rt.fold(8, 4112) == 0 and rt.kernels()[-1] == "chunk_gather_kernel"    # two parts: no words under capture
+
+
+def test_a_fold_whose_records_have_one_part_needs_no_claim_words(tmp_path):
+    in_process("folds_of_one_part", tmp_path)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]](Runtime(sys.argv[2]))
     print("SCENARIO DONE")
