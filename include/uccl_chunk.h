@@ -142,7 +142,7 @@ typedef struct uccl_launch_opts {
  * Scratch memory.  A call of few large records (at most 16 MiB of payload in chunks above 32 KiB, or at
  * most 32 chunks of 32 KiB; at most 128 records when no chunk size is given) is launched with several
  * workgroups per record so that it fills the machine; those workgroups
- * agree on the record's fate through two 64-bit claim words per record (on a 128-byte line of their
+ * agree on the record's fate through a 64-bit claim word per record (on a 128-byte line of its
  * own) in an array inside the library's code object (36 MiB on every GPU the library runs on, until the process
  * ends).  It has one region per stream
  * handle, for the first 64 that issue such a call on the device (hipStreamPerThread: one per thread, for the first 16

@@ -115,8 +115,8 @@ uint32_t tiles_for(uint32_t n_descs, uint32_t tile) {
 
 // ---- claim words for records cut into parts ---------------------------------------------------
 //
-// Scratch memory of the split launch (see claim_enter): two 64-bit words per record of the call,
-// on a 128-byte line of their own.  Ordered calls keep their table in the same words
+// Scratch memory of the split launch (see claim_enter): one 64-bit word per record of the call,
+// on a 128-byte line of its own.  Ordered calls keep their table in the same words
 // (chunk_order_kernel), the acknowledgement report its segments' counts (ack_segments_kernel); every
 // word carries the tag of the call that wrote it in bits 16 and up, whatever the call, so each kind
 // finds the others' words stale.  Every device has kRegions regions for
@@ -129,8 +129,8 @@ uint32_t tiles_for(uint32_t n_descs, uint32_t tile) {
 // form that needs none.
 //
 // Tags come from one process-wide counter.  A call draws its tag and enqueues its launches while holding its
-// region's launch lock: the spill count of an ordered call needs tags that grow in the order in which the calls of a
-// region run, and the launches of two ordered calls on one stream must not come between each other, also
+// region's launch lock: claim words and the spill count of an ordered call need tags that grow in the order in which the
+// calls of a region run, and the launches of two ordered calls on one stream must not come between each other, also
 // when several host threads issue calls on that stream.  A launch may wait for room in its stream's queue; calls on
 // other streams do not wait with it.
 constexpr int kMaxDevices = 64;
@@ -487,6 +487,7 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
     if (tune.static_claims != nullptr) {
       // Every call shares the device's one array and finds what other calls left there stale by their tags.
       a.claims = tune.static_claims;
+      a.apart = 1u;
       a.faults = reinterpret_cast<uint32_t*>(tune.static_claims + UCCL_NOALLOC_MAX_DESCS * UCCL_CLAIM_STRIDE);
       hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
       if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
@@ -653,6 +654,7 @@ int apply_common(void* acc, void* out_stage, const void* recv_stage, const uccl_
   a.faults = nullptr;
   a.parts = 1u;
   a.tag = 0ull;
+  a.apart = 0u;
   if (ext) {
     if (overlaps(recv_stage, ext->recv_bytes, acc, ext->acc_bytes) ||
         overlaps(recv_stage, ext->recv_bytes, out_stage, ext->out_bytes) ||

@@ -41,7 +41,7 @@
 #define UCCL_CLAIM_STRIDE 16    // 64-bit words from one record's claim words to the next: one 128-byte line each
 #endif
 #ifndef UCCL_CLAIM_SPIN_LIMIT
-#define UCCL_CLAIM_SPIN_LIMIT (1u << 16)  // polls of a claim's outcome before a part gives up (see claim_await)
+#define UCCL_CLAIM_SPIN_LIMIT (1u << 16)  // polls of a claim word before a part gives up (see claim_await)
 #endif
 namespace {
 
@@ -60,12 +60,13 @@ struct Args {
   const uint32_t* n_ptr;  // optional: the record count is read from here (capped by n_descs)
   uint32_t n_descs;
   uint32_t allow_forward;
-  // one record cut into `parts` workgroups (see claim_enter): record k's claim words begin at claims[k * UCCL_CLAIM_STRIDE],
+  // one record cut into `parts` workgroups (see claim_enter): claims[k * UCCL_CLAIM_STRIDE] is record k's claim word,
   // tag is this call's own value, faults counts parts that gave up waiting for a decision
   unsigned long long* claims;
   uint32_t* faults;
   unsigned long long tag;
   uint32_t parts;
+  uint32_t apart;   // 1: the outcome has a word of its own
 };
 
 // ---- one record, several workgroups ------------------------------------------------------
@@ -75,54 +76,63 @@ struct Args {
 // below its share of the memory system's rate.  Such a call is launched with `parts` workgroups
 // per record, and the record's units are dealt over the wavefronts of all of them.  The sequence
 // number must still be decided exactly once, by one atomic OR on the bitmap, and every part that
-// has units must learn the outcome.  Record k of the call has two 64-bit claim words in scratch
-// memory: the first holds `tag << 16` of the last call that used it, the second that call's outcome
-// for its record, `tag << 16 | 1` = applied, `| 2` = not applied.  No two calls have the same tag.
+// has units must learn the outcome.  Record k of the call has a 64-bit claim word in scratch
+// memory, holding `tag << 16 | state`: the tag of the last call that used the word, and 0 = a part
+// is deciding, 1 = applied, 2 = not applied.  No two calls have the same tag.
 //
-//   enter    every part exchanges the first word for `tag << 16`, after the payload loads of
+//   enter    every part issues one atomic max of `tag << 16` on the word, after the payload loads of
 //            its first unit (memory operations return in order, so entering earlier would hold up
-//            the record itself).  Exactly one part of the call -- the first to get there -- finds another
-//            call's tag in the word: it decides.  Which of two calls that share a word was made first
-//            does not matter, only that they do not overlap.
+//            the record itself).  Tags grow from call to call in the order the calls run (the host
+//            draws the tag and enqueues the launch under one lock, and calls that share a word run
+//            on one stream), so exactly one part of the call -- the first to get there -- finds an
+//            older tag in the word: it decides.
 //   decide   the deciding part issues the bitmap atomic (or rejects the record) and stores
-//            the outcome in the second word.  It waits for nothing.
-//   await    the other parts poll the second word until it carries the call's tag.
+//            `tag << 16 | outcome`.  It waits for nothing.
+//   await    the other parts poll the word until it carries the call's tag and an outcome.
+//
+// The no-allocation calls share their words over all streams, so the order in which calls run need not be that of
+// their tags.  There (`apart` = 1) a part exchanges the word instead and decides if it finds any other tag, and the
+// outcome is in the next word, where no part that comes later can overwrite it.  Every part then waits for one
+// more load, which costs a call of many parts more (fold of 65 x 128 KiB from three senders, 16 parts, 9.4 -> 10.6 us;
+// 28 records in 8 parts nothing that can be measured), so calls with a region of their own have the other way.
 //
 // A part only ever waits for a part that is already running and never waits itself, so the wait
 // ends whatever order the hardware starts workgroups in.  It is bounded all the same: a part that
 // gives up counts itself in `faults` and streams nothing.  Claim words are read and written with
 // device-scope atomics only, so every part sees the one coherent copy whichever XCD it runs on;
-// each record's words have a 128-byte line to themselves (UCCL_CLAIM_STRIDE), because device-scope atomics
+// each record's word has a 128-byte line to itself (UCCL_CLAIM_STRIDE), because device-scope atomics
 // on one line are served one after the other and a call's parts all arrive at about the same time
 // (57 records x 8 parts: 6.2 us per call with the words packed, 5.4 us with a line each).
-// Nothing is ever cleared between calls: a stale word is recognised by its other tag.  The order table
+// Nothing is ever cleared between calls: a stale word is recognised by its tag.  The order table
 // of large calls (below) lives in the same words and carries its tag in the same bits, so either kind
 // of call finds the other's leftovers stale.
 struct Claim {
   bool decides;
-  unsigned long long outcome;   // the second word as it was on entry: the outcome may already be in it
+  unsigned long long seen;   // what the word with the outcome held: the outcome may already be in it
 };
 
-__device__ __forceinline__ Claim claim_enter(unsigned long long* claim, unsigned long long tag) {
+__device__ __forceinline__ Claim claim_enter(unsigned long long* claim, unsigned long long tag, uint32_t apart) {
+  if (apart == 0u) {
+    const unsigned long long was = __hip_atomic_fetch_max(claim, tag << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return {(was >> 16) < tag, was};
+  }
   const unsigned long long was = __hip_atomic_exchange(claim, tag << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const unsigned long long outcome = __hip_atomic_load(claim + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return {(was >> 16) != tag, outcome};
+  return {(was >> 16) != tag, __hip_atomic_load(claim + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)};
 }
 
-__device__ __forceinline__ void claim_publish(unsigned long long* claim, unsigned long long tag, bool win) {
-  __hip_atomic_store(claim + 1, (tag << 16) | (win ? 1ull : 2ull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void claim_publish(unsigned long long* claim, unsigned long long tag, uint32_t apart, bool win) {
+  __hip_atomic_store(claim + apart, (tag << 16) | (win ? 1ull : 2ull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// `seen`: the outcome word as this part's claim_enter found it.
-__device__ __forceinline__ bool claim_await(unsigned long long* claim, unsigned long long seen,
-                                            unsigned long long tag, uint32_t* faults) {
-  for (uint32_t polls = 0; (seen >> 16) != tag; ++polls) {
+__device__ __forceinline__ bool claim_await(unsigned long long* claim, unsigned long long seen, unsigned long long tag, uint32_t apart,
+                                            uint32_t* faults) {
+  for (uint32_t polls = 0; (seen >> 16) != tag || (seen & 3ull) == 0ull; ++polls) {
     if (polls >= UCCL_CLAIM_SPIN_LIMIT) {
       atomicAdd(faults, 1u);
       return false;
     }
     __builtin_amdgcn_s_sleep(1);
-    seen = __hip_atomic_load(claim + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    seen = __hip_atomic_load(claim + apart, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   return (seen & 3ull) == 1ull;
 }
@@ -525,7 +535,7 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
   if (tid == 0) {
     uint32_t win = 0u;
     Claim entered = {true, 0ull};
-    if constexpr (PARTS) entered = claim_enter(claim, g.tag);
+    if constexpr (PARTS) entered = claim_enter(claim, g.tag, g.apart);
     if (entered.decides) {
       if (ok) {
         const uint32_t bit = 1u << (seq & 31u);
@@ -533,9 +543,9 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
       } else if (is_record && g.rejected != nullptr) {  // a rejected record is counted once: by the part that decides
         atomicAdd(g.rejected, 1u);
       }
-      if constexpr (PARTS) claim_publish(claim, g.tag, win != 0u);
+      if constexpr (PARTS) claim_publish(claim, g.tag, g.apart, win != 0u);
     } else if (part_has_units) {  // a part without units has nothing to wait for
-      win = claim_await(claim, entered.outcome, g.tag, g.faults) ? 1u : 0u;
+      win = claim_await(claim, entered.seen, g.tag, g.apart, g.faults) ? 1u : 0u;
     }
     s_win = win;
   }
@@ -832,7 +842,7 @@ __global__ void __launch_bounds__(NT) chunk_gather_parts_kernel(const GatherArgs
     uint32_t win = 0u;
     unsigned long long* const claim = g.claims + static_cast<size_t>(k) * UCCL_CLAIM_STRIDE;
     Claim entered = {true, 0ull};
-    if (g.parts > 1u) entered = claim_enter(claim, g.tag);   // the only part has nobody to agree with
+    if (g.parts > 1u) entered = claim_enter(claim, g.tag, 0u);   // the only part has nobody to agree with
     if (entered.decides) {
       if (ok) {
         const uint32_t bit = 1u << (seq & 31u);
@@ -840,9 +850,9 @@ __global__ void __launch_bounds__(NT) chunk_gather_parts_kernel(const GatherArgs
       } else if (g.rejected != nullptr) {
         atomicAdd(g.rejected, 1u);
       }
-      if (g.parts > 1u) claim_publish(claim, g.tag, win != 0u);
+      if (g.parts > 1u) claim_publish(claim, g.tag, 0u, win != 0u);
     } else if (ok && part * kWaves < total) {  // a part without units has nothing to wait for
-      win = claim_await(claim, entered.outcome, g.tag, g.faults) ? 1u : 0u;
+      win = claim_await(claim, entered.seen, g.tag, 0u, g.faults) ? 1u : 0u;
     }
     s_win = win;
   }
