@@ -264,7 +264,10 @@ __global__ void __launch_bounds__(1024) ack_report_kernel(const uint32_t* __rest
 // kAckPolls polls counts that segment itself.
 constexpr uint32_t kAckSegWords = 1024;
 constexpr uint32_t kAckSegBits = kAckSegWords * 32;
-constexpr uint32_t kAckPolls = 4096;
+#ifndef UCCL_ACK_POLLS
+#define UCCL_ACK_POLLS 4096
+#endif
+constexpr uint32_t kAckPolls = UCCL_ACK_POLLS;
 constexpr uint32_t kAckMaxSegments = 8191;   // 268 M bits
 
 struct AckCounts {

@@ -204,6 +204,60 @@ def test_gather_tails(gpu_lib, dtype, es):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("how", ["stated", "unknown", "fold"])
+def test_captured_calls_have_no_table(gpu_lib, how):
+    """A call that would be ordered, captured: it takes the form without scratch words.  Replayed with an eager,
+    ordered call of the same kind on the same stream between the replays."""
+    import torch
+    from gpuhelp import to_dev
+    w = random_stream(960, F32, SUM, max_chunks=60, max_len=3000)
+    copies = 3072 // len(w["descs"]) + 1                                     # every record again and again
+    d = np.concatenate([w["descs"]] * copies)
+    n, dev_recv = len(d), to_dev(w["recv"])
+    opts = None if how == "unknown" else (hint_for(n), 0)
+    acc, out, seen = w["acc"].copy(), np.full(w["out_bytes"], 0xA5, dtype=np.uint8), oracle.new_seen(w["n_bits"])
+    if how == "fold":
+        f = np.zeros(n, dtype=GATHER_DESC)
+        for k in ("dst_off", "out_off", "len", "seq"):
+            f[k] = d[k]
+        f["n_src"], f["src_off"][:, 0] = 2, d["src_off"]
+        f["src_off"][:, 1] = d["src_off"][0]
+        _, first, which = np.unique(d["seq"], return_index=True, return_inverse=True)
+        f = f[first][which]                                                  # copies of a record are alike
+        oracle.reduce_gather(acc, out, w["recv"], f, seen, F32, SUM)
+        recs = to_dev(f)
+    else:
+        oracle.apply(acc, out, w["recv"], d, seen, F32, SUM)
+        recs = to_dev(d)
+    assert pkg.uccl_launch_ordered(n, opts, gather=how == "fold") == 1
+    bufs = [(to_dev(w["acc"]), torch.full((w["out_bytes"],), 0xA5, dtype=torch.uint8, device="cuda"),
+             torch.zeros((w["n_bits"] + 31) // 32, dtype=torch.int32, device="cuda")) for _ in range(2)]
+    acc0 = bufs[0][0].clone()
+
+    def issue(a, o, bitmap):
+        pkg.uccl_dedup_reset(bitmap, w["n_bits"])
+        if how == "fold":
+            pkg.uccl_chunk_reduce_gather(a, o, dev_recv, recs, n, bitmap, F32, SUM, opts=opts)
+        else:
+            pkg.uccl_chunk_apply_opts(a, o, dev_recv, recs, n, bitmap, F32, SUM, opts=opts)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        issue(*bufs[0])
+    with torch.cuda.stream(side):
+        for replay in range(4):
+            for a, o, _ in bufs:
+                a.copy_(acc0)
+                o.fill_(0xA5)
+            graph.replay()
+            issue(*bufs[1])
+            side.synchronize()
+            for a, o, bitmap in bufs:
+                assert np.array_equal(a.cpu().numpy(), acc.view(np.uint8)) and np.array_equal(o.cpu().numpy(), out), (how, replay)
+                assert np.array_equal(bitmap.cpu().numpy(), oracle.pack_bitmap(seen).view(np.int32))
+
+
+@pytest.mark.gpu
 def test_timing_events_span_an_ordered_call(gpu_lib):
     """Start on the first launch, stop on the last: 3200 records of 32 KiB are read twice and written twice (400 MiB, no
     less than 52 us at 8 TB/s), the first of the two launches alone takes some 6 us."""
@@ -246,10 +300,12 @@ def test_per_thread_streams_do_not_share_scratch_words(gpu_lib):
         try:
             torch.cuda.set_device(0)
             n = len(w["descs"])
+            together.wait(30)                      # no thread is done before another has begun
             for acc, out, bitmap in sets:
                 pkg.uccl_chunk_apply_opts(acc, out, recv, descs, n, bitmap, F32, SUM, opts=(hint_for(n), 0), stream=per_thread)
         except Exception as e:  # noqa: BLE001 - reported by the main thread
             failed.append(e)
+    together = threading.Barrier(len(work))
     threads = [threading.Thread(target=issue, args=(w, sets, recv, descs)) for w, _, sets, recv, descs in work]
     for t in threads:
         t.start()
