@@ -853,7 +853,7 @@ def main():
                   else "working set fits the 256 MB last-level cache: an effective, not an HBM, figure")
     shape = (args.records_per_call or dom["records"], (opts[0], args.parts), bool(calls[0].get("gather")), dom["op"] != "COPY")
     # what the library says it launches for the dominant call
-    ordered = pkg.uccl_launch_ordered(*shape)
+    ordered = 0 if args.graph else pkg.uccl_launch_ordered(*shape)   # a captured call has no scratch words
     kernel_name = "{0}_order_kernel + {0}_ordered_kernel".format("gather" if shape[2] else "chunk") if ordered else pkg.uccl_launch_plan(*shape)["kernel"]
 
     result = headline(args.workload, args, payload, per_step, args.steps, args.warmup,

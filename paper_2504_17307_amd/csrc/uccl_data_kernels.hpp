@@ -38,7 +38,7 @@
 #define UCCL_XCD_CONTIGUOUS 0   // 1: chunk_flat_kernel gives each of the 8 XCDs one contiguous eighth of the tiles
 #endif
 #ifndef UCCL_CLAIM_STRIDE
-#define UCCL_CLAIM_STRIDE 16    // 64-bit words from one record's claim words to the next: one 128-byte line each
+#define UCCL_CLAIM_STRIDE 16    // 64-bit words from one record's claim word to the next: one 128-byte line each
 #endif
 #ifndef UCCL_CLAIM_SPIN_LIMIT
 #define UCCL_CLAIM_SPIN_LIMIT (1u << 16)  // polls of a claim word before a part gives up (see claim_await)
