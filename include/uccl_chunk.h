@@ -96,8 +96,7 @@ typedef struct uccl_extents {
  *                at most 128 records take one workgroup per record, sized to the chunk).  Calls of much payload
  *                (records x chunk_bytes: 96 MiB for a reduction, 192 MiB or chunks of 64 KiB for a copy; chunks
  *                of 16 KiB and more) are streamed in destination order, by two launches (see "Scratch
- *                memory" below); calls of 3072 to 16383 records of unknown size are decided by a launch of their
- *                own too, and streamed in arrival order.  State the size that
+ *                memory" below); so are calls of 3072 to 8191 records of unknown size.  State the size that
  *                most records of the call have: records much shorter than stated leave workgroups without work.
  *   parts        workgroups per record for calls of few, large records (Appendix C.4: small
  *                messages are where the kernel's fixed costs show): 0 = the library decides,
@@ -421,7 +420,7 @@ int uccl_feed_destroy(uccl_feed* feed);
  * are to be had (see "Scratch memory"); a call that finds none is launched with one
  * workgroup per record, or per tile of small records.
  * `ordered` > 0: where scratch memory is to be had and the records are in device memory, apply and scatter calls (not the indirect and
- * no-allocation ones, nor a feed's hand-overs) and uccl_chunk_reduce_gather decide the records first and then stream them, in destination order if the chunk size is known, in that many
+ * no-allocation ones, nor a feed's hand-overs) and uccl_chunk_reduce_gather decide the records first and stream them in destination order, in that many
  * pairs of launches (chunk_order_kernel and chunk_ordered_kernel, or their gather_ forms); the other fields say what the call is launched as otherwise.
  * UCCL_EINVAL for a NULL `plan` or options the data-path calls would refuse.  Utility, no passage
  * of the paper. */

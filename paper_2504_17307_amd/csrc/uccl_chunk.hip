@@ -129,7 +129,7 @@ uint32_t tiles_for(uint32_t n_descs, uint32_t tile) {
 // form that needs none.
 //
 // Tags come from one process-wide counter.  A call draws its tag and enqueues its launches while holding its
-// region's launch lock: claim words and the spill count of an ordered call need tags that grow in the order in which the
+// region's launch lock: claim words need tags that grow in the order in which the
 // calls of a region run, and the launches of two ordered calls on one stream must not come between each other, also
 // when several host threads issue calls on that stream.  A launch may wait for room in its stream's queue; calls on
 // other streams do not wait with it.
@@ -341,20 +341,17 @@ struct Plan {
 // Several sources per record (how many, the host does not know), 128 KiB chunks: 48 MiB of destination from one
 // source 35.3 / 32.4, from seven 82.7 / 90.0; 96 MiB 64.1 / 65.7 and 164 / 197; in 32 KiB chunks 66.0 / 69.8 and 172 / 190.
 //
-// With the chunk size unknown the same form is taken for another reason.  A workgroup per record decides
+// With the chunk size unknown the same form is taken for another reason too.  A workgroup per record decides
 // its sequence number with an atomic of its own, atomics of neighbouring records meet on one 128-byte line of
 // the bitmap, and such atomics are served one after the other, about 6.5 ns each: 5000 records take 30 us whatever
-// their size, while the order kernel's wavefronts issue 64 at a time.  Nothing is gained by the order itself, and with
-// windows of sequence numbers that are partly used most of them would share entries of the table, so a record's entry is its own index.
-// Four parts an entry suit records of any size as long as the alternative is a workgroup per record; where that is
-// tiles of four (8192 records and more), whose workgroups are few, one part of 8 KiB.  Copies have two vectors per
-// lane there too (they do better with larger units, see plan_apply).  Measured, fp32 with forward, bitmap reset
-// included, us, this form / the other; sums, sequence numbers in one run: 3072 records of 64 B 18 / 23, 4 KiB 20 / 26, 9 KB
-// 26 / 31, 32 KiB 59 / 64, 128 KiB 318 / 317; 8191 of 64 B 27 / 43, 9 KB 48 / 68, 64 KiB 413 / 414; in windows of 256 numbers of which 64
-// are used: 3072 of 64 B 16 / 17, 9 KB 25 / 28, 8191 of 9 KB 48 / 65 (entries by sequence number 32 / 29 and 60 / 50); copies: 3072 of
-// 9 KB 25 / 29, 32 KiB 49.5 / 48.5, 64 KiB 90 / 93, 8191 of 32 KiB 110.5 / 108.3.  From 8192 records on, sums: 8192 of 64 B 17 / 21, 9 KB 49 / 53,
-// 16 383 of 64 B 22 / 31, 4 KiB 44 / 51, 9 KB 85 / 93, 32 KiB 409 / 414; copies 16 383 of 4 KiB 36 / 44, 9 KB 71 / 73, 32 KiB 310 / 316; in
-// windows 16 383 of 64 B 21 / 24, copies of 16 KiB 114 / 114.  (In four parts by sequence number 16 383 of 64 B 44, copies of 4 KiB 49.)
+// their size, while the order kernel's wavefronts issue 64 at a time.  Four parts an entry suit records of any
+// size (ring steps over three sets of buffers, us, this form / one workgroup per record: 28 MiB in 4 KiB chunks 56 / 91, 64 MiB
+// in 9 KB 84 / 108, 256 MiB in 32 KiB 275 / 291, 400 MiB in 64 KiB 515 / 528; all-to-all, chunks of 8 KiB 29 / 35, of 16 KiB 35.4 / 33.0, of
+// 64 KiB 117 / 120).  Entries by arrival instead would lose no order where windows of sequence numbers are partly used (64 of 256:
+// 5000 of 4 KiB 28 by sequence number, 23 by arrival, 32 other form; of 16 KiB 64, 48, 55), but all of it elsewhere (256 MiB in 32 KiB 294).
+// Where the alternative is tiles of four records (8192 and more), whose atomics are few, the other form is taken: small
+// records lose too much to workgroups without work (16 383 of 64 B 44 / 31, 60 MiB in 4 KiB 91 / 85; windows partly used 44 / 25),
+// for what 16 - 24 KiB chunks would gain (256 MiB 281 / 308).
 //
 // A record shorter than stated leaves workgroups without work, at about 0.43 ns each, which the host cannot know: 8000
 // records of 4 KiB stated as 128 KiB 144 / 53, as 32 KiB 47 / 53.  So no record has more than kOrderMaxParts of them: 8000 of
@@ -370,14 +367,15 @@ struct Plan {
 // a stated number of parts asks for the other form.  The batcher's hand-overs stay with the other form: a hand-over
 // that fails is offered again, so it must not leave sequence numbers decided whose payload has not moved, and its
 // chunk size is the largest length in it, which may be one record's.
-constexpr uint32_t kOrderRecords = kRegionRecords * UCCL_CLAIM_STRIDE / 2 - 1;   // two words each, and the spill count
-static_assert(kOrderRecords <= 0x3FFFu, "a table entry has 14 bits for the record");
+constexpr uint32_t kOrderRecords = 0x3FFFu;
+static_assert(2u * kOrderRecords <= kRegionWords, "two words each; a table entry has 14 bits for the record");
 constexpr uint32_t kOrderChunk = 16u << 10;
 constexpr uint64_t kOrderBytes = 96ull << 20;
 constexpr uint32_t kOrderCopyChunk = 64u << 10;        // copies: chunks of this size from kOrderBytes on,
 constexpr uint64_t kOrderCopyBytes = 192ull << 20;     // smaller ones from here on
-constexpr uint32_t kOrderUnknownRecords = 3072;        // chunk size unknown: from this many records to one table full
-constexpr uint32_t kOrderUnknownTiles = 8192;          // where its alternative is tiles of four records (flat_tile)
+constexpr uint32_t kOrderUnknownRecords = 3072;        // chunk size unknown: from this many records
+constexpr uint32_t kOrderUnknownTiles = 8192;          // to less than this many: tiles from here on (flat_tile)
+constexpr uint32_t kOrderUnknownParts = 4;
 constexpr uint32_t kMaxLaunchThreads = 0xFFFFFFFFu;    // HIP counts a launch's threads in 32 bits
 constexpr uint32_t kOrderMaxParts = 32;   // longer records are walked
 
@@ -389,17 +387,13 @@ bool in_device_memory(const void* p) {
 }
 
 struct OrderPlan {
-  uint32_t launches, parts, unroll;
-  bool by_seq;
+  uint32_t launches, parts;
 };
-constexpr OrderPlan kNotOrdered = {0u, 1u, 1u, false};
+constexpr OrderPlan kNotOrdered = {0u, 1u};
 
 OrderPlan plan_ordered(uint32_t n_descs, const Tuning& tune, bool reads_acc, bool gather) {
-  if (tune.parts == 0u && tune.chunk_bytes == 0u && !gather) {
-    if (n_descs < kOrderUnknownRecords || n_descs > kOrderRecords) return kNotOrdered;
-    const bool tiles = n_descs >= kOrderUnknownTiles;
-    return {1u, tiles ? 1u : 4u, tiles || !reads_acc ? 2u : 1u, false};
-  }
+  if (tune.parts == 0u && tune.chunk_bytes == 0u && !gather)
+    return n_descs >= kOrderUnknownRecords && n_descs < kOrderUnknownTiles ? OrderPlan{1u, kOrderUnknownParts} : kNotOrdered;
   if (tune.parts != 0u || tune.chunk_bytes < kOrderChunk || n_descs == 0u) return kNotOrdered;
   // A count that is too large for the form of one launch is refused there, before anything is enqueued: a count that
   // is none (-1) must not become a quarter of a million launches.
@@ -408,7 +402,7 @@ OrderPlan plan_ordered(uint32_t n_descs, const Tuning& tune, bool reads_acc, boo
   const uint64_t least = reads_acc || tune.chunk_bytes >= kOrderCopyChunk ? kOrderBytes : kOrderCopyBytes;
   if (static_cast<uint64_t>(n_descs / launches) * tune.chunk_bytes < least) return kNotOrdered;
   const uint32_t parts = (tune.chunk_bytes - 1u) / kOrderPartBytes + 1u;
-  return {launches, parts < kOrderMaxParts ? parts : kOrderMaxParts, 1u, true};
+  return {launches, parts < kOrderMaxParts ? parts : kOrderMaxParts};
 }
 
 Plan plan_apply(uint32_t n_descs, const Tuning& tune, bool reads_acc) {
@@ -449,10 +443,7 @@ int launch_ordered(void (*order)(KernelArgs, OrderArgs), void (*stream)(KernelAr
     a.n_descs = static_cast<uint32_t>(static_cast<uint64_t>(n) * (i + 1u) / o.launches) - from;
     OrderArgs t;
     t.words = region;
-    t.spilled = region + kRegionWords - 1u;
     t.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
-    t.part_bytes = kOrderPartBytes * o.unroll;
-    t.entries = o.by_seq ? a.n_descs : 0u;
     t_start = i == 0u ? begin : nullptr;
     t_stop = i == 0u ? end : nullptr;
     rc = launch_kernel(order, (a.n_descs + 255u) / 256u, 256, s, a, t);
@@ -473,8 +464,7 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
       std::lock_guard<std::mutex> in_order(*region.launch_lock);
       // held back only where the records are known to be large: empty parts want as many workgroups as there can be
       const uint32_t lds = Op::kReadsAcc && tune.chunk_bytes != 0u ? kOrderReduceLds : 0u;
-      return launch_ordered<Args>(chunk_order_kernel<Op::kEs>, ordered.unroll == 1u ? chunk_ordered_kernel<1, Op> : chunk_ordered_kernel<2, Op>, lds, a, s,
-                                  ordered, region.words);
+      return launch_ordered<Args>(chunk_order_kernel<Op::kEs>, chunk_ordered_kernel<Op>, lds, a, s, ordered, region.words);
     }
   }
   Plan p = plan_apply(a.n_descs, tune, Op::kReadsAcc);

@@ -353,8 +353,7 @@ __global__ void __launch_bounds__(NT) chunk_flat_kernel(const Args g) {
 //            atomic exchange; n = records of the launch).  Sequence numbers ascend with the destination
 //            in a collective's stream and a call covers about one run of them, so the table lists the
 //            winners in destination order.  Two winners of one entry (sequence numbers that are no run)
-//            are both served: the one that was there goes to the spill list, in any order.  (Calls of unknown
-//            chunk size are ordered for another reason, see plan_ordered: there a record's entry is its own index.)
+//            are both served: the one that was there moves to a second list, to the entry of its own index.
 //   stream   workgroup b takes 4 KiB part b mod `parts` of the record in entry b / parts: no atomic, no
 //            barrier, no LDS.  Consecutive workgroups run on different XCDs; runs of kOrderRun of them
 //            (128 KiB) are laid out so that each XCD works on one contiguous piece (1 GiB reduce-scatter
@@ -363,42 +362,31 @@ __global__ void __launch_bounds__(NT) chunk_flat_kernel(const Args g) {
 //            not use (562 us; eight 609, seven 591, five 591); copies are not (the 256 MiB bf16 step: 269 us
 //            either way; five 283).
 //
-// Words of the table and the spill list carry the call's tag as claim words do, so nothing is cleared.
-// Entry i of the table is word 2 i and entry i of the spill list word 2 i + 1: one load serves both.  An entry
+// Words of both lists carry the call's tag as claim words do, so nothing is cleared.
+// Entry i of the table is word 2 i and entry i of the second list word 2 i + 1: one load serves both.  (That list
+// needs no atomics and spreads over all workgroups: with windows of 256 sequence numbers of which 64 are used three
+// records of four are on it; numbered by a counter instead, 16 383 records of 16 KiB take 229 us, so 209.)  An entry
 // also says whether its record has no more than one, two or four parts, so that a workgroup whose part
 // does not exist leaves without reading the record.  Which of an entry's workgroups takes which part turns
 // with the entry: records shorter than `parts` parts would otherwise leave the same workgroups idle every time,
 // and as workgroups are dealt to the shader engines in turn, the same engines (5000 records of 4 KiB each
 // in four parts: 73 us the two phases without, 47 with it).
 constexpr uint32_t kOrderThreads = 256;            // 4 KiB per stream: one vector per lane
-constexpr uint32_t kOrderPartBytes = kOrderThreads * 16u;   // of a part; twice that with two vectors per lane
+constexpr uint32_t kOrderPartBytes = kOrderThreads * 16u;
 constexpr uint32_t kOrderRun = 32;
 constexpr uint32_t kOrderReduceLds = 24576;
 
 struct OrderArgs {
   unsigned long long* words;    // 2 * n_descs words: tag << 16 | size class << 14 | record
-  unsigned long long* spilled;  // tag << 16 | length of the spill list
   unsigned long long tag;
-  uint32_t part_bytes;
-  uint32_t entries;             // a record's entry is its sequence number modulo this; 0: its index
 };
 
-// Record k (below 2^14), a first arrival, into the table.
-__device__ __forceinline__ void order_put(const OrderArgs& t, uint32_t seq, uint32_t k, uint32_t len) {
-  const uint32_t size = len <= t.part_bytes ? 0u : len <= 2u * t.part_bytes ? 1u : len <= 4u * t.part_bytes ? 2u : 3u;
-  const unsigned long long entry = (t.tag << 16) | (size << 14) | k;
-  if (t.entries == 0u) {
-    t.words[2u * static_cast<size_t>(k)] = entry;
-    return;
-  }
-  const unsigned long long was = __hip_atomic_exchange(t.words + 2u * static_cast<size_t>(seq % t.entries), entry,
+// Record k (below 2^14), a first arrival, into the table of a launch of n records.
+__device__ __forceinline__ void order_put(const OrderArgs& t, uint32_t n, uint32_t seq, uint32_t k, uint32_t len) {
+  const uint32_t size = len <= kOrderPartBytes ? 0u : len <= 2u * kOrderPartBytes ? 1u : len <= 4u * kOrderPartBytes ? 2u : 3u;
+  const unsigned long long was = __hip_atomic_exchange(t.words + 2u * static_cast<size_t>(seq % n), (t.tag << 16) | (size << 14) | k,
                                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if ((was >> 16) == t.tag) {
-    // the count starts at this call's tag whichever lane gets there first: an older call's is smaller
-    __hip_atomic_fetch_max(t.spilled, t.tag << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned long long at = __hip_atomic_fetch_add(t.spilled, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xFFFFu;
-    t.words[2u * at + 1u] = was;   // at < winners <= n
-  }
+  if ((was >> 16) == t.tag) t.words[2u * (static_cast<size_t>(was) & 0x3FFFu) + 1u] = was;   // a record is displaced once at most
 }
 
 // Whether `entry` is of this call and its record has a part `part` (size class 3: any number of parts).
@@ -430,35 +418,35 @@ __global__ void __launch_bounds__(256) chunk_order_kernel(const Args g, const Or
   }
   const uint32_t bit = 1u << (seq & 31u);
   if ((atomicOr(g.bitmap + (seq >> 5), bit) & bit) != 0u) return;
-  order_put(t, seq, k, hi.z);
+  order_put(t, g.n_descs, seq, k, hi.z);
 }
 
-// Part `part` of record k, U vectors per lane: units part * 4 + wavefront, then every parts * 4 units (a record longer
+// Part `part` of record k: units part * 4 + wavefront, then every parts * 4 units (a record longer
 // than all its parts).
-template <int U, class Op>
+template <class Op>
 __device__ __forceinline__ void ordered_part(const Args& g, uint32_t k, uint32_t part) {
-  constexpr uint32_t kUnit = 64u * U, kWaves = kOrderThreads / 64;
+  constexpr uint32_t kUnit = 64u, kWaves = kOrderThreads / 64;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
   const uccl_chunk_desc d = g.descs[k];   // the same address in every lane
   const uint32_t vecs = (d.len >> 4) + ((d.len & 15u) != 0u ? 1u : 0u);
   const uint32_t total = (vecs + kUnit - 1u) / kUnit;
   for (uint32_t u = part * kWaves + wave; u < total; u += g.parts * kWaves) {
     if (d.out_off == UCCL_NO_FORWARD)
-      stream_unit<U, Op, false, true>(g.recv + d.src_off, g.acc + d.dst_off, nullptr, d.len, u, lane);
+      stream_unit<1, Op, false, true>(g.recv + d.src_off, g.acc + d.dst_off, nullptr, d.len, u, lane);
     else if (d.out_off & UCCL_FORWARD_ONLY)
-      stream_unit<U, Op, true, false>(g.recv + d.src_off, g.acc + d.dst_off, g.out + (d.out_off & ~UCCL_FORWARD_ONLY), d.len, u, lane);
+      stream_unit<1, Op, true, false>(g.recv + d.src_off, g.acc + d.dst_off, g.out + (d.out_off & ~UCCL_FORWARD_ONLY), d.len, u, lane);
     else
-      stream_unit<U, Op, true, true>(g.recv + d.src_off, g.acc + d.dst_off, g.out + d.out_off, d.len, u, lane);
+      stream_unit<1, Op, true, true>(g.recv + d.src_off, g.acc + d.dst_off, g.out + d.out_off, d.len, u, lane);
   }
 }
 
-template <int U, class Op>
+template <class Op>
 __global__ void __launch_bounds__(kOrderThreads) chunk_ordered_kernel(const Args g, const OrderArgs t) {
   const uint32_t b = order_position(), entry = b / g.parts, part = (b + entry) % g.parts;
   const unsigned long long first = t.words[2u * static_cast<size_t>(entry)];
-  const unsigned long long spill = t.words[2u * static_cast<size_t>(entry) + 1u];
-  if (order_has(t, first, part)) ordered_part<U, Op>(g, order_record(first), part);
-  if (order_has(t, spill, part)) ordered_part<U, Op>(g, order_record(spill), part);
+  const unsigned long long second = t.words[2u * static_cast<size_t>(entry) + 1u];
+  if (order_has(t, first, part)) ordered_part<Op>(g, order_record(first), part);
+  if (order_has(t, second, part)) ordered_part<Op>(g, order_record(second), part);
 }
 
 // ---- calls of few records --------------------------------------------------------------------
@@ -884,7 +872,7 @@ __global__ void __launch_bounds__(256) gather_order_kernel(const GatherArgs g, c
   }
   const uint32_t bit = 1u << (seq & 31u);
   if ((atomicOr(g.bitmap + (seq >> 5), bit) & bit) != 0u) return;
-  order_put(t, seq, k, len);
+  order_put(t, g.n_descs, seq, k, len);
 }
 
 template <class Op>
@@ -903,9 +891,9 @@ template <class Op>
 __global__ void __launch_bounds__(kOrderThreads) gather_ordered_kernel(const GatherArgs g, const OrderArgs t) {
   const uint32_t b = order_position(), entry = b / g.parts, part = (b + entry) % g.parts;
   const unsigned long long first = t.words[2u * static_cast<size_t>(entry)];
-  const unsigned long long spill = t.words[2u * static_cast<size_t>(entry) + 1u];
+  const unsigned long long second = t.words[2u * static_cast<size_t>(entry) + 1u];
   if (order_has(t, first, part)) ordered_gather_part<Op>(g, order_record(first), part);
-  if (order_has(t, spill, part)) ordered_gather_part<Op>(g, order_record(spill), part);
+  if (order_has(t, second, part)) ordered_gather_part<Op>(g, order_record(second), part);
 }
 
 // ---- sender side: tensor buffer -> staged chunks + send records --------------------------------

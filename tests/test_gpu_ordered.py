@@ -1,5 +1,5 @@
 """Calls that are streamed in destination order (chunk_order_kernel, chunk_ordered_kernel): the rule that
-picks them (CPU), and parity at the edges of the table, its spill list, parts and launches (GPU).  The rule
+picks them (CPU), and parity at the edges of the table, its second list, parts and launches (GPU).  The rule
 looks at the stated chunk size alone, and results never depend on it, so small records with a large stated
 size reach every branch."""
 import numpy as np
@@ -25,7 +25,7 @@ def test_rule():
     assert copy(TABLE, 16 * KiB) == 1 and copy(TABLE + 1, 16 * KiB) == 0                 # whose shares have to be worth it
     assert copy(6144, 32 * KiB) == 1 and copy(6143, 32 * KiB) == 0 and copy(1536, 64 * KiB) == 1 and copy(1535, 64 * KiB) == 0
     assert ordered(1 << 20, (32 * KiB, 1)) == 0                                          # parts stated
-    assert [ordered(n, None) for n in (3071, 3072, TABLE, TABLE + 1)] == [0, 1, 1, 0]    # no size given
+    assert [ordered(n, None) for n in (3071, 3072, 8191, 8192)] == [0, 1, 1, 0]    # no size given
     assert ordered(5000, (0, 0), gather=True) == 0 and ordered(5000, (0, 1)) == 0
     assert ordered(0, (32 * KiB, 0)) == 0
     # counts that one workgroup per record (two records of 16 KiB) could not be launched for are refused, not split
@@ -69,7 +69,7 @@ def hint_for(n):
     return max(16384, -(-192 * MiB // (n // launches)) + 15 & ~15)
 
 
-# how the sequence numbers meet the table: one run; all of them in one entry (the rest spills); a few per entry
+# how the sequence numbers meet the table: one run; all of them in one entry (the rest on the second list); a few per entry
 SPREAD = {"run": lambda n, seq: seq, "one entry": lambda n, seq: seq * n, "pairs": lambda n, seq: (seq // 2) + (seq % 2) * (3 * n)}
 
 
@@ -87,7 +87,7 @@ def test_random_streams(gpu_lib, spread, dtype, op):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n,stated", [(TABLE - 1, True), (TABLE, True), (TABLE + 1, True), (2 * TABLE + 1, True), (40001, True), (3072, False), (8191, False), (8192, False), (TABLE, False)])
+@pytest.mark.parametrize("n,stated", [(TABLE - 1, True), (TABLE, True), (TABLE + 1, True), (2 * TABLE + 1, True), (40001, True), (3072, False), (8191, False)])
 def test_table_and_launch_edges(gpu_lib, n, stated):
     """Calls around one and two launches' worth of records, in shuffled order with repeats and some
     out-of-range sequence numbers; records of 0..48 bytes, and a few that are longer than all parts of one."""

@@ -39,8 +39,8 @@ class Runtime:
             return 1
         scratch = None
         if name in ("chunk_order_kernel", "chunk_ordered_kernel", "gather_order_kernel", "gather_ordered_kernel"):
-            words = C.cast(args[1], C.POINTER(C.c_uint64))           # OrderArgs: words, spilled, tag
-            scratch = words[0], words[2], words[3] & 0xFFFFFFFF, words[3] >> 32   # and bytes of a part, entries
+            words = C.cast(args[1], C.POINTER(C.c_uint64))           # OrderArgs: words, tag
+            scratch = words[0], words[1]
         elif name == "ack_segments_kernel":
             scratch = C.cast(args[5], C.POINTER(C.c_uint64))[0], C.cast(args[6], C.POINTER(C.c_uint64))[0]
         self.launches.append((name, grid, block, lds, stream or 0, scratch))
@@ -238,15 +238,18 @@ def test_records_outside_device_memory_are_read_once(tmp_path):
 
 
 def unknown_sizes(rt):
-    for n, op, parts, part_bytes in ((3072, 0, 4, 4096), (8191, 0, 4, 4096), (3072, pkg.UCCL_COPY, 4, 8192), (8191, pkg.UCCL_COPY, 4, 8192),
-                                     (8192, 0, 1, 8192), (16383, 0, 1, 8192), (8192, pkg.UCCL_COPY, 1, 8192), (16383, pkg.UCCL_COPY, 1, 8192)):
-        rt.launches.clear()
-        assert rt.apply(n, op=op) == 0
-        (order, _, _, _, _, scratch), (stream, grid, block, _, _, _) = rt.launches
-        # no entries by sequence number: windows of numbers that are partly used would meet in few of them
-        assert (order, stream, grid, block, scratch[2:]) == ("chunk_order_kernel", "chunk_ordered_kernel", n * parts, 256, (part_bytes, 0)), n
-    rt.launches.clear()
-    assert rt.apply(8000, 32 * KiB) == 0 and rt.launches[0][5][2:] == (4096, 8000) and rt.launches[1][1] == 8 * 8000
+    for op in (0, pkg.UCCL_COPY):
+        for n in (3072, 8191):
+            rt.launches.clear()
+            assert rt.apply(n, op=op) == 0
+            assert [l[:3] for l in rt.launches] == [("chunk_order_kernel", -(-n // 256), 256), ("chunk_ordered_kernel", 4 * n, 256)]
+        for n in (3071, 8192, 16383):      # from 8192 on: tiles of four records
+            rt.launches.clear()
+            assert rt.apply(n, op=op) == 0 and [l[:2] for l in rt.launches] == [("chunk_flat_kernel", n if n < 8192 else -(-n // 4))]
+
+
+def test_calls_of_unknown_size_take_tiles_where_there_are_many_records(tmp_path):
+    in_process("unknown_sizes", tmp_path)
 
 
 def stated_sizes(rt):
