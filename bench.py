@@ -36,11 +36,11 @@ METRIC = "reduced payload GB/s (dedup+place+reduce+forward of one rank's chunk s
 # kernel source it was measured on, identified by the hash of the HIP source files.
 MEASURED_TRAFFIC = {
     # (workload, source_hash() of the files under csrc/): bytes per launch
-    ("config1", "e3cdccda022a1ee5"): 14888152,
-    ("config2", "e3cdccda022a1ee5"): 1008563096,
-    ("config3", "e3cdccda022a1ee5"): 3626326858,
-    ("config4", "e3cdccda022a1ee5"): 108179920,
-    ("direct-rs", "e3cdccda022a1ee5"): 1208717772,
+    ("config1", "513f954255dab2ae"): 14888928,
+    ("config2", "513f954255dab2ae"): 1008560398,
+    ("config3", "513f954255dab2ae"): 3626320066,
+    ("config4", "513f954255dab2ae"): 108171840,
+    ("direct-rs", "513f954255dab2ae"): 1208724706,
 }
 
 WORKLOADS = {

@@ -472,12 +472,13 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
     a.parts = p.parts;
     const auto launch_parts = [&](unsigned long long tag) {
       a.tag = tag;
-      return launch_kernel(chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, true>, a.n_descs * p.parts, UCCL_PART_THREADS, s, a);
+      return launch_kernel(tune.static_claims != nullptr ? chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, true, true>
+                                                         : chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, true, false>,
+                           a.n_descs * p.parts, UCCL_PART_THREADS, s, a);
     };
     if (tune.static_claims != nullptr) {
       // Every call shares the device's one array and finds what other calls left there stale by their tags.
       a.claims = tune.static_claims;
-      a.apart = 1u;
       a.faults = reinterpret_cast<uint32_t*>(tune.static_claims + UCCL_NOALLOC_MAX_DESCS * UCCL_CLAIM_STRIDE);
       hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
       if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
@@ -644,7 +645,6 @@ int apply_common(void* acc, void* out_stage, const void* recv_stage, const uccl_
   a.faults = nullptr;
   a.parts = 1u;
   a.tag = 0ull;
-  a.apart = 0u;
   if (ext) {
     if (overlaps(recv_stage, ext->recv_bytes, acc, ext->acc_bytes) ||
         overlaps(recv_stage, ext->recv_bytes, out_stage, ext->out_bytes) ||

@@ -66,7 +66,6 @@ struct Args {
   uint32_t* faults;
   unsigned long long tag;
   uint32_t parts;
-  uint32_t apart;   // 1: the outcome has a word of its own
 };
 
 // ---- one record, several workgroups ------------------------------------------------------
@@ -91,10 +90,11 @@ struct Args {
 //   await    the other parts poll the word until it carries the call's tag and an outcome.
 //
 // The no-allocation calls share their words over all streams, so the order in which calls run need not be that of
-// their tags.  There (`apart` = 1) a part exchanges the word instead and decides if it finds any other tag, and the
+// their tags.  There (APART) a part exchanges the word instead and decides if it finds any other tag, and the
 // outcome is in the next word, where no part that comes later can overwrite it.  Every part then waits for one
 // more load, which costs a call of many parts more (fold of 65 x 128 KiB from three senders, 16 parts, 9.4 -> 10.6 us;
-// 28 records in 8 parts nothing that can be measured), so calls with a region of their own have the other way.
+// 28 records in 8 parts nothing that can be measured), so calls with a region of their own have the other way, in
+// a kernel of its own (choosing at run time costs a 4 MiB ring step 2 %).
 //
 // A part only ever waits for a part that is already running and never waits itself, so the wait
 // ends whatever order the hardware starts workgroups in.  It is bounded all the same: a part that
@@ -111,28 +111,31 @@ struct Claim {
   unsigned long long seen;   // what the word with the outcome held: the outcome may already be in it
 };
 
-__device__ __forceinline__ Claim claim_enter(unsigned long long* claim, unsigned long long tag, uint32_t apart) {
-  if (apart == 0u) {
+template <bool APART>
+__device__ __forceinline__ Claim claim_enter(unsigned long long* claim, unsigned long long tag) {
+  if constexpr (!APART) {
     const unsigned long long was = __hip_atomic_fetch_max(claim, tag << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return {(was >> 16) < tag, was};
+  } else {
+    const unsigned long long was = __hip_atomic_exchange(claim, tag << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return {(was >> 16) != tag, __hip_atomic_load(claim + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)};
   }
-  const unsigned long long was = __hip_atomic_exchange(claim, tag << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return {(was >> 16) != tag, __hip_atomic_load(claim + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)};
 }
 
-__device__ __forceinline__ void claim_publish(unsigned long long* claim, unsigned long long tag, uint32_t apart, bool win) {
-  __hip_atomic_store(claim + apart, (tag << 16) | (win ? 1ull : 2ull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+template <bool APART>
+__device__ __forceinline__ void claim_publish(unsigned long long* claim, unsigned long long tag, bool win) {
+  __hip_atomic_store(claim + (APART ? 1 : 0), (tag << 16) | (win ? 1ull : 2ull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ bool claim_await(unsigned long long* claim, unsigned long long seen, unsigned long long tag, uint32_t apart,
-                                            uint32_t* faults) {
+template <bool APART>
+__device__ __forceinline__ bool claim_await(unsigned long long* claim, unsigned long long seen, unsigned long long tag, uint32_t* faults) {
   for (uint32_t polls = 0; (seen >> 16) != tag || (seen & 3ull) == 0ull; ++polls) {
     if (polls >= UCCL_CLAIM_SPIN_LIMIT) {
       atomicAdd(faults, 1u);
       return false;
     }
     __builtin_amdgcn_s_sleep(1);
-    seen = __hip_atomic_load(claim + apart, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    seen = __hip_atomic_load(claim + (APART ? 1 : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   return (seen & 3ull) == 1ull;
 }
@@ -476,7 +479,7 @@ __device__ __forceinline__ void finish_unit(const u32x4 (&rv)[U], const u32x4 (&
   }
 }
 
-template <int NT, int U, class Op, bool PARTS>
+template <int NT, int U, class Op, bool PARTS, bool APART = false>
 __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
   constexpr uint32_t kUnit = 64u * U;
   constexpr uint32_t kWaves = NT / 64;
@@ -523,7 +526,7 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
   if (tid == 0) {
     uint32_t win = 0u;
     Claim entered = {true, 0ull};
-    if constexpr (PARTS) entered = claim_enter(claim, g.tag, g.apart);
+    if constexpr (PARTS) entered = claim_enter<APART>(claim, g.tag);
     if (entered.decides) {
       if (ok) {
         const uint32_t bit = 1u << (seq & 31u);
@@ -531,9 +534,9 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
       } else if (is_record && g.rejected != nullptr) {  // a rejected record is counted once: by the part that decides
         atomicAdd(g.rejected, 1u);
       }
-      if constexpr (PARTS) claim_publish(claim, g.tag, g.apart, win != 0u);
+      if constexpr (PARTS) claim_publish<APART>(claim, g.tag, win != 0u);
     } else if (part_has_units) {  // a part without units has nothing to wait for
-      win = claim_await(claim, entered.seen, g.tag, g.apart, g.faults) ? 1u : 0u;
+      win = claim_await<APART>(claim, entered.seen, g.tag, g.faults) ? 1u : 0u;
     }
     s_win = win;
   }
@@ -830,7 +833,7 @@ __global__ void __launch_bounds__(NT) chunk_gather_parts_kernel(const GatherArgs
     uint32_t win = 0u;
     unsigned long long* const claim = g.claims + static_cast<size_t>(k) * UCCL_CLAIM_STRIDE;
     Claim entered = {true, 0ull};
-    if (g.parts > 1u) entered = claim_enter(claim, g.tag, 0u);   // the only part has nobody to agree with
+    if (g.parts > 1u) entered = claim_enter<false>(claim, g.tag);   // the only part has nobody to agree with
     if (entered.decides) {
       if (ok) {
         const uint32_t bit = 1u << (seq & 31u);
@@ -838,9 +841,9 @@ __global__ void __launch_bounds__(NT) chunk_gather_parts_kernel(const GatherArgs
       } else if (g.rejected != nullptr) {
         atomicAdd(g.rejected, 1u);
       }
-      if (g.parts > 1u) claim_publish(claim, g.tag, 0u, win != 0u);
+      if (g.parts > 1u) claim_publish<false>(claim, g.tag, win != 0u);
     } else if (ok && part * kWaves < total) {  // a part without units has nothing to wait for
-      win = claim_await(claim, entered.seen, g.tag, 0u, g.faults) ? 1u : 0u;
+      win = claim_await<false>(claim, entered.seen, g.tag, g.faults) ? 1u : 0u;
     }
     s_win = win;
   }
