@@ -36,11 +36,11 @@ METRIC = "reduced payload GB/s (dedup+place+reduce+forward of one rank's chunk s
 # kernel source it was measured on, identified by the hash of the HIP source files.
 MEASURED_TRAFFIC = {
     # (workload, source_hash() of the files under csrc/): bytes per launch
-    ("config1", "513f954255dab2ae"): 14888928,
-    ("config2", "513f954255dab2ae"): 1008560398,
-    ("config3", "513f954255dab2ae"): 3626320066,
-    ("config4", "513f954255dab2ae"): 108171840,
-    ("direct-rs", "513f954255dab2ae"): 1208724706,
+    ("config1", "ba5be6cd6a9bb4c9"): 14890512,
+    ("config2", "ba5be6cd6a9bb4c9"): 1008563310,
+    ("config3", "ba5be6cd6a9bb4c9"): 3626310490,
+    ("config4", "ba5be6cd6a9bb4c9"): 108168288,
+    ("direct-rs", "ba5be6cd6a9bb4c9"): 1208711420,
 }
 
 WORKLOADS = {
