@@ -669,7 +669,7 @@ def main():
     import torch
     import paper_2504_17307_amd as pkg
     assert torch.cuda.is_available(), "bench.py needs a GPU"
-    pkg.uccl_init()   # loads the library (raises if it is not built) and makes its scratch memory
+    pkg.uccl_init()   # loads the library (raises if it is not built) and its code object
     if args.workload == "config5-graph":
         return bench_graph_feed(args, pkg, torch)
     if args.workload == "config5-feed":
