@@ -114,6 +114,39 @@ def test_table_and_launch_edges(gpu_lib, n, stated):
         check(w, (hint_for(n) if stated else 0, 0), rejected=int(bad.sum()))
 
 
+# how the 64 sequence numbers of a wavefront meet its slots: two words; one number, 32 numbers of one word twice each; a word
+# per lane, all in one slot; the same, two lanes a word; words of two slots only; the largest numbers
+SLOTS = {"in order": lambda i: i, "one number": lambda i: i // 64, "one word": lambda i: i // 64 * 32 + i % 32,
+         "one slot": lambda i: i % 64 * 4096 + i // 64, "one slot, pairs": lambda i: i % 32 * 4096 + i // 64 * 2 + i // 32 % 2,
+         "two slots": lambda i: i % 64 // 2 * 4096 + i % 2 * 32 + i // 64 % 32 + i // 2048 * (1 << 17), "largest": lambda i: (1 << 32) - 1 - i}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("meet", sorted(SLOTS))
+def test_sequence_numbers_of_a_wavefront(gpu_lib, meet):
+    """One atomic per bitmap word and wavefront: every number is taken once, by one of its records."""
+    import torch
+    from gpuhelp import to_dev
+    n, g = 3072 + 37, np.random.default_rng(5)
+    seq = SLOTS[meet](np.arange(n, dtype=np.int64))
+    d = np.zeros(n, dtype=DESC)
+    at = np.unique(seq, return_inverse=True)[1]                      # copies of a number are alike
+    d["src_off"] = d["dst_off"] = at * 16
+    d["out_off"], d["len"], d["seq"] = NO_FORWARD, 16, seq
+    acc0, recv = g.random(n * 4, dtype=np.float32), g.random(n * 4, dtype=np.float32)
+    exp = acc0.copy()
+    exp[:(int(at.max()) + 1) * 4] += recv[:(int(at.max()) + 1) * 4]
+    assert pkg.uccl_launch_ordered(n) == 1
+    acc, bitmap = to_dev(acc0), torch.zeros((int(seq.max()) + 32) // 32, dtype=torch.int32, device="cuda")
+    bits = np.zeros(len(bitmap), dtype=np.uint32)
+    np.bitwise_or.at(bits, seq >> 5, np.uint32(1) << (seq & 31).astype(np.uint32))
+    for again in range(2):                                            # the second call finds every bit set
+        pkg.uccl_chunk_apply(acc, None, to_dev(recv), to_dev(d), n, bitmap, F32, SUM)
+        torch.cuda.synchronize()
+        assert np.array_equal(acc.cpu().numpy().view(np.float32), exp), again
+        assert np.array_equal(bitmap.cpu().numpy().view(np.uint32), bits)
+
+
 @pytest.mark.gpu
 def test_calls_in_turn_share_a_region(gpu_lib):
     """Ordered calls and calls cut into parts in turn on one stream: they share its scratch words, and each
