@@ -148,7 +148,8 @@ typedef struct uccl_launch_opts {
  * handle, for the first 64 that issue such a call on the device (hipStreamPerThread: one per thread, for the first 16
  * threads).  A region is never given back; a stream created later under the handle of a destroyed one takes it over
  * (hipStreamDestroy waits for the work on the stream).  Calls that are
- * streamed in destination order (uccl_launch_opts) keep that order, folds of small chunks their claim words and
+ * streamed in destination order (uccl_launch_opts) keep that order, calls of hundreds of records the outcome of every 64 of
+ * them, folds of small chunks their claim words and
  * uccl_dedup_report its counts in a second region of the stream, of which there are 64 too.  If the stream has no region, or is being captured into a graph, the
  * call is launched in the form that needs no scratch
  * memory instead (one workgroup per record or per tile of records): slower, same result.  No
@@ -166,7 +167,7 @@ int uccl_init(void);
 /*
  * uccl_chunk_apply_noalloc -- uccl_chunk_apply for callers that cannot allocate device memory:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
- * operation and result; the claim words of records cut into parts (see "Scratch memory" above)
+ * operation and result; the claim words of records cut into parts (at most 128 records; see "Scratch memory" above)
  * live in an array that needs no region: UCCL_NOALLOC_MAX_DESCS
  * lines of 128 bytes + 256 bytes = 256.25 KiB, held like the regions.  Calls are cut under capture too.
  *   - n_descs > UCCL_NOALLOC_MAX_DESCS returns UCCL_ETOOBIG and enqueues nothing.  (Calls that
@@ -422,6 +423,8 @@ int uccl_feed_destroy(uccl_feed* feed);
  * `ordered` > 0: where scratch memory is to be had and the records are in device memory, apply and scatter calls (not the indirect and
  * no-allocation ones, nor a feed's hand-overs) and uccl_chunk_reduce_gather decide the records first and stream them in destination order, in that many
  * pairs of launches (chunk_order_kernel and chunk_ordered_kernel, or their gather_ forms); the other fields say what the call is launched as otherwise.
+ * `grouped` > 0: in the same circumstances (the no-allocation calls included), unless it is ordered, such a call of hundreds of records is one
+ * launch of chunk_group_kernel, in which the first workgroup of every 64 records decides them for the others.
  * UCCL_EINVAL for a NULL `plan` or options the data-path calls would refuse.  Utility, no passage
  * of the paper. */
 enum { UCCL_KERNEL_FLAT = 0, UCCL_KERNEL_FEW = 1, UCCL_KERNEL_GATHER = 2, UCCL_KERNEL_GATHER_PARTS = 3 };
@@ -433,7 +436,7 @@ typedef struct uccl_plan {
   uint32_t groups;            /* workgroups in the launch */
   uint32_t unit_bytes;        /* bytes per stream a wavefront moves per trip */
   uint32_t ordered;           /* pairs of launches of the ordered form, 0 = not ordered */
-  uint32_t reserved;          /* 0 */
+  uint32_t grouped;           /* workgroups per record of the form that decides 64 records at once, 0 = not that form */
 } uccl_plan;
 int uccl_launch_plan(uint32_t n_descs, const uccl_launch_opts* opts, int gather, int reads_acc, uccl_plan* plan);
 

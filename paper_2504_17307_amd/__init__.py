@@ -37,7 +37,7 @@ class uccl_launch_opts(C.Structure):
 class uccl_plan(C.Structure):
     _fields_ = [("kernel", C.c_uint32), ("records_per_group", C.c_uint32), ("parts", C.c_uint32),
                 ("threads", C.c_uint32), ("groups", C.c_uint32), ("unit_bytes", C.c_uint32),
-                ("ordered", C.c_uint32), ("reserved", C.c_uint32)]
+                ("ordered", C.c_uint32), ("grouped", C.c_uint32)]
 
 
 KERNEL_NAMES = ("chunk_flat_kernel", "chunk_few_kernel", "chunk_gather_kernel", "chunk_gather_parts_kernel")
@@ -386,7 +386,7 @@ def uccl_launch_plan(n_descs, opts=None, gather=False, reads_acc=True) -> dict:
     """What a call of ``n_descs`` records with these options is launched as (host arithmetic only)."""
     p = uccl_plan()
     _call("uccl_launch_plan", int(n_descs), _opts(opts), int(bool(gather)), int(bool(reads_acc)), C.byref(p))
-    d = {k: getattr(p, k) for k, _ in uccl_plan._fields_ if k not in ("ordered", "reserved")}
+    d = {k: getattr(p, k) for k, _ in uccl_plan._fields_ if k not in ("ordered", "grouped")}
     d["kernel"] = KERNEL_NAMES[p.kernel]
     return d
 
@@ -396,6 +396,13 @@ def uccl_launch_ordered(n_descs, opts=None, gather=False, reads_acc=True) -> int
     p = uccl_plan()
     _call("uccl_launch_plan", int(n_descs), _opts(opts), int(bool(gather)), int(bool(reads_acc)), C.byref(p))
     return p.ordered
+
+
+def uccl_launch_grouped(n_descs, opts=None, gather=False, reads_acc=True) -> int:
+    """``uccl_plan.grouped``: workgroups per record of a call whose records are decided 64 at a time, 0 = they are not."""
+    p = uccl_plan()
+    _call("uccl_launch_plan", int(n_descs), _opts(opts), int(bool(gather)), int(bool(reads_acc)), C.byref(p))
+    return p.grouped
 
 
 def uccl_time_next_launch(start_event, stop_event):

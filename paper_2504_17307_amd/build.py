@@ -9,8 +9,8 @@ CSRC = os.path.join(PKG, "csrc")
 SRC = os.path.join(CSRC, "uccl_chunk.hip")  # the one translation unit; it includes the .hpp files beside it
 INC = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libuccl_chunk.so")
-# aids of bench.py (dense streaming kernels) and of the tests (the report's recount), a library of their own
-PROBE_SRC = [os.path.join(PKG, "probe", f) for f in ("stream_probe.hip", "report_probe.hip")]
+# aids of bench.py (dense streaming kernels) and of the tests (the report's recount, late decisions), a library of their own
+PROBE_SRC = [os.path.join(PKG, "probe", f) for f in ("stream_probe.hip", "report_probe.hip", "group_probe.hip")]
 PROBE_LIB = os.path.join(PKG, "probe", "libuccl_probe.so")
 
 HIPCC_FLAGS = [
@@ -42,7 +42,7 @@ def build(extra_flags=(), out=LIB, verbose=False) -> str:
 def build_probe(verbose=False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = PROBE_LIB + f".tmp{os.getpid()}"
-    cmd = [hipcc, *HIPCC_FLAGS, f"-I{CSRC}", *PROBE_SRC, "-o", tmp]
+    cmd = [hipcc, *HIPCC_FLAGS, f"-I{INC}", f"-I{CSRC}", *PROBE_SRC, "-o", tmp]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)

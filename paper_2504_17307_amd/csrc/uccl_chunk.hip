@@ -426,6 +426,44 @@ Plan plan_apply(uint32_t n_descs, const Tuning& tune, bool reads_acc) {
   return {kRouteOne, 1u, 1u, UCCL_FLAT_THREADS, unroll};
 }
 
+// Calls of hundreds of records are decided 64 records at a time (chunk_group_kernel).  `threads` 0 = not this form, which
+// needs a region and records in device memory (each workgroup reads its record four times), a count known to
+// the host (the indirect call's capacity may be mostly empty) and no stated number of parts.
+//
+// Workgroups and where the lines lie (ring steps of reduce and copy phase with reset over three sets of buffers, 130 - 2900
+// records, 4 - 128 KiB, us, the form before / this one; all-to-all alike).  Four wavefronts a workgroup, a trip of one, two or
+// four vectors a lane that covers the chunk, longer chunks 16 KiB a workgroup:
+//   to 8 KiB: 130 records 11.0 / 11.2, 200 11.7 / 11.0, 900 x 4 KiB 16.8 / 14.6, 1800 x 6 KB 29.8 / 22.5, 2900 x 8 KiB 42.0 / 38.9,
+//             5120 x 4 KiB 40 / 43
+//   to 16 KiB (before: a workgroup of 1024 a record): 260 15.1 / 15.2, 330 x 16 KiB 16.2 / 15.8, 900 x 9 KB 27.3 / 18.6; 5120 x 16 KiB 101 / 105
+//   to 32 KiB: 200 16.6 / 16.7, 260 21.6 / 18.8, 640 36.0 / 32.5; 1280 54.8 / 57.3
+//   above, from where a call is no longer cut into parts: 260 x 64 KiB 35.3 / 26.9, 330 38.1 / 33.4; 1280 98.5 / 103
+// With the size unknown four vectors a lane, and eight wavefronts while records are few enough to want them: 330 records of 4, 16,
+// 32, 64 KiB 14.4 / 12.5, 17.1 / 15.8, 23.9 / 22.3, 38.1 / 38.3; 1280 30.5 / 16.2, 39.6 / 32.5, 55.1 / 56.0, 98.3 / 100.6; 2560 53.4 / 26.8, 67.6 / 55.6,
+// 101.9 / 95.3, 203.9 / 208.5.  (What 64 KiB chunks lose, 16 KiB of each at a time, two workgroups a record win back, and lose half
+// of what the small ones gain: 1280 of 4, 32, 64 KiB 23.5, 57.2, 97.8.)
+struct GroupPlan {
+  uint32_t threads, unroll, parts;
+};
+constexpr GroupPlan kNotGrouped = {0u, 0u, 1u};
+constexpr uint32_t kGroupFewest = 192u;
+constexpr uint32_t kGroupMost = 3000u;
+constexpr uint64_t kGroupBytes = 40ull << 20;   // of payload, in chunks above 8 KiB
+static_assert((kGroupMost + kGroup - 1) / kGroup * UCCL_CLAIM_STRIDE <= kRegionWords, "a line a group");
+
+GroupPlan plan_group(uint32_t n_descs, const Tuning& tune) {
+  if (tune.parts != 0u || n_descs < kGroupFewest || n_descs > kGroupMost) return kNotGrouped;
+  const uint32_t chunk = tune.chunk_bytes;
+  if (chunk == 0u) return {n_descs < 640u ? 512u : 256u, 4u, 1u};
+  if (chunk <= 4096u) return {256u, 1u, 1u};
+  if (chunk <= 8192u) return {256u, 2u, 1u};
+  const uint64_t bytes = static_cast<uint64_t>(n_descs) * chunk;
+  const GroupPlan p = {256u, 4u, (chunk - 1u) / 16384u + 1u};
+  if (chunk <= 16384u) return n_descs >= 320u && bytes <= kGroupBytes ? p : kNotGrouped;
+  if (chunk <= 32768u) return n_descs >= 256u && bytes <= (24ull << 20) ? p : kNotGrouped;
+  return bytes > (16ull << 20) && bytes <= kGroupBytes ? p : kNotGrouped;
+}
+
 // `region`: the stream's scratch words; called with its launch lock held.  HIP has no reason of its
 // own to refuse a later launch of a call after it took the first: all are in one code object, their
 // grids stay within 16383 * 32 workgroups of 256 threads, and a stop event that it does not take is refused with the first
@@ -466,6 +504,20 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
       // held back only where the records are known to be large: empty parts want as many workgroups as there can be
       const uint32_t lds = Op::kReadsAcc && tune.chunk_bytes != 0u ? kOrderReduceLds : 0u;
       return launch_ordered<Args>(chunk_order_kernel<Op::kEs>, chunk_ordered_kernel<Op>, lds, a, s, ordered, region.words);
+    }
+  }
+  const GroupPlan grouped = a.n_ptr == nullptr ? plan_group(a.n_descs, tune) : kNotGrouped;
+  if (grouped.threads != 0u && in_device_memory(a.descs)) {
+    const Region region = claim_region(s, kOtherCalls);
+    if (region.words != nullptr) {
+      std::lock_guard<std::mutex> in_order(*region.launch_lock);
+      a.claims = region.words;
+      a.faults = region.faults;
+      a.parts = grouped.parts;
+      a.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
+      const auto kernel = grouped.threads == 512u ? chunk_group_kernel<512, 4, Op> : grouped.unroll == 4u ? chunk_group_kernel<256, 4, Op>
+                          : grouped.unroll == 2u ? chunk_group_kernel<256, 2, Op> : chunk_group_kernel<256, 1, Op>;
+      return launch_kernel(kernel, a.n_descs * a.parts, grouped.threads, s, a);
     }
   }
   Plan p = plan_apply(a.n_descs, tune, Op::kReadsAcc);
@@ -1153,7 +1205,7 @@ int uccl_launch_plan(uint32_t n_descs, const uccl_launch_opts* opts, int gather,
   const uint64_t groups = p.route == kRouteTile ? tiles_for(n_descs, p.tile) : static_cast<uint64_t>(n_descs) * p.parts;
   plan->groups = static_cast<uint32_t>(groups);
   plan->ordered = plan_ordered(n_descs, tune, gather || reads_acc, gather != 0).launches;
-  plan->reserved = 0u;
+  plan->grouped = gather ? 0u : plan_group(n_descs, tune).parts * (plan_group(n_descs, tune).threads != 0u);
   return UCCL_OK;
 }
 

@@ -617,6 +617,172 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
   }
 }
 
+// ---- calls of hundreds of records -------------------------------------------------------------------
+//
+// With a workgroup per record that decides for itself, the atomics of n single lanes meet on one or two lines of the
+// bitmap, some 6.5 ns each; tiles of records have few atomics but leave compute units idle below some 4000
+// records.  Here a workgroup takes one record (or one of `parts` parts of it) and loads its payload at
+// once, but records are decided kGroup at a time (decide_wave), by the first wavefront of the group's first
+// workgroup; the others poll for the outcome, which comes at about the time their payload does.  What is left is the
+// chain record, LDS, atomic OR, outcome, payload store.  Measured, us a pass of reset, SUM with forward and COPY with
+// forward, before / now: 949 x 5.7 KB of unknown size 25.4 / 13.2; 4 KiB chunks 320 records 12.6 / 11.8,
+// 1280 18.8 / 16.1, 2560 28.7 / 25.8; 640 x 8 KiB 18.1 / 15.2; 640 x 16 KiB 26.2 / 20.9; 320 x 128 KiB 64.8 / 56.2.
+//
+// A group's line of scratch words holds a claim word and its outcome, a bit per record in four words, all as
+// `tag << 16 | value`.  A wavefront that has polled kGroupPolls times exchanges the claim word as well and decides if the
+// first workgroup has not begun to; so everyone waits for a wavefront that is running and waits for nobody, and the
+// wait ends whatever order the hardware starts workgroups in.  It is bounded all the same, as in claim_await.
+//
+// Not for larger calls: each round of workgroups that the chip holds waits for its decisions once more (10 240 x 4 KiB
+// 62 / 78 us; deciding a round ahead takes 63, and gives smaller calls nothing).
+#ifndef UCCL_GROUP_POLLS
+#define UCCL_GROUP_POLLS 4096
+#endif
+#ifndef UCCL_GROUP_LEADS
+#define UCCL_GROUP_LEADS 1      // 0: the group's first workgroup waits like the others (a test's build)
+#endif
+constexpr uint32_t kGroup = 64;
+constexpr uint32_t kGroupPolls = UCCL_GROUP_POLLS;
+
+// Lane 0 asks to decide the group; what the claim word held says whether it may (group_is_ours).
+__device__ __forceinline__ unsigned long long group_enter(unsigned long long* line, unsigned long long tag, uint32_t lane) {
+  unsigned long long was = 0ull;
+  if (lane == 0) was = __hip_atomic_exchange(line, tag << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return was;
+}
+__device__ __forceinline__ bool group_is_ours(unsigned long long was, unsigned long long tag) {
+  return __builtin_amdgcn_readfirstlane(static_cast<uint32_t>((was >> 16) != tag)) != 0u;
+}
+__device__ __forceinline__ void group_publish(unsigned long long* line, unsigned long long tag, unsigned long long outcome, uint32_t lane) {
+  if (lane < 4u)
+    __hip_atomic_store(line + 1u + lane, (tag << 16) | ((outcome >> (16u * lane)) & 0xFFFFull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Whether record `in` of the group is a first arrival.  By all lanes of a workgroup's first wavefront.  `decides`: it
+// has entered first, and found `was`.  `waits`: it has a use for the answer.  again(): the group's records are read (a
+// later claim).  decide(): the ballot of their first arrivals.
+template <class Again, class Decide>
+__device__ __forceinline__ bool group_outcome(unsigned long long* line, unsigned long long tag, unsigned long long was, bool decides, bool waits,
+                                              uint32_t in, uint32_t lane, uint32_t* faults, Again again, Decide decide) {
+  for (uint32_t polls = 0;; ++polls) {
+    if (decides || polls == kGroupPolls) {
+      if (!decides) {
+        was = group_enter(line, tag, lane);
+        again();
+      }
+      decides = false;
+      if (group_is_ours(was, tag)) {
+        const unsigned long long outcome = decide();
+        group_publish(line, tag, outcome, lane);
+        return ((outcome >> in) & 1ull) != 0ull;
+      }
+    }
+    if (!waits) return false;
+    unsigned long long seen = 0ull;
+    if (lane == 0) seen = __hip_atomic_load(line + 1u + (in >> 4), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!group_is_ours(seen, tag)) return ((__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(seen)) >> (in & 15u)) & 1u) != 0u;
+    if (polls >= UCCL_CLAIM_SPIN_LIMIT) {
+      if (lane == 0) atomicAdd(faults, 1u);
+      return false;
+    }
+    __builtin_amdgcn_s_sleep(1);
+  }
+}
+
+// At most 80 scalar and 64 vector registers a wavefront: eight wavefronts on a SIMD (with 86 scalar ones the hardware
+// holds seven).
+#define UCCL_FULL_OCCUPANCY __attribute__((amdgpu_num_sgpr(80), amdgpu_waves_per_eu(8)))
+
+template <int NT, int U, class Op>
+__global__ void __launch_bounds__(NT) UCCL_FULL_OCCUPANCY chunk_group_kernel(const Args g) {
+  constexpr uint32_t kUnit = 64u * U;
+  constexpr uint32_t kWaves = NT / 64;
+  __shared__ DecideSlots s;
+  __shared__ uint32_t s_win;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t k = blockIdx.x / g.parts, part = (blockIdx.x + k) % g.parts;   // the launch has n_descs * parts workgroups
+  const uint32_t in = k % kGroup, base = k - in;
+  const bool decides = UCCL_GROUP_LEADS && wave == 0u && blockIdx.x == base * g.parts;
+  unsigned long long* const line = g.claims + static_cast<size_t>(base / kGroup) * UCCL_CLAIM_STRIDE;
+  unsigned long long was = 0ull;
+  if (decides) was = group_enter(line, g.tag, lane);
+  // every lane reads the workgroup's record; where the group is decided, lane i reads record i of the group
+  const uint32_t mine = decides && base + lane < g.n_descs ? base + lane : k;
+  const u32x4* p = reinterpret_cast<const u32x4*>(g.descs + mine);
+  u32x4 lo = p[0], hi = p[1];
+  const uint64_t src = wave_uniform(lo.x | (static_cast<uint64_t>(lo.y) << 32));   // of lane 0: that is record k in either case
+  const uint64_t dst = wave_uniform(lo.z | (static_cast<uint64_t>(lo.w) << 32));
+  const uint64_t out = wave_uniform(hi.x | (static_cast<uint64_t>(hi.y) << 32));
+  const uint32_t len = __builtin_amdgcn_readfirstlane(hi.z);
+  const bool ok = record_ok<Op::kEs>(g, src, dst, out, len, __builtin_amdgcn_readfirstlane(hi.w));
+
+  const uint32_t nvec = len >> 4;
+  const uint32_t vecs = nvec + ((len & 15u) != 0u ? 1u : 0u);
+  const uint32_t total = (vecs + kUnit - 1u) / kUnit;
+  const uint32_t stride = kWaves * g.parts;
+  const uint32_t u0 = part * kWaves + wave;
+  const uint32_t first_vec = u0 * kUnit + lane;
+  const bool have = ok && u0 < total;
+  const bool part_has_units = ok && part * kWaves < total;  // uniform over the workgroup
+  const u32x4* rp = reinterpret_cast<const u32x4*>(g.recv + src) + first_vec;
+  u32x4* ap = reinterpret_cast<u32x4*>(g.acc + dst) + first_vec;
+  u32x4 rv[U], av[U];
+  const auto load = [&] {   // in bounds whether or not this record turns out to be the first arrival
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (first_vec + u * 64 < nvec) rv[u] = __builtin_nontemporal_load(rp + u * 64);
+    if constexpr (Op::kReadsAcc) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (first_vec + u * 64 < nvec) av[u] = ap[u * 64];
+    }
+  };
+  if (have && !decides) load();
+  if (wave == 0u) {
+    const bool win = group_outcome(
+        line, g.tag, was, decides, part_has_units, in, lane, g.faults,
+        [&] {
+          const u32x4* q = reinterpret_cast<const u32x4*>(g.descs + (base + lane < g.n_descs ? base + lane : k));
+          lo = q[0];
+          hi = q[1];
+        },
+        [&] {
+          const bool is_record = base + lane < g.n_descs;
+          const bool good = is_record && record_ok<Op::kEs>(g, lo.x | (static_cast<uint64_t>(lo.y) << 32), lo.z | (static_cast<uint64_t>(lo.w) << 32),
+                                                            hi.x | (static_cast<uint64_t>(hi.y) << 32), hi.z, hi.w);
+          if (is_record && !good && g.rejected != nullptr) atomicAdd(g.rejected, 1u);
+          return __ballot(decide_wave(s, g.bitmap, good, hi.w, lane));
+        });
+    if (have && decides) load();   // memory operations return in order: issued earlier, they would hold up the decision
+    if (lane == 0) s_win = win ? 1u : 0u;
+  }
+  if (!part_has_units) return;   // the whole workgroup
+  __syncthreads();
+  if (s_win == 0u) return;
+  const bool fwd = out != UCCL_NO_FORWARD;
+  const bool relay = fwd && (out & UCCL_FORWARD_ONLY) != 0;
+  char* o = g.out + (out & ~UCCL_FORWARD_ONLY);
+  if (have) {
+    u32x4* op = reinterpret_cast<u32x4*>(o) + first_vec;
+    if (!fwd) finish_unit<U, Op, false, true>(rv, av, ap, op, first_vec, nvec);
+    else if (relay) finish_unit<U, Op, true, false>(rv, av, ap, op, first_vec, nvec);
+    else finish_unit<U, Op, true, true>(rv, av, ap, op, first_vec, nvec);
+    const uint32_t rem = len & 15u;
+    if (rem != 0u && nvec >= u0 * kUnit && nvec < (u0 + 1u) * kUnit) {  // the unit that holds the partial vector
+      const uint64_t off = static_cast<uint64_t>(nvec) << 4;
+      if (!fwd) stream_tail<Op, false, true>(g.recv + src + off, g.acc + dst + off, nullptr, rem, lane);
+      else if (relay) stream_tail<Op, true, false>(g.recv + src + off, g.acc + dst + off, o + off, rem, lane);
+      else stream_tail<Op, true, true>(g.recv + src + off, g.acc + dst + off, o + off, rem, lane);
+    }
+  }
+  for (uint32_t u = u0 + stride; u < total; u += stride) {
+    if (!fwd) stream_unit<U, Op, false, true>(g.recv + src, g.acc + dst, nullptr, len, u, lane);
+    else if (relay) stream_unit<U, Op, true, false>(g.recv + src, g.acc + dst, o, len, u, lane);
+    else stream_unit<U, Op, true, true>(g.recv + src, g.acc + dst, o, len, u, lane);
+  }
+}
+
 // ---- several sources per destination chunk ---------------------------------------------
 //
 // Section 2.1: the kernel reduces transport buffers "from multiple sender GPUs" into the
