@@ -855,7 +855,7 @@ def main():
     # what the library says it launches for the dominant call
     ordered = 0 if args.graph else pkg.uccl_launch_ordered(*shape)   # a captured call has no scratch words
     grouped = 0 if args.graph or ordered else pkg.uccl_launch_grouped(*shape)
-    kernel_name = "chunk_group_kernel" if grouped else "{0}_order_kernel + {0}_ordered_kernel".format("gather" if shape[2] else "chunk") if ordered else pkg.uccl_launch_plan(*shape)["kernel"]
+    kernel_name = ("gather" if shape[2] else "chunk") + "_group_kernel" if grouped else "{0}_order_kernel + {0}_ordered_kernel".format("gather" if shape[2] else "chunk") if ordered else pkg.uccl_launch_plan(*shape)["kernel"]
 
     result = headline(args.workload, args, payload, per_step, args.steps, args.warmup,
                       {0: "f32", 1: "bf16", 2: "f16", 3: "i32"}[w.dtype],

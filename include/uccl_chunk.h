@@ -424,7 +424,7 @@ int uccl_feed_destroy(uccl_feed* feed);
  * no-allocation ones, nor a feed's hand-overs) and uccl_chunk_reduce_gather decide the records first and stream them in destination order, in that many
  * pairs of launches (chunk_order_kernel and chunk_ordered_kernel, or their gather_ forms); the other fields say what the call is launched as otherwise.
  * `grouped` > 0: in the same circumstances (the no-allocation calls included), unless it is ordered, such a call of hundreds of records is one
- * launch of chunk_group_kernel, in which the first workgroup of every 64 records decides them for the others.
+ * launch of chunk_group_kernel (or gather_group_kernel), in which the first workgroup of every 64 records decides them for the others.
  * UCCL_EINVAL for a NULL `plan` or options the data-path calls would refuse.  Utility, no passage
  * of the paper. */
 enum { UCCL_KERNEL_FLAT = 0, UCCL_KERNEL_FEW = 1, UCCL_KERNEL_GATHER = 2, UCCL_KERNEL_GATHER_PARTS = 3 };

@@ -448,6 +448,7 @@ struct GroupPlan {
 constexpr GroupPlan kNotGrouped = {0u, 0u, 1u};
 constexpr uint32_t kGroupFewest = 192u;
 constexpr uint32_t kGroupMost = 3000u;
+constexpr uint32_t kGatherSmallRecords = 288u;  // folds of small chunks: cut into parts to this many (gather_parts)
 constexpr uint64_t kGroupBytes = 40ull << 20;   // of payload, in chunks above 8 KiB
 static_assert((kGroupMost + kGroup - 1) / kGroup * UCCL_CLAIM_STRIDE <= kRegionWords, "a line a group");
 
@@ -462,6 +463,33 @@ GroupPlan plan_group(uint32_t n_descs, const Tuning& tune) {
   if (chunk <= 16384u) return n_descs >= 320u && bytes <= kGroupBytes ? p : kNotGrouped;
   if (chunk <= 32768u) return n_descs >= 256u && bytes <= (24ull << 20) ? p : kNotGrouped;
   return bytes > (16ull << 20) && bytes <= kGroupBytes ? p : kNotGrouped;
+}
+
+// The same for folds (gather_group_kernel); workgroups per record, 0 = not this form.  How many sources a record has, the
+// host does not know: the lines lie where one source loses nothing to speak of.  The forms before come in rounds of one
+// workgroup of 1024 a compute unit (these take 66 registers and more), so what this one gains depends on how full
+// the last of those is.  Measured (fold with reset over three sets of buffers, sources 1, 2 or 3, 7, us or ratio, before / now):
+//   small chunks, from where they are no longer cut into parts: 300 x 4, 8 KiB 1.03 1.02 1.57, 1.04 1.11 1.44; 1500 1.09 1.13 1.09, 1.22 1.17 1.15; 2800 1.05 1.04 1.10,
+//       1.13 1.16 1.14.  Two workgroups a chunk of 8 KiB while the chip holds them all (600 8.2 9.3 12.9 us, one 9.2 10.2 13.2; 1200 13.6 16.2 22.3, one
+//       11.6 14.4 20.5).  Not 640 - 1024 in chunks above 4 KiB, one tile of four each compute unit: 760 and 830 x 6 KB 0.97 0.97 0.94, 0.90 0.92 0.97
+//   9 KB 1000 0.90 0.88 0.93; 16 KiB 470 0.94 0.97 1.05, 700 1.18 1.14 1.20, 1240 1.09 1.11 1.16, 2400 0.95 1.05 1.04
+//   larger ones, not cut into parts above 16 MiB: 32 KiB 530 1.03 1.00 1.22, 850 1.00 1.02 1.17, 1200 0.97 1.06 1.07; 132 and 150 x 128 KiB 1.03 1.01 1.21, 1.00 1.01 1.18,
+//       180 x 96 KiB 0.92 0.97 1.13, 200 x 128 KiB 0.93 1.01 1.12; 262, 300 x 128 KiB 1.14 1.20 1.38, 1.08 1.13 1.28, 350 x 48 KiB 1.07 1.08 1.12, 400 x 96 KiB 0.92 1.00 1.11
+//   size unknown, chunks of 4, 16, 128 KiB, one source / three: 132 0.93 0.85 1.03 / 0.94 0.91 1.08, 200 0.98 1.00 0.85 / 0.98 1.06 0.98, 300 1.10 1.17 1.12 / 1.13 1.29 1.21,
+//       700 1.40 1.25 1.00 / 1.43 1.18 0.99, 1200 1.83 1.26 0.99 / 1.94 1.15 .., 2900 1.32 1.06 .. / 1.33 1.08 .. in two parts (one: 2400 x 64 KiB 0.91)
+uint32_t group_gather_parts(uint32_t n_descs, const Tuning& tune) {
+  const uint32_t chunk = tune.chunk_bytes;
+  if (tune.parts != 0u || n_descs > kGroupMost) return 0u;
+  if (chunk == 0u) return n_descs <= 256u ? 0u : n_descs < 450u ? 4u : n_descs < 900u ? 2u : n_descs < 1500u ? 1u : 2u;
+  const uint64_t bytes = static_cast<uint64_t>(n_descs) * chunk;
+  if (chunk <= 8192u) {
+    if (n_descs <= kGatherSmallRecords) return 0u;
+    return chunk <= 4096u || n_descs > 1024u ? 1u : n_descs <= 640u ? 2u : 0u;
+  }
+  if (chunk <= 16384u) return chunk > 12288u && n_descs >= 550u && bytes <= (20ull << 20) ? 2u : 0u;
+  if (bytes <= (16ull << 20)) return 0u;
+  const bool takes = chunk <= 32768u ? bytes <= (28ull << 20) : n_descs <= 160u || (n_descs > 256u && n_descs <= 360u);
+  return takes && bytes <= (48ull << 20) ? (chunk - 1u) / 8192u + 1u : 0u;
 }
 
 // `region`: the stream's scratch words; called with its launch lock held.  HIP has no reason of its
@@ -594,7 +622,6 @@ int launch_gather(const GatherArgs& a, hipStream_t s) {
 // records, which as tiles leave most compute units idle (event pairs, bf16, tiles -> parts; seven sources:
 // 8 x 4 KiB 9.2 -> 5.5 us, 65 x 16 KiB 11.4 -> 6.4, 256 x 9 KB 14.6 -> 8.8; one source: 65 x 4 KiB 6.0 -> 4.8,
 // 256 x 4 KiB 6.7 -> 6.6, but 400 x 4 KiB 7.1 -> 7.9, hence the limit).
-constexpr uint32_t kGatherSmallRecords = 288;
 uint32_t gather_parts(uint32_t n_descs, uint32_t chunk_bytes) {
   if (chunk_bytes == 0u) return n_descs <= 64u ? 8u : n_descs <= 128u ? 4u : 1u;
   if (static_cast<uint64_t>(n_descs) * chunk_bytes > (16ull << 20)) return 1u;
@@ -629,6 +656,18 @@ int launch_gather_tile(GatherArgs& a, hipStream_t s, const Tuning& tune) {
     if (region.words != nullptr) {
       std::lock_guard<std::mutex> in_order(*region.launch_lock);
       return launch_ordered<GatherArgs>(gather_order_kernel<Op::kEs>, gather_ordered_kernel<Op>, 0u, a, s, ordered, region.words);
+    }
+  }
+  const uint32_t grouped = group_gather_parts(a.n_descs, tune);
+  if (grouped != 0u && in_device_memory(a.descs)) {
+    const Region region = claim_region(s, kOtherCalls);
+    if (region.words != nullptr) {
+      std::lock_guard<std::mutex> in_order(*region.launch_lock);
+      a.claims = region.words;
+      a.faults = region.faults;
+      a.parts = grouped;
+      a.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
+      return launch_kernel(gather_group_kernel<Op>, a.n_descs * a.parts, 256, s, a);
     }
   }
   Plan p = plan_gather(a.n_descs, tune);
@@ -1205,7 +1244,8 @@ int uccl_launch_plan(uint32_t n_descs, const uccl_launch_opts* opts, int gather,
   const uint64_t groups = p.route == kRouteTile ? tiles_for(n_descs, p.tile) : static_cast<uint64_t>(n_descs) * p.parts;
   plan->groups = static_cast<uint32_t>(groups);
   plan->ordered = plan_ordered(n_descs, tune, gather || reads_acc, gather != 0).launches;
-  plan->grouped = gather ? 0u : plan_group(n_descs, tune).parts * (plan_group(n_descs, tune).threads != 0u);
+  const GroupPlan grouped = plan_group(n_descs, tune);
+  plan->grouped = gather ? group_gather_parts(n_descs, tune) : grouped.threads != 0u ? grouped.parts : 0u;
   return UCCL_OK;
 }
 

@@ -9,7 +9,7 @@ import pytest
 import oracle
 import paper_2504_17307_amd as pkg
 from randstream import random_stream
-from synth.layout import DESC, NO_FORWARD, FORWARD_ONLY, F32, BF16, F16, I32, SUM, MAX, MIN, COPY, PROD
+from synth.layout import DESC, GATHER_DESC, NO_FORWARD, FORWARD_ONLY, F32, BF16, F16, I32, SUM, MAX, MIN, COPY, PROD
 
 KiB = 1024
 
@@ -22,11 +22,19 @@ def test_rule():
     assert [grouped(n, (32 * KiB, 0)) for n in (255, 256, 768, 769)] == [0, 2, 2, 0]        # 24 MiB
     assert [grouped(n, (64 * KiB, 0)) for n in (256, 257, 640, 641)] == [0, 4, 4, 0]        # from where they are not cut into parts
     assert grouped(1000, (4 * KiB, 1)) == 0 and grouped(1000, (0, 1)) == 0                   # parts stated
-    assert grouped(1000, (4 * KiB, 0), gather=True) == 0
+    fold = lambda n, c=None: grouped(n, None if c is None else (c, 0), gather=True)
+    assert [fold(n, 4 * KiB) for n in (288, 289, 3000, 3001)] == [0, 1, 1, 0]
+    assert [fold(n, 8 * KiB) for n in (288, 289, 640, 641, 1024, 1025)] == [0, 2, 2, 0, 0, 1]
+    assert [fold(n, 16 * KiB) for n in (549, 550, 1280, 1281)] == [0, 2, 2, 0] and fold(700, 12 * KiB) == 0    # 20 MiB
+    assert [fold(n, 32 * KiB) for n in (512, 513, 896, 897)] == [0, 4, 4, 0]                 # 28 MiB
+    assert [fold(n, 128 * KiB) for n in (128, 129, 160, 161, 256, 257, 360, 361)] == [0, 16, 16, 0, 0, 16, 16, 0]
+    assert [fold(n) for n in (256, 257, 450, 900, 1500, 3000, 3001)] == [0, 4, 2, 1, 2, 2, 0]
+    assert grouped(1000, (4 * KiB, 1), gather=True) == 0
     for n in (192, 700, 3000):
         for c in (0, 64, 4 * KiB, 8 * KiB, 9008, 32 * KiB, 128 * KiB, 1 << 20, 2 ** 32 - 1):
             assert not (grouped(n, (c, 0)) and pkg.uccl_launch_ordered(n, (c, 0)))
             assert n * grouped(n, (c, 0)) <= 40 * 64 + 3000                                  # workgroups without work are few
+            assert not (fold(n, c) and pkg.uccl_launch_ordered(n, (c, 0), gather=True)) and n * fold(n, c) <= 48 * 128 + 3000
 
 
 def run(w, opts, streams=1, entry=None):
@@ -101,6 +109,45 @@ def test_random_streams(gpu_lib, dtype, op):
         w["descs"] = np.concatenate([w["descs"]] * copies)[:3000 if chunk < 9000 else 270]
         print(dtype, op, seed, len(w["descs"]), flush=True)
         check(w, (chunk, 0), streams=1 + seed % 2)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,chunk,dtype,op", [(257, 0, F32, SUM), (450, 0, BF16, SUM), (289, 4096, F32, MAX), (320, 8192, BF16, SUM), (550, 16384, F16, MIN),
+                                              (513, 32768, I32, PROD), (257, 65536, F32, SUM), (900, 0, BF16, MAX), (1500, 0, F32, SUM), (3000, 4096, F32, SUM)])
+def test_folds(gpu_lib, n, chunk, dtype, op):
+    """One to sixteen sources, repeats, keep / forward / relay, records with a bad source or sequence number; against the oracle,
+    and the form it replaces against it too."""
+    import torch
+    from gpuhelp import to_dev
+    w, _ = edges(n, n + 2, trip=4096)
+    src, g, es = w["descs"], np.random.default_rng(n), {F32: 4, I32: 4}.get(dtype, 2)
+    kind = {F32: np.float32, I32: np.int32, BF16: np.uint16, F16: np.float16}[dtype]
+    total = w["out_bytes"]
+    draw = {F32: lambda m: g.random(m, dtype=np.float32), I32: lambda m: g.integers(-9, 9, m).astype(np.int32), F16: lambda m: g.random(m).astype(np.float16),
+            BF16: lambda m: (g.random(m, dtype=np.float32).view(np.uint32) >> 16).astype(np.uint16)}[dtype]
+    acc, recv = draw(total // es).view(kind), draw(3 * total // es).view(kind)
+    d = np.zeros(n, dtype=GATHER_DESC)
+    for f in ("dst_off", "out_off", "len", "seq"):
+        d[f] = src[f]
+    many = int(src["seq"].max()) + 1
+    d["n_src"] = g.integers(1, 17, many)[src["seq"]]
+    d["src_off"] = (g.integers(0, total // 16, (many, 16)).astype(np.uint64) * np.uint64(16))[src["seq"]]
+    wrong = g.random(many)[src["seq"]] < 0.05
+    d["src_off"][wrong, d["n_src"][wrong] - 1] += 8                                              # the last one that is named
+    d["src_off"][d["n_src"] < 16, 15] += 8                                                       # one that is not
+    good = ~wrong & (d["seq"] < w["n_bits"])
+    e, o, seen = acc.copy(), np.full(total, 0xA5, dtype=np.uint8), oracle.new_seen(w["n_bits"])
+    oracle.reduce_gather(e, o, recv, d[good], seen, dtype, op)
+    assert pkg.uccl_launch_grouped(n, (chunk, 0), gather=True) > 0 and pkg.uccl_launch_grouped(n, (chunk, 1), gather=True) == 0
+    for opts in ((chunk, 0), (chunk, 1)):
+        print(n, chunk, dtype, op, opts, flush=True)
+        da, do = to_dev(acc), torch.full((total,), 0xA5, dtype=torch.uint8, device="cuda")
+        bitmap, rejected = torch.zeros((w["n_bits"] + 31) // 32, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+        for again in range(2):                                                                   # the second call finds every bit set
+            pkg.uccl_chunk_reduce_gather(da, do, to_dev(recv), to_dev(d), n, bitmap, dtype, op, n_rejected=rejected, n_bits=w["n_bits"], opts=opts)
+            torch.cuda.synchronize()
+        assert np.array_equal(da.cpu().numpy(), e.view(np.uint8)) and np.array_equal(do.cpu().numpy(), o), opts
+        assert np.array_equal(bitmap.cpu().numpy(), oracle.pack_bitmap(seen).view(np.int32)) and int(rejected) == 2 * int((~good).sum())
 
 
 @pytest.mark.gpu
