@@ -8,6 +8,7 @@ a torch.cuda.Stream, an integer hipStream_t, or None for torch's current stream.
 There is no CPU fallback: if the shared library cannot be loaded, load() raises.
 """
 import ctypes as C
+import functools
 import os
 import threading
 
@@ -193,19 +194,35 @@ def uccl_prepare(func, *args, **kwargs):
         (typed, cargs, name), = _tls.pending
     finally:
         _tls.pending = None
-    # converted to C here, once: a function object of its own without argument types takes C values as they
-    # are (a call of 12 arguments: 0.35 us of conversions each time otherwise, a tenth of a launch)
-    fn = _lib[name]
-    fn.restype = typed.restype
-    cargs = tuple(t(a) if isinstance(a, int) else a for t, a in zip(typed.argtypes, cargs))
+    fn = _lib[name]   # the arguments are converted to C here, once
+    return _extension().Prepared(C.cast(fn, C.c_void_p).value, tuple(map(_c_value, typed.argtypes, cargs)), functools.partial(_raise, name),
+                                (args, kwargs, cargs, fn))
 
-    def enqueue():
-        code = fn(*cargs)
-        if code != UCCL_OK:
-            raise UcclError(code, name)
 
-    enqueue.keeps = (args, kwargs)
-    return enqueue
+def _raise(name, code):
+    raise UcclError(code, name)
+
+
+def _c_value(t, a):
+    """What a C parameter of type ``t`` gets for the marshalled argument ``a``, as a whole number; a pointer's is its address."""
+    if a is None:
+        return 0
+    if isinstance(a, int):
+        return t(a).value or 0 if issubclass(t, C._SimpleCData) else a
+    return C.cast(a, C.c_void_p).value or 0
+
+
+def _extension():
+    """The extension that makes prepared calls (built with the library)."""
+    try:
+        from . import _prepared as m
+    except ImportError:
+        from .build import PREPARED_LIB, build_prepared
+        if os.path.exists(PREPARED_LIB):
+            raise
+        build_prepared()
+        from . import _prepared as m
+    return m
 
 
 def _extents(extents, acc, out_stage, recv_stage, n_bits):

@@ -2,6 +2,7 @@
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -12,6 +13,10 @@ LIB = os.path.join(PKG, "libuccl_chunk.so")
 # aids of bench.py (dense streaming kernels) and of the tests (the report's recount, late decisions), a library of their own
 PROBE_SRC = [os.path.join(PKG, "probe", f) for f in ("stream_probe.hip", "report_probe.hip", "group_probe.hip")]
 PROBE_LIB = os.path.join(PKG, "probe", "libuccl_probe.so")
+
+# prepared calls of the Python binding: a CPython extension, host code only
+PREPARED_SRC = os.path.join(CSRC, "prepared_call.c")
+PREPARED_LIB = os.path.join(PKG, "_prepared.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -50,6 +55,18 @@ def build_probe(verbose=False) -> str:
     return PROBE_LIB
 
 
+def build_prepared(verbose=False) -> str:
+    tmp = PREPARED_LIB + f".tmp{os.getpid()}"
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-shared", "-fPIC", "-Wall", "-Wextra", "-Wno-missing-field-initializers", "-Wno-cast-function-type",
+           "-I" + sysconfig.get_paths()["include"], PREPARED_SRC, "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, PREPARED_LIB)
+    return PREPARED_LIB
+
+
 if __name__ == "__main__":
     print(build(sys.argv[1:], verbose=True))
     print(build_probe(verbose=True))
+    print(build_prepared(verbose=True))

@@ -167,6 +167,44 @@ def test_prepare_marshals_once_and_repeats_the_c_call():
         pkg.uccl_chunk_apply(A + 8, None, B, D, 1, M, 0, 0, stream=0)
 
 
+def test_prepared_calls_pass_every_argument():
+    """One to thirteen whole numbers and pointers arrive as they were given, call after call, from several threads; the objects
+    that the arguments point into are kept; no arguments are taken."""
+    import ctypes as C
+    import gc
+    import threading
+    import weakref
+    from paper_2504_17307_amd import _prepared
+    for n in range(14):
+        got = []
+        kind = C.CFUNCTYPE(C.c_int, *[(C.c_uint64, C.c_uint32, C.c_int, C.c_void_p)[i % 4] for i in range(n)])
+        f = kind(lambda *a: got.append(a) or 0)
+        values = [((1 << 63) + 12345, (1 << 32) - 7, -5, 0x7FFF12345678)[i % 4] + (i // 4) for i in range(n)]
+        call = _prepared.Prepared(C.cast(f, C.c_void_p).value, tuple(values), print, None)
+        threads = [threading.Thread(target=lambda: [call() for _ in range(50)]) for _ in range(3)]
+        [t.start() for t in threads], [t.join() for t in threads]
+        assert got == [tuple(values)] * 150, n
+    codes = []
+    fails = C.CFUNCTYPE(C.c_int)(lambda: -3)
+    assert _prepared.Prepared(C.cast(fails, C.c_void_p).value, (), codes.append, None)() is None and codes == [-3]
+    with pytest.raises(TypeError):
+        call(1)
+    with pytest.raises(ValueError):
+        _prepared.Prepared(1, (0,) * 14, print, None)
+
+    class Kept:
+        pass
+    k = Kept()
+    call = _prepared.Prepared(C.cast(fails, C.c_void_p).value, (), codes.append, (k,))
+    k.cycle, gone = call, weakref.ref(k)
+    del k
+    gc.collect()
+    assert gone() is not None and call.keeps[0] is gone()
+    del call
+    gc.collect()
+    assert gone() is None
+
+
 def test_launch_plan_rules():
     """Host logic: which launch a call gets (uccl_launch_plan is the rule the data-path calls apply)."""
     plan = pkg.uccl_launch_plan
