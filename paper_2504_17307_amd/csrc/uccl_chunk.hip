@@ -539,8 +539,7 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
     const Region region = claim_region(s, kOtherCalls);
     if (region.words != nullptr) {
       std::lock_guard<std::mutex> in_order(*region.launch_lock);
-      a.claims = region.words;
-      a.faults = region.faults;
+      a.use(region.words, region.faults);
       a.parts = grouped.parts;
       a.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
       const auto kernel = grouped.threads == 512u ? chunk_group_kernel<512, 4, Op> : grouped.unroll == 4u ? chunk_group_kernel<256, 4, Op>
@@ -559,8 +558,7 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
     };
     if (tune.static_claims != nullptr) {
       // Every call shares the device's one array and finds what other calls left there stale by their tags.
-      a.claims = tune.static_claims;
-      a.faults = reinterpret_cast<uint32_t*>(tune.static_claims + UCCL_NOALLOC_MAX_DESCS * UCCL_CLAIM_STRIDE);
+      a.use(tune.static_claims, tune.static_claims + UCCL_NOALLOC_MAX_DESCS * UCCL_CLAIM_STRIDE);
       hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
       if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
         (void)hipGetLastError();
@@ -583,8 +581,7 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
     const Region region = claim_region(s, kCutCalls);
     if (region.words != nullptr) {
       std::lock_guard<std::mutex> in_order(*region.launch_lock);
-      a.claims = region.words;
-      a.faults = region.faults;
+      a.use(region.words, region.faults);
       return launch_parts(g_next_tag.fetch_add(1, std::memory_order_relaxed));
     }
     a.parts = 1u;
@@ -663,8 +660,7 @@ int launch_gather_tile(GatherArgs& a, hipStream_t s, const Tuning& tune) {
     const Region region = claim_region(s, kOtherCalls);
     if (region.words != nullptr) {
       std::lock_guard<std::mutex> in_order(*region.launch_lock);
-      a.claims = region.words;
-      a.faults = region.faults;
+      a.use(region.words, region.faults);
       a.parts = grouped;
       a.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
       return launch_kernel(gather_group_kernel<Op>, a.n_descs * a.parts, 256, s, a);
@@ -676,8 +672,7 @@ int launch_gather_tile(GatherArgs& a, hipStream_t s, const Tuning& tune) {
     const Region region = claim_region(s, p.unroll == 1u ? kOtherCalls : kCutCalls);   // small chunks have another form that is nearly as good
     if (region.words != nullptr) {
       std::lock_guard<std::mutex> in_order(*region.launch_lock);
-      a.claims = region.words;
-      a.faults = region.faults;
+      a.use(region.words, region.faults);
       a.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
       a.parts = p.parts;
       return p.unroll == 1u ? launch_kernel(chunk_gather_parts_kernel<UCCL_PART_THREADS, 1, Op>, a.n_descs * p.parts, UCCL_PART_THREADS, s, a)
@@ -734,7 +729,7 @@ int apply_common(void* acc, void* out_stage, const void* recv_stage, const uccl_
   a.n_descs = n_descs;
   a.allow_forward = allow_forward ? 1u : 0u;
   a.claims = nullptr;
-  a.faults = nullptr;
+  a.faults_at = 0u;
   a.parts = 1u;
   a.tag = 0ull;
   if (ext) {
@@ -1049,7 +1044,8 @@ int uccl_chunk_reduce_gather(void* acc, void* out_stage, const void* recv_stage,
   a.rejected = n_rejected;
   a.n_descs = n_descs;
   a.claims = nullptr;
-  a.faults = nullptr;
+  a.faults_at = 0u;
+  a.allow_forward = 1u;
   a.tag = 0ull;
   a.parts = 1u;
   if (extents) {

@@ -52,24 +52,42 @@ struct Extents {
   uint64_t acc_bytes, out_bytes, recv_bytes, n_bits;
 };
 
-struct Args {
+// What the claim words of a call (see claim_enter) are: its share of them, its own tag, workgroups per record, and
+// where, from `claims`, the 64-bit word lies that counts the parts that gave up waiting.
+//
+// 112 bytes of arguments are what HIP launches at full speed; from 120 on a launch takes the host 0.65 us more (2.70 / 3.35
+// us in a loop of launches, 0.05 in a process in which launches are faster): so the words are packed.
+struct ClaimArgs {
+  unsigned long long* claims;
+  uint32_t parts : 16;
+  unsigned long long tag : 48;
+  uint32_t faults_at : 31;
+  uint32_t allow_forward : 1;
+  uint32_t n_descs;
+
+  __host__ __device__ uint32_t* faults() const { return reinterpret_cast<uint32_t*>(claims + faults_at); }
+  void use(unsigned long long* words, const void* counter) {
+    claims = words;
+    faults_at = static_cast<uint32_t>(static_cast<const unsigned long long*>(counter) - words);
+  }
+};
+static_assert(sizeof(ClaimArgs) == 24, "packed");
+
+template <class Desc>
+struct Buffers {
   char* acc;
   char* out;
   const char* recv;
-  const uccl_chunk_desc* descs;
+  const Desc* descs;
   uint32_t* bitmap;
   uint32_t* rejected;
   Extents ext;
-  const uint32_t* n_ptr;  // optional: the record count is read from here (capped by n_descs)
-  uint32_t n_descs;
-  uint32_t allow_forward;
-  // one record cut into `parts` workgroups (see claim_enter): claims[k * UCCL_CLAIM_STRIDE] is record k's claim word,
-  // tag is this call's own value, faults counts parts that gave up waiting for a decision
-  unsigned long long* claims;
-  uint32_t* faults;
-  unsigned long long tag;
-  uint32_t parts;
 };
+
+struct Args : Buffers<uccl_chunk_desc>, ClaimArgs {
+  const uint32_t* n_ptr;  // optional: the record count is read from here (capped by n_descs)
+};
+static_assert(sizeof(Args) == 112, "see ClaimArgs");
 
 // ---- one record, several workgroups ------------------------------------------------------
 //
@@ -403,9 +421,9 @@ __device__ __forceinline__ bool order_has(const OrderArgs& t, unsigned long long
 __device__ __forceinline__ uint32_t order_record(unsigned long long entry) { return static_cast<uint32_t>(entry) & 0x3FFFu; }
 
 // The n_descs * parts workgroups of a launch in the order of their work: workgroup b runs on XCD b mod 8.
-__device__ __forceinline__ uint32_t order_position() {
+__device__ __forceinline__ uint32_t order_position(uint32_t grid) {
   const uint32_t b = blockIdx.x, group = b / (8u * kOrderRun), in = b % (8u * kOrderRun);
-  return (group + 1u) * (8u * kOrderRun) <= gridDim.x ? group * (8u * kOrderRun) + (in & 7u) * kOrderRun + (in >> 3) : b;
+  return (group + 1u) * (8u * kOrderRun) <= grid ? group * (8u * kOrderRun) + (in & 7u) * kOrderRun + (in >> 3) : b;
 }
 
 // ---- 64 sequence numbers at once ----------------------------------------------------------------
@@ -499,7 +517,7 @@ __device__ __forceinline__ void ordered_part(const Args& g, uint32_t k, uint32_t
 
 template <class Op>
 __global__ void __launch_bounds__(kOrderThreads) chunk_ordered_kernel(const Args g, const OrderArgs t) {
-  const uint32_t b = order_position(), entry = b / g.parts, part = (b + entry) % g.parts;
+  const uint32_t b = order_position(g.n_descs * g.parts), entry = b / g.parts, part = (b + entry) % g.parts;
   const unsigned long long first = t.words[2u * static_cast<size_t>(entry)];
   const unsigned long long second = t.words[2u * static_cast<size_t>(entry) + 1u];
   if (order_has(t, first, part)) ordered_part<Op>(g, order_record(first), part);
@@ -590,7 +608,7 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
       }
       if constexpr (PARTS) claim_publish<APART>(claim, g.tag, win != 0u);
     } else if (part_has_units) {  // a part without units has nothing to wait for
-      win = claim_await<APART>(claim, entered.seen, g.tag, g.faults) ? 1u : 0u;
+      win = claim_await<APART>(claim, entered.seen, g.tag, g.faults()) ? 1u : 0u;
     }
     s_win = win;
   }
@@ -740,7 +758,7 @@ __global__ void __launch_bounds__(NT) UCCL_FULL_OCCUPANCY chunk_group_kernel(con
   if (have && !decides) load();
   if (wave == 0u) {
     const bool win = group_outcome(
-        line, g.tag, was, decides, part_has_units, in, lane, g.faults,
+        line, g.tag, was, decides, part_has_units, in, lane, g.faults(),
         [&] {
           const u32x4* q = reinterpret_cast<const u32x4*>(g.descs + (base + lane < g.n_descs ? base + lane : k));
           lo = q[0];
@@ -792,21 +810,8 @@ __global__ void __launch_bounds__(NT) UCCL_FULL_OCCUPANCY chunk_group_kernel(con
 // dealing as chunk_flat_kernel; per unit a wavefront keeps the running value in registers
 // (widened to binary32 for 16-bit types); sources are loaded in batches, all loads of a
 // batch in flight before the folds, which then run in the listed order.
-struct GatherArgs {
-  char* acc;
-  char* out;
-  const char* recv;
-  const uccl_gather_desc* descs;
-  uint32_t* bitmap;
-  uint32_t* rejected;
-  Extents ext;
-  uint32_t n_descs;
-  // records cut into parts (chunk_gather_parts_kernel; see claim_enter)
-  unsigned long long* claims;
-  uint32_t* faults;
-  unsigned long long tag;
-  uint32_t parts;
-};
+struct GatherArgs : Buffers<uccl_gather_desc>, ClaimArgs {};
+static_assert(sizeof(GatherArgs) <= 112, "see ClaimArgs");
 
 // What a record must satisfy but for its sources, and what each of them must.
 template <uint32_t kEs>
@@ -1082,7 +1087,7 @@ __global__ void __launch_bounds__(NT) chunk_gather_parts_kernel(const GatherArgs
       }
       if (g.parts > 1u) claim_publish<false>(claim, g.tag, win != 0u);
     } else if (ok && part * kWaves < total) {  // a part without units has nothing to wait for
-      win = claim_await<false>(claim, entered.seen, g.tag, g.faults) ? 1u : 0u;
+      win = claim_await<false>(claim, entered.seen, g.tag, g.faults()) ? 1u : 0u;
     }
     s_win = win;
   }
@@ -1135,7 +1140,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_num_sgpr(80))) gath
   if (have && !decides) gather_fold<U, kBatch, Op>(g, t, dst, len, n_src, src, u0 * kUnit, lane);   // in bounds whatever the record's fate
   if (wave == 0u) {
     const bool win = group_outcome(
-        line, g.tag, was, decides, part_has_units, in, lane, g.faults,
+        line, g.tag, was, decides, part_has_units, in, lane, g.faults(),
         [&] {
           const u32x4* q = reinterpret_cast<const u32x4*>(g.descs + (base + lane < g.n_descs ? base + lane : k));
           lo = q[0];
@@ -1198,7 +1203,7 @@ __device__ __forceinline__ void ordered_gather_part(const GatherArgs& g, uint32_
 
 template <class Op>
 __global__ void __launch_bounds__(kOrderThreads) gather_ordered_kernel(const GatherArgs g, const OrderArgs t) {
-  const uint32_t b = order_position(), entry = b / g.parts, part = (b + entry) % g.parts;
+  const uint32_t b = order_position(g.n_descs * g.parts), entry = b / g.parts, part = (b + entry) % g.parts;
   const unsigned long long first = t.words[2u * static_cast<size_t>(entry)];
   const unsigned long long second = t.words[2u * static_cast<size_t>(entry) + 1u];
   if (order_has(t, first, part)) ordered_gather_part<Op>(g, order_record(first), part);

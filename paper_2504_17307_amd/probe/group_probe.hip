@@ -22,8 +22,7 @@ extern "C" int uccl_probe_group(void* acc, void* out, const void* recv, const vo
   a.ext = Extents{UINT64_MAX, UINT64_MAX, UINT64_MAX, n_bits};
   a.n_descs = n;
   a.allow_forward = 1u;
-  a.claims = reinterpret_cast<unsigned long long*>(words);
-  a.faults = reinterpret_cast<uint32_t*>(words + static_cast<size_t>((n - 1) / kGroup + 1) * UCCL_CLAIM_STRIDE);
+  a.use(reinterpret_cast<unsigned long long*>(words), words + static_cast<size_t>((n - 1) / kGroup + 1) * UCCL_CLAIM_STRIDE);
   a.tag = tag;
   a.parts = parts;
   chunk_group_kernel<256, 1, OpF32<kSum>><<<dim3(n * parts), dim3(256), 0, static_cast<hipStream_t>(stream)>>>(a);
