@@ -401,12 +401,15 @@ __global__ void __launch_bounds__(256) ack_segments_kernel(const uint32_t* __res
   uint32_t ks = before_seg + at + ((incl - mine) >> 16);
   const uint32_t below = __shfl_up(q.word[3], 1, 64);   // every lane takes part
   uint32_t ke = ks - (((lane == 0 ? before : below) >> 31) & q.word[0] & 1u);
+  // a lane's ordinals only grow: past the ranges that are to be written there is nothing left to look at (report and status of
+  // 16 slots, every third chunk missing, 64 ranges, 33 836 and 1 572 200 bits 11.3 / 9.9 us, 11.6 / 9.8; every 97th 6.9 / 6.8, 7.5 / 6.7)
+  const uint64_t beyond = static_cast<uint64_t>(skip) + max_ranges;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    for (uint32_t m = q.starts[j]; m; m &= m - 1, ++ks)
-      if (ks >= skip && ks - skip < max_ranges) ranges[2 * static_cast<uint64_t>(ks - skip)] = (w4 + j) * 32 + (__ffs(m) - 1);
-    for (uint32_t m = q.ends[j]; m; m &= m - 1, ++ke)
-      if (ke >= skip && ke - skip < max_ranges) ranges[2 * static_cast<uint64_t>(ke - skip) + 1] = (w4 + j) * 32 + (__ffs(m) - 1) + 1;
+    for (uint32_t m = q.starts[j]; m != 0u && ks < beyond; m &= m - 1, ++ks)
+      if (ks >= skip) ranges[2 * static_cast<uint64_t>(ks - skip)] = (w4 + j) * 32 + (__ffs(m) - 1);
+    for (uint32_t m = q.ends[j]; m != 0u && ke < beyond; m &= m - 1, ++ke)
+      if (ke >= skip) ranges[2 * static_cast<uint64_t>(ke - skip) + 1] = (w4 + j) * 32 + (__ffs(m) - 1) + 1;
   }
 }
 
