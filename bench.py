@@ -502,7 +502,7 @@ def bench_calls(args, pkg, torch):
             d["dst_off"] = d["out_off"] = perm.astype(np.uint64) * chunk
             d["len"], d["seq"] = chunk, perm
             recs = to_dev(torch, d)
-            row = dict(chunk_bytes=chunk, records=n, algorithmic_bytes=n * (4 * chunk + 36), launch=pkg.uccl_launch_plan(n, (chunk, 0)))
+            row = dict(chunk_bytes=chunk, records=n, algorithmic_bytes=n * (4 * chunk + 36), launch=pkg.uccl_launch_plan(n, (chunk, 0)), grouped=pkg.uccl_launch_grouped(n, (chunk, 0)))
             for label, parts in (("auto", 0), ("uncut", 1), ("parts8", 8), ("parts16", 16)):
                 if parts > 1 and (chunk < (32 << 10) or n * parts > 4096):
                     continue   # a workgroup takes several records of smaller chunks: parts do not apply
@@ -525,7 +525,7 @@ def bench_calls(args, pkg, torch):
                 d["src_off"][:, j] = (j * n + np.arange(n, dtype=np.uint64)) * chunk
             recs = to_dev(torch, d)
             row = dict(chunk_bytes=chunk, records=n, sources=n_src, algorithmic_bytes=n * ((n_src + 2) * chunk + 164),
-                       launch=pkg.uccl_launch_plan(n, (chunk, 0), gather=True))
+                       launch=pkg.uccl_launch_plan(n, (chunk, 0), gather=True), grouped=pkg.uccl_launch_grouped(n, (chunk, 0), gather=True))
             for label, parts in (("auto", 0), ("uncut", 1)):
                 row[label + "_us"] = call_us(lambda s: pkg.uccl_chunk_reduce_gather(
                     s["acc"], None, s["recv"], recs, n, s["bm"], F32, SUM, opts=(chunk, parts)), n)

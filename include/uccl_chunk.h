@@ -448,8 +448,8 @@ int uccl_launch_plan(uint32_t n_descs, const uccl_launch_opts* opts, int gather,
  * last.  One-shot: cleared by the launch (also by a launch that fails). */
 int uccl_time_next_launch(void* start_event, void* stop_event);
 
-/* Diagnostics: parts of split records that gave up waiting for their record's decision so far, on the
- * current device (synchronous read-back).  Always 0 on working hardware, unless no-allocation calls overlap. */
+/* Diagnostics: workgroups that gave up waiting for their record's decision so far (parts of split records, calls of
+ * hundreds of records), on the current device (synchronous read-back).  Always 0 on working hardware, unless no-allocation calls overlap. */
 int uccl_claim_timeouts(uint64_t* count);
 
 /* Utilities, no passage of the paper: text of a return code; HIP's text for the last
