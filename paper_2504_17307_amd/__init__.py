@@ -194,13 +194,24 @@ def uccl_prepare(func, *args, **kwargs):
         (typed, cargs, name), = _tls.pending
     finally:
         _tls.pending = None
-    fn = _lib[name]   # the arguments are converted to C here, once
-    return _extension().Prepared(C.cast(fn, C.c_void_p).value, tuple(map(_c_value, typed.argtypes, cargs)), functools.partial(_raise, name),
-                                (args, kwargs, cargs, fn))
+    # the arguments are converted to C here, once
+    return (_extension or _load_extension()).Prepared(_address(name), tuple(map(_c_value, typed.argtypes, cargs)), functools.partial(_raise, name),
+                                                      (args, kwargs, cargs, _lib))
 
 
 def _raise(name, code):
     raise UcclError(code, name)
+
+
+def _address(name):
+    """Where the loaded library's function is."""
+    known = _lib.__dict__.setdefault("_addresses", {})
+    if name not in known:
+        known[name] = C.cast(getattr(_lib, name), C.c_void_p).value
+    return known[name]
+
+
+_BYREF = type(C.byref(C.c_int()))
 
 
 def _c_value(t, a):
@@ -209,20 +220,25 @@ def _c_value(t, a):
         return 0
     if isinstance(a, int):
         return t(a).value or 0 if issubclass(t, C._SimpleCData) else a
-    return C.cast(a, C.c_void_p).value or 0
+    return C.addressof(a._obj) if type(a) is _BYREF else C.cast(a, C.c_void_p).value or 0
 
 
-def _extension():
+_extension = None
+
+
+def _load_extension():
     """The extension that makes prepared calls (built with the library)."""
+    global _extension
     try:
-        from . import _prepared as m
+        from . import _prepared
     except ImportError:
         from .build import PREPARED_LIB, build_prepared
         if os.path.exists(PREPARED_LIB):
             raise
         build_prepared()
-        from . import _prepared as m
-    return m
+        from . import _prepared
+    _extension = _prepared
+    return _prepared
 
 
 def _extents(extents, acc, out_stage, recv_stage, n_bits):
