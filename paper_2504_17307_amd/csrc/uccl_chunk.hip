@@ -429,9 +429,9 @@ Plan plan_apply(uint32_t n_descs, const Tuning& tune, bool reads_acc) {
   return {kRouteOne, 1u, 1u, UCCL_FLAT_THREADS, unroll};
 }
 
-// Calls of hundreds of records are decided 64 records at a time (chunk_group_kernel).  `threads` 0 = not this form, which
-// needs a region and records in device memory (each workgroup reads its record four times), a count known to
-// the host (the indirect call's capacity may be mostly empty) and no stated number of parts.
+// Calls of hundreds of records are decided 64 records at a time (chunk_group_kernel).  This form needs a region and records
+// in device memory (each workgroup reads its record four times), a count known to the host (the indirect call's
+// capacity may be mostly empty) and no stated number of parts.
 //
 // Workgroups and where the lines lie (ring steps of reduce and copy phase with reset over three sets of buffers, 130 - 2900
 // records, 4 - 128 KiB, us, the form before / this one; all-to-all alike).  Four wavefronts a workgroup, a trip of one, two or
@@ -441,14 +441,21 @@ Plan plan_apply(uint32_t n_descs, const Tuning& tune, bool reads_acc) {
 //   to 16 KiB (before: a workgroup of 1024 a record): 260 15.1 / 15.2, 330 x 16 KiB 16.2 / 15.8, 900 x 9 KB 27.3 / 18.6; 5120 x 16 KiB 101 / 105
 //   to 32 KiB: 200 16.6 / 16.7, 260 21.6 / 18.8, 640 36.0 / 32.5; 1280 54.8 / 57.3
 //   above, from where a call is no longer cut into parts: 260 x 64 KiB 35.3 / 26.9, 330 38.1 / 33.4; 1280 98.5 / 103
-// With the size unknown four vectors a lane, and eight wavefronts while records are few enough to want them: 330 records of 4, 16,
-// 32, 64 KiB 14.4 / 12.5, 17.1 / 15.8, 23.9 / 22.3, 38.1 / 38.3; 1280 30.5 / 16.2, 39.6 / 32.5, 55.1 / 56.0, 98.3 / 100.6; 2560 53.4 / 26.8, 67.6 / 55.6,
-// 101.9 / 95.3, 203.9 / 208.5.  (What 64 KiB chunks lose, 16 KiB of each at a time, two workgroups a record win back, and lose half
-// of what the small ones gain: 1280 of 4, 32, 64 KiB 23.5, 57.2, 97.8.)
+// With the size unknown, two to four parts of 16 KiB, all records' first ones first (group_place), so that a call in which some
+// records are long does not wait for one workgroup to walk each of them: as many parts as cost records of 4 KiB
+// next to nothing.  Measured, us a pass of reset and call, a workgroup of 1024 that decides for itself / one part here / this,
+// SUM with forward (COPY):
+//   four parts, to 640 records (one part: of 512 threads): 192 x 64 KiB 13.1 / 13.8 / 11.3 (8.9 / 9.3 / 8.0), 256 x 64 KiB 15.5 / 16.7 / 13.3, 480 x 4 KiB 9.8 / 6.9 / 6.8, 480 x 128 KiB
+//     43.1 / 42.8 / 43.7; 400 records of 4 - 256 KiB, spread over the logarithm, 42.7 / 43.2 / 27.6, of 64 B - 1 MiB 125 / 122 / 57
+//   three, to 1500: 900 x 64 B, 4, 64 KiB 10.4 / 6.2 / 7.0, 11.5 / 7.1 / 7.8, 41.8 / 41.8 / 41.0; 900 of 4 - 256 KiB 54.4 / 67.8 / 51.5 (46.2 / 58.8 / 43.0; two parts
+//     57.0, four 46.8); 1280 x 4 KiB 13.4 / 8.4 / 8.6
+//   two: 2000 x 4, 16, 64 KiB 16.3 / 10.7 / 10.4, 26.0 / 25.5 / 26.4, 105 / 103 / 103; 2000 of 4 - 256 KiB 118 / 138 / 121 (three parts 116, but 12.0 for the 4 KiB
+//     ones); 3000 x 4 KiB 22.6 / 14.0 / 14.8, of 64 B - 1 MiB 359 / 375 / 335
+constexpr uint32_t kGroupThreads = 256;
 struct GroupPlan {
-  uint32_t threads, unroll, parts;
+  uint32_t unroll, parts;   // vectors a lane and trip (0 = not this form), workgroups a record
 };
-constexpr GroupPlan kNotGrouped = {0u, 0u, 1u};
+constexpr GroupPlan kNotGrouped = {0u, 0u};
 constexpr uint32_t kGroupFewest = 192u;
 constexpr uint32_t kGroupMost = 3000u;
 constexpr uint32_t kGatherSmallRecords = 288u;  // folds of small chunks: cut into parts to this many (gather_parts)
@@ -458,11 +465,11 @@ static_assert((kGroupMost + kGroup - 1) / kGroup * UCCL_CLAIM_STRIDE <= kRegionW
 GroupPlan plan_group(uint32_t n_descs, const Tuning& tune) {
   if (tune.parts != 0u || n_descs < kGroupFewest || n_descs > kGroupMost) return kNotGrouped;
   const uint32_t chunk = tune.chunk_bytes;
-  if (chunk == 0u) return {n_descs < 640u ? 512u : 256u, 4u, 1u};
-  if (chunk <= 4096u) return {256u, 1u, 1u};
-  if (chunk <= 8192u) return {256u, 2u, 1u};
+  if (chunk == 0u) return {4u, n_descs <= 640u ? 4u : n_descs <= 1500u ? 3u : 2u};
+  if (chunk <= 4096u) return {1u, 1u};
+  if (chunk <= 8192u) return {2u, 1u};
   const uint64_t bytes = static_cast<uint64_t>(n_descs) * chunk;
-  const GroupPlan p = {256u, 4u, (chunk - 1u) / 16384u + 1u};
+  const GroupPlan p = {4u, (chunk - 1u) / 16384u + 1u};
   if (chunk <= 16384u) return n_descs >= 320u && bytes <= kGroupBytes ? p : kNotGrouped;
   if (chunk <= 32768u) return n_descs >= 256u && bytes <= (24ull << 20) ? p : kNotGrouped;
   return bytes > (16ull << 20) && bytes <= kGroupBytes ? p : kNotGrouped;
@@ -538,16 +545,17 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
     }
   }
   const GroupPlan grouped = a.n_ptr == nullptr ? plan_group(a.n_descs, tune) : kNotGrouped;
-  if (grouped.threads != 0u && in_device_memory(a.descs)) {
+  if (grouped.unroll != 0u && in_device_memory(a.descs)) {
     const Region region = claim_region(s, kOtherCalls);
     if (region.words != nullptr) {
       std::lock_guard<std::mutex> in_order(*region.launch_lock);
       a.use(region.words, region.faults);
       a.parts = grouped.parts;
       a.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
-      const auto kernel = grouped.threads == 512u ? chunk_group_kernel<512, 4, Op> : grouped.unroll == 4u ? chunk_group_kernel<256, 4, Op>
-                          : grouped.unroll == 2u ? chunk_group_kernel<256, 2, Op> : chunk_group_kernel<256, 1, Op>;
-      return launch_kernel(kernel, a.n_descs * a.parts, grouped.threads, s, a);
+      a.part_major = tune.chunk_bytes == 0u ? 1u : 0u;
+      const auto kernel = grouped.unroll == 4u ? chunk_group_kernel<kGroupThreads, 4, Op> : grouped.unroll == 2u ? chunk_group_kernel<kGroupThreads, 2, Op>
+                                                                                          : chunk_group_kernel<kGroupThreads, 1, Op>;
+      return launch_kernel(kernel, a.n_descs * a.parts, kGroupThreads, s, a);
     }
   }
   Plan p = plan_apply(a.n_descs, tune, Op::kReadsAcc);
@@ -733,6 +741,7 @@ int apply_common(void* acc, void* out_stage, const void* recv_stage, const uccl_
   a.allow_forward = allow_forward ? 1u : 0u;
   a.claims = nullptr;
   a.faults_at = 0u;
+  a.part_major = 0u;
   a.parts = 1u;
   a.tag = 0ull;
   if (ext) {
@@ -1048,6 +1057,7 @@ int uccl_chunk_reduce_gather(void* acc, void* out_stage, const void* recv_stage,
   a.n_descs = n_descs;
   a.claims = nullptr;
   a.faults_at = 0u;
+  a.part_major = 0u;
   a.allow_forward = 1u;
   a.tag = 0ull;
   a.parts = 1u;
@@ -1243,8 +1253,7 @@ int uccl_launch_plan(uint32_t n_descs, const uccl_launch_opts* opts, int gather,
   const uint64_t groups = p.route == kRouteTile ? tiles_for(n_descs, p.tile) : static_cast<uint64_t>(n_descs) * p.parts;
   plan->groups = static_cast<uint32_t>(groups);
   plan->ordered = plan_ordered(n_descs, tune, gather || reads_acc, gather != 0).launches;
-  const GroupPlan grouped = plan_group(n_descs, tune);
-  plan->grouped = gather ? group_gather_parts(n_descs, tune) : grouped.threads != 0u ? grouped.parts : 0u;
+  plan->grouped = gather ? group_gather_parts(n_descs, tune) : plan_group(n_descs, tune).parts;
   return UCCL_OK;
 }
 

@@ -17,7 +17,7 @@ KiB = 1024
 def test_rule():
     grouped = pkg.uccl_launch_grouped
     assert [grouped(n, (4 * KiB, 0)) for n in (191, 192, 3000, 3001)] == [0, 1, 1, 0]
-    assert [grouped(n) for n in (191, 192, 640, 3000, 3001)] == [0, 1, 1, 1, 0]
+    assert [grouped(n) for n in (191, 192, 640, 641, 1500, 1501, 3000, 3001)] == [0, 4, 4, 3, 3, 2, 2, 0]     # some may be long
     assert [grouped(n, (16 * KiB, 0)) for n in (319, 320, 2560, 2561)] == [0, 1, 1, 0]     # 40 MiB
     assert [grouped(n, (32 * KiB, 0)) for n in (255, 256, 768, 769)] == [0, 2, 2, 0]        # 24 MiB
     assert [grouped(n, (64 * KiB, 0)) for n in (256, 257, 640, 641)] == [0, 4, 4, 0]        # from where they are not cut into parts
@@ -33,7 +33,7 @@ def test_rule():
     for n in (192, 700, 3000):
         for c in (0, 64, 4 * KiB, 8 * KiB, 9008, 32 * KiB, 128 * KiB, 1 << 20, 2 ** 32 - 1):
             assert not (grouped(n, (c, 0)) and pkg.uccl_launch_ordered(n, (c, 0)))
-            assert n * grouped(n, (c, 0)) <= 40 * 64 + 3000                                  # workgroups without work are few
+            assert n * grouped(n, (c, 0)) <= 6000                                  # workgroups without work are few
             assert not (fold(n, c) and pkg.uccl_launch_ordered(n, (c, 0), gather=True)) and n * fold(n, c) <= 48 * 128 + 3000
 
 
@@ -74,7 +74,7 @@ def edges(n, seed, op=SUM, trip=16384, least=0):
     unique = n - n // 16
     seq = np.concatenate([np.arange(unique), g.integers(0, unique, n - unique)])[g.permutation(n)]
     lens = g.integers(least, 13, unique) * 4
-    for at in (1024, 4096, 8192, trip, 2 * trip, 4 * trip):
+    for at in (1024, 4096, 8192, 16384, trip, 2 * trip, 4 * trip):
         lens[g.integers(0, unique, 8)] = at + np.array([-16, -4, 0, 4, 8, 12, 16, 20])
     at = np.concatenate([[0], np.cumsum((lens + 15) // 16 * 16)])
     d = np.zeros(n, dtype=DESC)
@@ -90,11 +90,11 @@ def edges(n, seed, op=SUM, trip=16384, least=0):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n,chunk", [(192, 0), (193, 4096), (255, 8192), (256, 0), (257, 32768), (320, 16384), (639, 0), (640, 0), (300, 65536),
-                                     (160 * 4, 65536), (3000, 0), (3000, 4096), (2945, 8192)])
+@pytest.mark.parametrize("n,chunk", [(192, 0), (193, 4096), (255, 8192), (256, 0), (257, 32768), (320, 16384), (640, 0), (641, 0), (300, 65536),
+                                     (160 * 4, 65536), (1500, 0), (1501, 0), (3000, 0), (3000, 4096), (2945, 8192)])
 def test_edges(gpu_lib, n, chunk):
     for op in (SUM, COPY):
-        w, bad = edges(n, n, op)
+        w, bad = edges(n, n, op, trip=16384 * pkg.uccl_launch_grouped(n, (chunk, 0)))   # of all parts
         print(n, chunk, op, flush=True)
         check(w, (chunk, 0), rejected=bad, streams=1 + (op == COPY))   # the second stream finds every bit set, or takes its share
 

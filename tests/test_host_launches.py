@@ -67,7 +67,7 @@ class Runtime:
         return [l[0] for l in self.launches]
 
 
-KERNELS = ("chunk_order_kernel", "chunk_ordered_kernel", "gather_order_kernel", "gather_ordered_kernel", "chunk_flat_kernel", "chunk_few_kernel",
+KERNELS = ("chunk_group_kernel", "gather_group_kernel", "chunk_order_kernel", "chunk_ordered_kernel", "gather_order_kernel", "gather_ordered_kernel", "chunk_flat_kernel", "chunk_few_kernel",
            "chunk_gather_parts_kernel", "chunk_gather_kernel", "ack_segments_kernel", "ack_report_kernel", "fill_words_kernel")
 
 
@@ -279,6 +279,18 @@ def folds_of_one_part(rt):
 
 def test_a_fold_whose_records_have_one_part_needs_no_claim_words(tmp_path):
     in_process("folds_of_one_part", tmp_path)
+
+
+def unknown_sizes_of_hundreds(rt):
+    for op in (0, pkg.UCCL_COPY):
+        for n, parts in ((192, 4), (640, 4), (641, 3), (1500, 3), (1501, 2), (3000, 2)):
+            rt.launches.clear()
+            assert rt.apply(n, op=op) == 0 and [l[:3] for l in rt.launches] == [("chunk_group_kernel", parts * n, 256)], (n, op)
+
+
+def test_a_long_record_of_unknown_size_has_several_workgroups(tmp_path):
+    """A call of hundreds of records of different lengths does not wait for one small workgroup to walk each of the long ones."""
+    in_process("unknown_sizes_of_hundreds", tmp_path)
 
 
 if __name__ == "__main__":
