@@ -485,12 +485,16 @@ GroupPlan plan_group(uint32_t n_descs, const Tuning& tune) {
 //   9 KB 1000 0.90 0.88 0.93; 16 KiB 470 0.94 0.97 1.05, 700 1.18 1.14 1.20, 1240 1.09 1.11 1.16, 2400 0.95 1.05 1.04
 //   larger ones, not cut into parts above 16 MiB: 32 KiB 530 1.03 1.00 1.22, 850 1.00 1.02 1.17, 1200 0.97 1.06 1.07; 132 and 150 x 128 KiB 1.03 1.01 1.21, 1.00 1.01 1.18,
 //       180 x 96 KiB 0.92 0.97 1.13, 200 x 128 KiB 0.93 1.01 1.12; 262, 300 x 128 KiB 1.14 1.20 1.38, 1.08 1.13 1.28, 350 x 48 KiB 1.07 1.08 1.12, 400 x 96 KiB 0.92 1.00 1.11
-//   size unknown, chunks of 4, 16, 128 KiB, one source / three: 132 0.93 0.85 1.03 / 0.94 0.91 1.08, 200 0.98 1.00 0.85 / 0.98 1.06 0.98, 300 1.10 1.17 1.12 / 1.13 1.29 1.21,
-//       700 1.40 1.25 1.00 / 1.43 1.18 0.99, 1200 1.83 1.26 0.99 / 1.94 1.15 .., 2900 1.32 1.06 .. / 1.33 1.08 .. in two parts (one: 2400 x 64 KiB 0.91)
+// With the size unknown, all records' first parts come first (group_place), each of 4 KiB a trip, and their number is what a call needs in which some
+// records are long, us, before / this (f32 SUM of three sources; f16 MAX of one, which takes the most registers):
+//   six parts, to 800 records: 260 x 4, 64 KiB 8.9 / 7.4, 25.5 / 19.5; 9.6 / 7.3, 19.2 / 16.7; 450 x 64, 128 KiB 30.4 / 29.5, 52.3 / 55.2; 22.7 / 22.6, 35.9 / 37.0;
+//     450 records of 4 - 256 KiB, spread over the logarithm, 44.7 / 37.4; 37.1 / 33.9 (four parts 40.3; 39.1); 700 x 4, 64 KiB 13.3 / 8.1, 43.8 / 41.6
+//   four: 900 x 4, 64, 128 KiB 15.2 / 8.7, 55.1 / 52.1, 120 / 122 (one part 8.1, 52.6, 122); 900 of 4 - 256 KiB 68.0 / 62.2; 54.3 / 53.1 (one part 102; 107);
+//     1500 x 4, 128 KiB 20.4 / 11.8, 194 / 200; 2900 x 4, 16 KiB 33.7 / 21.6, 48.9 / 46.2
 uint32_t group_gather_parts(uint32_t n_descs, const Tuning& tune) {
   const uint32_t chunk = tune.chunk_bytes;
   if (tune.parts != 0u || n_descs > kGroupMost) return 0u;
-  if (chunk == 0u) return n_descs <= 256u ? 0u : n_descs < 450u ? 4u : n_descs < 900u ? 2u : n_descs < 1500u ? 1u : 2u;
+  if (chunk == 0u) return n_descs <= 256u ? 0u : n_descs <= 800u ? 6u : 4u;
   const uint64_t bytes = static_cast<uint64_t>(n_descs) * chunk;
   if (chunk <= 8192u) {
     if (n_descs <= kGatherSmallRecords) return 0u;
@@ -673,6 +677,7 @@ int launch_gather_tile(GatherArgs& a, hipStream_t s, const Tuning& tune) {
       std::lock_guard<std::mutex> in_order(*region.launch_lock);
       a.use(region.words, region.faults);
       a.parts = grouped;
+      a.part_major = tune.chunk_bytes == 0u ? 1u : 0u;
       a.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
       return launch_kernel(gather_group_kernel<Op>, a.n_descs * a.parts, 256, s, a);
     }

@@ -1136,9 +1136,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_num_sgpr(80))) gath
   __shared__ uint32_t s_win;
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint32_t k = blockIdx.x / g.parts, part = (blockIdx.x + k) % g.parts;   // the launch has n_descs * parts workgroups
-  const uint32_t in = k % kGroup, base = k - in;
-  const bool decides = wave == 0u && blockIdx.x == base * g.parts;
+  const GroupPlace place = group_place(g);   // the launch has n_descs * parts workgroups
+  const uint32_t k = place.k, part = place.part, in = place.in, base = place.base;
+  const bool decides = wave == 0u && place.first;
   unsigned long long* const line = g.claims + static_cast<size_t>(base / kGroup) * UCCL_CLAIM_STRIDE;
   unsigned long long was = 0ull;
   if (decides) was = group_enter(line, g.tag, lane);

@@ -286,6 +286,9 @@ def unknown_sizes_of_hundreds(rt):
         for n, parts in ((192, 4), (640, 4), (641, 3), (1500, 3), (1501, 2), (3000, 2)):
             rt.launches.clear()
             assert rt.apply(n, op=op) == 0 and [l[:3] for l in rt.launches] == [("chunk_group_kernel", parts * n, 256)], (n, op)
+    for n, parts in ((257, 6), (800, 6), (801, 4), (3000, 4)):
+        rt.launches.clear()
+        assert rt.fold(n, 0) == 0 and [l[:3] for l in rt.launches] == [("gather_group_kernel", parts * n, 256)], n
 
 
 def test_a_long_record_of_unknown_size_has_several_workgroups(tmp_path):
