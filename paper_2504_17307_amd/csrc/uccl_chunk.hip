@@ -485,12 +485,20 @@ GroupPlan plan_group(uint32_t n_descs, const Tuning& tune) {
 //   9 KB 1000 0.90 0.88 0.93; 16 KiB 470 0.94 0.97 1.05, 700 1.18 1.14 1.20, 1240 1.09 1.11 1.16, 2400 0.95 1.05 1.04
 //   larger ones, not cut into parts above 16 MiB: 32 KiB 530 1.03 1.00 1.22, 850 1.00 1.02 1.17, 1200 0.97 1.06 1.07; 132 and 150 x 128 KiB 1.03 1.01 1.21, 1.00 1.01 1.18,
 //       180 x 96 KiB 0.92 0.97 1.13, 200 x 128 KiB 0.93 1.01 1.12; 262, 300 x 128 KiB 1.14 1.20 1.38, 1.08 1.13 1.28, 350 x 48 KiB 1.07 1.08 1.12, 400 x 96 KiB 0.92 1.00 1.11
+//   fewer and larger: no less worth it (f32 SUM of seven sources, f16 MAX of one): 1 x 48 MiB 8520 / 84, 3550 / 36, 16 x 2 MiB 370 / 56, 156 / 27, 60 x 512 KiB 108 / 52,
+//       49 / 26, 128 x 160 KiB 47 / 38, 21 / 19.  All workgroups of 64 records read one line for their outcome, and what a record has
+//       no use for costs 0.4 - 0.7 ns each (1 x 4 KiB stated as 48 MiB in 6144 workgroups 7.9, in 4096 6.4, in the form before 6.3 - 6.8), so they are
+//       4096 at most; 1 x 48 MiB then takes 84 (36) us, in 6144 83 (38), in 2048 86 (41).
+// A duplicate costs its first trip's payload reads: folds that are issued again whole 300 x 128 KiB from seven sources 6.2 / 27, 2900 x 4 KiB 7.9 / 20, from
+// one 7.3 / 10.6; a look at the bitmap before the payload would make these 12, 8.6, 8.2 and every other call 0.4 - 0.5 us longer.
 // With the size unknown, all records' first parts come first (group_place), each of 4 KiB a trip, and their number is what a call needs in which some
 // records are long, us, before / this (f32 SUM of three sources; f16 MAX of one, which takes the most registers):
 //   six parts, to 800 records: 260 x 4, 64 KiB 8.9 / 7.4, 25.5 / 19.5; 9.6 / 7.3, 19.2 / 16.7; 450 x 64, 128 KiB 30.4 / 29.5, 52.3 / 55.2; 22.7 / 22.6, 35.9 / 37.0;
 //     450 records of 4 - 256 KiB, spread over the logarithm, 44.7 / 37.4; 37.1 / 33.9 (four parts 40.3; 39.1); 700 x 4, 64 KiB 13.3 / 8.1, 43.8 / 41.6
 //   four: 900 x 4, 64, 128 KiB 15.2 / 8.7, 55.1 / 52.1, 120 / 122 (one part 8.1, 52.6, 122); 900 of 4 - 256 KiB 68.0 / 62.2; 54.3 / 53.1 (one part 102; 107);
 //     1500 x 4, 128 KiB 20.4 / 11.8, 194 / 200; 2900 x 4, 16 KiB 33.7 / 21.6, 48.9 / 46.2
+constexpr uint32_t kGroupFoldMost = 4096u;   // workgroups of a call of at most 160 records
+static_assert(kGroupFoldMost <= 0xFFFFu, "ClaimArgs::parts");
 uint32_t group_gather_parts(uint32_t n_descs, const Tuning& tune) {
   const uint32_t chunk = tune.chunk_bytes;
   if (tune.parts != 0u || n_descs > kGroupMost) return 0u;
@@ -503,7 +511,9 @@ uint32_t group_gather_parts(uint32_t n_descs, const Tuning& tune) {
   if (chunk <= 16384u) return chunk > 12288u && n_descs >= 550u && bytes <= (20ull << 20) ? 2u : 0u;
   if (bytes <= (16ull << 20)) return 0u;
   const bool takes = chunk <= 32768u ? bytes <= (28ull << 20) : n_descs <= 160u || (n_descs > 256u && n_descs <= 360u);
-  return takes && bytes <= (48ull << 20) ? (chunk - 1u) / 8192u + 1u : 0u;
+  if (!takes || bytes > (48ull << 20)) return 0u;
+  const uint32_t parts = (chunk - 1u) / 8192u + 1u, most = n_descs > 160u ? parts : kGroupFoldMost / n_descs;
+  return parts < most ? parts : most;
 }
 
 // `region`: the stream's scratch words; called with its launch lock held.  HIP has no reason of its

@@ -28,8 +28,12 @@ def test_rule():
     assert [fold(n, 16 * KiB) for n in (549, 550, 1280, 1281)] == [0, 2, 2, 0] and fold(700, 12 * KiB) == 0    # 20 MiB
     assert [fold(n, 32 * KiB) for n in (512, 513, 896, 897)] == [0, 4, 4, 0]                 # 28 MiB
     assert [fold(n, 128 * KiB) for n in (128, 129, 160, 161, 256, 257, 360, 361)] == [0, 16, 16, 0, 0, 16, 16, 0]
+    assert [fold(1, c << 20) for c in (16, 17, 48, 49)] == [0, 2176, 4096, 0] and fold(2, 20 << 20) == 2048 and fold(16, 2 << 20) == 256   # few and large
     assert [fold(n) for n in (256, 257, 800, 801, 3000, 3001)] == [0, 6, 6, 4, 4, 0]         # some may be long
     assert grouped(1000, (4 * KiB, 1), gather=True) == 0
+    for n in (1, 2, 7, 16, 60, 128, 160):
+        for c in range(1 << 20, 52 << 20, 1 << 20):
+            assert n * fold(n, c) <= 4096
     for n in (192, 700, 3000):
         for c in (0, 64, 4 * KiB, 8 * KiB, 9008, 32 * KiB, 128 * KiB, 1 << 20, 2 ** 32 - 1):
             assert not (grouped(n, (c, 0)) and pkg.uccl_launch_ordered(n, (c, 0)))
@@ -113,7 +117,8 @@ def test_random_streams(gpu_lib, dtype, op):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,chunk,dtype,op", [(257, 0, F32, SUM), (800, 0, BF16, SUM), (289, 4096, F32, MAX), (320, 8192, BF16, SUM), (550, 16384, F16, MIN),
-                                              (513, 32768, I32, PROD), (257, 65536, F32, SUM), (801, 0, BF16, MAX), (3000, 0, F32, SUM), (3000, 4096, F32, SUM)])
+                                              (513, 32768, I32, PROD), (257, 65536, F32, SUM), (801, 0, BF16, MAX), (3000, 0, F32, SUM), (3000, 4096, F32, SUM),
+                                              (1, 48 << 20, F32, SUM), (2, 20 << 20, F16, MAX), (16, 2 << 20, BF16, SUM), (63, 300 << 10, I32, SUM), (130, 200 << 10, F32, MIN)])
 def test_folds(gpu_lib, n, chunk, dtype, op):
     """One to sixteen sources, repeats, keep / forward / relay, records with a bad source or sequence number; against the oracle,
     and the form it replaces against it too."""

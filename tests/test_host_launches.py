@@ -291,6 +291,18 @@ def unknown_sizes_of_hundreds(rt):
         assert rt.fold(n, 0) == 0 and [l[:3] for l in rt.launches] == [("gather_group_kernel", parts * n, 256)], n
 
 
+def few_large_folds(rt):
+    for n, chunk, parts in ((1, 48 * MiB, 4096), (1, 17 * MiB, 2176), (2, 20 * MiB, 2048), (16, 3 * MiB, 256), (60, 512 * KiB, 64), (129, 300 * KiB, 31), (128, 128 * KiB, None)):
+        rt.launches.clear()
+        assert rt.fold(n, chunk) == 0
+        assert [l[:3] for l in rt.launches] == ([("gather_group_kernel", n * parts, 256)] if parts else [("chunk_gather_parts_kernel", 2048, 256)]), (n, chunk)
+
+
+def test_few_large_folds_take_a_bounded_number_of_workgroups(tmp_path):
+    """All of them wait for one line of scratch words, and the stated size may be far above the records'."""
+    in_process("few_large_folds", tmp_path)
+
+
 def test_a_long_record_of_unknown_size_has_several_workgroups(tmp_path):
     """A call of hundreds of records of different lengths does not wait for one small workgroup to walk each of the long ones."""
     in_process("unknown_sizes_of_hundreds", tmp_path)
