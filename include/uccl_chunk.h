@@ -143,14 +143,14 @@ typedef struct uccl_launch_opts {
  * most 32 chunks of 32 KiB; at most 128 records when no chunk size is given) is launched with several
  * workgroups per record so that it fills the machine; those workgroups
  * agree on the record's fate through a 64-bit claim word per record (on a 128-byte line of its
- * own) in an array inside the library's code object (36 MiB on every GPU the library runs on, until the process
+ * own) in an array inside the library's code object (36.5 MiB on every GPU the library runs on, until the process
  * ends).  It has one region per stream
  * handle, for the first 64 that issue such a call on the device (hipStreamPerThread: one per thread, for the first 16
  * threads).  A region is never given back; a stream created later under the handle of a destroyed one takes it over
  * (hipStreamDestroy waits for the work on the stream).  Calls that are
- * streamed in destination order (uccl_launch_opts) keep that order, calls of hundreds of records the outcome of every 64 of
- * them, folds of small chunks their claim words and
- * uccl_dedup_report its counts in a second region of the stream, of which there are 64 too.  If the stream has no region, or is being captured into a graph, the
+ * streamed in destination order (uccl_launch_opts) keep that order, folds of small chunks their claim words and
+ * uccl_dedup_report its counts in a second region of the stream, calls of hundreds of records (and folds of few large
+ * ones) the outcome of every 64 records in a third; there are 64 (16) of each.  If the stream has no region, or is being captured into a graph, the
  * call is launched in the form that needs no scratch
  * memory instead (one workgroup per record or per tile of records): slower, same result.  No
  * data-path call allocates; the first call on a device loads the library's code object.

@@ -63,13 +63,15 @@
 // gave up waiting: 256.25 KiB.
 static __device__ __align__(256) unsigned long long scratch[UCCL_NOALLOC_MAX_DESCS * UCCL_CLAIM_STRIDE + 32];
 
-// The regions that streams own (see claim_region), then the same counter: 36 MiB.
+// The regions that streams own (see claim_region), large ones first, then the same counter: 36.5 MiB.
 constexpr uint32_t kRegionRecords = 2048;  // most records a split call can have
 constexpr uint32_t kRegionWords = kRegionRecords * UCCL_CLAIM_STRIDE;
-enum RegionUse : uint32_t { kCutCalls, kOtherCalls, kThreads, kRegionUses };
-constexpr uint32_t kGroupRegions = 64, kThreadRegions = 16;   // streams with regions: for either use; threads
-constexpr uint32_t kRegions = 2 * kGroupRegions + kThreadRegions;
-static __device__ __align__(256) unsigned long long regions[kRegions * kRegionWords + 32];
+constexpr uint32_t kGroupRegionWords = 48 * UCCL_CLAIM_STRIDE;   // calls of hundreds of records: a line for 64 of them
+enum RegionUse : uint32_t { kCutCalls, kOtherCalls, kThreads, kGroupCalls, kGroupThreads, kRegionUses };
+constexpr uint32_t kStreamRegions = 64, kThreadRegions = 16;   // streams with regions, for each use; threads
+constexpr uint32_t kLargeRegions = 2 * kStreamRegions + kThreadRegions, kRegions = kLargeRegions + kStreamRegions + kThreadRegions;
+constexpr size_t kAllRegionWords = static_cast<size_t>(kLargeRegions) * kRegionWords + static_cast<size_t>(kRegions - kLargeRegions) * kGroupRegionWords;
+static __device__ __align__(256) unsigned long long regions[kAllRegionWords + 32];
 
 namespace {
 
@@ -125,7 +127,7 @@ uint32_t tiles_for(uint32_t n_descs, uint32_t tile) {
 // finds the others' words stale.  Every device has kRegions regions for
 // kRegionRecords records each, one per stream handle that has issued such a call: one for its cut calls and another
 // for everything else, so that streams which only ask for reports, say, leave the cut calls theirs (these gain
-// most).  Calls on
+// most); and small ones for calls of hundreds of records, which any stream may have.  Calls on
 // one stream run in order, so they can share a region; calls on different streams may overlap, so
 // they never do.  A call whose stream finds no free region, or that is being captured into a graph
 // (a replay would carry the captured tag again, and could overlap with anything), is launched in the
@@ -141,7 +143,7 @@ constexpr int kMaxDevices = 64;
 struct RegionOwners {
   std::mutex lock;                       // guards the table's growth
   std::atomic<uint32_t> n{0};
-  std::atomic<uintptr_t> key[kGroupRegions];
+  std::atomic<uintptr_t> key[kStreamRegions];
 };
 struct ClaimPool {
   RegionOwners owners[kRegionUses];
@@ -182,7 +184,7 @@ int current_device(int* dev) {
 }
 
 uint32_t* region_faults(unsigned long long* base) {
-  return reinterpret_cast<uint32_t*>(base + static_cast<size_t>(kRegions) * kRegionWords);
+  return reinterpret_cast<uint32_t*>(base + kAllRegionWords);
 }
 
 // Whose region it is: 0 marks a free entry, the null stream is 1.  hipStreamPerThread is one handle for a stream of each
@@ -213,7 +215,8 @@ Region claim_region(hipStream_t stream, RegionUse use) {
   if (cap != hipStreamCaptureStatusNone) return r;
   unsigned long long* base = nullptr;
   if (device_array(g_regions, HIP_SYMBOL(regions), dev, &base) != UCCL_OK) { (void)hipGetLastError(); return r; }
-  if (stream == hipStreamPerThread) use = kThreads;
+  if (stream == hipStreamPerThread) use = use == kGroupCalls ? kGroupThreads : kThreads;
+  constexpr uint32_t kFirst[kRegionUses] = {0, kStreamRegions, 2 * kStreamRegions, kLargeRegions, kLargeRegions + kStreamRegions};
   RegionOwners& o = g_pools[dev].owners[use];
   const uintptr_t key = region_key(stream);
   uint32_t n = o.n.load(std::memory_order_acquire), at = 0;
@@ -223,13 +226,14 @@ Region claim_region(hipStream_t stream, RegionUse use) {
     n = o.n.load(std::memory_order_acquire);
     while (at < n && o.key[at].load(std::memory_order_relaxed) != key) ++at;   // only the new entries: old ones stay
     if (at == n) {
-      if (n == (use == kThreads ? kThreadRegions : kGroupRegions)) return r;
+      if (n == (use == kThreads || use == kGroupThreads ? kThreadRegions : kStreamRegions)) return r;
       o.key[n].store(key, std::memory_order_relaxed);
       o.n.store(n + 1, std::memory_order_release);
     }
   }
-  const uint32_t index = use * kGroupRegions + at;
-  r.words = base + static_cast<size_t>(index) * kRegionWords;
+  const uint32_t index = kFirst[use] + at;
+  r.words = index < kLargeRegions ? base + static_cast<size_t>(index) * kRegionWords
+                                  : base + static_cast<size_t>(kLargeRegions) * kRegionWords + static_cast<size_t>(index - kLargeRegions) * kGroupRegionWords;
   r.faults = region_faults(base);
   r.launch_lock = &g_pools[dev].launch_lock[index];
   return r;
@@ -460,7 +464,7 @@ constexpr uint32_t kGroupFewest = 192u;
 constexpr uint32_t kGroupMost = 3000u;
 constexpr uint32_t kGatherSmallRecords = 288u;  // folds of small chunks: cut into parts to this many (gather_parts)
 constexpr uint64_t kGroupBytes = 40ull << 20;   // of payload, in chunks above 8 KiB
-static_assert((kGroupMost + kGroup - 1) / kGroup * UCCL_CLAIM_STRIDE <= kRegionWords, "a line a group");
+static_assert((kGroupMost + kGroup - 1) / kGroup * UCCL_CLAIM_STRIDE <= kGroupRegionWords, "a line a group");
 
 GroupPlan plan_group(uint32_t n_descs, const Tuning& tune) {
   if (tune.parts != 0u || n_descs < kGroupFewest || n_descs > kGroupMost) return kNotGrouped;
@@ -560,7 +564,7 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
   }
   const GroupPlan grouped = a.n_ptr == nullptr ? plan_group(a.n_descs, tune) : kNotGrouped;
   if (grouped.unroll != 0u && in_device_memory(a.descs)) {
-    const Region region = claim_region(s, kOtherCalls);
+    const Region region = claim_region(s, kGroupCalls);
     if (region.words != nullptr) {
       std::lock_guard<std::mutex> in_order(*region.launch_lock);
       a.use(region.words, region.faults);
@@ -682,7 +686,7 @@ int launch_gather_tile(GatherArgs& a, hipStream_t s, const Tuning& tune) {
   }
   const uint32_t grouped = group_gather_parts(a.n_descs, tune);
   if (grouped != 0u && in_device_memory(a.descs)) {
-    const Region region = claim_region(s, kOtherCalls);
+    const Region region = claim_region(s, kGroupCalls);
     if (region.words != nullptr) {
       std::lock_guard<std::mutex> in_order(*region.launch_lock);
       a.use(region.words, region.faults);

@@ -281,6 +281,29 @@ def test_a_fold_whose_records_have_one_part_needs_no_claim_words(tmp_path):
     in_process("folds_of_one_part", tmp_path)
 
 
+def hundreds_on_many_streams(rt):
+    import threading
+    for k in range(80):
+        assert rt.apply(300, stream=0x1000 + 16 * k) == pkg.UCCL_OK
+    assert rt.kernels() == ["chunk_group_kernel"] * 64 + ["chunk_few_kernel"] * 16
+    for k in range(64):   # the streams of the large calls and the reports come later
+        rt.launches.clear()
+        assert rt.apply(8000, 32 * KiB, stream=0x9000 + 16 * k) == 0 and rt.report(1572200, stream=0x9000 + 16 * k) == 0
+        assert rt.kernels() == ["chunk_order_kernel", "chunk_ordered_kernel", "ack_segments_kernel"], k
+    rt.launches.clear()
+    per_thread = 2
+    for call, times in ((lambda: rt.fold(300, 0, per_thread), 20), (lambda: rt.apply(8000, 32 * KiB, per_thread), 16)):
+        for _ in range(times):
+            t = threading.Thread(target=call)
+            t.start()
+            t.join()
+    assert rt.kernels() == ["gather_group_kernel"] * 16 + ["chunk_gather_kernel"] * 4 + ["chunk_order_kernel", "chunk_ordered_kernel"] * 16
+
+
+def test_streams_with_calls_of_hundreds_leave_the_others_their_regions(tmp_path):
+    in_process("hundreds_on_many_streams", tmp_path)
+
+
 def unknown_sizes_of_hundreds(rt):
     for op in (0, pkg.UCCL_COPY):
         for n, parts in ((192, 4), (640, 4), (641, 3), (1500, 3), (1501, 2), (3000, 2)):
