@@ -562,7 +562,7 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
       return launch_ordered<Args>(chunk_order_kernel<Op::kEs>, chunk_ordered_kernel<Op>, lds, a, s, ordered, region.words);
     }
   }
-  const GroupPlan grouped = a.n_ptr == nullptr ? plan_group(a.n_descs, tune) : kNotGrouped;
+  const GroupPlan grouped = a.n_ptr == nullptr && !tune.one_launch ? plan_group(a.n_descs, tune) : kNotGrouped;   // a feed's slots are pinned
   if (grouped.unroll != 0u && in_device_memory(a.descs)) {
     const Region region = claim_region(s, kGroupCalls);
     if (region.words != nullptr) {

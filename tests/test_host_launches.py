@@ -182,6 +182,21 @@ def test_a_feed_hand_over_is_one_launch_per_lane(tmp_path):
     in_process("feed_hand_over", tmp_path)
 
 
+def feed_of_hundreds(rt):
+    import numpy as np
+    rt.answer["hipPointerGetAttributes"] = 1
+    d = np.zeros(300, dtype=[("off", "<u8", 3), ("len", "<u4"), ("seq", "<u4")])
+    d["seq"], d["len"] = np.arange(300), 4096
+    feed = C.c_void_p()
+    assert rt.lib.uccl_feed_create(C.byref(feed), A, OUT, RECV, BITS, 0, 0, 3, 3000, 2, None) == 0
+    assert rt.lib.uccl_feed_push(feed, 0, d.ctypes.data, 300) == 0 and rt.lib.uccl_feed_flush(feed) == 0
+    assert rt.kernels() == ["chunk_flat_kernel"] and "hipPointerGetAttributes" not in rt.calls
+
+
+def test_a_feed_does_not_ask_where_its_own_pinned_slots_are(tmp_path):
+    in_process("feed_of_hundreds", tmp_path)
+
+
 def unusable_event(rt):
     bad = 0x5000
     rt.refuse = lambda kernel, stream, start, stop: bad in (start, stop)
