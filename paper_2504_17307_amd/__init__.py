@@ -227,16 +227,14 @@ _extension = None
 
 
 def _load_extension():
-    """The extension that makes prepared calls (built with the library)."""
+    """The extension that makes prepared calls (built with the library, and first only if no file exists)."""
     global _extension
-    try:
-        from . import _prepared
-    except ImportError:
-        from .build import PREPARED_LIB, build_prepared
-        if os.path.exists(PREPARED_LIB):
-            raise
+    from .build import PREPARED_LIB, PREPARED_SRC, build_prepared
+    if not os.path.exists(PREPARED_LIB):
         build_prepared()
-        from . import _prepared
+    elif os.path.getmtime(PREPARED_SRC) > os.path.getmtime(PREPARED_LIB):
+        raise RuntimeError(f"{PREPARED_LIB} is older than its source: rebuild (python -m paper_2504_17307_amd.build)")
+    from . import _prepared
     _extension = _prepared
     return _prepared
 

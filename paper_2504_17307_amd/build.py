@@ -14,9 +14,9 @@ LIB = os.path.join(PKG, "libuccl_chunk.so")
 PROBE_SRC = [os.path.join(PKG, "probe", f) for f in ("stream_probe.hip", "report_probe.hip", "group_probe.hip")]
 PROBE_LIB = os.path.join(PKG, "probe", "libuccl_probe.so")
 
-# prepared calls of the Python binding: a CPython extension, host code only
+# prepared calls of the Python binding: a CPython extension, host code only, for the interpreter that builds it
 PREPARED_SRC = os.path.join(CSRC, "prepared_call.c")
-PREPARED_LIB = os.path.join(PKG, "_prepared.so")
+PREPARED_LIB = os.path.join(PKG, "_prepared" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

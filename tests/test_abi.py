@@ -205,6 +205,22 @@ def test_prepared_calls_pass_every_argument():
     assert gone() is None
 
 
+def test_the_extension_is_of_this_interpreter_and_of_the_present_source(monkeypatch, tmp_path):
+    """It calls raw addresses and reads object layouts: what another interpreter or an older source built is not loaded."""
+    import sysconfig
+    from paper_2504_17307_amd import build
+    assert build.PREPARED_LIB.endswith("_prepared" + sysconfig.get_config_var("EXT_SUFFIX"))
+    monkeypatch.setattr(pkg, "_extension", None)
+    assert pkg._load_extension().__file__ == build.PREPARED_LIB
+    newer = tmp_path / "prepared_call.c"
+    newer.write_text("")
+    os.utime(newer, (os.path.getmtime(build.PREPARED_LIB) + 60,) * 2)
+    monkeypatch.setattr(build, "PREPARED_SRC", str(newer))
+    monkeypatch.setattr(pkg, "_extension", None)
+    with pytest.raises(RuntimeError, match="older than its source"):
+        pkg.uccl_prepare(pkg.uccl_chunk_apply, 0x10000, None, 0x20000, 0x30000, 0, 0x40000, 0, 0, stream=0)
+
+
 def test_launch_plan_rules():
     """Host logic: which launch a call gets (uccl_launch_plan is the rule the data-path calls apply)."""
     plan = pkg.uccl_launch_plan
