@@ -10,6 +10,7 @@ There is no CPU fallback: if the shared library cannot be loaded, load() raises.
 import ctypes as C
 import functools
 import os
+import subprocess
 import threading
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
@@ -194,13 +195,30 @@ def uccl_prepare(func, *args, **kwargs):
         (typed, cargs, name), = _tls.pending
     finally:
         _tls.pending = None
+    extension = _extension if _extension is not None else _load_extension()
+    if not extension:
+        return _prepared_by_ctypes(typed, cargs, name, (args, kwargs))
     # the arguments are converted to C here, once
-    return (_extension or _load_extension()).Prepared(_address(name), tuple(map(_c_value, typed.argtypes, cargs)), functools.partial(_raise, name),
-                                                      (args, kwargs, cargs, _lib))
+    return extension.Prepared(_address(name), tuple(map(_c_value, typed.argtypes, cargs)), functools.partial(_raise, name), (args, kwargs, cargs, _lib))
 
 
 def _raise(name, code):
     raise UcclError(code, name)
+
+
+def _prepared_by_ctypes(typed, cargs, name, keeps):
+    """The same without the extension: a function object of its own without argument types takes C values as they are."""
+    fn = _lib[name]
+    fn.restype = typed.restype
+    cargs = tuple(t(a) if isinstance(a, int) else a for t, a in zip(typed.argtypes, cargs))
+
+    def enqueue():
+        code = fn(*cargs)
+        if code != UCCL_OK:
+            raise UcclError(code, name)
+
+    enqueue.keeps = keeps
+    return enqueue
 
 
 def _address(name):
@@ -223,15 +241,21 @@ def _c_value(t, a):
     return C.addressof(a._obj) if type(a) is _BYREF else C.cast(a, C.c_void_p).value or 0
 
 
-_extension = None
+_extension = None   # False: it cannot be built here
 
 
 def _load_extension():
-    """The extension that makes prepared calls (built with the library, and first only if no file exists)."""
+    """The extension that makes prepared calls (built with the library, and first only if no file exists).  Without a
+    compiler or the interpreter's headers, or where arguments are passed in another way, calls are prepared by ctypes,
+    which costs each some 0.3 us more; one that is there and does not load is an error."""
     global _extension
     from .build import PREPARED_LIB, PREPARED_SRC, build_prepared
     if not os.path.exists(PREPARED_LIB):
-        build_prepared()
+        try:
+            build_prepared()
+        except (OSError, subprocess.CalledProcessError):
+            _extension = False
+            return _extension
     elif os.path.getmtime(PREPARED_SRC) > os.path.getmtime(PREPARED_LIB):
         raise RuntimeError(f"{PREPARED_LIB} is older than its source: rebuild (python -m paper_2504_17307_amd.build)")
     from . import _prepared

@@ -3,6 +3,7 @@ host-side argument checks return the documented codes before anything is enqueue
 import ctypes as C
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -219,6 +220,24 @@ def test_the_extension_is_of_this_interpreter_and_of_the_present_source(monkeypa
     monkeypatch.setattr(pkg, "_extension", None)
     with pytest.raises(RuntimeError, match="older than its source"):
         pkg.uccl_prepare(pkg.uccl_chunk_apply, 0x10000, None, 0x20000, 0x30000, 0, 0x40000, 0, 0, stream=0)
+
+
+@pytest.mark.parametrize("failure", [FileNotFoundError("gcc"), subprocess.CalledProcessError(1, "gcc")])
+def test_calls_can_be_prepared_where_the_extension_cannot_be_built(monkeypatch, tmp_path, failure):
+    """No compiler, no headers of the interpreter, another calling convention: the same calls, by ctypes."""
+    from paper_2504_17307_amd import build
+
+    def fails(verbose=False):
+        raise failure
+    monkeypatch.setattr(build, "PREPARED_LIB", str(tmp_path / "none.so"))
+    monkeypatch.setattr(build, "build_prepared", fails)
+    monkeypatch.setattr(pkg, "_extension", None)
+    for _ in range(2):
+        call = pkg.uccl_prepare(pkg.uccl_chunk_apply_opts, 0x10008, None, 0x20000, 0x30000, 1, 0x40000, 0, 0, opts=(4096, 0), stream=0)
+        with pytest.raises(pkg.UcclError) as e:
+            call()
+        assert e.value.code == pkg.UCCL_EALIGN
+    assert pkg.uccl_prepare(pkg.uccl_chunk_apply, 0x10000, None, 0x20000, 0x30000, 0, 0x40000, 0, 0, stream=0)() is None
 
 
 def test_launch_plan_rules():
