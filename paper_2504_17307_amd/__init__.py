@@ -199,7 +199,7 @@ def uccl_prepare(func, *args, **kwargs):
     if not extension:
         return _prepared_by_ctypes(typed, cargs, name, (args, kwargs))
     # the arguments are converted to C here, once
-    return extension.Prepared(_address(name), tuple(map(_c_value, typed.argtypes, cargs)), functools.partial(_raise, name), (args, kwargs, cargs, _lib))
+    return extension.Prepared(_address(name), tuple(map(_c_value, typed.argtypes, cargs)), functools.partial(_raise, name), (args, kwargs), (cargs, _lib), name)
 
 
 def _raise(name, code):
@@ -217,7 +217,7 @@ def _prepared_by_ctypes(typed, cargs, name, keeps):
         if code != UCCL_OK:
             raise UcclError(code, name)
 
-    enqueue.keeps = keeps
+    enqueue.keeps, enqueue.__name__ = keeps, name
     return enqueue
 
 

@@ -17,7 +17,9 @@ typedef struct {
   void* fn;
   int n;
   uint64_t a[MOST];
-  PyObject *failed, *keeps;   /* called with a code other than 0; what the arguments point into */
+  PyObject *failed, *keeps;   /* called with a code other than 0; what the caller gave */
+  PyObject *holds, *name;     /* what else the arguments point into; of the function (either may be NULL) */
+  PyObject *dict, *weak;
 } Prepared;
 
 /* Every argument of the ABI's functions is a pointer or a whole number of at most 64 bits: each takes one integer
@@ -69,12 +71,12 @@ static PyObject* prepared_vectorcall(PyObject* self, PyObject* const* args, size
 
 static PyObject* prepared_new(PyTypeObject* type, PyObject* args, PyObject* kw) {
   unsigned long long fn;
-  PyObject *values, *failed, *keeps;
+  PyObject *values, *failed, *keeps, *holds = NULL, *name = NULL;
   if (kw != NULL && PyDict_GET_SIZE(kw) != 0) {
     PyErr_SetString(PyExc_TypeError, "no keyword arguments");
     return NULL;
   }
-  if (!PyArg_ParseTuple(args, "KO!OO", &fn, &PyTuple_Type, &values, &failed, &keeps)) return NULL;
+  if (!PyArg_ParseTuple(args, "KO!OO|OO", &fn, &PyTuple_Type, &values, &failed, &keeps, &holds, &name)) return NULL;
   const Py_ssize_t n = PyTuple_GET_SIZE(values);
   if (fn == 0 || n > MOST || !PyCallable_Check(failed)) {
     PyErr_SetString(PyExc_ValueError, "a function's address, at most 13 whole numbers, a callable and what to keep");
@@ -89,6 +91,10 @@ static PyObject* prepared_new(PyTypeObject* type, PyObject* args, PyObject* kw) 
   p->failed = failed;
   Py_INCREF(keeps);
   p->keeps = keeps;
+  Py_XINCREF(holds);
+  p->holds = holds;
+  Py_XINCREF(name);
+  p->name = name;
   for (Py_ssize_t i = 0; i < n; ++i) {
     p->a[i] = PyLong_AsUnsignedLongLongMask(PyTuple_GET_ITEM(values, i));
     if (PyErr_Occurred()) {
@@ -102,20 +108,30 @@ static PyObject* prepared_new(PyTypeObject* type, PyObject* args, PyObject* kw) 
 static int prepared_traverse(PyObject* self, visitproc visit, void* arg) {
   Py_VISIT(((Prepared*)self)->failed);
   Py_VISIT(((Prepared*)self)->keeps);
+  Py_VISIT(((Prepared*)self)->holds);
+  Py_VISIT(((Prepared*)self)->name);
+  Py_VISIT(((Prepared*)self)->dict);
   return 0;
 }
 static int prepared_clear(PyObject* self) {
   Py_CLEAR(((Prepared*)self)->failed);
   Py_CLEAR(((Prepared*)self)->keeps);
+  Py_CLEAR(((Prepared*)self)->holds);
+  Py_CLEAR(((Prepared*)self)->name);
+  Py_CLEAR(((Prepared*)self)->dict);
   return 0;
 }
 static void prepared_dealloc(PyObject* self) {
   PyObject_GC_UnTrack(self);
+  if (((Prepared*)self)->weak != NULL) PyObject_ClearWeakRefs(self);
   prepared_clear(self);
   Py_TYPE(self)->tp_free(self);
 }
 
-static PyMemberDef members[] = {{"keeps", T_OBJECT_EX, offsetof(Prepared, keeps), READONLY, NULL}, {NULL, 0, 0, 0, NULL}};
+static PyMemberDef members[] = {{"keeps", T_OBJECT_EX, offsetof(Prepared, keeps), READONLY, NULL},
+                                {"__name__", T_OBJECT_EX, offsetof(Prepared, name), 0, NULL},
+                                {NULL, 0, 0, 0, NULL}};
+static PyGetSetDef getset[] = {{"__dict__", PyObject_GenericGetDict, PyObject_GenericSetDict, NULL, NULL}, {NULL, NULL, NULL, NULL, NULL}};
 static PyTypeObject prepared_type = {
     PyVarObject_HEAD_INIT(NULL, 0).tp_name = "paper_2504_17307_amd._prepared.Prepared",
     .tp_basicsize = sizeof(Prepared),
@@ -126,6 +142,9 @@ static PyTypeObject prepared_type = {
     .tp_traverse = prepared_traverse,
     .tp_clear = prepared_clear,
     .tp_members = members,
+    .tp_getset = getset,
+    .tp_dictoffset = offsetof(Prepared, dict),
+    .tp_weaklistoffset = offsetof(Prepared, weak),
     .tp_new = prepared_new,
 };
 static struct PyModuleDef module = {PyModuleDef_HEAD_INIT, "_prepared", NULL, -1, NULL, NULL, NULL, NULL, NULL};

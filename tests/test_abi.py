@@ -206,6 +206,28 @@ def test_prepared_calls_pass_every_argument():
     assert gone() is None
 
 
+def test_a_prepared_call_is_an_object_like_others():
+    """It takes attributes and weak references, says which call it makes, and keeps what it was given; none of that leaks."""
+    import gc
+    import weakref
+
+    class Kept(int):
+        pass
+    acc = Kept(0x10000)
+    call = pkg.uccl_prepare(pkg.uccl_chunk_apply, acc, None, 0x20000, 0x30000, 0, 0x40000, 0, 0, stream=0)
+    assert call.__name__ == "uccl_chunk_apply"
+    args, kwargs = call.keeps
+    assert args[0] is acc and kwargs == {"stream": 0}
+    call.label, acc.cycle = ["of", "the", "caller"], call
+    assert call.label[0] == "of" and vars(call) == {"label": call.label}
+    gone = weakref.ref(call)
+    assert gone() is call
+    call()
+    del call, acc, args, kwargs
+    gc.collect()
+    assert gone() is None
+
+
 def test_the_extension_is_of_this_interpreter_and_of_the_present_source(monkeypatch, tmp_path):
     """It calls raw addresses and reads object layouts: what another interpreter or an older source built is not loaded."""
     import sysconfig
