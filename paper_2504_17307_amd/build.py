@@ -11,7 +11,7 @@ SRC = os.path.join(CSRC, "uccl_chunk.hip")  # the one translation unit; it inclu
 INC = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libuccl_chunk.so")
 # aids of bench.py (dense streaming kernels) and of the tests (the report's recount, late decisions), a library of their own
-PROBE_SRC = [os.path.join(PKG, "probe", f) for f in ("stream_probe.hip", "report_probe.hip", "group_probe.hip")]
+PROBE_SRC = [os.path.join(PKG, "probe", f) for f in ("stream_probe.hip", "report_probe.hip", "group_probe.hip", "late_probe.hip")]
 PROBE_LIB = os.path.join(PKG, "probe", "libuccl_probe.so")
 
 # prepared calls of the Python binding: a CPython extension, host code only, for the interpreter that builds it

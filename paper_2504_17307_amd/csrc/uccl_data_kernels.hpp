@@ -661,7 +661,7 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
 #define UCCL_GROUP_POLLS 4096
 #endif
 #ifndef UCCL_GROUP_LEADS
-#define UCCL_GROUP_LEADS 1      // 0: the group's first workgroup waits like the others (a test's build)
+#define UCCL_GROUP_LEADS 1      // tests' builds: 0 the group's first workgroup waits like the others, 2 it comes late
 #endif
 constexpr uint32_t kGroup = 64;
 constexpr uint32_t kGroupPolls = UCCL_GROUP_POLLS;
@@ -671,6 +671,13 @@ __device__ __forceinline__ unsigned long long group_enter(unsigned long long* li
   unsigned long long was = 0ull;
   if (lane == 0) was = __hip_atomic_exchange(line, tag << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return was;
+}
+// What the leader does first.  Nothing; in a test's build it waits for another to begin to decide (not for long: there may be none).
+__device__ __forceinline__ void group_lead(unsigned long long* line, unsigned long long tag) {
+#if UCCL_GROUP_LEADS == 2
+  for (uint32_t polls = 0; polls < 4096u && (__hip_atomic_load(line, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16) != tag; ++polls)
+    __builtin_amdgcn_s_sleep(1);
+#endif
 }
 __device__ __forceinline__ bool group_is_ours(unsigned long long was, unsigned long long tag) {
   return __builtin_amdgcn_readfirstlane(static_cast<uint32_t>((was >> 16) != tag)) != 0u;
@@ -748,7 +755,10 @@ __global__ void __launch_bounds__(NT) UCCL_FULL_OCCUPANCY chunk_group_kernel(con
   const bool decides = UCCL_GROUP_LEADS && wave == 0u && place.first;
   unsigned long long* const line = g.claims + static_cast<size_t>(base / kGroup) * UCCL_CLAIM_STRIDE;
   unsigned long long was = 0ull;
-  if (decides) was = group_enter(line, g.tag, lane);
+  if (decides) {
+    group_lead(line, g.tag);
+    was = group_enter(line, g.tag, lane);
+  }
   // every lane reads the workgroup's record; where the group is decided, lane i reads record i of the group
   const uint32_t mine = decides && base + lane < g.n_descs ? base + lane : k;
   const u32x4* p = reinterpret_cast<const u32x4*>(g.descs + mine);
@@ -1138,10 +1148,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_num_sgpr(80))) gath
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const GroupPlace place = group_place(g);   // the launch has n_descs * parts workgroups
   const uint32_t k = place.k, part = place.part, in = place.in, base = place.base;
-  const bool decides = wave == 0u && place.first;
+  const bool decides = UCCL_GROUP_LEADS && wave == 0u && place.first;
   unsigned long long* const line = g.claims + static_cast<size_t>(base / kGroup) * UCCL_CLAIM_STRIDE;
   unsigned long long was = 0ull;
-  if (decides) was = group_enter(line, g.tag, lane);
+  if (decides) {
+    group_lead(line, g.tag);
+    was = group_enter(line, g.tag, lane);
+  }
   // every lane reads the workgroup's record; where the group is decided, lane i reads record i of the group
   const u32x4* p = reinterpret_cast<const u32x4*>(g.descs + (decides && base + lane < g.n_descs ? base + lane : k));
   u32x4 lo = p[0], hi = p[1];

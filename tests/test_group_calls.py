@@ -115,16 +115,8 @@ def test_random_streams(gpu_lib, dtype, op):
         check(w, (chunk, 0), streams=1 + seed % 2)
 
 
-@pytest.mark.gpu
-@pytest.mark.parametrize("n,chunk,dtype,op", [(257, 0, F32, SUM), (800, 0, BF16, SUM), (289, 4096, F32, MAX), (320, 8192, BF16, SUM), (550, 16384, F16, MIN),
-                                              (513, 32768, I32, PROD), (257, 65536, F32, SUM), (801, 0, BF16, MAX), (3000, 0, F32, SUM), (3000, 4096, F32, SUM),
-                                              (1, 48 << 20, F32, SUM), (2, 20 << 20, F16, MAX), (16, 2 << 20, BF16, SUM), (63, 300 << 10, I32, SUM), (130, 200 << 10, F32, MIN)])
-def test_folds(gpu_lib, n, chunk, dtype, op):
-    """One to sixteen sources, repeats, keep / forward / relay, records with a bad source or sequence number; against the oracle,
-    and the form it replaces against it too."""
-    import torch
-    from gpuhelp import to_dev
-    w, _ = edges(n, n + 2, trip=4096 * pkg.uccl_launch_grouped(n, (chunk, 0), gather=True))      # of all parts
+def fold_records(w, n, dtype):
+    """The calls' records as folds: records, accumulator, slots, and which records are valid."""
     src, g, es = w["descs"], np.random.default_rng(n), {F32: 4, I32: 4}.get(dtype, 2)
     kind = {F32: np.float32, I32: np.int32, BF16: np.uint16, F16: np.float16}[dtype]
     total = w["out_bytes"]
@@ -141,6 +133,21 @@ def test_folds(gpu_lib, n, chunk, dtype, op):
     d["src_off"][wrong, d["n_src"][wrong] - 1] += 8                                              # the last one that is named
     d["src_off"][d["n_src"] < 16, 15] += 8                                                       # one that is not
     good = ~wrong & (d["seq"] < w["n_bits"])
+    return d, acc, recv, good
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,chunk,dtype,op", [(257, 0, F32, SUM), (800, 0, BF16, SUM), (289, 4096, F32, MAX), (320, 8192, BF16, SUM), (550, 16384, F16, MIN),
+                                              (513, 32768, I32, PROD), (257, 65536, F32, SUM), (801, 0, BF16, MAX), (3000, 0, F32, SUM), (3000, 4096, F32, SUM),
+                                              (1, 48 << 20, F32, SUM), (2, 20 << 20, F16, MAX), (16, 2 << 20, BF16, SUM), (63, 300 << 10, I32, SUM), (130, 200 << 10, F32, MIN)])
+def test_folds(gpu_lib, n, chunk, dtype, op):
+    """One to sixteen sources, repeats, keep / forward / relay, records with a bad source or sequence number; against the oracle,
+    and the form it replaces against it too."""
+    import torch
+    from gpuhelp import to_dev
+    w, _ = edges(n, n + 2, trip=4096 * pkg.uccl_launch_grouped(n, (chunk, 0), gather=True))      # of all parts
+    d, acc, recv, good = fold_records(w, n, dtype)
+    total = w["out_bytes"]
     e, o, seen = acc.copy(), np.full(total, 0xA5, dtype=np.uint8), oracle.new_seen(w["n_bits"])
     oracle.reduce_gather(e, o, recv, d[good], seen, dtype, op)
     assert pkg.uccl_launch_grouped(n, (chunk, 0), gather=True) > 0 and pkg.uccl_launch_grouped(n, (chunk, 1), gather=True) == 0
@@ -183,6 +190,107 @@ def test_late_decisions(gpu_lib, n, parts):
         for name, g, e in zip(("acc", "out", "bitmap", "rejected"), (acc, out, bitmap, rejected), exp):
             assert np.array_equal(g.cpu().numpy(), e), (name, tag)
         assert int(words[(n - 1) // 64 * 16 + 16]) == 0                                          # nobody gave up
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("late", [False, True])
+@pytest.mark.parametrize("what", ["one vector", "four vectors", "fold"])
+@pytest.mark.parametrize("n,parts,major", [(64, 3, 0), (65, 16, 0), (300, 6, 1), (700, 4, 1), (1500, 2, 1)])
+def test_late_decisions_of_every_form(gpu_lib, n, parts, major, what, late):
+    """Nobody leads, or the leader begins when another wavefront has: one of them decides, for apply and fold, in either order of
+    the parts.  `late`: the first group has bad records only, so nobody waits there and the leader decides after all."""
+    import torch
+    from gpuhelp import to_dev
+    from paper_2504_17307_amd.build import PROBE_LIB
+    lib, fold = C.CDLL(PROBE_LIB), what == "fold"
+    f = getattr(lib, ("uccl_probe_group_fold" if fold else "uccl_probe_group_apply") + ("_late" if late else ""))
+    f.argtypes = [C.c_void_p] * 4 + [C.c_uint32, C.c_void_p, C.c_uint64, C.c_void_p] + [C.c_uint32] * (2 if fold else 3) + [C.c_void_p, C.c_uint64, C.c_void_p]
+    w, _ = edges(n, n + 3, trip=parts * (16384 if what == "four vectors" else 4096), least=1)
+    if late:
+        w["descs"]["seq"][:64] = w["n_bits"] + 3
+    d, acc, recv = w["descs"], w["acc"], w["recv"]
+    good = d["seq"] < w["n_bits"]
+    if fold:
+        d, acc, recv, good = fold_records(w, n, F32)
+    assert late or all(good[g:g + 64].any() for g in range(0, n, 64))       # a group of bad records alone has nobody waiting
+    e, o, seen = acc.copy(), np.full(w["out_bytes"], 0xA5, dtype=np.uint8), oracle.new_seen(w["n_bits"])
+    (oracle.reduce_gather if fold else oracle.apply)(e, o, recv, d[good], seen, F32, SUM)
+    exp = (e.view(np.uint8), o, oracle.pack_bitmap(seen).view(np.int32), np.array([(~good).sum()], dtype=np.int32))
+    words = torch.zeros(((n - 1) // 64 + 2) * 16, dtype=torch.int64, device="cuda")
+    for tag in (1, 2, 3):                                                    # stale words of earlier calls
+        da, dr, dd = to_dev(acc), to_dev(recv), to_dev(d)
+        out = torch.full((w["out_bytes"],), 0xA5, dtype=torch.uint8, device="cuda")
+        bitmap, rejected = torch.zeros((w["n_bits"] + 31) // 32, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        print(n, parts, major, what, late, tag, flush=True)
+        args = [parts, major] + ([] if fold else [4 if what == "four vectors" else 1])
+        assert f(da.data_ptr(), out.data_ptr(), dr.data_ptr(), dd.data_ptr(), n, bitmap.data_ptr(), w["n_bits"], rejected.data_ptr(), *args,
+                 words.data_ptr(), tag, torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        for name, g, x in zip(("acc", "out", "bitmap", "rejected"), (da, out, bitmap, rejected), exp):
+            assert np.array_equal(g.cpu().numpy(), x), (name, tag)
+        assert int(words[(n - 1) // 64 * 16 + 16]) == 0                      # nobody gave up
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [192, 641, 2048])
+def test_no_allocation_calls(gpu_lib, n):
+    """The no-allocation entry point has the same form, eager; captured the one without scratch words, each replay checked."""
+    import torch
+    from gpuhelp import to_dev
+    w, _ = edges(n, n + 4, trip=16384 * pkg.uccl_launch_grouped(n))
+    w["descs"] = np.ascontiguousarray(np.resize(w["descs"][w["descs"]["seq"] < w["n_bits"]], n))    # the call is not a checked one
+    exp = expected(w)
+    recv, descs, acc0 = to_dev(w["recv"]), to_dev(w["descs"]), to_dev(w["acc"])
+    sets = [(acc0.clone(), torch.zeros(w["out_bytes"], dtype=torch.uint8, device="cuda"), torch.zeros((w["n_bits"] + 31) // 32, dtype=torch.int32, device="cuda"))
+            for _ in range(2)]
+
+    def issue(a, o, b):
+        pkg.uccl_dedup_reset(b, w["n_bits"])
+        pkg.uccl_chunk_apply_noalloc(a, o, recv, descs, n, b, F32, SUM)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        issue(*sets[0])
+    with torch.cuda.stream(side):
+        for replay in range(3):
+            for a, o, b in sets:
+                a.copy_(acc0), o.fill_(0xA5)
+            graph.replay()
+            issue(*sets[1])
+            side.synchronize()
+            for got in sets:
+                for name, t, x in zip(("acc", "out", "bitmap"), got, exp):
+                    assert np.array_equal(t.cpu().numpy()[:len(x)], x[:len(t)]), (name, replay)
+    assert pkg.uccl_claim_timeouts() == 0
+
+
+@pytest.mark.gpu
+def test_threads_that_share_a_stream(gpu_lib):
+    """Calls of several threads on one stream share its words: every call has its own outcome."""
+    import threading
+    import torch
+    from gpuhelp import to_dev
+    stream, jobs = torch.cuda.Stream(), []
+    for k in range(4):
+        w, bad = edges(500, 50 + k)
+        recv, descs = to_dev(w["recv"]), to_dev(w["descs"])
+        sets = [(to_dev(w["acc"]), torch.full((w["out_bytes"],), 0xA5, dtype=torch.uint8, device="cuda"),
+                 torch.zeros((w["n_bits"] + 31) // 32, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")) for _ in range(6)]
+        jobs.append((w, expected(w, bad), recv, descs, sets))
+    torch.cuda.synchronize()
+
+    def work(job):
+        w, _, recv, descs, sets = job
+        for a, o, b, r in sets:
+            pkg.uccl_chunk_apply_opts(a, o, recv, descs, 500, b, F32, SUM, n_rejected=r, n_bits=w["n_bits"], stream=stream)
+    threads = [threading.Thread(target=work, args=(j,)) for j in jobs]
+    [t.start() for t in threads], [t.join() for t in threads]
+    torch.cuda.synchronize()
+    for _, exp, _, _, sets in jobs:
+        for got in sets:
+            for name, t, x in zip(("acc", "out", "bitmap", "rejected"), got, exp):
+                assert np.array_equal(t.cpu().numpy(), x), name
 
 
 @pytest.mark.gpu
