@@ -41,6 +41,9 @@ class Runtime:
         if name in ("chunk_order_kernel", "chunk_ordered_kernel", "gather_order_kernel", "gather_ordered_kernel"):
             words = C.cast(args[1], C.POINTER(C.c_uint64))           # OrderArgs: words, tag
             scratch = words[0], words[1]
+        elif name in ("chunk_group_kernel", "gather_group_kernel"):
+            words = C.cast(args[0] + 80, C.POINTER(C.c_uint64))       # ClaimArgs, after ten words of Buffers: claims, parts : 16 | tag : 48
+            scratch = words[0], words[1] >> 16
         elif name == "ack_segments_kernel":
             scratch = C.cast(args[5], C.POINTER(C.c_uint64))[0], C.cast(args[6], C.POINTER(C.c_uint64))[0]
         self.launches.append((name, grid, block, lds, stream or 0, scratch))
@@ -317,6 +320,52 @@ def hundreds_on_many_streams(rt):
 
 def test_streams_with_calls_of_hundreds_leave_the_others_their_regions(tmp_path):
     in_process("hundreds_on_many_streams", tmp_path)
+
+
+def forms_of_hundreds(rt):
+    import threading
+    lib, group, opts = rt.lib, lambda wgs, k="chunk": [(k + "_group_kernel", wgs, 256)], lambda c: C.byref(pkg.uccl_launch_opts(c, 0))
+    extents = C.byref(pkg.uccl_extents(MiB, MiB, MiB, 3000))
+    calls = [   # (call, its launches, and the kernel of the form it has without scratch words or for records in host memory)
+        (lambda s=0: rt.apply(300, 4 * KiB, s), group(300), "chunk_flat_kernel"), (lambda s=0: rt.apply(300, 8 * KiB, s), group(300), "chunk_flat_kernel"),
+        (lambda s=0: rt.apply(320, 16 * KiB, s), group(320), "chunk_few_kernel"), (lambda s=0: rt.apply(256, 32 * KiB, s), group(512), "chunk_few_kernel"),
+        (lambda s=0: rt.apply(257, 64 * KiB, s, op=pkg.UCCL_COPY), group(4 * 257), "chunk_few_kernel"), (lambda s=0: rt.apply(192, stream=s), group(4 * 192), "chunk_few_kernel"),
+        (lambda s=0: lib.uccl_chunk_apply_checked(A, OUT, RECV, DESCS, 700, BITS, 0, 0, extents, None, s), group(3 * 700), "chunk_few_kernel"),
+        (lambda s=0: lib.uccl_chunk_apply_noalloc(A, OUT, RECV, DESCS, 2048, BITS, 0, 0, s), group(2 * 2048), "chunk_flat_kernel"),
+        (lambda s=0: lib.uccl_chunk_scatter(A, RECV, DESCS, 500, BITS, s), group(4 * 500), "chunk_few_kernel"),
+        (lambda s=0: lib.uccl_chunk_scatter_opts(A, RECV, DESCS, 500, BITS, None, None, opts(8 * KiB), s), group(500), "chunk_flat_kernel"),
+        (lambda s=0: rt.fold(289, 4 * KiB, s), group(289, "gather"), "chunk_gather_kernel"), (lambda s=0: rt.fold(320, 8 * KiB, s), group(640, "gather"), "chunk_gather_kernel"),
+        (lambda s=0: rt.fold(257, 0, s), group(6 * 257, "gather"), "chunk_gather_kernel")]
+    tags, words = [], set()
+    for call, launches, other in calls:
+        rt.launches.clear()
+        assert call() == 0 and [l[:3] for l in rt.launches] == launches, (launches, rt.launches)
+        at, tag = rt.launches[0][5]
+        tags.append(tag), words.add(at)
+        for name, what in (("hipPointerGetAttributes", 1), ("hipPointerGetAttributes", -1), ("hipStreamIsCapturing", 1), ("hipStreamIsCapturing", -1)):
+            rt.answer[name] = what
+            rt.launches.clear()
+            assert call() == 0 and rt.kernels() == [other], (launches, name, what, rt.kernels())
+            del rt.answer[name]
+    assert tags == sorted(set(tags)) and len(words) == 1             # one stream: the same words, another tag each time
+    rt.launches.clear()                                              # a count that the host does not know, and stated parts
+    assert lib.uccl_chunk_apply_indirect(A, OUT, RECV, DESCS, BITS, 300, BITS, 0, 0, None, None, None, None) == 0 and rt.apply(300, 0, parts=1) == 0
+    assert rt.kernels() == ["chunk_few_kernel"] * 2
+    per_thread, own = 2, []
+    for stream in (0x1000, 0x2000, per_thread):
+        rt.launches.clear()
+        assert rt.apply(300, stream=stream) == 0 and rt.fold(300, 0, stream) == 0
+        own.append({l[5][0] for l in rt.launches})
+    assert all(len(x) == 1 for x in own) and len(set().union(words, *own)) == 4
+    rt.launches.clear()
+    threads = [threading.Thread(target=lambda: [rt.apply(300, stream=0x1000) for _ in range(200)]) for _ in range(4)]
+    [t.start() for t in threads], [t.join() for t in threads]
+    order = [l[5][1] for l in rt.launches]
+    assert len(order) == 800 and order == sorted(set(order))         # tags grow in the order of the launches
+
+
+def test_calls_of_hundreds_are_launched_in_their_form_and_in_the_other_without_scratch_words(tmp_path):
+    in_process("forms_of_hundreds", tmp_path)
 
 
 def unknown_sizes_of_hundreds(rt):
