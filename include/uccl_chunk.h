@@ -93,7 +93,8 @@ typedef struct uccl_extents {
  *   chunk_bytes  the transport's chunk size (the control path chooses it per connection: 32 KB by
  *                default, Section 3.3 "control coalescing"; Appendix A onChunkSize), 0 = unknown.
  *                Sets how many records a workgroup takes: about 32 KiB of payload per workgroup (calls of
- *                at most 128 records take one workgroup per record, sized to the chunk).  Calls of much payload
+ *                at most 128 records take one workgroup per record, sized to the chunk, calls of hundreds one or more,
+ *                see `grouped` in uccl_plan).  Calls of much payload
  *                (records x chunk_bytes: 96 MiB for a reduction, 192 MiB or chunks of 64 KiB for a copy; chunks
  *                of 16 KiB and more) are streamed in destination order, by two launches (see "Scratch
  *                memory" below); so are calls of 3072 to 8191 records of unknown size.  State the size that
@@ -146,14 +147,17 @@ typedef struct uccl_launch_opts {
  * own) in an array inside the library's code object (36.5 MiB on every GPU the library runs on, until the process
  * ends).  It has one region per stream
  * handle, for the first 64 that issue such a call on the device (hipStreamPerThread: one per thread, for the first 16
- * threads).  A region is never given back; a stream created later under the handle of a destroyed one takes it over
+ * threads, for cut calls and what is said of the second region below).  A region is never given back; a stream created later under the handle of a destroyed one takes it over
  * (hipStreamDestroy waits for the work on the stream).  Calls that are
  * streamed in destination order (uccl_launch_opts) keep that order, folds of small chunks their claim words and
- * uccl_dedup_report its counts in a second region of the stream, calls of hundreds of records (and folds of few large
- * ones) the outcome of every 64 records in a third; there are 64 (16) of each.  If the stream has no region, or is being captured into a graph, the
+ * uccl_dedup_report its counts in a second region of the stream, of which there are 64 too.  Calls of hundreds of records
+ * (and folds of few large ones), which decide 64 records at a time, keep the outcome in small regions of their own, for 64 streams and 16
+ * threads.  If the stream has no region, or is being captured into a graph, the
  * call is launched in the form that needs no scratch
- * memory instead (one workgroup per record or per tile of records): slower, same result.  No
- * data-path call allocates; the first call on a device loads the library's code object.
+ * memory instead (one workgroup per record or per tile of records): slower, same result.
+ * Workgroups that wait for a decision wait for one that is running; should it not come within 65536 polls (tens of milliseconds),
+ * they give up: the records' bits are then set, their payload not moved or not all of it, and uccl_claim_timeouts counts them.
+ * No data-path call allocates; the first call on a device loads the library's code object.
  */
 int uccl_chunk_apply(void* acc, void* out_stage, const void* recv_stage,
                      const uccl_chunk_desc* descs, uint32_t n_descs, uint32_t* dedup_bitmap,
@@ -169,10 +173,12 @@ int uccl_init(void);
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
  * operation and result; the claim words of records cut into parts (at most 128 records; see "Scratch memory" above)
  * live in an array that needs no region: UCCL_NOALLOC_MAX_DESCS
- * lines of 128 bytes + 256 bytes = 256.25 KiB, held like the regions.  Calls are cut under capture too.
+ * lines of 128 bytes + 256 bytes = 256.25 KiB, held like the regions.  Calls are cut under capture too.  Calls of 192 records
+ * and more decide 64 records at a time as uccl_chunk_apply does, in the stream's small region, and like there not
+ * without one or under capture; they do not touch the array.
  *   - n_descs > UCCL_NOALLOC_MAX_DESCS returns UCCL_ETOOBIG and enqueues nothing.  (Calls that
  *     large are never cut into parts; uccl_chunk_apply serves them, and allocates nothing either.)
- *   - Every call on a GPU shares that GPU's array, whatever the stream.  A split call may be captured and
+ *   - Every call of at most 128 records on a GPU shares that GPU's array, whatever the stream.  A split call may be captured and
  *     replayed: a captured one first clears its own words with a small fill kernel, then runs.
  *     Calls (or replays) that overlap in time on one GPU race on the array: keep them on one
  *     stream, or order them.  Calls that do not overlap may run in any order.
@@ -423,8 +429,10 @@ int uccl_feed_destroy(uccl_feed* feed);
  * `ordered` > 0: where scratch memory is to be had and the records are in device memory, apply and scatter calls (not the indirect and
  * no-allocation ones, nor a feed's hand-overs) and uccl_chunk_reduce_gather decide the records first and stream them in destination order, in that many
  * pairs of launches (chunk_order_kernel and chunk_ordered_kernel, or their gather_ forms); the other fields say what the call is launched as otherwise.
- * `grouped` > 0: in the same circumstances (the no-allocation calls included), unless it is ordered, such a call of hundreds of records is one
- * launch of chunk_group_kernel (or gather_group_kernel), in which the first workgroup of every 64 records decides them for the others.
+ * `grouped` > 0: in the same circumstances (the no-allocation calls included), unless it is ordered, such a call (of hundreds of records, or a fold of
+ * few large ones) is one launch of chunk_group_kernel (or gather_group_kernel) with that many workgroups of 256 threads a record, in which the
+ * first workgroup of every 64 records decides them for the others.  A duplicate
+ * costs the payload reads of one trip, 4 to 16 KiB, of each of its workgroups there.
  * UCCL_EINVAL for a NULL `plan` or options the data-path calls would refuse.  Utility, no passage
  * of the paper. */
 enum { UCCL_KERNEL_FLAT = 0, UCCL_KERNEL_FEW = 1, UCCL_KERNEL_GATHER = 2, UCCL_KERNEL_GATHER_PARTS = 3 };

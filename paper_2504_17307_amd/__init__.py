@@ -1,4 +1,4 @@
-"""Thin ctypes binding of libuccl_chunk.so (the C ABI declared in include/uccl_chunk.h).
+"""Thin binding of libuccl_chunk.so (the C ABI declared in include/uccl_chunk.h) by ctypes; prepared calls by a small extension.
 
 Argument marshalling only: every step of the data path (dedup, place, combine, write,
 forward) runs in the HIP kernels.  Buffers are device memory owned by the caller, passed

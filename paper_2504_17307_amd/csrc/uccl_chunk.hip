@@ -25,8 +25,8 @@
 // writes, which depends on the order of the accesses: they decide all sequence numbers in a small
 // launch of its own and stream the winners in destination order in a second one.
 //
-// Calls of hundreds of records take one record a workgroup and load its payload at once, while one wavefront of every 64
-// records decides them for the others.
+// Calls of hundreds of records take a record, or a part of one, a workgroup and load its payload at once, while one
+// wavefront of every 64 records decides them for the others.
 //
 // Calls of few records (Appendix C.4: small messages are where fixed costs show) take another
 // kernel, which shortens the chain of latencies instead: one record per workgroup, payload
