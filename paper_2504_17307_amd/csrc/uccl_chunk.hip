@@ -570,9 +570,9 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
       a.use(region.words, region.faults);
       a.parts = grouped.parts;
       a.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
-      a.part_major = tune.chunk_bytes == 0u ? 1u : 0u;
-      const auto kernel = grouped.unroll == 4u ? chunk_group_kernel<kGroupThreads, 4, Op> : grouped.unroll == 2u ? chunk_group_kernel<kGroupThreads, 2, Op>
-                                                                                          : chunk_group_kernel<kGroupThreads, 1, Op>;
+      const auto kernel = tune.chunk_bytes == 0u ? chunk_group_kernel<kGroupThreads, 4, Op, true>
+                          : grouped.unroll == 4u ? chunk_group_kernel<kGroupThreads, 4, Op, false>
+                          : grouped.unroll == 2u ? chunk_group_kernel<kGroupThreads, 2, Op, false> : chunk_group_kernel<kGroupThreads, 1, Op, false>;
       return launch_kernel(kernel, a.n_descs * a.parts, kGroupThreads, s, a);
     }
   }
@@ -691,9 +691,8 @@ int launch_gather_tile(GatherArgs& a, hipStream_t s, const Tuning& tune) {
       std::lock_guard<std::mutex> in_order(*region.launch_lock);
       a.use(region.words, region.faults);
       a.parts = grouped;
-      a.part_major = tune.chunk_bytes == 0u ? 1u : 0u;
       a.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
-      return launch_kernel(gather_group_kernel<Op>, a.n_descs * a.parts, 256, s, a);
+      return launch_kernel(tune.chunk_bytes == 0u ? gather_group_kernel<Op, true> : gather_group_kernel<Op, false>, a.n_descs * a.parts, 256, s, a);
     }
   }
   Plan p = plan_gather(a.n_descs, tune);
@@ -760,7 +759,6 @@ int apply_common(void* acc, void* out_stage, const void* recv_stage, const uccl_
   a.allow_forward = allow_forward ? 1u : 0u;
   a.claims = nullptr;
   a.faults_at = 0u;
-  a.part_major = 0u;
   a.parts = 1u;
   a.tag = 0ull;
   if (ext) {
@@ -1076,7 +1074,6 @@ int uccl_chunk_reduce_gather(void* acc, void* out_stage, const void* recv_stage,
   a.n_descs = n_descs;
   a.claims = nullptr;
   a.faults_at = 0u;
-  a.part_major = 0u;
   a.allow_forward = 1u;
   a.tag = 0ull;
   a.parts = 1u;

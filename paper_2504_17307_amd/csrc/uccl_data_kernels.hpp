@@ -61,8 +61,7 @@ struct ClaimArgs {
   unsigned long long* claims;
   uint32_t parts : 16;
   unsigned long long tag : 48;
-  uint32_t faults_at : 30;
-  uint32_t part_major : 1;   // group kernels: see group_place
+  uint32_t faults_at : 31;
   uint32_t allow_forward : 1;
   uint32_t n_descs;
 
@@ -720,29 +719,25 @@ __device__ __forceinline__ bool group_outcome(unsigned long long* line, unsigned
 
 // Workgroup b's record and part.  Records whose size is stated come one after the other, so that the chip works on one
 // window of the payload; the parts turn with the record (see order_position).  Where it is not, most parts may have nothing to
-// do, so part 0 of every record comes first and the others after it (part_major): what a short record does not need is then
+// do, so part 0 of every record comes first and the others after it (PART_MAJOR): what a short record does not need is then
 // launched when the payload of all is on its way (1280 records of unknown size in two parts, 4 / 32 / 64 KiB, us a pass: record
 // by record 11.8 / 31.9 / 55.1, this way 8.7 / 31.0 / 54.9, one part 8.7 / 30.2 / 54.7).
 struct GroupPlace {
   uint32_t k, part, in, base;   // record, part, and the record's place in its group, which begins at `base`
   bool first;                   // the first workgroup of the group that is launched
 };
+template <bool PART_MAJOR>
 __device__ __forceinline__ GroupPlace group_place(const ClaimArgs& g) {
   GroupPlace p;
-  if (g.part_major) {
-    p.k = blockIdx.x % g.n_descs;
-    p.part = blockIdx.x / g.n_descs;
-  } else {
-    p.k = blockIdx.x / g.parts;
-    p.part = (blockIdx.x + p.k) % g.parts;
-  }
+  p.k = PART_MAJOR ? blockIdx.x % g.n_descs : blockIdx.x / g.parts;
+  p.part = PART_MAJOR ? blockIdx.x / g.n_descs : (blockIdx.x + p.k) % g.parts;
   p.in = p.k % kGroup;
   p.base = p.k - p.in;
-  p.first = blockIdx.x == (g.part_major ? p.base : p.base * g.parts);
+  p.first = blockIdx.x == (PART_MAJOR ? p.base : p.base * g.parts);
   return p;
 }
 
-template <int NT, int U, class Op>
+template <int NT, int U, class Op, bool PART_MAJOR>
 __global__ void __launch_bounds__(NT) UCCL_FULL_OCCUPANCY chunk_group_kernel(const Args g) {
   constexpr uint32_t kUnit = 64u * U;
   constexpr uint32_t kWaves = NT / 64;
@@ -750,7 +745,7 @@ __global__ void __launch_bounds__(NT) UCCL_FULL_OCCUPANCY chunk_group_kernel(con
   __shared__ uint32_t s_win;
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const GroupPlace place = group_place(g);   // the launch has n_descs * parts workgroups
+  const GroupPlace place = group_place<PART_MAJOR>(g);   // the launch has n_descs * parts workgroups
   const uint32_t k = place.k, part = place.part, in = place.in, base = place.base;
   const bool decides = UCCL_GROUP_LEADS && wave == 0u && place.first;
   unsigned long long* const line = g.claims + static_cast<size_t>(base / kGroup) * UCCL_CLAIM_STRIDE;
@@ -1137,7 +1132,7 @@ __global__ void __launch_bounds__(NT) chunk_gather_parts_kernel(const GatherArgs
 
 // Hundreds of records: decided 64 at a time, as in chunk_group_kernel; every wavefront folds its first unit meanwhile.  One
 // vector a lane and all of up to eight sources in flight (two vectors, four sources: 600 x 8 KiB from seven 13.9 / 16.0 us).
-template <class Op>
+template <class Op, bool PART_MAJOR>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_num_sgpr(80))) gather_group_kernel(const GatherArgs g) {
   constexpr int U = 1, kBatch = 8;
   constexpr uint32_t kUnit = 64u * U;
@@ -1146,7 +1141,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_num_sgpr(80))) gath
   __shared__ uint32_t s_win;
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const GroupPlace place = group_place(g);   // the launch has n_descs * parts workgroups
+  const GroupPlace place = group_place<PART_MAJOR>(g);   // the launch has n_descs * parts workgroups
   const uint32_t k = place.k, part = place.part, in = place.in, base = place.base;
   const bool decides = UCCL_GROUP_LEADS && wave == 0u && place.first;
   unsigned long long* const line = g.claims + static_cast<size_t>(base / kGroup) * UCCL_CLAIM_STRIDE;

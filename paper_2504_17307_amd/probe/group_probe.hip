@@ -13,8 +13,8 @@
 namespace {
 template <class GroupArgs, class Desc>
 bool probe_args(GroupArgs& a, void* acc, void* out, const void* recv, const void* descs, uint32_t n, uint32_t* bitmap, uint64_t n_bits, uint32_t* rejected,
-                uint32_t parts, uint32_t part_major, uint64_t* words, uint64_t tag) {
-  if (!acc || !recv || !descs || !bitmap || !words || n == 0 || n > (1u << 20) || parts == 0 || parts > 64 || part_major > 1 || tag == 0) return false;
+                uint32_t parts, uint64_t* words, uint64_t tag) {
+  if (!acc || !recv || !descs || !bitmap || !words || n == 0 || n > (1u << 20) || parts == 0 || parts > 64 || tag == 0) return false;
   a = {};
   a.acc = static_cast<char*>(acc);
   a.out = static_cast<char*>(out);
@@ -28,7 +28,6 @@ bool probe_args(GroupArgs& a, void* acc, void* out, const void* recv, const void
   a.use(reinterpret_cast<unsigned long long*>(words), words + static_cast<size_t>((n - 1) / kGroup + 1) * UCCL_CLAIM_STRIDE);
   a.tag = tag;
   a.parts = parts;
-  a.part_major = part_major;
   return true;
 }
 int launched() { return hipGetLastError() == hipSuccess ? 0 : -1; }
@@ -41,10 +40,12 @@ extern "C" int UCCL_PROBE(uccl_probe_group_apply)(void* acc, void* out, const vo
                                                   uint32_t* rejected, uint32_t parts, uint32_t part_major, uint32_t unroll, uint64_t* words, uint64_t tag,
                                                   void* stream) {
   Args a;
-  if ((unroll != 1u && unroll != 4u) ||
-      !probe_args<Args, uccl_chunk_desc>(a, acc, out, recv, descs, n, bitmap, n_bits, rejected, parts, part_major, words, tag))
+  if ((unroll != 1u && unroll != 4u) || part_major > 1u ||
+      !probe_args<Args, uccl_chunk_desc>(a, acc, out, recv, descs, n, bitmap, n_bits, rejected, parts, words, tag))
     return -1;
-  const auto kernel = unroll == 1u ? chunk_group_kernel<256, 1, OpF32<kSum>> : chunk_group_kernel<256, 4, OpF32<kSum>>;
+  using Sum = OpF32<kSum>;
+  const auto kernel = unroll == 1u ? (part_major ? chunk_group_kernel<256, 1, Sum, true> : chunk_group_kernel<256, 1, Sum, false>)
+                                   : (part_major ? chunk_group_kernel<256, 4, Sum, true> : chunk_group_kernel<256, 4, Sum, false>);
   kernel<<<dim3(n * parts), dim3(256), 0, static_cast<hipStream_t>(stream)>>>(a);
   return launched();
 }
@@ -53,8 +54,9 @@ extern "C" int UCCL_PROBE(uccl_probe_group_apply)(void* acc, void* out, const vo
 extern "C" int UCCL_PROBE(uccl_probe_group_fold)(void* acc, void* out, const void* recv, const void* descs, uint32_t n, uint32_t* bitmap, uint64_t n_bits,
                                                  uint32_t* rejected, uint32_t parts, uint32_t part_major, uint64_t* words, uint64_t tag, void* stream) {
   GatherArgs a;
-  if (!probe_args<GatherArgs, uccl_gather_desc>(a, acc, out, recv, descs, n, bitmap, n_bits, rejected, parts, part_major, words, tag)) return -1;
-  gather_group_kernel<OpF32<kSum>><<<dim3(n * parts), dim3(256), 0, static_cast<hipStream_t>(stream)>>>(a);
+  if (part_major > 1u || !probe_args<GatherArgs, uccl_gather_desc>(a, acc, out, recv, descs, n, bitmap, n_bits, rejected, parts, words, tag)) return -1;
+  const auto kernel = part_major ? gather_group_kernel<OpF32<kSum>, true> : gather_group_kernel<OpF32<kSum>, false>;
+  kernel<<<dim3(n * parts), dim3(256), 0, static_cast<hipStream_t>(stream)>>>(a);
   return launched();
 }
 
