@@ -455,6 +455,8 @@ Plan plan_apply(uint32_t n_descs, const Tuning& tune, bool reads_acc) {
 //     57.0, four 46.8); 1280 x 4 KiB 13.4 / 8.4 / 8.6
 //   two: 2000 x 4, 16, 64 KiB 16.3 / 10.7 / 10.4, 26.0 / 25.5 / 26.4, 105 / 103 / 103; 2000 of 4 - 256 KiB 118 / 138 / 121 (three parts 116, but 12.0 for the 4 KiB
 //     ones); 3000 x 4 KiB 22.6 / 14.0 / 14.8, of 64 B - 1 MiB 359 / 375 / 335
+// Where they lose to the forms before: a call of duplicates only, whose payload is read for nothing (2900 x 4 KiB 7.2 / 8.4); sequence numbers of which no two share a bitmap word (2900 x 4 KiB 13.2 / 13.8); few records much shorter than stated
+// (192 x 2 KiB stated as 8 KiB 5.3 / 5.8, as 200 KiB 6.2 / 7.0).
 constexpr uint32_t kGroupThreads = 256;
 struct GroupPlan {
   uint32_t unroll, parts;   // vectors a lane and trip (0 = not this form), workgroups a record
@@ -493,6 +495,9 @@ GroupPlan plan_group(uint32_t n_descs, const Tuning& tune) {
 //       49 / 26, 128 x 160 KiB 47 / 38, 21 / 19.  All workgroups of 64 records read one line for their outcome, and what a record has
 //       no use for costs 0.4 - 0.7 ns each (1 x 4 KiB stated as 48 MiB in 6144 workgroups 7.9, in 4096 6.4, in the form before 6.3 - 6.8), so they are
 //       4096 at most; 1 x 48 MiB then takes 84 (36) us, in 6144 83 (38), in 2048 86 (41).
+//   types (f32 and bf16 SUM, f16 MAX, bf16 MIN): selections of 16-bit elements need 75 - 77 vector registers, six wavefronts a
+//       SIMD instead of eight, and gain alike: 530 x 32 KiB 1.06 1.14 1.27 (f16 MAX; f32 1.09 1.12 1.23), 850 0.96 1.06 1.21 (1.05 1.09 1.15), 300 x 128 KiB 1.08 1.17
+//       1.33 (1.06 1.16 1.28); the least are one source of bf16 in 2900 x 8 KiB and 1240 x 16 KiB, 0.97
 // A duplicate costs its first trip's payload reads: folds that are issued again whole 300 x 128 KiB from seven sources 6.2 / 27, 2900 x 4 KiB 7.9 / 20, from
 // one 7.3 / 10.6; a look at the bitmap before the payload would make these 12, 8.6, 8.2 and every other call 0.4 - 0.5 us longer.
 // With the size unknown, all records' first parts come first (group_place), each of 4 KiB a trip, and their number is what a call needs in which some

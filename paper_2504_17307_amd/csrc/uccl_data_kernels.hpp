@@ -646,8 +646,8 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
 // once, but records are decided kGroup at a time (decide_wave), by the first wavefront of the group's first
 // workgroup; the others poll for the outcome, which comes at about the time their payload does.  What is left is the
 // chain record, LDS, atomic OR, outcome, payload store.  Measured, us a pass of reset, SUM with forward and COPY with
-// forward, before / now: 949 x 5.7 KB of unknown size 25.4 / 13.2; 4 KiB chunks 320 records 12.6 / 11.8,
-// 1280 18.8 / 16.1, 2560 28.7 / 25.8; 640 x 8 KiB 18.1 / 15.2; 640 x 16 KiB 26.2 / 20.9; 320 x 128 KiB 64.8 / 56.2.
+// forward, before / now: 949 x 5.7 KB of unknown size 25.3 / 14.2; 4 KiB chunks 320 records 12.6 / 10.8,
+// 1280 19.4 / 15.7, 2560 28.2 / 25.8; 640 x 8 KiB 18.1 / 15.2; 640 x 16 KiB 26.2 / 20.9; 320 x 128 KiB 64.8 / 56.2.
 //
 // A group's line of scratch words holds a claim word and its outcome, a bit per record in four words, all as
 // `tag << 16 | value`.  A wavefront that has polled kGroupPolls times exchanges the claim word as well and decides if the
