@@ -36,11 +36,11 @@ METRIC = "reduced payload GB/s (dedup+place+reduce+forward of one rank's chunk s
 # kernel source it was measured on, identified by the hash of the HIP source files.
 MEASURED_TRAFFIC = {
     # (workload, source_hash() of the files under csrc/): bytes per launch
-    ("config1", "ba5be6cd6a9bb4c9"): 14890512,
-    ("config2", "ba5be6cd6a9bb4c9"): 1008563310,
-    ("config3", "ba5be6cd6a9bb4c9"): 3626310490,
-    ("config4", "ba5be6cd6a9bb4c9"): 108168288,
-    ("direct-rs", "ba5be6cd6a9bb4c9"): 1208711420,
+    ("config1", "dc08f2adc9ae2e6d"): 14895584,
+    ("config2", "dc08f2adc9ae2e6d"): 1008442322,
+    ("config3", "dc08f2adc9ae2e6d"): 3626220358,
+    ("config4", "dc08f2adc9ae2e6d"): 108170480,
+    ("direct-rs", "dc08f2adc9ae2e6d"): 1208729112,
 }
 
 WORKLOADS = {
