@@ -36,11 +36,11 @@ METRIC = "reduced payload GB/s (dedup+place+reduce+forward of one rank's chunk s
 # kernel source it was measured on, identified by the hash of the HIP source files.
 MEASURED_TRAFFIC = {
     # (workload, source_hash() of the files under csrc/): bytes per launch
-    ("config1", "dc08f2adc9ae2e6d"): 14895584,
-    ("config2", "dc08f2adc9ae2e6d"): 1008442322,
-    ("config3", "dc08f2adc9ae2e6d"): 3626220358,
-    ("config4", "dc08f2adc9ae2e6d"): 108170480,
-    ("direct-rs", "dc08f2adc9ae2e6d"): 1208729112,
+    ("config1", "7993dd2079021ab8"): 14883648,
+    ("config2", "7993dd2079021ab8"): 1008443070,
+    ("config3", "7993dd2079021ab8"): 3626221412,
+    ("config4", "7993dd2079021ab8"): 108167032,
+    ("direct-rs", "7993dd2079021ab8"): 1208730106,
 }
 
 WORKLOADS = {

@@ -482,9 +482,11 @@ GroupPlan plan_group(uint32_t n_descs, const Tuning& tune) {
 }
 
 // The same for folds (gather_group_kernel); workgroups per record, 0 = not this form.  How many sources a record has, the
-// host does not know: the lines lie where one source loses nothing to speak of.  The forms before come in rounds of one
-// workgroup of 1024 a compute unit (these take 66 registers and more), so what this one gains depends on how full
-// the last of those is.  Measured (fold with reset over three sets of buffers, sources 1, 2 or 3, 7, us or ratio, before / now):
+// host does not know: the lines lie where one source loses nothing to speak of.  The forms before come in rounds of 256 workgroups of
+// 1024, one a compute unit (they take 66 registers and more), and a round costs the same however full it is, so what this form gains depends on how
+// full the last of those is.  Above 32 KiB a workgroup of theirs takes a record: taken where their first round is to 160 / 256 full, or their second to 104 / 256
+// (360 records).  4 - 8 KiB, tiles of four: not where one round is 160 / 256 full and more.
+// Measured (fold with reset over three sets of buffers, sources 1, 2 or 3, 7, us or ratio, before / now):
 //   small chunks, from where they are no longer cut into parts: 300 x 4, 8 KiB 1.03 1.02 1.57, 1.04 1.11 1.44; 1500 1.09 1.13 1.09, 1.22 1.17 1.15; 2800 1.05 1.04 1.10,
 //       1.13 1.16 1.14.  Two workgroups a chunk of 8 KiB while the chip holds them all (600 8.2 9.3 12.9 us, one 9.2 10.2 13.2; 1200 13.6 16.2 22.3, one
 //       11.6 14.4 20.5).  Not 640 - 1024 in chunks above 4 KiB, one tile of four each compute unit: 760 and 830 x 6 KB 0.97 0.97 0.94, 0.90 0.92 0.97
