@@ -248,11 +248,11 @@ struct Tuning {
   bool one_launch = false;  // the call may be offered again after an error: all of it is enqueued, or nothing
 };
 
-template <int T, int U, class Op>
+template <int T, int U, class Op, Through H = kNoThrough>
 int launch_flat(const Args& a, hipStream_t s) {
   uint32_t tiles = tiles_for(a.n_descs, T);
   if (UCCL_XCD_CONTIGUOUS) tiles = (tiles + 7u) / 8u * 8u;   // whole eighths; tiles past the records find none
-  return launch_kernel(chunk_flat_kernel<UCCL_FLAT_THREADS, T, U, Op>, tiles, UCCL_FLAT_THREADS, s, a);
+  return launch_kernel(chunk_flat_kernel<UCCL_FLAT_THREADS, T, U, Op, H>, tiles, UCCL_FLAT_THREADS, s, a);
 }
 
 // Records per workgroup: enough that a tile holds about 32 KiB of payload per stream when the
@@ -527,6 +527,25 @@ uint32_t group_gather_parts(uint32_t n_descs, const Tuning& tune) {
   return parts < most ? parts : most;
 }
 
+// Which stores a call's kernel writes through (see Through).  Lines: chunks of whole lines of 128 bytes.  Two chunks share a line where
+// they are no such multiple, or their segment does not begin on one, which the host cannot see; what is shared costs more than writing through
+// gives once the call has left the last-level cache.  Calls cut into parts (16 MiB at most) write through always.  Measured, us a pass, as
+// the masks say / through; "odd": segments that begin off a line:
+//   tiles and single records (chunk_flat_kernel), the combined accumulator as before: 128 messages in 4 KiB chunks 56.5 / 55.7, 60 MiB in 4 KiB 74.0 / 73.1, odd
+//     75.3 / 75.0, 80 MiB in 32 KiB 50.3 / 49.6; not the copies of a record a workgroup (all-to-all of 32 MiB in 64 KiB 38.9 / 39.5)
+//   a workgroup a record: all-to-all in 16 KiB chunks 23.9 / 23.1, 38 MiB in 32 KiB odd 52.0 / 48.5, 60 MiB odd 71.0 / 76.8; 33 008 bytes 52.9 / 55.3;
+//     all-to-all of 9 008 19.2 / 20.7
+//   decided 64 at a time: 8 x 1 MiB messages in 4 KiB chunks 27.9 / 24.9, 6 000 bytes 12 MiB 21.5 / 20.9, 30 000 bytes 22 MiB 34.3 / 35.4.  Of unknown
+//     size 3.6 MB 13.3 / 12.1 and 33 MB 35.5 / 34.6, but 60 MB in 98 256-byte chunks 41.1 / 44.3: not taken.
+//   in destination order, by record: 256 MiB bf16 262 / 256, 1 GiB 554 / 549, 100 MiB in 64 KiB 104 / 101, odd 256 MiB 260 / 260
+bool in_lines(const Tuning& tune) { return tune.chunk_bytes != 0u && tune.chunk_bytes % 128u == 0u; }
+bool few_through(const Args& a, const Tuning& tune) {   // a workgroup a record; one written stream (no staging) at any size
+  return in_lines(tune) && (a.out == nullptr || static_cast<uint64_t>(a.n_descs) * tune.chunk_bytes <= (40ull << 20));
+}
+bool group_through(const Args& a, const Tuning& tune) {
+  return tune.chunk_bytes != 0u && (in_lines(tune) || static_cast<uint64_t>(a.n_descs) * tune.chunk_bytes <= (16ull << 20));
+}
+
 // `region`: the stream's scratch words; called with its launch lock held.  HIP has no reason of its
 // own to refuse a later launch of a call after it took the first: all are in one code object, their
 // grids stay within 16383 * 32 workgroups of 256 threads, and a stop event that it does not take is refused with the first
@@ -566,7 +585,7 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
       std::lock_guard<std::mutex> in_order(*region.launch_lock);
       // held back only where the records are known to be large: empty parts want as many workgroups as there can be
       const uint32_t lds = Op::kReadsAcc && tune.chunk_bytes != 0u ? kOrderReduceLds : 0u;
-      return launch_ordered<Args>(chunk_order_kernel<Op::kEs>, chunk_ordered_kernel<Op>, lds, a, s, ordered, region.words);
+      return launch_ordered<Args>(chunk_order_kernel<Op::kEs>, in_lines(tune) ? chunk_ordered_kernel<Op, kAllThrough> : chunk_ordered_kernel<Op, kNoThrough>, lds, a, s, ordered, region.words);
     }
   }
   const GroupPlan grouped = a.n_ptr == nullptr && !tune.one_launch ? plan_group(a.n_descs, tune) : kNotGrouped;   // a feed's slots are pinned
@@ -577,9 +596,11 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
       a.use(region.words, region.faults);
       a.parts = grouped.parts;
       a.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
-      const auto kernel = tune.chunk_bytes == 0u ? chunk_group_kernel<kGroupThreads, 4, Op, true>
-                          : grouped.unroll == 4u ? chunk_group_kernel<kGroupThreads, 4, Op, false>
-                          : grouped.unroll == 2u ? chunk_group_kernel<kGroupThreads, 2, Op, false> : chunk_group_kernel<kGroupThreads, 1, Op, false>;
+      const bool through = group_through(a, tune);
+      const auto kernel = tune.chunk_bytes == 0u ? chunk_group_kernel<kGroupThreads, 4, Op, true, kNoThrough>
+                          : grouped.unroll == 4u ? (through ? chunk_group_kernel<kGroupThreads, 4, Op, false, kAllThrough> : chunk_group_kernel<kGroupThreads, 4, Op, false, kNoThrough>)
+                          : grouped.unroll == 2u ? (through ? chunk_group_kernel<kGroupThreads, 2, Op, false, kAllThrough> : chunk_group_kernel<kGroupThreads, 2, Op, false, kNoThrough>)
+                                                 : chunk_group_kernel<kGroupThreads, 1, Op, false, kAllThrough>;   // 12 MB at most
       return launch_kernel(kernel, a.n_descs * a.parts, kGroupThreads, s, a);
     }
   }
@@ -588,8 +609,8 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
     a.parts = p.parts;
     const auto launch_parts = [&](unsigned long long tag) {
       a.tag = tag;
-      return launch_kernel(tune.static_claims != nullptr ? chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, true, true>
-                                                         : chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, true, false>,
+      return launch_kernel(tune.static_claims != nullptr ? chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, kAllThrough, true, true>
+                                                         : chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, kAllThrough, true, false>,
                            a.n_descs * p.parts, UCCL_PART_THREADS, s, a);
     };
     if (tune.static_claims != nullptr) {
@@ -624,19 +645,29 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
     p.route = a.n_descs < kFewRecords ? kRouteFew : kRouteOne;   // no claim words to be had: uncut
   }
   switch (p.route) {
-    case kRouteHalf: return launch_kernel(chunk_few_kernel<1024, 1, Op, false>, a.n_descs, 1024, s, a);
-    case kRouteSmall1: return launch_kernel(chunk_few_kernel<256, 1, Op, false>, a.n_descs, 256, s, a);
-    case kRouteSmall2: return launch_kernel(chunk_few_kernel<256, 2, Op, false>, a.n_descs, 256, s, a);
+    case kRouteHalf:
+      return launch_kernel(few_through(a, tune) ? chunk_few_kernel<1024, 1, Op, kAllThrough, false> : chunk_few_kernel<1024, 1, Op, kNoThrough, false>, a.n_descs, 1024, s, a);
+    case kRouteSmall1: return launch_kernel(chunk_few_kernel<256, 1, Op, kNoThrough, false>, a.n_descs, 256, s, a);   // next to nothing to write back
+    case kRouteSmall2: return launch_kernel(chunk_few_kernel<256, 2, Op, kNoThrough, false>, a.n_descs, 256, s, a);
     case kRouteFew:
-      return launch_kernel(chunk_few_kernel<UCCL_FEW_THREADS, UCCL_FEW_UNROLL, Op, false>, a.n_descs,
-                           UCCL_FEW_THREADS, s, a);
+      return launch_kernel(few_through(a, tune) ? chunk_few_kernel<UCCL_FEW_THREADS, UCCL_FEW_UNROLL, Op, kAllThrough, false>
+                                                : chunk_few_kernel<UCCL_FEW_THREADS, UCCL_FEW_UNROLL, Op, kNoThrough, false>,
+                           a.n_descs, UCCL_FEW_THREADS, s, a);
     case kRouteTile:
       if (p.tile >= 32) return launch_flat<32, UCCL_FLAT_UNROLL, Op>(a, s);
       if (p.tile >= 16) return launch_flat<16, UCCL_FLAT_UNROLL, Op>(a, s);
+      if (in_lines(tune)) {
+        if (p.tile >= 8) return launch_flat<8, UCCL_FLAT_UNROLL, Op, kAllButCombined>(a, s);
+        if (p.tile >= 4) return launch_flat<4, UCCL_FLAT_UNROLL, Op, kAllButCombined>(a, s);
+        return launch_flat<2, UCCL_FLAT_UNROLL, Op, kAllButCombined>(a, s);
+      }
       if (p.tile >= 8) return launch_flat<8, UCCL_FLAT_UNROLL, Op>(a, s);
       if (p.tile >= 4) return launch_flat<4, UCCL_FLAT_UNROLL, Op>(a, s);
       return launch_flat<2, UCCL_FLAT_UNROLL, Op>(a, s);
-    default: return launch_flat<1, Op::kReadsAcc ? UCCL_FLAT1_REDUCE_UNROLL : UCCL_FLAT_UNROLL, Op>(a, s);
+    default: {
+      constexpr int kUnroll = Op::kReadsAcc ? UCCL_FLAT1_REDUCE_UNROLL : UCCL_FLAT_UNROLL;
+      return Op::kReadsAcc && in_lines(tune) ? launch_flat<1, kUnroll, Op, kAllButCombined>(a, s) : launch_flat<1, kUnroll, Op>(a, s);
+    }
   }
 }
 

@@ -270,12 +270,12 @@ __device__ __forceinline__ void dedup_tile(const Args& g, Tile<T>& s, uint32_t t
 }
 
 // One unit = 64*U consecutive 16-byte vectors of a chunk, streamed by one wavefront.
-template <int U, class Op, bool FWD, bool WB>
+template <int U, class Op, bool FWD, bool WB, Through T>
 __device__ __forceinline__ void stream_unit(const char* r, char* a, char* o, uint32_t len,
                                             uint32_t trip, uint32_t lane) {
   constexpr uint32_t kPolicy = cache_policy<Op, FWD, WB>();
-  constexpr bool kNtRecv = (kPolicy & 8u) != 0, kNtOut = (kPolicy & 4u) != 0;
-  constexpr bool kNtAccLoad = (kPolicy & 2u) != 0, kNtAccStore = (kPolicy & 1u) != 0;
+  constexpr bool kNtRecv = (kPolicy & 8u) != 0, kNtAccLoad = (kPolicy & 2u) != 0;
+  constexpr uint32_t kAccStore = acc_store<Op, FWD, WB, T>(), kOutStore = out_store<Op, FWD, WB, T>();
   constexpr uint32_t kUnit = 64u * U;
   const uint32_t nvec = len >> 4;
   const uint32_t v0 = trip * kUnit;
@@ -294,8 +294,8 @@ __device__ __forceinline__ void stream_unit(const char* r, char* a, char* o, uin
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const u32x4 t = combine<Op>(av[u], rv[u]);
-      if (WB) store16<kNtAccStore>(ap + u * 64, t);
-      if (FWD) store16<kNtOut>(op + u * 64, t);
+      if (WB) store16<kAccStore>(ap + u * 64, t);
+      if (FWD) store16<kOutStore>(op + u * 64, t);
     }
     return;
   }
@@ -307,8 +307,8 @@ __device__ __forceinline__ void stream_unit(const char* r, char* a, char* o, uin
       u32x4 av = rv;
       if constexpr (Op::kReadsAcc) av = load16<kNtAccLoad>(ap + u * 64);
       const u32x4 t = combine<Op>(av, rv);
-      if (WB) store16<kNtAccStore>(ap + u * 64, t);
-      if (FWD) store16<kNtOut>(op + u * 64, t);
+      if (WB) store16<kAccStore>(ap + u * 64, t);
+      if (FWD) store16<kOutStore>(op + u * 64, t);
     }
   }
   const uint32_t rem = len & 15u;
@@ -318,10 +318,25 @@ __device__ __forceinline__ void stream_unit(const char* r, char* a, char* o, uin
   }
 }
 
+// One unit of a chunk by what its record says of forwarding.
+template <int U, class Op, Through T>
+__device__ __forceinline__ void chunk_unit(const Args& g, uint64_t src, uint64_t dst, uint64_t out, uint32_t len, uint32_t trip, uint32_t lane) {
+  const char* const r = g.recv + src;
+  char* const a = g.acc + dst;
+  if (out == UCCL_NO_FORWARD) stream_unit<U, Op, false, true, T>(r, a, nullptr, len, trip, lane);
+  else if (out & UCCL_FORWARD_ONLY) stream_unit<U, Op, true, false, T>(r, a, g.out + (out & ~UCCL_FORWARD_ONLY), len, trip, lane);
+  else stream_unit<U, Op, true, true, T>(r, a, g.out + out, len, trip, lane);
+}
+
+// Whether the record's written streams begin on lines (the accumulator's place counts also where it is not kept).
+__device__ __forceinline__ bool record_on_lines(const Args& g, uint64_t dst, uint64_t out) {
+  return on_lines(g.acc + dst, out == UCCL_NO_FORWARD ? nullptr : g.out + (out & ~UCCL_FORWARD_ONLY));
+}
+
 // The winners' units are numbered consecutively across the tile and dealt round-robin to the
 // wavefronts of the workgroup, so the machine sees the same stream whether a tile holds one
 // 128 KiB chunk or thirty-two 4 KiB chunks.
-template <int NT, int T, int U, class Op>
+template <int NT, int T, int U, class Op, Through H>
 __global__ void __launch_bounds__(NT) chunk_flat_kernel(const Args g) {
   constexpr uint32_t kUnit = 64u * U;
   constexpr uint32_t kWaves = NT / 64;
@@ -354,12 +369,7 @@ __global__ void __launch_bounds__(NT) chunk_flat_kernel(const Args g) {
     const uint64_t dst = wave_uniform(s.dst[w]);
     const uint64_t out = wave_uniform(s.out[w]);
     const uint32_t len = __builtin_amdgcn_readfirstlane(s.len[w]);
-    if (out == UCCL_NO_FORWARD)
-      stream_unit<U, Op, false, true>(g.recv + src, g.acc + dst, nullptr, len, trip, lane);
-    else if (out & UCCL_FORWARD_ONLY)
-      stream_unit<U, Op, true, false>(g.recv + src, g.acc + dst, g.out + (out & ~UCCL_FORWARD_ONLY), len, trip, lane);
-    else
-      stream_unit<U, Op, true, true>(g.recv + src, g.acc + dst, g.out + out, len, trip, lane);
+    chunk_unit<U, Op, H>(g, src, dst, out, len, trip, lane);
   }
 }
 
@@ -497,31 +507,31 @@ __global__ void __launch_bounds__(kOrderThreads) chunk_order_kernel(const Args g
 }
 
 // Part `part` of record k: units part * 4 + wavefront, then every parts * 4 units (a record longer
-// than all its parts).
-template <class Op>
+// than all its parts).  H: as a record's stores are written if it begins on lines, which is looked at here: one branch a part.
+// (In the kernels of few and of hundreds of records such a branch costs more than it gives, 1.05 - 1.4 times: there the host chooses.)
+template <class Op, Through H>
 __device__ __forceinline__ void ordered_part(const Args& g, uint32_t k, uint32_t part) {
   constexpr uint32_t kUnit = 64u, kWaves = kOrderThreads / 64;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
   const uccl_chunk_desc d = g.descs[k];   // the same address in every lane
   const uint32_t vecs = (d.len >> 4) + ((d.len & 15u) != 0u ? 1u : 0u);
   const uint32_t total = (vecs + kUnit - 1u) / kUnit;
-  for (uint32_t u = part * kWaves + wave; u < total; u += g.parts * kWaves) {
-    if (d.out_off == UCCL_NO_FORWARD)
-      stream_unit<1, Op, false, true>(g.recv + d.src_off, g.acc + d.dst_off, nullptr, d.len, u, lane);
-    else if (d.out_off & UCCL_FORWARD_ONLY)
-      stream_unit<1, Op, true, false>(g.recv + d.src_off, g.acc + d.dst_off, g.out + (d.out_off & ~UCCL_FORWARD_ONLY), d.len, u, lane);
-    else
-      stream_unit<1, Op, true, true>(g.recv + d.src_off, g.acc + d.dst_off, g.out + d.out_off, d.len, u, lane);
+  if (H != kNoThrough && record_on_lines(g, d.dst_off, d.out_off)) {
+    for (uint32_t u = part * kWaves + wave; u < total; u += g.parts * kWaves)
+      chunk_unit<1, Op, H>(g, d.src_off, d.dst_off, d.out_off, d.len, u, lane);
+  } else {
+    for (uint32_t u = part * kWaves + wave; u < total; u += g.parts * kWaves)
+      chunk_unit<1, Op, kNoThrough>(g, d.src_off, d.dst_off, d.out_off, d.len, u, lane);
   }
 }
 
-template <class Op>
+template <class Op, Through H>
 __global__ void __launch_bounds__(kOrderThreads) chunk_ordered_kernel(const Args g, const OrderArgs t) {
   const uint32_t b = order_position(g.n_descs * g.parts), entry = b / g.parts, part = (b + entry) % g.parts;
   const unsigned long long first = t.words[2u * static_cast<size_t>(entry)];
   const unsigned long long second = t.words[2u * static_cast<size_t>(entry) + 1u];
-  if (order_has(t, first, part)) ordered_part<Op>(g, order_record(first), part);
-  if (order_has(t, second, part)) ordered_part<Op>(g, order_record(second), part);
+  if (order_has(t, first, part)) ordered_part<Op, H>(g, order_record(first), part);
+  if (order_has(t, second, part)) ordered_part<Op, H>(g, order_record(second), part);
 }
 
 // ---- calls of few records --------------------------------------------------------------------
@@ -536,22 +546,52 @@ __global__ void __launch_bounds__(kOrderThreads) chunk_ordered_kernel(const Args
 // which is why calls of many records, where duplicates are many and latency is hidden by the
 // number of workgroups anyway, use chunk_flat_kernel.  PARTS: blockIdx.x = record * parts + part
 // (see claim_enter).
-template <int U, class Op, bool FWD, bool WB>
+template <int U, class Op, bool FWD, bool WB, Through T>
 __device__ __forceinline__ void finish_unit(const u32x4 (&rv)[U], const u32x4 (&av)[U], u32x4* ap,
                                             u32x4* op, uint32_t first_vec, uint32_t nvec) {
-  constexpr uint32_t kPolicy = cache_policy<Op, FWD, WB>();
-  constexpr bool kNtOut = (kPolicy & 4u) != 0, kNtAccStore = (kPolicy & 1u) != 0;
+  constexpr uint32_t kAccStore = acc_store<Op, FWD, WB, T>(), kOutStore = out_store<Op, FWD, WB, T>();
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     if (first_vec + u * 64 < nvec) {
       const u32x4 t = combine<Op>(Op::kReadsAcc ? av[u] : rv[u], rv[u]);
-      if (WB) store16<kNtAccStore>(ap + u * 64, t);
-      if (FWD) store16<kNtOut>(op + u * 64, t);
+      if (WB) store16<kAccStore>(ap + u * 64, t);
+      if (FWD) store16<kOutStore>(op + u * 64, t);
     }
   }
 }
 
-template <int NT, int U, class Op, bool PARTS, bool APART = false>
+// The wavefront's share of a record that is a first arrival: its first unit (u0), which is in registers if it has one, then
+// every stride-th.
+template <int U, class Op, Through T>
+__device__ __forceinline__ void finish_record(const Args& g, const u32x4 (&rv)[U], const u32x4 (&av)[U], uint64_t src, uint64_t dst, uint64_t out,
+                                              uint32_t len, bool have, uint32_t u0, uint32_t total, uint32_t stride, uint32_t lane) {
+  constexpr uint32_t kUnit = 64u * U;
+  const uint32_t nvec = len >> 4, first_vec = u0 * kUnit + lane;
+  const bool fwd = out != UCCL_NO_FORWARD;
+  const bool relay = fwd && (out & UCCL_FORWARD_ONLY) != 0;
+  char* const o = g.out + (out & ~UCCL_FORWARD_ONLY);
+  if (have) {
+    u32x4* ap = reinterpret_cast<u32x4*>(g.acc + dst) + first_vec;
+    u32x4* op = reinterpret_cast<u32x4*>(o) + first_vec;
+    if (!fwd) finish_unit<U, Op, false, true, T>(rv, av, ap, op, first_vec, nvec);
+    else if (relay) finish_unit<U, Op, true, false, T>(rv, av, ap, op, first_vec, nvec);
+    else finish_unit<U, Op, true, true, T>(rv, av, ap, op, first_vec, nvec);
+    const uint32_t rem = len & 15u;
+    if (rem != 0u && nvec >= u0 * kUnit && nvec < (u0 + 1u) * kUnit) {  // the unit that holds the partial vector
+      const uint64_t off = static_cast<uint64_t>(nvec) << 4;
+      if (!fwd) stream_tail<Op, false, true>(g.recv + src + off, g.acc + dst + off, nullptr, rem, lane);
+      else if (relay) stream_tail<Op, true, false>(g.recv + src + off, g.acc + dst + off, o + off, rem, lane);
+      else stream_tail<Op, true, true>(g.recv + src + off, g.acc + dst + off, o + off, rem, lane);
+    }
+  }
+  for (uint32_t u = u0 + stride; u < total; u += stride) {
+    if (!fwd) stream_unit<U, Op, false, true, T>(g.recv + src, g.acc + dst, nullptr, len, u, lane);
+    else if (relay) stream_unit<U, Op, true, false, T>(g.recv + src, g.acc + dst, o, len, u, lane);
+    else stream_unit<U, Op, true, true, T>(g.recv + src, g.acc + dst, o, len, u, lane);
+  }
+}
+
+template <int NT, int U, class Op, Through H, bool PARTS, bool APART = false>
 __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
   constexpr uint32_t kUnit = 64u * U;
   constexpr uint32_t kWaves = NT / 64;
@@ -583,7 +623,7 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
   const bool have = ok && u0 < total;
   const bool part_has_units = ok && part * kWaves < total;  // uniform over the workgroup
   const u32x4* rp = reinterpret_cast<const u32x4*>(g.recv + src) + first_vec;
-  u32x4* ap = reinterpret_cast<u32x4*>(g.acc + dst) + first_vec;
+  const u32x4* ap = reinterpret_cast<const u32x4*>(g.acc + dst) + first_vec;
   u32x4 rv[U], av[U];
   if (have) {  // in bounds whether or not this record turns out to be the first arrival
 #pragma unroll
@@ -614,27 +654,7 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
   }
   __syncthreads();
   if (s_win != 0u) {
-    const bool fwd = out != UCCL_NO_FORWARD;
-    const bool relay = fwd && (out & UCCL_FORWARD_ONLY) != 0;
-    char* o = g.out + (out & ~UCCL_FORWARD_ONLY);
-    if (have) {
-      u32x4* op = reinterpret_cast<u32x4*>(o) + first_vec;
-      if (!fwd) finish_unit<U, Op, false, true>(rv, av, ap, op, first_vec, nvec);
-      else if (relay) finish_unit<U, Op, true, false>(rv, av, ap, op, first_vec, nvec);
-      else finish_unit<U, Op, true, true>(rv, av, ap, op, first_vec, nvec);
-      const uint32_t rem = len & 15u;
-      if (rem != 0u && nvec >= u0 * kUnit && nvec < (u0 + 1u) * kUnit) {  // the unit that holds the partial vector
-        const uint64_t off = static_cast<uint64_t>(nvec) << 4;
-        if (!fwd) stream_tail<Op, false, true>(g.recv + src + off, g.acc + dst + off, nullptr, rem, lane);
-        else if (relay) stream_tail<Op, true, false>(g.recv + src + off, g.acc + dst + off, o + off, rem, lane);
-        else stream_tail<Op, true, true>(g.recv + src + off, g.acc + dst + off, o + off, rem, lane);
-      }
-    }
-    for (uint32_t u = u0 + stride; u < total; u += stride) {
-      if (!fwd) stream_unit<U, Op, false, true>(g.recv + src, g.acc + dst, nullptr, len, u, lane);
-      else if (relay) stream_unit<U, Op, true, false>(g.recv + src, g.acc + dst, o, len, u, lane);
-      else stream_unit<U, Op, true, true>(g.recv + src, g.acc + dst, o, len, u, lane);
-    }
+    finish_record<U, Op, H>(g, rv, av, src, dst, out, len, have, u0, total, stride, lane);
   }
 }
 
@@ -737,7 +757,7 @@ __device__ __forceinline__ GroupPlace group_place(const ClaimArgs& g) {
   return p;
 }
 
-template <int NT, int U, class Op, bool PART_MAJOR>
+template <int NT, int U, class Op, bool PART_MAJOR, Through H = kAllThrough>
 __global__ void __launch_bounds__(NT) UCCL_FULL_OCCUPANCY chunk_group_kernel(const Args g) {
   constexpr uint32_t kUnit = 64u * U;
   constexpr uint32_t kWaves = NT / 64;
@@ -773,7 +793,7 @@ __global__ void __launch_bounds__(NT) UCCL_FULL_OCCUPANCY chunk_group_kernel(con
   const bool have = ok && u0 < total;
   const bool part_has_units = ok && part * kWaves < total;  // uniform over the workgroup
   const u32x4* rp = reinterpret_cast<const u32x4*>(g.recv + src) + first_vec;
-  u32x4* ap = reinterpret_cast<u32x4*>(g.acc + dst) + first_vec;
+  const u32x4* ap = reinterpret_cast<const u32x4*>(g.acc + dst) + first_vec;
   u32x4 rv[U], av[U];
   const auto load = [&] {   // in bounds whether or not this record turns out to be the first arrival
 #pragma unroll
@@ -807,27 +827,7 @@ __global__ void __launch_bounds__(NT) UCCL_FULL_OCCUPANCY chunk_group_kernel(con
   if (!part_has_units) return;   // the whole workgroup
   __syncthreads();
   if (s_win == 0u) return;
-  const bool fwd = out != UCCL_NO_FORWARD;
-  const bool relay = fwd && (out & UCCL_FORWARD_ONLY) != 0;
-  char* o = g.out + (out & ~UCCL_FORWARD_ONLY);
-  if (have) {
-    u32x4* op = reinterpret_cast<u32x4*>(o) + first_vec;
-    if (!fwd) finish_unit<U, Op, false, true>(rv, av, ap, op, first_vec, nvec);
-    else if (relay) finish_unit<U, Op, true, false>(rv, av, ap, op, first_vec, nvec);
-    else finish_unit<U, Op, true, true>(rv, av, ap, op, first_vec, nvec);
-    const uint32_t rem = len & 15u;
-    if (rem != 0u && nvec >= u0 * kUnit && nvec < (u0 + 1u) * kUnit) {  // the unit that holds the partial vector
-      const uint64_t off = static_cast<uint64_t>(nvec) << 4;
-      if (!fwd) stream_tail<Op, false, true>(g.recv + src + off, g.acc + dst + off, nullptr, rem, lane);
-      else if (relay) stream_tail<Op, true, false>(g.recv + src + off, g.acc + dst + off, o + off, rem, lane);
-      else stream_tail<Op, true, true>(g.recv + src + off, g.acc + dst + off, o + off, rem, lane);
-    }
-  }
-  for (uint32_t u = u0 + stride; u < total; u += stride) {
-    if (!fwd) stream_unit<U, Op, false, true>(g.recv + src, g.acc + dst, nullptr, len, u, lane);
-    else if (relay) stream_unit<U, Op, true, false>(g.recv + src, g.acc + dst, o, len, u, lane);
-    else stream_unit<U, Op, true, true>(g.recv + src, g.acc + dst, o, len, u, lane);
-  }
+  finish_record<U, Op, H>(g, rv, av, src, dst, out, len, have, u0, total, stride, lane);
 }
 
 // ---- several sources per destination chunk ---------------------------------------------
@@ -883,7 +883,10 @@ __device__ __forceinline__ bool gather_sources_ok(const GatherArgs& g, const ucc
 // One unit (64 * U vectors from vector v0 on) of one destination chunk: the accumulator's value and the
 // sources folded into it in the listed order (fold), the result written back and / or forwarded (store).
 // Sources are loaded in batches of B, all loads of a batch issued before the folds.  src(j): offset of
-// source j, the same in every lane.
+// source j, the same in every lane.  ACC: how the result is stored.  Through, and in the ordered form not kept for a reader, us a pass,
+// default policy / this: 128 MiB in 128 KiB chunks from seven sources 205.6 / 189.7, 100 MiB in 20 000-byte ones from three 104.5 / 98.8; tiles 60 MiB
+// in 4 KiB chunks from three 62.3 / 58.8; decided 64 at a time 20 MiB in 64 KiB chunks from seven 36.8 / 35.5, 6 MiB in 4 KiB chunks from one 8.9 / 8.7.
+// Calls cut into parts keep the default policy: they are over before there is much to write back (1.8 MiB from two sources 7.1 / 7.6).
 template <int U, class Op>
 struct GatherUnit {
   bool live[U];
@@ -928,7 +931,7 @@ __device__ __forceinline__ void gather_fold(const GatherArgs& g, GatherUnit<U, O
   }
 }
 
-template <int U, class Op, class Src>
+template <int U, uint32_t ACC, class Op, class Src>
 __device__ __forceinline__ void gather_store(const GatherArgs& g, const GatherUnit<U, Op>& u, uint64_t dst, uint64_t out, uint32_t len,
                                              uint32_t n_src, Src src, uint32_t v0, uint32_t lane) {
   constexpr uint32_t kUnit = 64u * U;
@@ -942,8 +945,8 @@ __device__ __forceinline__ void gather_store(const GatherArgs& g, const GatherUn
     if (!u.live[i]) continue;
     u32x4 t;
     t.x = Op::close(u.st[i][0]); t.y = Op::close(u.st[i][1]); t.z = Op::close(u.st[i][2]); t.w = Op::close(u.st[i][3]);
-    if (keep) ap[i * 64] = t;
-    if (fwd) __builtin_nontemporal_store(t, op + i * 64);
+    if (keep) store16<ACC>(ap + i * 64, t);
+    if (fwd) store16<kOnce>(op + i * 64, t);
   }
   // the last len % 16 bytes, element by element, by the unit that holds vector index nvec.  The whole wavefront walks
   // the sources (src may read another lane's register); only the loads and stores are the lanes' that have an element.
@@ -980,13 +983,13 @@ __device__ __forceinline__ void gather_store(const GatherArgs& g, const GatherUn
 }
 
 // Both, with the sources' offsets in memory (src[], the same address in every lane).
-template <int U, class Op>
+template <int U, uint32_t ACC, class Op>
 __device__ __forceinline__ void gather_unit(const GatherArgs& g, uint64_t dst, uint64_t out, uint32_t len,
                                             uint32_t n_src, const uint64_t* src, uint32_t v0, uint32_t lane) {
   const auto at = [src](uint32_t j) { return wave_uniform(src[j]); };
   GatherUnit<U, Op> t;
   gather_fold<U, UCCL_GATHER_BATCH, Op>(g, t, dst, len, n_src, at, v0, lane);
-  gather_store<U, Op>(g, t, dst, out, len, n_src, at, v0, lane);
+  gather_store<U, ACC, Op>(g, t, dst, out, len, n_src, at, v0, lane);
 }
 
 template <int T>
@@ -1063,7 +1066,7 @@ __global__ void __launch_bounds__(NT) chunk_gather_kernel(const GatherArgs g) {
     }
     w = __builtin_amdgcn_readfirstlane(w);
     const uint32_t v0 = (u - __builtin_amdgcn_readfirstlane(s.first[w])) * kUnit;
-    gather_unit<U, Op>(g, wave_uniform(s.dst[w]), wave_uniform(s.out[w]), __builtin_amdgcn_readfirstlane(s.len[w]),
+    gather_unit<U, kThrough, Op>(g, wave_uniform(s.dst[w]), wave_uniform(s.out[w]), __builtin_amdgcn_readfirstlane(s.len[w]),
                        __builtin_amdgcn_readfirstlane(s.n_src[w]), s.src[w], v0, lane);
   }
 }
@@ -1123,10 +1126,10 @@ __global__ void __launch_bounds__(NT) chunk_gather_parts_kernel(const GatherArgs
   }
   __syncthreads();
   if (s_win == 0u) return;   // uniform over the workgroup
-  if (have) gather_store<U, Op>(g, t, dst, out, len, n_src, src, u0 * kUnit, lane);
+  if (have) gather_store<U, kCached, Op>(g, t, dst, out, len, n_src, src, u0 * kUnit, lane);
   for (uint32_t u = u0 + kWaves * g.parts; u < total; u += kWaves * g.parts) {
     gather_fold<U, kBatch, Op>(g, t, dst, len, n_src, src, u * kUnit, lane);
-    gather_store<U, Op>(g, t, dst, out, len, n_src, src, u * kUnit, lane);
+    gather_store<U, kCached, Op>(g, t, dst, out, len, n_src, src, u * kUnit, lane);
   }
 }
 
@@ -1192,10 +1195,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_num_sgpr(80))) gath
   if (!part_has_units) return;   // the whole workgroup
   __syncthreads();
   if (s_win == 0u) return;
-  if (have) gather_store<U, Op>(g, t, dst, out, len, n_src, src, u0 * kUnit, lane);
+  if (have) gather_store<U, kThrough, Op>(g, t, dst, out, len, n_src, src, u0 * kUnit, lane);
   for (uint32_t u = u0 + kWaves * g.parts; u < total; u += kWaves * g.parts) {
     gather_fold<U, kBatch, Op>(g, t, dst, len, n_src, src, u * kUnit, lane);
-    gather_store<U, Op>(g, t, dst, out, len, n_src, src, u * kUnit, lane);
+    gather_store<U, kThrough, Op>(g, t, dst, out, len, n_src, src, u * kUnit, lane);
   }
 }
 
@@ -1231,7 +1234,7 @@ __device__ __forceinline__ void ordered_gather_part(const GatherArgs& g, uint32_
   const uint32_t vecs = (len >> 4) + ((len & 15u) != 0u ? 1u : 0u);
   const uint32_t total = (vecs + kUnit - 1u) / kUnit;
   for (uint32_t u = part * kWaves + wave; u < total; u += g.parts * kWaves)
-    gather_unit<1, Op>(g, d->dst_off, d->out_off, len, d->n_src, d->src_off, u * kUnit, lane);
+    gather_unit<1, kThroughOnce, Op>(g, d->dst_off, d->out_off, len, d->n_src, d->src_off, u * kUnit, lane);
 }
 
 template <class Op>

@@ -37,10 +37,31 @@ __device__ __forceinline__ u32x4 load16(const u32x4* p) {
   if constexpr (NT) return __builtin_nontemporal_load(p);
   else return *p;
 }
-template <bool NT>
+__device__ __forceinline__ uint64_t wave_uniform(uint64_t v) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32));
+  return lo | (static_cast<uint64_t>(hi) << 32);
+}
+
+// How a wavefront's 16 bytes a lane are stored: with the default policy, non-temporally, or written through the XCD's L2 to
+// the memory side as they are issued.  What is only in an L2 when a kernel ends (dirty lines, up to 4 MiB an XCD) has to be
+// written back before the next kernel of the stream starts, with nothing else in flight: a fill of 1.3 us takes 4.5 behind a
+// kernel that stored 30 MB.  Stored through, the lines leave while others are still being computed, and all of it ends
+// earlier.  The accumulator is kept for its next reader (kThrough), the staging copy is not (kThroughOnce).
+enum Store : uint32_t { kCached = 0, kOnce = 1, kThrough = 17, kThroughOnce = 19 };   // from 16 on: bits sc0, nt (2), sc1 of a buffer store
+
+// The wavefront's active lanes are the first ones, at consecutive vectors.
+template <uint32_t HOW>
 __device__ __forceinline__ void store16(u32x4* p, u32x4 v) {
-  if constexpr (NT) __builtin_nontemporal_store(v, p);
-  else *p = v;
+  if constexpr (HOW >= 16u) {
+    const uint64_t base = wave_uniform(reinterpret_cast<uint64_t>(p));
+    const __amdgpu_buffer_rsrc_t lines = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>(base), 0, 1024, 0x00020000);
+    __builtin_amdgcn_raw_buffer_store_b128(v, lines, (threadIdx.x & 63u) * 16u, 0, HOW);
+  } else if constexpr (HOW == kOnce) {
+    __builtin_nontemporal_store(v, p);
+  } else {
+    *p = v;
+  }
 }
 
 __device__ __forceinline__ float as_f32(uint32_t u) { return __uint_as_float(u); }
@@ -164,6 +185,32 @@ constexpr uint32_t cache_policy() {
   return FWD ? (WB ? UCCL_POLICY_COPY_FWD : UCCL_POLICY_COPY_RELAY) : UCCL_POLICY_COPY_KEEP;
 }
 
+// Which stores of a chunk are written through: none (the masks above), both, or both but the combined accumulator.
+// Measured, us a pass of the whole ring step or call, as the masks say / through (three sets of buffers):
+//   1 GiB reduce-scatter 559 / 548, 256 MiB bf16 262 / 256, 100 MiB in 64 KiB chunks 104 / 101, 64 MiB in 32 KiB chunks 70.4 / 66.6,
+//   4 MiB in parts 10.9 / 10.6, 8 MiB 14.2 / 13.4; all-to-all of 20 MiB a peer 29.2 / 26.9; 14 MB in 4 KB chunks 17.0 / 16.0
+// Tiles of records (4 KiB chunks, 128 messages) lose by it where they combine, 56.5 / 58.5, and gain with the
+// accumulator as before, 55.7.  Reads change nothing (accumulator loaded non-temporally 0.5 % slower).  With the nt bit on the
+// accumulator too the step of 256 MiB takes 283: the copy phase no longer finds it in the last-level cache.
+// A line that two wavefronts write each a part of goes to memory twice, so where chunks do not begin on a line it does
+// not pay once they are no longer in the last-level cache (64 MiB in 8 944-byte chunks 78 / 87, 20 000 282 / 297).
+enum Through { kNoThrough, kAllThrough, kAllButCombined };
+template <class Op, bool FWD, bool WB, Through T>
+constexpr uint32_t acc_store() {
+  if (T == kAllThrough || (T == kAllButCombined && !Op::kReadsAcc)) return kThrough;
+  return (cache_policy<Op, FWD, WB>() & 1u) != 0u ? kOnce : kCached;
+}
+template <class Op, bool FWD, bool WB, Through T>
+constexpr uint32_t out_store() {
+  if (T != kNoThrough) return kThroughOnce;
+  return (cache_policy<Op, FWD, WB>() & 4u) != 0u ? kOnce : kCached;
+}
+
+// Whether a chunk's written streams begin on a line of 128 bytes.
+__device__ __forceinline__ bool on_lines(const char* acc, const char* out) {
+  return ((reinterpret_cast<uintptr_t>(acc) | reinterpret_cast<uintptr_t>(out)) & 127u) == 0u;
+}
+
 template <class Op>
 __device__ __forceinline__ u32x4 combine(u32x4 a, u32x4 r) {
   u32x4 t;
@@ -172,12 +219,6 @@ __device__ __forceinline__ u32x4 combine(u32x4 a, u32x4 r) {
   t.z = Op::word(a.z, r.z);
   t.w = Op::word(a.w, r.w);
   return t;
-}
-
-__device__ __forceinline__ uint64_t wave_uniform(uint64_t v) {
-  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
-  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32));
-  return lo | (static_cast<uint64_t>(hi) << 32);
 }
 
 }  // namespace
