@@ -532,12 +532,13 @@ uint32_t group_gather_parts(uint32_t n_descs, const Tuning& tune) {
 // gives once the call has left the last-level cache.  Calls cut into parts (16 MiB at most) write through always.  Measured, us a pass, as
 // the masks say / through; "odd": segments that begin off a line:
 //   tiles and single records (chunk_flat_kernel), the combined accumulator as before: 128 messages in 4 KiB chunks 56.5 / 55.7, 60 MiB in 4 KiB 74.0 / 73.1, odd
-//     75.3 / 75.0, 80 MiB in 32 KiB 50.3 / 49.6; not the copies of a record a workgroup (all-to-all of 32 MiB in 64 KiB 38.9 / 39.5)
+//     75.3 / 75.0, 80 MiB in 32 KiB 50.3 / 49.6; not the copies of a record a workgroup, which were not measured by themselves
 //   a workgroup a record: all-to-all in 16 KiB chunks 23.9 / 23.1, 38 MiB in 32 KiB odd 52.0 / 48.5, 60 MiB odd 71.0 / 76.8; 33 008 bytes 52.9 / 55.3;
 //     all-to-all of 9 008 19.2 / 20.7
 //   decided 64 at a time: 8 x 1 MiB messages in 4 KiB chunks 27.9 / 24.9, 6 000 bytes 12 MiB 21.5 / 20.9, 30 000 bytes 22 MiB 34.3 / 35.4.  Of unknown
 //     size 3.6 MB 13.3 / 12.1 and 33 MB 35.5 / 34.6, but 60 MB in 98 256-byte chunks 41.1 / 44.3: not taken.
-//   in destination order, by record: 256 MiB bf16 262 / 256, 1 GiB 554 / 549, 100 MiB in 64 KiB 104 / 101, odd 256 MiB 260 / 260
+//   in destination order, by record: 256 MiB bf16 262 / 256, 1 GiB 554 / 549, 100 MiB in 64 KiB 104 / 101, odd 256 MiB 260 / 260;
+//     not copies that forward nothing (all-to-all of 32 MiB in 64 KiB 38.9 / 39.5)
 bool in_lines(const Tuning& tune) { return tune.chunk_bytes != 0u && tune.chunk_bytes % 128u == 0u; }
 bool few_through(const Args& a, const Tuning& tune) {   // a workgroup a record; one written stream (no staging) at any size
   return in_lines(tune) && (a.out == nullptr || static_cast<uint64_t>(a.n_descs) * tune.chunk_bytes <= (40ull << 20));
@@ -585,7 +586,7 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
       std::lock_guard<std::mutex> in_order(*region.launch_lock);
       // held back only where the records are known to be large: empty parts want as many workgroups as there can be
       const uint32_t lds = Op::kReadsAcc && tune.chunk_bytes != 0u ? kOrderReduceLds : 0u;
-      return launch_ordered<Args>(chunk_order_kernel<Op::kEs>, in_lines(tune) ? chunk_ordered_kernel<Op, kAllThrough> : chunk_ordered_kernel<Op, kNoThrough>, lds, a, s, ordered, region.words);
+      return launch_ordered<Args>(chunk_order_kernel<Op::kEs>, in_lines(tune) && (Op::kReadsAcc || a.out != nullptr) ? chunk_ordered_kernel<Op, kAllThrough> : chunk_ordered_kernel<Op, kNoThrough>, lds, a, s, ordered, region.words);
     }
   }
   const GroupPlan grouped = a.n_ptr == nullptr && !tune.one_launch ? plan_group(a.n_descs, tune) : kNotGrouped;   // a feed's slots are pinned

@@ -561,9 +561,9 @@ __device__ __forceinline__ void finish_unit(const u32x4 (&rv)[U], const u32x4 (&
 }
 
 // The wavefront's share of a record that is a first arrival: its first unit (u0), which is in registers if it has one, then
-// every stride-th.
+// every stride-th.  ap: where its first unit goes in the accumulator.
 template <int U, class Op, Through T>
-__device__ __forceinline__ void finish_record(const Args& g, const u32x4 (&rv)[U], const u32x4 (&av)[U], uint64_t src, uint64_t dst, uint64_t out,
+__device__ __forceinline__ void finish_record(const Args& g, const u32x4 (&rv)[U], const u32x4 (&av)[U], u32x4* ap, uint64_t src, uint64_t dst, uint64_t out,
                                               uint32_t len, bool have, uint32_t u0, uint32_t total, uint32_t stride, uint32_t lane) {
   constexpr uint32_t kUnit = 64u * U;
   const uint32_t nvec = len >> 4, first_vec = u0 * kUnit + lane;
@@ -571,7 +571,6 @@ __device__ __forceinline__ void finish_record(const Args& g, const u32x4 (&rv)[U
   const bool relay = fwd && (out & UCCL_FORWARD_ONLY) != 0;
   char* const o = g.out + (out & ~UCCL_FORWARD_ONLY);
   if (have) {
-    u32x4* ap = reinterpret_cast<u32x4*>(g.acc + dst) + first_vec;
     u32x4* op = reinterpret_cast<u32x4*>(o) + first_vec;
     if (!fwd) finish_unit<U, Op, false, true, T>(rv, av, ap, op, first_vec, nvec);
     else if (relay) finish_unit<U, Op, true, false, T>(rv, av, ap, op, first_vec, nvec);
@@ -623,7 +622,7 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
   const bool have = ok && u0 < total;
   const bool part_has_units = ok && part * kWaves < total;  // uniform over the workgroup
   const u32x4* rp = reinterpret_cast<const u32x4*>(g.recv + src) + first_vec;
-  const u32x4* ap = reinterpret_cast<const u32x4*>(g.acc + dst) + first_vec;
+  u32x4* ap = reinterpret_cast<u32x4*>(g.acc + dst) + first_vec;
   u32x4 rv[U], av[U];
   if (have) {  // in bounds whether or not this record turns out to be the first arrival
 #pragma unroll
@@ -654,7 +653,7 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
   }
   __syncthreads();
   if (s_win != 0u) {
-    finish_record<U, Op, H>(g, rv, av, src, dst, out, len, have, u0, total, stride, lane);
+    finish_record<U, Op, H>(g, rv, av, ap, src, dst, out, len, have, u0, total, stride, lane);
   }
 }
 
@@ -793,7 +792,7 @@ __global__ void __launch_bounds__(NT) UCCL_FULL_OCCUPANCY chunk_group_kernel(con
   const bool have = ok && u0 < total;
   const bool part_has_units = ok && part * kWaves < total;  // uniform over the workgroup
   const u32x4* rp = reinterpret_cast<const u32x4*>(g.recv + src) + first_vec;
-  const u32x4* ap = reinterpret_cast<const u32x4*>(g.acc + dst) + first_vec;
+  u32x4* ap = reinterpret_cast<u32x4*>(g.acc + dst) + first_vec;
   u32x4 rv[U], av[U];
   const auto load = [&] {   // in bounds whether or not this record turns out to be the first arrival
 #pragma unroll
@@ -827,7 +826,7 @@ __global__ void __launch_bounds__(NT) UCCL_FULL_OCCUPANCY chunk_group_kernel(con
   if (!part_has_units) return;   // the whole workgroup
   __syncthreads();
   if (s_win == 0u) return;
-  finish_record<U, Op, H>(g, rv, av, src, dst, out, len, have, u0, total, stride, lane);
+  finish_record<U, Op, H>(g, rv, av, ap, src, dst, out, len, have, u0, total, stride, lane);
 }
 
 // ---- several sources per destination chunk ---------------------------------------------
