@@ -318,16 +318,6 @@ __device__ __forceinline__ void stream_unit(const char* r, char* a, char* o, uin
   }
 }
 
-// One unit of a chunk by what its record says of forwarding.
-template <int U, class Op, Through T>
-__device__ __forceinline__ void chunk_unit(const Args& g, uint64_t src, uint64_t dst, uint64_t out, uint32_t len, uint32_t trip, uint32_t lane) {
-  const char* const r = g.recv + src;
-  char* const a = g.acc + dst;
-  if (out == UCCL_NO_FORWARD) stream_unit<U, Op, false, true, T>(r, a, nullptr, len, trip, lane);
-  else if (out & UCCL_FORWARD_ONLY) stream_unit<U, Op, true, false, T>(r, a, g.out + (out & ~UCCL_FORWARD_ONLY), len, trip, lane);
-  else stream_unit<U, Op, true, true, T>(r, a, g.out + out, len, trip, lane);
-}
-
 // Whether the record's written streams begin on lines (the accumulator's place counts also where it is not kept).
 __device__ __forceinline__ bool record_on_lines(const Args& g, uint64_t dst, uint64_t out) {
   return on_lines(g.acc + dst, out == UCCL_NO_FORWARD ? nullptr : g.out + (out & ~UCCL_FORWARD_ONLY));
@@ -369,7 +359,12 @@ __global__ void __launch_bounds__(NT) chunk_flat_kernel(const Args g) {
     const uint64_t dst = wave_uniform(s.dst[w]);
     const uint64_t out = wave_uniform(s.out[w]);
     const uint32_t len = __builtin_amdgcn_readfirstlane(s.len[w]);
-    chunk_unit<U, Op, H>(g, src, dst, out, len, trip, lane);
+    if (out == UCCL_NO_FORWARD)
+      stream_unit<U, Op, false, true, H>(g.recv + src, g.acc + dst, nullptr, len, trip, lane);
+    else if (out & UCCL_FORWARD_ONLY)
+      stream_unit<U, Op, true, false, H>(g.recv + src, g.acc + dst, g.out + (out & ~UCCL_FORWARD_ONLY), len, trip, lane);
+    else
+      stream_unit<U, Op, true, true, H>(g.recv + src, g.acc + dst, g.out + out, len, trip, lane);
   }
 }
 
@@ -510,19 +505,25 @@ __global__ void __launch_bounds__(kOrderThreads) chunk_order_kernel(const Args g
 // than all its parts).  H: as a record's stores are written if it begins on lines, which is looked at here: one branch a part.
 // (In the kernels of few and of hundreds of records such a branch costs more than it gives, 1.05 - 1.4 times: there the host chooses.)
 template <class Op, Through H>
-__device__ __forceinline__ void ordered_part(const Args& g, uint32_t k, uint32_t part) {
+__device__ __forceinline__ void ordered_units(const Args& g, const uccl_chunk_desc& d, uint32_t part) {
   constexpr uint32_t kUnit = 64u, kWaves = kOrderThreads / 64;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
-  const uccl_chunk_desc d = g.descs[k];   // the same address in every lane
   const uint32_t vecs = (d.len >> 4) + ((d.len & 15u) != 0u ? 1u : 0u);
   const uint32_t total = (vecs + kUnit - 1u) / kUnit;
-  if (H != kNoThrough && record_on_lines(g, d.dst_off, d.out_off)) {
-    for (uint32_t u = part * kWaves + wave; u < total; u += g.parts * kWaves)
-      chunk_unit<1, Op, H>(g, d.src_off, d.dst_off, d.out_off, d.len, u, lane);
-  } else {
-    for (uint32_t u = part * kWaves + wave; u < total; u += g.parts * kWaves)
-      chunk_unit<1, Op, kNoThrough>(g, d.src_off, d.dst_off, d.out_off, d.len, u, lane);
+  for (uint32_t u = part * kWaves + wave; u < total; u += g.parts * kWaves) {
+    if (d.out_off == UCCL_NO_FORWARD)
+      stream_unit<1, Op, false, true, H>(g.recv + d.src_off, g.acc + d.dst_off, nullptr, d.len, u, lane);
+    else if (d.out_off & UCCL_FORWARD_ONLY)
+      stream_unit<1, Op, true, false, H>(g.recv + d.src_off, g.acc + d.dst_off, g.out + (d.out_off & ~UCCL_FORWARD_ONLY), d.len, u, lane);
+    else
+      stream_unit<1, Op, true, true, H>(g.recv + d.src_off, g.acc + d.dst_off, g.out + d.out_off, d.len, u, lane);
   }
+}
+template <class Op, Through H>
+__device__ __forceinline__ void ordered_part(const Args& g, uint32_t k, uint32_t part) {
+  const uccl_chunk_desc d = g.descs[k];   // the same address in every lane
+  if (H != kNoThrough && record_on_lines(g, d.dst_off, d.out_off)) ordered_units<Op, H>(g, d, part);
+  else ordered_units<Op, kNoThrough>(g, d, part);
 }
 
 template <class Op, Through H>
@@ -557,36 +558,6 @@ __device__ __forceinline__ void finish_unit(const u32x4 (&rv)[U], const u32x4 (&
       if (WB) store16<kAccStore>(ap + u * 64, t);
       if (FWD) store16<kOutStore>(op + u * 64, t);
     }
-  }
-}
-
-// The wavefront's share of a record that is a first arrival: its first unit (u0), which is in registers if it has one, then
-// every stride-th.  ap: where its first unit goes in the accumulator.
-template <int U, class Op, Through T>
-__device__ __forceinline__ void finish_record(const Args& g, const u32x4 (&rv)[U], const u32x4 (&av)[U], u32x4* ap, uint64_t src, uint64_t dst, uint64_t out,
-                                              uint32_t len, bool have, uint32_t u0, uint32_t total, uint32_t stride, uint32_t lane) {
-  constexpr uint32_t kUnit = 64u * U;
-  const uint32_t nvec = len >> 4, first_vec = u0 * kUnit + lane;
-  const bool fwd = out != UCCL_NO_FORWARD;
-  const bool relay = fwd && (out & UCCL_FORWARD_ONLY) != 0;
-  char* const o = g.out + (out & ~UCCL_FORWARD_ONLY);
-  if (have) {
-    u32x4* op = reinterpret_cast<u32x4*>(o) + first_vec;
-    if (!fwd) finish_unit<U, Op, false, true, T>(rv, av, ap, op, first_vec, nvec);
-    else if (relay) finish_unit<U, Op, true, false, T>(rv, av, ap, op, first_vec, nvec);
-    else finish_unit<U, Op, true, true, T>(rv, av, ap, op, first_vec, nvec);
-    const uint32_t rem = len & 15u;
-    if (rem != 0u && nvec >= u0 * kUnit && nvec < (u0 + 1u) * kUnit) {  // the unit that holds the partial vector
-      const uint64_t off = static_cast<uint64_t>(nvec) << 4;
-      if (!fwd) stream_tail<Op, false, true>(g.recv + src + off, g.acc + dst + off, nullptr, rem, lane);
-      else if (relay) stream_tail<Op, true, false>(g.recv + src + off, g.acc + dst + off, o + off, rem, lane);
-      else stream_tail<Op, true, true>(g.recv + src + off, g.acc + dst + off, o + off, rem, lane);
-    }
-  }
-  for (uint32_t u = u0 + stride; u < total; u += stride) {
-    if (!fwd) stream_unit<U, Op, false, true, T>(g.recv + src, g.acc + dst, nullptr, len, u, lane);
-    else if (relay) stream_unit<U, Op, true, false, T>(g.recv + src, g.acc + dst, o, len, u, lane);
-    else stream_unit<U, Op, true, true, T>(g.recv + src, g.acc + dst, o, len, u, lane);
   }
 }
 
@@ -653,7 +624,27 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
   }
   __syncthreads();
   if (s_win != 0u) {
-    finish_record<U, Op, H>(g, rv, av, ap, src, dst, out, len, have, u0, total, stride, lane);
+    const bool fwd = out != UCCL_NO_FORWARD;
+    const bool relay = fwd && (out & UCCL_FORWARD_ONLY) != 0;
+    char* const o = g.out + (out & ~UCCL_FORWARD_ONLY);
+    if (have) {
+      u32x4* op = reinterpret_cast<u32x4*>(o) + first_vec;
+      if (!fwd) finish_unit<U, Op, false, true, H>(rv, av, ap, op, first_vec, nvec);
+      else if (relay) finish_unit<U, Op, true, false, H>(rv, av, ap, op, first_vec, nvec);
+      else finish_unit<U, Op, true, true, H>(rv, av, ap, op, first_vec, nvec);
+      const uint32_t rem = len & 15u;
+      if (rem != 0u && nvec >= u0 * kUnit && nvec < (u0 + 1u) * kUnit) {  // the unit that holds the partial vector
+        const uint64_t off = static_cast<uint64_t>(nvec) << 4;
+        if (!fwd) stream_tail<Op, false, true>(g.recv + src + off, g.acc + dst + off, nullptr, rem, lane);
+        else if (relay) stream_tail<Op, true, false>(g.recv + src + off, g.acc + dst + off, o + off, rem, lane);
+        else stream_tail<Op, true, true>(g.recv + src + off, g.acc + dst + off, o + off, rem, lane);
+      }
+    }
+    for (uint32_t u = u0 + stride; u < total; u += stride) {
+      if (!fwd) stream_unit<U, Op, false, true, H>(g.recv + src, g.acc + dst, nullptr, len, u, lane);
+      else if (relay) stream_unit<U, Op, true, false, H>(g.recv + src, g.acc + dst, o, len, u, lane);
+      else stream_unit<U, Op, true, true, H>(g.recv + src, g.acc + dst, o, len, u, lane);
+    }
   }
 }
 
@@ -826,7 +817,27 @@ __global__ void __launch_bounds__(NT) UCCL_FULL_OCCUPANCY chunk_group_kernel(con
   if (!part_has_units) return;   // the whole workgroup
   __syncthreads();
   if (s_win == 0u) return;
-  finish_record<U, Op, H>(g, rv, av, ap, src, dst, out, len, have, u0, total, stride, lane);
+  const bool fwd = out != UCCL_NO_FORWARD;
+  const bool relay = fwd && (out & UCCL_FORWARD_ONLY) != 0;
+  char* const o = g.out + (out & ~UCCL_FORWARD_ONLY);
+  if (have) {
+    u32x4* op = reinterpret_cast<u32x4*>(o) + first_vec;
+    if (!fwd) finish_unit<U, Op, false, true, H>(rv, av, ap, op, first_vec, nvec);
+    else if (relay) finish_unit<U, Op, true, false, H>(rv, av, ap, op, first_vec, nvec);
+    else finish_unit<U, Op, true, true, H>(rv, av, ap, op, first_vec, nvec);
+    const uint32_t rem = len & 15u;
+    if (rem != 0u && nvec >= u0 * kUnit && nvec < (u0 + 1u) * kUnit) {  // the unit that holds the partial vector
+      const uint64_t off = static_cast<uint64_t>(nvec) << 4;
+      if (!fwd) stream_tail<Op, false, true>(g.recv + src + off, g.acc + dst + off, nullptr, rem, lane);
+      else if (relay) stream_tail<Op, true, false>(g.recv + src + off, g.acc + dst + off, o + off, rem, lane);
+      else stream_tail<Op, true, true>(g.recv + src + off, g.acc + dst + off, o + off, rem, lane);
+    }
+  }
+  for (uint32_t u = u0 + stride; u < total; u += stride) {
+    if (!fwd) stream_unit<U, Op, false, true, H>(g.recv + src, g.acc + dst, nullptr, len, u, lane);
+    else if (relay) stream_unit<U, Op, true, false, H>(g.recv + src, g.acc + dst, o, len, u, lane);
+    else stream_unit<U, Op, true, true, H>(g.recv + src, g.acc + dst, o, len, u, lane);
+  }
 }
 
 // ---- several sources per destination chunk ---------------------------------------------
