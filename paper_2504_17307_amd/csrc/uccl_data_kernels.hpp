@@ -282,6 +282,8 @@ __device__ __forceinline__ void stream_unit(const char* r, char* a, char* o, uin
   const u32x4* rp = reinterpret_cast<const u32x4*>(r) + v0 + lane;
   u32x4* ap = reinterpret_cast<u32x4*>(a) + v0 + lane;
   u32x4* op = reinterpret_cast<u32x4*>(o) + v0 + lane;
+  const StoreUnit<kAccStore, kUnit> kept(reinterpret_cast<u32x4*>(a) + v0, ap);
+  const StoreUnit<kOutStore, kUnit> forwarded(reinterpret_cast<u32x4*>(o) + v0, op);
   if (v0 + kUnit <= nvec) {
     u32x4 rv[U], av[U];
 #pragma unroll
@@ -294,8 +296,8 @@ __device__ __forceinline__ void stream_unit(const char* r, char* a, char* o, uin
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const u32x4 t = combine<Op>(av[u], rv[u]);
-      if (WB) store16<kAccStore>(ap + u * 64, t);
-      if (FWD) store16<kOutStore>(op + u * 64, t);
+      if (WB) kept.put(u * 64, lane, t);
+      if (FWD) forwarded.put(u * 64, lane, t);
     }
     return;
   }
@@ -307,8 +309,8 @@ __device__ __forceinline__ void stream_unit(const char* r, char* a, char* o, uin
       u32x4 av = rv;
       if constexpr (Op::kReadsAcc) av = load16<kNtAccLoad>(ap + u * 64);
       const u32x4 t = combine<Op>(av, rv);
-      if (WB) store16<kAccStore>(ap + u * 64, t);
-      if (FWD) store16<kOutStore>(op + u * 64, t);
+      if (WB) kept.put(u * 64, lane, t);
+      if (FWD) forwarded.put(u * 64, lane, t);
     }
   }
   const uint32_t rem = len & 15u;
@@ -548,25 +550,32 @@ __global__ void __launch_bounds__(kOrderThreads) chunk_ordered_kernel(const Args
 // number of workgroups anyway, use chunk_flat_kernel.  PARTS: blockIdx.x = record * parts + part
 // (see claim_enter).
 template <int U, class Op, bool FWD, bool WB, Through T>
-__device__ __forceinline__ void finish_unit(const u32x4 (&rv)[U], const u32x4 (&av)[U], u32x4* ap,
-                                            u32x4* op, uint32_t first_vec, uint32_t nvec) {
-  constexpr uint32_t kAccStore = acc_store<Op, FWD, WB, T>(), kOutStore = out_store<Op, FWD, WB, T>();
+__device__ __forceinline__ void finish_unit(const u32x4 (&rv)[U], const u32x4 (&av)[U], u32x4* au, u32x4* ou, u32x4* ap, u32x4* op, uint32_t lane,
+                                            uint32_t first_vec, uint32_t nvec) {
+  const StoreUnit<acc_store<Op, FWD, WB, T>(), 64u * U> kept(au, ap);
+  const StoreUnit<out_store<Op, FWD, WB, T>(), 64u * U> forwarded(ou, op);
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     if (first_vec + u * 64 < nvec) {
       const u32x4 t = combine<Op>(Op::kReadsAcc ? av[u] : rv[u], rv[u]);
-      if (WB) store16<kAccStore>(ap + u * 64, t);
-      if (FWD) store16<kOutStore>(op + u * 64, t);
+      if (WB) kept.put(u * 64, lane, t);
+      if (FWD) forwarded.put(u * 64, lane, t);
     }
   }
 }
+
+// Waits for the wavefront's loads (vmcnt 0), once.  Left to itself the compiler waits in front of each vector that a lane may not
+// have, and as loads and stores are counted together, that is for the store of the vector before: one that is written through takes its time
+// (ring of 24 MiB bf16 in 32 KiB chunks, decided 64 at a time, 31.5 / 30.2 us; 40 MiB f32, a workgroup a record, 49.3 / 47.9).
+__device__ __forceinline__ void await_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
 template <int NT, int U, class Op, Through H, bool PARTS, bool APART = false>
 __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
   constexpr uint32_t kUnit = 64u * U;
   constexpr uint32_t kWaves = NT / 64;
   __shared__ uint32_t s_win;
-  const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63u;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u;
+  const uint32_t wave = H == kNoThrough ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6);   // a scalar where units' places are
   const uint32_t k = PARTS ? blockIdx.x / g.parts : blockIdx.x;   // the launch has n_descs (* parts) workgroups
   const uint32_t part = PARTS ? blockIdx.x % g.parts : 0u;
 
@@ -627,11 +636,14 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
     const bool fwd = out != UCCL_NO_FORWARD;
     const bool relay = fwd && (out & UCCL_FORWARD_ONLY) != 0;
     char* const o = g.out + (out & ~UCCL_FORWARD_ONLY);
+    if constexpr (H != kNoThrough) await_loads();
     if (have) {
       u32x4* op = reinterpret_cast<u32x4*>(o) + first_vec;
-      if (!fwd) finish_unit<U, Op, false, true, H>(rv, av, ap, op, first_vec, nvec);
-      else if (relay) finish_unit<U, Op, true, false, H>(rv, av, ap, op, first_vec, nvec);
-      else finish_unit<U, Op, true, true, H>(rv, av, ap, op, first_vec, nvec);
+      u32x4* const au = reinterpret_cast<u32x4*>(g.acc + dst) + u0 * kUnit;
+      u32x4* const ou = reinterpret_cast<u32x4*>(o) + u0 * kUnit;
+      if (!fwd) finish_unit<U, Op, false, true, H>(rv, av, au, ou, ap, op, lane, first_vec, nvec);
+      else if (relay) finish_unit<U, Op, true, false, H>(rv, av, au, ou, ap, op, lane, first_vec, nvec);
+      else finish_unit<U, Op, true, true, H>(rv, av, au, ou, ap, op, lane, first_vec, nvec);
       const uint32_t rem = len & 15u;
       if (rem != 0u && nvec >= u0 * kUnit && nvec < (u0 + 1u) * kUnit) {  // the unit that holds the partial vector
         const uint64_t off = static_cast<uint64_t>(nvec) << 4;
@@ -820,11 +832,14 @@ __global__ void __launch_bounds__(NT) UCCL_FULL_OCCUPANCY chunk_group_kernel(con
   const bool fwd = out != UCCL_NO_FORWARD;
   const bool relay = fwd && (out & UCCL_FORWARD_ONLY) != 0;
   char* const o = g.out + (out & ~UCCL_FORWARD_ONLY);
+  if constexpr (H != kNoThrough) await_loads();
   if (have) {
     u32x4* op = reinterpret_cast<u32x4*>(o) + first_vec;
-    if (!fwd) finish_unit<U, Op, false, true, H>(rv, av, ap, op, first_vec, nvec);
-    else if (relay) finish_unit<U, Op, true, false, H>(rv, av, ap, op, first_vec, nvec);
-    else finish_unit<U, Op, true, true, H>(rv, av, ap, op, first_vec, nvec);
+    u32x4* const au = reinterpret_cast<u32x4*>(g.acc + dst) + u0 * kUnit;
+    u32x4* const ou = reinterpret_cast<u32x4*>(o) + u0 * kUnit;
+    if (!fwd) finish_unit<U, Op, false, true, H>(rv, av, au, ou, ap, op, lane, first_vec, nvec);
+    else if (relay) finish_unit<U, Op, true, false, H>(rv, av, au, ou, ap, op, lane, first_vec, nvec);
+    else finish_unit<U, Op, true, true, H>(rv, av, au, ou, ap, op, lane, first_vec, nvec);
     const uint32_t rem = len & 15u;
     if (rem != 0u && nvec >= u0 * kUnit && nvec < (u0 + 1u) * kUnit) {  // the unit that holds the partial vector
       const uint64_t off = static_cast<uint64_t>(nvec) << 4;
@@ -948,15 +963,17 @@ __device__ __forceinline__ void gather_store(const GatherArgs& g, const GatherUn
   const uint32_t nvec = len >> 4;
   const bool fwd = out != UCCL_NO_FORWARD;
   const bool keep = !(fwd && (out & UCCL_FORWARD_ONLY));
-  u32x4* ap = reinterpret_cast<u32x4*>(g.acc + dst) + v0 + lane;
-  u32x4* op = reinterpret_cast<u32x4*>(g.out + (out & ~UCCL_FORWARD_ONLY)) + v0 + lane;
+  u32x4* au = reinterpret_cast<u32x4*>(g.acc + dst) + v0;
+  u32x4* ou = reinterpret_cast<u32x4*>(g.out + (out & ~UCCL_FORWARD_ONLY)) + v0;
+  const StoreUnit<ACC, kUnit> kept(au, au + lane);
+  const StoreUnit<kOnce, kUnit> forwarded(ou, ou + lane);
 #pragma unroll
   for (int i = 0; i < U; ++i) {
     if (!u.live[i]) continue;
     u32x4 t;
     t.x = Op::close(u.st[i][0]); t.y = Op::close(u.st[i][1]); t.z = Op::close(u.st[i][2]); t.w = Op::close(u.st[i][3]);
-    if (keep) store16<ACC>(ap + i * 64, t);
-    if (fwd) store16<kOnce>(op + i * 64, t);
+    if (keep) kept.put(i * 64, lane, t);
+    if (fwd) forwarded.put(i * 64, lane, t);
   }
   // the last len % 16 bytes, element by element, by the unit that holds vector index nvec.  The whole wavefront walks
   // the sources (src may read another lane's register); only the loads and stores are the lanes' that have an element.

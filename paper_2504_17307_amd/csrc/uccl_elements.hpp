@@ -42,6 +42,7 @@ __device__ __forceinline__ uint64_t wave_uniform(uint64_t v) {
   const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32));
   return lo | (static_cast<uint64_t>(hi) << 32);
 }
+__device__ __forceinline__ char* wave_uniform(char* p) { return reinterpret_cast<char*>(wave_uniform(reinterpret_cast<uint64_t>(p))); }
 
 // How a wavefront's 16 bytes a lane are stored: with the default policy, non-temporally, or written through the XCD's L2 to
 // the memory side as they are issued.  What is only in an L2 when a kernel ends (dirty lines, up to 4 MiB an XCD) has to be
@@ -50,19 +51,27 @@ __device__ __forceinline__ uint64_t wave_uniform(uint64_t v) {
 // earlier.  The accumulator is kept for its next reader (kThrough), the staging copy is not (kThroughOnce).
 enum Store : uint32_t { kCached = 0, kOnce = 1, kThrough = 17, kThroughOnce = 19 };   // from 16 on: bits sc0, nt (2), sc1 of a buffer store
 
-// The wavefront's active lanes are the first ones, at consecutive vectors.
-template <uint32_t HOW>
-__device__ __forceinline__ void store16(u32x4* p, u32x4 v) {
-  if constexpr (HOW >= 16u) {
-    const uint64_t base = wave_uniform(reinterpret_cast<uint64_t>(p));
-    const __amdgpu_buffer_rsrc_t lines = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>(base), 0, 1024, 0x00020000);
-    __builtin_amdgcn_raw_buffer_store_b128(v, lines, (threadIdx.x & 63u) * 16u, 0, HOW);
-  } else if constexpr (HOW == kOnce) {
-    __builtin_nontemporal_store(v, p);
-  } else {
-    *p = v;
+// One unit of a written stream, UNIT vectors, of which a lane stores those at `at` + lane.  `unit`: its first vector, the same in every
+// lane; `mine`: the lane's own first one.  Written through, the lanes share one descriptor a unit, two scalars and two constants,
+// hold no address, and the offset within the unit is the instruction's.  (A descriptor for every 16 bytes, from the lanes' pointers, takes
+// chunk_few_kernel<1024, 4> of f32 from 50 vector registers to 72, so from two workgroups on a compute unit to one; this way it takes 56.)
+template <uint32_t HOW, uint32_t UNIT>
+struct StoreUnit {
+  static_assert(UNIT <= 256u, "the instruction's offset has 12 bits");
+  char* place;
+  __device__ __forceinline__ StoreUnit(u32x4* unit, u32x4* mine)
+      : place(HOW >= 16u ? wave_uniform(reinterpret_cast<char*>(unit)) : reinterpret_cast<char*>(mine)) {}
+  __device__ __forceinline__ void put(uint32_t at, uint32_t lane, u32x4 v) const {
+    if constexpr (HOW >= 16u) {
+      const __amdgpu_buffer_rsrc_t lines = __builtin_amdgcn_make_buffer_rsrc(place, 0, UNIT * 16u, 0x00020000);
+      __builtin_amdgcn_raw_buffer_store_b128(v, lines, lane * 16u + at * 16u, 0, HOW);
+    } else if constexpr (HOW == kOnce) {
+      __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(place) + at);
+    } else {
+      reinterpret_cast<u32x4*>(place)[at] = v;
+    }
   }
-}
+};
 
 __device__ __forceinline__ float as_f32(uint32_t u) { return __uint_as_float(u); }
 __device__ __forceinline__ uint32_t as_u32(float f) { return __float_as_uint(f); }
