@@ -529,8 +529,10 @@ uint32_t group_gather_parts(uint32_t n_descs, const Tuning& tune) {
 
 // Which stores a call's kernel writes through (see Through).  Lines: chunks of whole lines of 128 bytes.  Two chunks share a line where
 // they are no such multiple, or their segment does not begin on one, which the host cannot see; what is shared costs more than writing through
-// gives once the call has left the last-level cache.  Calls cut into parts (16 MiB at most) write through always.  Measured, us a pass, as
-// the masks say / through; "odd": segments that begin off a line:
+// gives once the call has left the last-level cache.  Measured, us a pass, as the masks say / through; "odd": segments that begin off a line:
+//   cut into parts, ring of 4 MiB in 64 KiB chunks 11.1 / 9.9, 32 MiB 41.4 / 39.5, odd 41.5 / 39.9, 64 MiB 67.9 / 65.2, 128 MiB 130.4 / 130.3; off lines 8 MiB in 66 000-byte
+//     chunks 18.2 / 16.8, 16 MiB 27.8 / 26.9, 32 MiB 43.7 / 43.8, 64 MiB 71.6 / 75.0, 128 MiB 140 / 154.  Of unknown size, chosen by record in the
+//     kernel: 64 MiB in 1 MiB chunks 74.4 / 69.9, in chunks of 1 MiB and 16 bytes 79.2 / 78.3 (all written through 90.6)
 //   tiles and single records (chunk_flat_kernel), the combined accumulator as before: 128 messages in 4 KiB chunks 56.5 / 55.7, 60 MiB in 4 KiB 74.0 / 73.1, odd
 //     75.3 / 75.0, 80 MiB in 32 KiB 50.3 / 49.6; not the copies of a record a workgroup, which were not measured by themselves
 //   a workgroup a record: all-to-all in 16 KiB chunks 23.9 / 23.1, 38 MiB in 32 KiB odd 52.0 / 48.5, 60 MiB odd 71.0 / 76.8; 33 008 bytes 52.9 / 55.3;
@@ -543,8 +545,8 @@ bool in_lines(const Tuning& tune) { return tune.chunk_bytes != 0u && tune.chunk_
 bool few_through(const Args& a, const Tuning& tune) {   // a workgroup a record; one written stream (no staging) at any size
   return in_lines(tune) && (a.out == nullptr || static_cast<uint64_t>(a.n_descs) * tune.chunk_bytes <= (40ull << 20));
 }
-bool group_through(const Args& a, const Tuning& tune) {
-  return tune.chunk_bytes != 0u && (in_lines(tune) || static_cast<uint64_t>(a.n_descs) * tune.chunk_bytes <= (16ull << 20));
+bool lines_or_small(const Args& a, const Tuning& tune) {   // decided 64 at a time, cut into parts
+  return tune.chunk_bytes != 0u && (in_lines(tune) || static_cast<uint64_t>(a.n_descs) * tune.chunk_bytes <= kThroughBytes);
 }
 
 // `region`: the stream's scratch words; called with its launch lock held.  HIP has no reason of its
@@ -597,7 +599,7 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
       a.use(region.words, region.faults);
       a.parts = grouped.parts;
       a.tag = g_next_tag.fetch_add(1, std::memory_order_relaxed);
-      const bool through = group_through(a, tune);
+      const bool through = lines_or_small(a, tune);
       const auto kernel = tune.chunk_bytes == 0u ? chunk_group_kernel<kGroupThreads, 4, Op, true, kNoThrough>
                           : grouped.unroll == 4u ? (through ? chunk_group_kernel<kGroupThreads, 4, Op, false, kAllThrough> : chunk_group_kernel<kGroupThreads, 4, Op, false, kNoThrough>)
                           : grouped.unroll == 2u ? (through ? chunk_group_kernel<kGroupThreads, 2, Op, false, kAllThrough> : chunk_group_kernel<kGroupThreads, 2, Op, false, kNoThrough>)
@@ -610,8 +612,10 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
     a.parts = p.parts;
     const auto launch_parts = [&](unsigned long long tag) {
       a.tag = tag;
-      return launch_kernel(tune.static_claims != nullptr ? chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, kAllThrough, true, true>
-                                                         : chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, kAllThrough, true, false>,
+      return launch_kernel(tune.static_claims != nullptr ? chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, kByRecord, true, true>
+                           : tune.chunk_bytes == 0u      ? chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, kByRecord, true, false>
+                           : lines_or_small(a, tune)     ? chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, kAllThrough, true, false>
+                                                         : chunk_few_kernel<UCCL_PART_THREADS, UCCL_PART_UNROLL, Op, kNoThrough, true, false>,
                            a.n_descs * p.parts, UCCL_PART_THREADS, s, a);
     };
     if (tune.static_claims != nullptr) {

@@ -632,18 +632,20 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
     s_win = win;
   }
   __syncthreads();
-  if (s_win != 0u) {
-    const bool fwd = out != UCCL_NO_FORWARD;
-    const bool relay = fwd && (out & UCCL_FORWARD_ONLY) != 0;
-    char* const o = g.out + (out & ~UCCL_FORWARD_ONLY);
-    if constexpr (H != kNoThrough) await_loads();
+  if (s_win == 0u) return;
+  const bool fwd = out != UCCL_NO_FORWARD;
+  const bool relay = fwd && (out & UCCL_FORWARD_ONLY) != 0;
+  char* const o = g.out + (out & ~UCCL_FORWARD_ONLY);
+  const auto finish = [&](auto how) {
+    constexpr Through kHow = decltype(how)::value;
+    if constexpr (kHow != kNoThrough) await_loads();
     if (have) {
       u32x4* op = reinterpret_cast<u32x4*>(o) + first_vec;
       u32x4* const au = reinterpret_cast<u32x4*>(g.acc + dst) + u0 * kUnit;
       u32x4* const ou = reinterpret_cast<u32x4*>(o) + u0 * kUnit;
-      if (!fwd) finish_unit<U, Op, false, true, H>(rv, av, au, ou, ap, op, lane, first_vec, nvec);
-      else if (relay) finish_unit<U, Op, true, false, H>(rv, av, au, ou, ap, op, lane, first_vec, nvec);
-      else finish_unit<U, Op, true, true, H>(rv, av, au, ou, ap, op, lane, first_vec, nvec);
+      if (!fwd) finish_unit<U, Op, false, true, kHow>(rv, av, au, ou, ap, op, lane, first_vec, nvec);
+      else if (relay) finish_unit<U, Op, true, false, kHow>(rv, av, au, ou, ap, op, lane, first_vec, nvec);
+      else finish_unit<U, Op, true, true, kHow>(rv, av, au, ou, ap, op, lane, first_vec, nvec);
       const uint32_t rem = len & 15u;
       if (rem != 0u && nvec >= u0 * kUnit && nvec < (u0 + 1u) * kUnit) {  // the unit that holds the partial vector
         const uint64_t off = static_cast<uint64_t>(nvec) << 4;
@@ -653,11 +655,16 @@ __global__ void __launch_bounds__(NT) chunk_few_kernel(const Args g) {
       }
     }
     for (uint32_t u = u0 + stride; u < total; u += stride) {
-      if (!fwd) stream_unit<U, Op, false, true, H>(g.recv + src, g.acc + dst, nullptr, len, u, lane);
-      else if (relay) stream_unit<U, Op, true, false, H>(g.recv + src, g.acc + dst, o, len, u, lane);
-      else stream_unit<U, Op, true, true, H>(g.recv + src, g.acc + dst, o, len, u, lane);
+      if (!fwd) stream_unit<U, Op, false, true, kHow>(g.recv + src, g.acc + dst, nullptr, len, u, lane);
+      else if (relay) stream_unit<U, Op, true, false, kHow>(g.recv + src, g.acc + dst, o, len, u, lane);
+      else stream_unit<U, Op, true, true, kHow>(g.recv + src, g.acc + dst, o, len, u, lane);
     }
-  }
+  };
+  // The size not stated: the record's own says whether the call is likely to be small.  One choice between two bodies costs nothing to speak of; one at
+  // each store costs records that are long 7 - 10 %, as the loads of their later units no longer overlap.
+  if constexpr (H != kByRecord) finish(Stores<H>());
+  else if (static_cast<uint64_t>(len) * g.n_descs <= kThroughBytes || record_on_lines(g, dst, out)) finish(Stores<kAllThrough>());
+  else finish(Stores<kNoThrough>());
 }
 
 // ---- calls of hundreds of records -------------------------------------------------------------------
