@@ -915,10 +915,13 @@ __device__ __forceinline__ bool gather_sources_ok(const GatherArgs& g, const ucc
 // One unit (64 * U vectors from vector v0 on) of one destination chunk: the accumulator's value and the
 // sources folded into it in the listed order (fold), the result written back and / or forwarded (store).
 // Sources are loaded in batches of B, all loads of a batch issued before the folds.  src(j): offset of
-// source j, the same in every lane.  ACC: how the result is stored.  Through, and in the ordered form not kept for a reader, us a pass,
-// default policy / this: 128 MiB in 128 KiB chunks from seven sources 205.6 / 189.7, 100 MiB in 20 000-byte ones from three 104.5 / 98.8; tiles 60 MiB
-// in 4 KiB chunks from three 62.3 / 58.8; decided 64 at a time 20 MiB in 64 KiB chunks from seven 36.8 / 35.5, 6 MiB in 4 KiB chunks from one 8.9 / 8.7.
+// source j, the same in every lane.  ACC: how the result is stored.  Through, us a pass, default policy / this: tiles 60 MiB
+// in 4 KiB chunks from three sources 62.3 / 58.8, 64 MiB in 9 008-byte ones from two 53.9 / 52.3; decided 64 at a time 20 MiB in 64 KiB chunks from seven 36.8 / 35.5,
+// 30 MiB in 6 000-byte ones 63.3 / 60.7; in destination order 128 MiB in 128 KiB chunks from seven 206 / 197, 100 MiB in 20 000-byte ones from three 104.6 / 99.4.
 // Calls cut into parts keep the default policy: they are over before there is much to write back (1.8 MiB from two sources 7.1 / 7.6).
+// Never non-temporally: a fold's result has a reader.  In destination order the call alone would take less, with uccl_chunk_segment of the result after it
+// more, default policy / through / through and non-temporal: 128 MiB from one source 74.5 / 72.0 / 69.8, with it 110.9 / 108.1 / 115.9; from seven 206 / 197 / 190, 244.6 / 235.3 / 237.7;
+// 96 MiB from one 58.1 / 56.3 / 54.4, 84.1 / 82.6 / 88.2; 256 MiB bf16 from two 189 / 185 / 182, 261 / 257 / 278.  The forwarded copy is non-temporal, as it was.
 template <int U, class Op>
 struct GatherUnit {
   bool live[U];
@@ -966,6 +969,7 @@ __device__ __forceinline__ void gather_fold(const GatherArgs& g, GatherUnit<U, O
 template <int U, uint32_t ACC, class Op, class Src>
 __device__ __forceinline__ void gather_store(const GatherArgs& g, const GatherUnit<U, Op>& u, uint64_t dst, uint64_t out, uint32_t len,
                                              uint32_t n_src, Src src, uint32_t v0, uint32_t lane) {
+  static_assert(ACC == kCached || ACC == kThrough, "kept for the result's reader");
   constexpr uint32_t kUnit = 64u * U;
   const uint32_t nvec = len >> 4;
   const bool fwd = out != UCCL_NO_FORWARD;
@@ -1268,7 +1272,7 @@ __device__ __forceinline__ void ordered_gather_part(const GatherArgs& g, uint32_
   const uint32_t vecs = (len >> 4) + ((len & 15u) != 0u ? 1u : 0u);
   const uint32_t total = (vecs + kUnit - 1u) / kUnit;
   for (uint32_t u = part * kWaves + wave; u < total; u += g.parts * kWaves)
-    gather_unit<1, kThroughOnce, Op>(g, d->dst_off, d->out_off, len, d->n_src, d->src_off, u * kUnit, lane);
+    gather_unit<1, kThrough, Op>(g, d->dst_off, d->out_off, len, d->n_src, d->src_off, u * kUnit, lane);
 }
 
 template <class Op>
