@@ -670,8 +670,12 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
       if (p.tile >= 4) return launch_flat<4, UCCL_FLAT_UNROLL, Op>(a, s);
       return launch_flat<2, UCCL_FLAT_UNROLL, Op>(a, s);
     default: {
-      constexpr int kUnroll = Op::kReadsAcc ? UCCL_FLAT1_REDUCE_UNROLL : UCCL_FLAT_UNROLL;
-      return Op::kReadsAcc && in_lines(tune) ? launch_flat<1, kUnroll, Op, kAllButCombined>(a, s) : launch_flat<1, kUnroll, Op>(a, s);
+      if constexpr (Op::kReadsAcc) {
+        if (in_lines(tune)) return launch_flat<1, UCCL_FLAT1_REDUCE_UNROLL, Op, kAllButCombined>(a, s);
+        return launch_flat<1, UCCL_FLAT1_REDUCE_UNROLL, Op>(a, s);
+      } else {
+        return launch_flat<1, UCCL_FLAT_UNROLL, Op>(a, s);
+      }
     }
   }
 }

@@ -766,7 +766,7 @@ __device__ __forceinline__ GroupPlace group_place(const ClaimArgs& g) {
   return p;
 }
 
-template <int NT, int U, class Op, bool PART_MAJOR, Through H = kAllThrough>
+template <int NT, int U, class Op, bool PART_MAJOR, Through H>
 __global__ void __launch_bounds__(NT) UCCL_FULL_OCCUPANCY chunk_group_kernel(const Args g) {
   constexpr uint32_t kUnit = 64u * U;
   constexpr uint32_t kWaves = NT / 64;

@@ -44,8 +44,8 @@ extern "C" int UCCL_PROBE(uccl_probe_group_apply)(void* acc, void* out, const vo
       !probe_args<Args, uccl_chunk_desc>(a, acc, out, recv, descs, n, bitmap, n_bits, rejected, parts, words, tag))
     return -1;
   using Sum = OpF32<kSum>;
-  const auto kernel = unroll == 1u ? (part_major ? chunk_group_kernel<256, 1, Sum, true> : chunk_group_kernel<256, 1, Sum, false>)
-                                   : (part_major ? chunk_group_kernel<256, 4, Sum, true> : chunk_group_kernel<256, 4, Sum, false>);
+  const auto kernel = unroll == 1u ? (part_major ? chunk_group_kernel<256, 1, Sum, true, kNoThrough> : chunk_group_kernel<256, 1, Sum, false, kAllThrough>)
+                                   : (part_major ? chunk_group_kernel<256, 4, Sum, true, kNoThrough> : chunk_group_kernel<256, 4, Sum, false, kAllThrough>);
   kernel<<<dim3(n * parts), dim3(256), 0, static_cast<hipStream_t>(stream)>>>(a);
   return launched();
 }

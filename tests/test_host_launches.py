@@ -57,10 +57,10 @@ class Runtime:
         a = self.answer.get(name, 0)
         return a(subject or 0) if callable(a) else a
 
-    def apply(self, n, chunk=None, stream=0, op=0, parts=0):
+    def apply(self, n, chunk=None, stream=0, op=0, parts=0, dtype=0):
         if chunk is None:
-            return self.lib.uccl_chunk_apply(A, OUT, RECV, DESCS, n, BITS, 0, op, stream)
-        return self.lib.uccl_chunk_apply_opts(A, OUT, RECV, DESCS, n, BITS, 0, op, None, None, C.byref(pkg.uccl_launch_opts(chunk, parts)), stream)
+            return self.lib.uccl_chunk_apply(A, OUT, RECV, DESCS, n, BITS, dtype, op, stream)
+        return self.lib.uccl_chunk_apply_opts(A, OUT, RECV, DESCS, n, BITS, dtype, op, None, None, C.byref(pkg.uccl_launch_opts(chunk, parts)), stream)
 
     def fold(self, n, chunk, stream=0):
         return self.lib.uccl_chunk_reduce_gather(A, OUT, RECV, DESCS, n, BITS, 0, 0, None, None, C.byref(pkg.uccl_launch_opts(chunk, 0)), stream)
@@ -96,6 +96,24 @@ def stores_of_cut_calls(rt):
 def test_cut_calls_write_through_where_they_are_small_or_in_whole_lines(tmp_path):
     """Large chunks that share lines lose by it, up to 1.2 times: stated, the host sees it; not stated, the kernel looks at each record."""
     in_process("stores_of_cut_calls", tmp_path)
+
+
+def stores_of_the_shapes(rt):
+    """The table of calls that are run on a GPU for their stores: each gets the kernel that it is there for."""
+    import through_shapes as t
+    for n, chunk, stated, name, of_sum, of_copy in t.APPLY:
+        for op, kernel, mangled in ((pkg.UCCL_SUM, of_sum, "NS_5OpI32ILi0EEE"), (pkg.UCCL_SUM, of_sum, "NS_4Op16ILi0ENS_9WidenBF16EEE"), (pkg.UCCL_COPY, of_copy, "NS_4CopyE")):
+            rt.symbols.clear()
+            assert rt.apply(n, chunk if stated else None, op=op, dtype=pkg.UCCL_BF16 if "BF16" in mangled else pkg.UCCL_I32) == pkg.UCCL_OK
+            assert kernel.format(op=mangled) in rt.symbols[-1], (name, rt.symbols)
+    for n, chunk, name, kernel in t.FOLD:
+        rt.symbols.clear()
+        assert rt.fold(n, chunk) == pkg.UCCL_OK
+        assert kernel.format(op="NS_5OpF32ILi0EEE") in rt.symbols[-1], (name, rt.symbols)
+
+
+def test_calls_run_for_their_stores_get_the_kernels_they_are_for(tmp_path):
+    in_process("stores_of_the_shapes", tmp_path)
 
 
 def refused_counts(rt):
