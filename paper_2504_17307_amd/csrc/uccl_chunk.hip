@@ -255,6 +255,13 @@ int launch_flat(const Args& a, hipStream_t s) {
   return launch_kernel(chunk_flat_kernel<UCCL_FLAT_THREADS, T, U, Op, H>, tiles, UCCL_FLAT_THREADS, s, a);
 }
 
+template <class Op, Through H>
+int launch_tiles(const Args& a, hipStream_t s, uint32_t tile) {
+  if (tile >= 8) return launch_flat<8, UCCL_FLAT_UNROLL, Op, H>(a, s);
+  if (tile >= 4) return launch_flat<4, UCCL_FLAT_UNROLL, Op, H>(a, s);
+  return launch_flat<2, UCCL_FLAT_UNROLL, Op, H>(a, s);
+}
+
 // Records per workgroup: enough that a tile holds about 32 KiB of payload per stream when the
 // chunk size is known, otherwise grown with the record count.
 uint32_t flat_tile(uint32_t n_descs, uint32_t chunk_bytes) {
@@ -534,16 +541,20 @@ uint32_t group_gather_parts(uint32_t n_descs, const Tuning& tune) {
 //     chunks 18.2 / 16.8, 16 MiB 27.8 / 26.9, 32 MiB 43.7 / 43.8, 64 MiB 71.6 / 75.0, 128 MiB 140 / 154.  Of unknown size, chosen by record in the
 //     kernel: 64 MiB in 1 MiB chunks 74.4 / 69.9, in chunks of 1 MiB and 16 bytes 79.2 / 78.3 (all written through 90.6)
 //   tiles and single records (chunk_flat_kernel), the combined accumulator as before: 128 messages in 4 KiB chunks 56.5 / 55.7, 60 MiB in 4 KiB 74.0 / 73.1, odd
-//     75.3 / 75.0, 80 MiB in 32 KiB 50.3 / 49.6; not the copies of a record a workgroup, which were not measured by themselves
-//   a workgroup a record: all-to-all in 16 KiB chunks 23.9 / 23.1, 38 MiB in 32 KiB odd 52.0 / 48.5, 60 MiB odd 71.0 / 76.8; 33 008 bytes 52.9 / 55.3;
-//     all-to-all of 9 008 19.2 / 20.7
+//     75.3 / 75.0, 80 MiB in 32 KiB 50.3 / 49.6; not the copies of a record a workgroup, which were not measured by themselves.  Copies that forward nothing, to 96 MiB:
+//     all-to-all of 25 MiB in 4 KiB chunks 17.1 / 16.8, odd 17.3 / 17.0, 75 MiB 33.4 / 30.4, odd 34.8 / 31.1, 100 MiB 43.2 / 42.2, odd 44.6 / 44.5, 125 MiB 52.2 / 52.9, odd 54.3 / 58.9, 200 MiB 80.4 / 81.6,
+//     odd 85.1 / 97.5, in 8 KiB 80.6 / 81.1, odd 83.3 / 96.4; those that are forwarded at any size: copy phase of 256 MiB 126.1 / 117.2, odd 131.1 / 126.6
+//   a workgroup a record, no staging, to 96 MiB: all-to-all in 16 KiB chunks 23.9 / 23.1, 75 MiB 30.1 / 28.0, odd 30.5 / 28.6, 88 MiB odd 35.1 / 32.4, 107 MiB 41.3 / 42.5, odd 41.8 / 46.1, 57 MiB in 32 KiB
+//     odd 25.0 / 21.7; 33 008 bytes 52.9 / 55.3, 9 008 19.2 / 20.7.  With staging to 40 MiB: 38 MiB in 32 KiB odd 52.0 / 48.5, 60 MiB odd 71.0 / 76.8 (on lines 64 MiB would gain, 70.4 / 66.6)
 //   decided 64 at a time: 8 x 1 MiB messages in 4 KiB chunks 27.9 / 24.9, 6 000 bytes 12 MiB 21.5 / 20.9, 30 000 bytes 22 MiB 34.3 / 35.4.  Of unknown
 //     size 3.6 MB 13.3 / 12.1 and 33 MB 35.5 / 34.6, but 60 MB in 98 256-byte chunks 41.1 / 44.3: not taken.
 //   in destination order, by record: 256 MiB bf16 262 / 256, 1 GiB 554 / 549, 100 MiB in 64 KiB 104 / 101, odd 256 MiB 260 / 260;
 //     not copies that forward nothing (all-to-all of 32 MiB in 64 KiB 38.9 / 39.5)
 bool in_lines(const Tuning& tune) { return tune.chunk_bytes != 0u && tune.chunk_bytes % 128u == 0u; }
-bool few_through(const Args& a, const Tuning& tune) {   // a workgroup a record; one written stream (no staging) at any size
-  return in_lines(tune) && (a.out == nullptr || static_cast<uint64_t>(a.n_descs) * tune.chunk_bytes <= (40ull << 20));
+uint64_t payload(const Args& a, const Tuning& tune) { return static_cast<uint64_t>(a.n_descs) * tune.chunk_bytes; }
+constexpr uint64_t kLinesBytes = 96ull << 20;
+bool few_through(const Args& a, const Tuning& tune) {   // a workgroup a record
+  return in_lines(tune) && payload(a, tune) <= (a.out == nullptr ? kLinesBytes : 40ull << 20);
 }
 bool lines_or_small(const Args& a, const Tuning& tune) {   // decided 64 at a time, cut into parts
   return tune.chunk_bytes != 0u && (in_lines(tune) || static_cast<uint64_t>(a.n_descs) * tune.chunk_bytes <= kThroughBytes);
@@ -661,14 +672,11 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
     case kRouteTile:
       if (p.tile >= 32) return launch_flat<32, UCCL_FLAT_UNROLL, Op>(a, s);
       if (p.tile >= 16) return launch_flat<16, UCCL_FLAT_UNROLL, Op>(a, s);
-      if (in_lines(tune)) {
-        if (p.tile >= 8) return launch_flat<8, UCCL_FLAT_UNROLL, Op, kAllButCombined>(a, s);
-        if (p.tile >= 4) return launch_flat<4, UCCL_FLAT_UNROLL, Op, kAllButCombined>(a, s);
-        return launch_flat<2, UCCL_FLAT_UNROLL, Op, kAllButCombined>(a, s);
+      if (!in_lines(tune)) return launch_tiles<Op, kNoThrough>(a, s, p.tile);
+      if constexpr (!Op::kReadsAcc) {
+        if (payload(a, tune) > kLinesBytes) return launch_tiles<Op, kForwarded>(a, s, p.tile);
       }
-      if (p.tile >= 8) return launch_flat<8, UCCL_FLAT_UNROLL, Op>(a, s);
-      if (p.tile >= 4) return launch_flat<4, UCCL_FLAT_UNROLL, Op>(a, s);
-      return launch_flat<2, UCCL_FLAT_UNROLL, Op>(a, s);
+      return launch_tiles<Op, kAllButCombined>(a, s, p.tile);
     default: {
       if constexpr (Op::kReadsAcc) {
         if (in_lines(tune)) return launch_flat<1, UCCL_FLAT1_REDUCE_UNROLL, Op, kAllButCombined>(a, s);

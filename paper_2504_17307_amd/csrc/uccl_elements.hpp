@@ -205,13 +205,17 @@ constexpr uint32_t cache_policy() {
 // accumulator too the step of 256 MiB takes 283: the copy phase no longer finds it in the last-level cache.
 // A line that two wavefronts write each a part of goes to memory twice, so where chunks do not begin on a line it does
 // not pay once they are no longer in the last-level cache (64 MiB in 8 944-byte chunks 78 / 87, 20 000 282 / 297).
-enum Through { kNoThrough, kAllThrough, kAllButCombined, kByRecord };   // by record: none or both, chosen in the kernel
+enum Through {
+  kNoThrough, kAllThrough, kAllButCombined,
+  kByRecord,    // none or both, chosen in the kernel
+  kForwarded    // copies: both where the record is forwarded, else none
+};
 template <Through T>
 using Stores = std::integral_constant<Through, T>;
 constexpr uint64_t kThroughBytes = 16ull << 20;   // calls of this much payload write through whether their chunks are whole lines or not
 template <class Op, bool FWD, bool WB, Through T>
 constexpr uint32_t acc_store() {
-  if (T == kAllThrough || (T == kAllButCombined && !Op::kReadsAcc)) return kThrough;
+  if (T == kAllThrough || (T == kAllButCombined && !Op::kReadsAcc) || (T == kForwarded && FWD)) return kThrough;
   return (cache_policy<Op, FWD, WB>() & 1u) != 0u ? kOnce : kCached;
 }
 template <class Op, bool FWD, bool WB, Through T>

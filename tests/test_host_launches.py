@@ -57,10 +57,10 @@ class Runtime:
         a = self.answer.get(name, 0)
         return a(subject or 0) if callable(a) else a
 
-    def apply(self, n, chunk=None, stream=0, op=0, parts=0, dtype=0):
+    def apply(self, n, chunk=None, stream=0, op=0, parts=0, dtype=0, out=OUT):
         if chunk is None:
-            return self.lib.uccl_chunk_apply(A, OUT, RECV, DESCS, n, BITS, dtype, op, stream)
-        return self.lib.uccl_chunk_apply_opts(A, OUT, RECV, DESCS, n, BITS, dtype, op, None, None, C.byref(pkg.uccl_launch_opts(chunk, parts)), stream)
+            return self.lib.uccl_chunk_apply(A, out, RECV, DESCS, n, BITS, dtype, op, stream)
+        return self.lib.uccl_chunk_apply_opts(A, out, RECV, DESCS, n, BITS, dtype, op, None, None, C.byref(pkg.uccl_launch_opts(chunk, parts)), stream)
 
     def fold(self, n, chunk, stream=0):
         return self.lib.uccl_chunk_reduce_gather(A, OUT, RECV, DESCS, n, BITS, 0, 0, None, None, C.byref(pkg.uccl_launch_opts(chunk, 0)), stream)
@@ -105,7 +105,7 @@ def stores_of_the_shapes(rt):
         for op, kernel, mangled in ((pkg.UCCL_SUM, of_sum, "NS_5OpI32ILi0EEE"), (pkg.UCCL_SUM, of_sum, "NS_4Op16ILi0ENS_9WidenBF16EEE"), (pkg.UCCL_COPY, of_copy, "NS_4CopyE")):
             rt.symbols.clear()
             assert rt.apply(n, chunk if stated else None, op=op, dtype=pkg.UCCL_BF16 if "BF16" in mangled else pkg.UCCL_I32) == pkg.UCCL_OK
-            assert kernel.format(op=mangled) in rt.symbols[-1], (name, rt.symbols)
+            assert kernel is None or kernel.format(op=mangled) in rt.symbols[-1], (name, rt.symbols)
     for n, chunk, name, kernel in t.FOLD:
         rt.symbols.clear()
         assert rt.fold(n, chunk) == pkg.UCCL_OK
@@ -114,6 +114,21 @@ def stores_of_the_shapes(rt):
 
 def test_calls_run_for_their_stores_get_the_kernels_they_are_for(tmp_path):
     in_process("stores_of_the_shapes", tmp_path)
+
+
+def stores_of_large_copies(rt):
+    import through_shapes as t
+    for n, chunk, out, kernel in ((24576, 4 * KiB, None, t.flat(8, 2, t.BUT_COMBINED)), (24577, 4 * KiB, None, t.flat(8, 2, t.FORWARDED)), (12289, 8 * KiB, OUT, t.flat(4, 2, t.FORWARDED)),
+                                  (8192, 12 * KiB + 128, None, t.flat(2, 2, t.FORWARDED)), (6144, 16 * KiB, None, t.few(1024, 1, t.ALL, False)), (6145, 16 * KiB, None, t.few(1024, 1, t.NONE, False)),
+                                  (2561, 16 * KiB, OUT, t.few(1024, 1, t.NONE, False))):
+        rt.symbols.clear()
+        assert rt.apply(n, chunk, op=pkg.UCCL_COPY, out=out) == pkg.UCCL_OK
+        assert kernel.format(op="NS_4CopyE") in rt.symbols[-1], (n, chunk, rt.symbols)
+
+
+def test_large_copies_that_forward_nothing_keep_the_former_stores(tmp_path):
+    """Above 96 MiB what lines are shared costs more than writing through gives, up to 1.16 times."""
+    in_process("stores_of_large_copies", tmp_path)
 
 
 def refused_counts(rt):

@@ -1,6 +1,6 @@
 """Calls whose stores are written through: the smallest that get each launch, and which kernel (its template arguments) that is.
 tests/test_host_launches.py holds the table against what the library launches, tests/test_gpu_written_through.py runs it."""
-NONE, ALL, BUT_COMBINED, BY_RECORD = range(4)   # the library's Through
+NONE, ALL, BUT_COMBINED, BY_RECORD, FORWARDED = range(5)   # the library's Through
 
 
 def few(threads, unroll, stores, parts):
@@ -32,7 +32,8 @@ APPLY = [(57, 65536, True, "parts", few(256, 2, ALL, True), few(256, 2, ALL, Tru
          (300, 65536, True, "group of four", group(4, ALL), group(4, ALL)),
          (3200, 4096, True, "tiles of eight", flat(8, 2, BUT_COMBINED), flat(8, 2, BUT_COMBINED)),
          (3200, 8192, True, "tiles of four", flat(4, 2, BUT_COMBINED), flat(4, 2, BUT_COMBINED)),
-         (8200, 12288, True, "tiles of two", flat(2, 2, BUT_COMBINED), flat(2, 2, BUT_COMBINED)),
+         (8192, 12288, True, "tiles of two", flat(2, 2, BUT_COMBINED), flat(2, 2, BUT_COMBINED)),
+         (8200, 12288, True, "large tiles of two", None, flat(2, 2, FORWARDED)),
          (2100, 40960, True, "one record a tile", flat(1, 1, BUT_COMBINED), flat(1, 2, NONE)),
          (800, 131072, True, "ordered", ordered(ALL), ordered(ALL))]
 # records, chunk bytes, name, kernel of SUM
