@@ -543,7 +543,8 @@ uint32_t group_gather_parts(uint32_t n_descs, const Tuning& tune) {
 //   tiles and single records (chunk_flat_kernel), the combined accumulator as before: 128 messages in 4 KiB chunks 56.5 / 55.7, 60 MiB in 4 KiB 74.0 / 73.1, odd
 //     75.3 / 75.0, 80 MiB in 32 KiB 50.3 / 49.6; not the copies of a record a workgroup, which were not measured by themselves.  Copies that forward nothing, to 96 MiB:
 //     all-to-all of 25 MiB in 4 KiB chunks 17.1 / 16.8, odd 17.3 / 17.0, 75 MiB 33.4 / 30.4, odd 34.8 / 31.1, 100 MiB 43.2 / 42.2, odd 44.6 / 44.5, 125 MiB 52.2 / 52.9, odd 54.3 / 58.9, 200 MiB 80.4 / 81.6,
-//     odd 85.1 / 97.5, in 8 KiB 80.6 / 81.1, odd 83.3 / 96.4; those that are forwarded at any size: copy phase of 256 MiB 126.1 / 117.2, odd 131.1 / 126.6
+//     odd 85.1 / 97.5, in 8 KiB 80.6 / 81.1, odd 83.3 / 96.4; those that are forwarded at any size: copy phase of 256 MiB 126.1 / 117.2, odd 131.1 / 126.6.
+//     Combinations of 32-bit types to 96 MiB as well: reduce-scatter of 150 MiB 97.8 / 98.8, 256 MiB 159.9 / 161.3, odd 162.5 / 163.3, of bf16 164.5 / 161.8, in 8 KiB chunks 168.5 / 166.7
 //   a workgroup a record, no staging, to 96 MiB: all-to-all in 16 KiB chunks 23.9 / 23.1, 75 MiB 30.1 / 28.0, odd 30.5 / 28.6, 88 MiB odd 35.1 / 32.4, 107 MiB 41.3 / 42.5, odd 41.8 / 46.1, 57 MiB in 32 KiB
 //     odd 25.0 / 21.7; 33 008 bytes 52.9 / 55.3, 9 008 19.2 / 20.7.  With staging to 40 MiB: 38 MiB in 32 KiB odd 52.0 / 48.5, 60 MiB odd 71.0 / 76.8 (on lines 64 MiB would gain, 70.4 / 66.6)
 //   decided 64 at a time: 8 x 1 MiB messages in 4 KiB chunks 27.9 / 24.9, 6 000 bytes 12 MiB 21.5 / 20.9, 30 000 bytes 22 MiB 34.3 / 35.4.  Of unknown
@@ -673,9 +674,7 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
       if (p.tile >= 32) return launch_flat<32, UCCL_FLAT_UNROLL, Op>(a, s);
       if (p.tile >= 16) return launch_flat<16, UCCL_FLAT_UNROLL, Op>(a, s);
       if (!in_lines(tune)) return launch_tiles<Op, kNoThrough>(a, s, p.tile);
-      if constexpr (!Op::kReadsAcc) {
-        if (payload(a, tune) > kLinesBytes) return launch_tiles<Op, kForwarded>(a, s, p.tile);
-      }
+      if (payload(a, tune) > kLinesBytes) return launch_tiles<Op, !Op::kReadsAcc ? kForwarded : Op::kEs == 4 ? kNoThrough : kAllButCombined>(a, s, p.tile);
       return launch_tiles<Op, kAllButCombined>(a, s, p.tile);
     default: {
       if constexpr (Op::kReadsAcc) {

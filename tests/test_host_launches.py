@@ -131,6 +131,19 @@ def test_large_copies_that_forward_nothing_keep_the_former_stores(tmp_path):
     in_process("stores_of_large_copies", tmp_path)
 
 
+def stores_of_large_sums(rt):
+    import through_shapes as t
+    for n, dtype, mangled, stores in ((24576, pkg.UCCL_F32, "NS_5OpF32ILi0EEE", t.BUT_COMBINED), (24577, pkg.UCCL_F32, "NS_5OpF32ILi0EEE", t.NONE), (24577, pkg.UCCL_I32, "NS_5OpI32ILi0EEE", t.NONE),
+                                      (24577, pkg.UCCL_BF16, "NS_4Op16ILi0ENS_9WidenBF16EEE", t.BUT_COMBINED)):
+        rt.symbols.clear()
+        assert rt.apply(n, 4 * KiB, dtype=dtype) == pkg.UCCL_OK
+        assert t.flat(8, 2, stores).format(op=mangled) in rt.symbols[-1], (n, rt.symbols)
+
+
+def test_large_tiles_of_32_bit_sums_keep_the_former_stores(tmp_path):
+    in_process("stores_of_large_sums", tmp_path)
+
+
 def refused_counts(rt):
     for n, chunk in ((2 ** 32 - 1, 32 * KiB), (2 ** 32 - 1, 16 * KiB), (2 ** 32 - 1, 128 * KiB), (1 << 23, 128 * KiB), ((1 << 22) + 1, 32 * KiB)):
         assert rt.apply(n, chunk) == pkg.UCCL_ELAUNCH and rt.fold(n, chunk) == pkg.UCCL_ELAUNCH, (n, chunk)
