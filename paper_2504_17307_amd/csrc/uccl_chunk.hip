@@ -537,9 +537,10 @@ uint32_t group_gather_parts(uint32_t n_descs, const Tuning& tune) {
 // Which stores a call's kernel writes through (see Through).  Lines: chunks of whole lines of 128 bytes.  Two chunks share a line where
 // they are no such multiple, or their segment does not begin on one, which the host cannot see; what is shared costs more than writing through
 // gives once the call has left the last-level cache.  Measured, us a pass, as the masks say / through; "odd": segments that begin off a line:
-//   cut into parts, ring of 4 MiB in 64 KiB chunks 11.1 / 9.9, 32 MiB 41.4 / 39.5, odd 41.5 / 39.9, 64 MiB 67.9 / 65.2, 128 MiB 130.4 / 130.3; off lines 8 MiB in 66 000-byte
+//   cut into parts, ring of 4 MiB in 64 KiB chunks 11.1 / 9.9, 32 MiB 41.4 / 39.5, odd 41.5 / 39.9, 64 MiB 67.9 / 65.2, 100 MiB (a call has 7 / 8 of it)
+//     100.4 / 98.3, odd 101.5 / 99.8, 128 MiB 133.5 / 134.9, odd 134.7 / 136.5; off lines 8 MiB in 66 000-byte
 //     chunks 18.2 / 16.8, 16 MiB 27.8 / 26.9, 32 MiB 43.7 / 43.8, 64 MiB 71.6 / 75.0, 128 MiB 140 / 154.  Of unknown size, chosen by record in the
-//     kernel: 64 MiB in 1 MiB chunks 74.4 / 69.9, in chunks of 1 MiB and 16 bytes 79.2 / 78.3 (all written through 90.6)
+//     kernel: 64 MiB in 1 MiB chunks 74.4 / 69.9, 240 MiB in 2 MiB 286 / 283, in chunks of 1 MiB and 16 bytes 79.2 / 78.3 (all written through 90.6)
 //   tiles and single records (chunk_flat_kernel), the combined accumulator as before: 128 messages in 4 KiB chunks 56.5 / 55.7, 60 MiB in 4 KiB 74.0 / 73.1, odd
 //     75.3 / 75.0, 80 MiB in 32 KiB 50.3 / 49.6; not the copies of a record a workgroup, which were not measured by themselves.  Copies that forward nothing, to 96 MiB:
 //     all-to-all of 25 MiB in 4 KiB chunks 17.1 / 16.8, odd 17.3 / 17.0, 75 MiB 33.4 / 30.4, odd 34.8 / 31.1, 100 MiB 43.2 / 42.2, odd 44.6 / 44.5, 125 MiB 52.2 / 52.9, odd 54.3 / 58.9, 200 MiB 80.4 / 81.6,
@@ -558,7 +559,7 @@ bool few_through(const Args& a, const Tuning& tune) {   // a workgroup a record
   return in_lines(tune) && payload(a, tune) <= (a.out == nullptr ? kLinesBytes : 40ull << 20);
 }
 bool lines_or_small(const Args& a, const Tuning& tune) {   // decided 64 at a time, cut into parts
-  return tune.chunk_bytes != 0u && (in_lines(tune) || static_cast<uint64_t>(a.n_descs) * tune.chunk_bytes <= kThroughBytes);
+  return tune.chunk_bytes != 0u && payload(a, tune) <= (in_lines(tune) ? kLinesBytes : kThroughBytes);
 }
 
 // `region`: the stream's scratch words; called with its launch lock held.  HIP has no reason of its

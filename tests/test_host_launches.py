@@ -86,7 +86,7 @@ def in_process(scenario, tmp_path):
 
 def stores_of_cut_calls(rt):
     none, through, by_record = (f"chunk_few_kernelILi256ELi2ENS_5OpF32ILi0EEELNS_7ThroughE{k}ELb1ELb0" for k in (0, 1, 3))
-    for n, chunk, parts, stores in ((57, 64 * KiB, 0, through), (254, 66000, 0, through), (254, 66000, 8, through), (255, 66000, 8, none), (1000, 66000, 8, none), (1000, 64 * KiB, 8, through),
+    for n, chunk, parts, stores in ((57, 64 * KiB, 0, through), (254, 66000, 0, through), (254, 66000, 8, through), (255, 66000, 8, none), (1000, 66000, 8, none), (1000, 64 * KiB, 8, through), (1536, 64 * KiB, 8, through), (1537, 64 * KiB, 8, none),
                                     (2048, 128 * KiB + 16, 16, none), (300, 40016, 2, through), (64, None, 0, by_record), (128, None, 0, by_record), (500, 0, 8, by_record)):
         rt.symbols.clear()
         assert rt.apply(n, chunk, parts=parts) == pkg.UCCL_OK
