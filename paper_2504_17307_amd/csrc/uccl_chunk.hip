@@ -553,13 +553,17 @@ uint32_t group_gather_parts(uint32_t n_descs, const Tuning& tune) {
 //   in destination order, by record: 256 MiB bf16 262 / 256, 1 GiB 554 / 549, 100 MiB in 64 KiB 104 / 101, odd 256 MiB 260 / 260;
 //     not copies that forward nothing (all-to-all of 32 MiB in 64 KiB 38.9 / 39.5)
 bool in_lines(const Tuning& tune) { return tune.chunk_bytes != 0u && tune.chunk_bytes % 128u == 0u; }
-uint64_t payload(const Args& a, const Tuning& tune) { return static_cast<uint64_t>(a.n_descs) * tune.chunk_bytes; }
+template <class KernelArgs>
+uint64_t payload(const KernelArgs& a, const Tuning& tune) { return static_cast<uint64_t>(a.n_descs) * tune.chunk_bytes; }
 constexpr uint64_t kLinesBytes = 96ull << 20;
 bool few_through(const Args& a, const Tuning& tune) {   // a workgroup a record
   return in_lines(tune) && payload(a, tune) <= (a.out == nullptr ? kLinesBytes : 40ull << 20);
 }
 bool lines_or_small(const Args& a, const Tuning& tune) {   // decided 64 at a time, cut into parts
   return tune.chunk_bytes != 0u && payload(a, tune) <= (in_lines(tune) ? kLinesBytes : kThroughBytes);
+}
+bool gather_through(const GatherArgs& a, const Tuning& tune) {   // folds in tiles; see gather_store
+  return tune.chunk_bytes % 128u == 0u || payload(a, tune) <= (72ull << 20);
 }
 
 // `region`: the stream's scratch words; called with its launch lock held.  HIP has no reason of its
@@ -688,9 +692,16 @@ int launch_flat_tile(Args& a, hipStream_t s, const Tuning& tune) {
   }
 }
 
-template <int T, class Op>
+template <int T, class Op, Store ACC>
 int launch_gather(const GatherArgs& a, hipStream_t s) {
-  return launch_kernel(chunk_gather_kernel<1024, T, UCCL_GATHER_UNROLL, Op>, tiles_for(a.n_descs, T), 1024, s, a);
+  return launch_kernel(chunk_gather_kernel<1024, T, UCCL_GATHER_UNROLL, Op, ACC>, tiles_for(a.n_descs, T), 1024, s, a);
+}
+template <class Op, Store ACC>
+int launch_gather_tiles(const GatherArgs& a, hipStream_t s, uint32_t tile) {
+  if (tile >= 16) return launch_gather<16, Op, ACC>(a, s);
+  if (tile >= 8) return launch_gather<8, Op, ACC>(a, s);
+  if (tile >= 4) return launch_gather<4, Op, ACC>(a, s);
+  return launch_gather<2, Op, ACC>(a, s);
 }
 
 // Workgroups per multi-source record for a call of few of them.  A record moves n + 2 streams of its
@@ -765,13 +776,8 @@ int launch_gather_tile(GatherArgs& a, hipStream_t s, const Tuning& tune) {
     }
     p = plan_gather_uncut(a.n_descs, tune);   // no claim words to be had
   }
-  if (p.route == kRouteTile) {
-    if (p.tile >= 16) return launch_gather<16, Op>(a, s);
-    if (p.tile >= 8) return launch_gather<8, Op>(a, s);
-    if (p.tile >= 4) return launch_gather<4, Op>(a, s);
-    return launch_gather<2, Op>(a, s);
-  }
-  return launch_gather<1, Op>(a, s);
+  if (p.route != kRouteTile) return launch_gather<1, Op, kThrough>(a, s);
+  return gather_through(a, tune) ? launch_gather_tiles<Op, kThrough>(a, s, p.tile) : launch_gather_tiles<Op, kCached>(a, s, p.tile);
 }
 
 bool misaligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) != 0; }

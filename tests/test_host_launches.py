@@ -144,6 +144,17 @@ def test_large_tiles_of_32_bit_sums_keep_the_former_stores(tmp_path):
     in_process("stores_of_large_sums", tmp_path)
 
 
+def stores_of_folds_in_tiles(rt):
+    for n, chunk, tile, stores in ((16384, 4 * KiB, 8, 17), (65536, 4 * KiB, 8, 17), (8381, 9008, 4, 17), (8382, 9008, 4, 0), (12583, 6000, 4, 0), (600, 66000, 1, 17), (8192, 0, 4, 17)):
+        rt.symbols.clear()
+        assert rt.fold(n, chunk) == pkg.UCCL_OK
+        assert f"chunk_gather_kernelILi1024ELi{tile}ELi2ENS_5OpF32ILi0EEELNS_5StoreE{stores}EE" in rt.symbols[-1], (n, chunk, rt.symbols)
+
+
+def test_large_folds_of_chunks_that_share_lines_keep_the_default_policy(tmp_path):
+    in_process("stores_of_folds_in_tiles", tmp_path)
+
+
 def refused_counts(rt):
     for n, chunk in ((2 ** 32 - 1, 32 * KiB), (2 ** 32 - 1, 16 * KiB), (2 ** 32 - 1, 128 * KiB), (1 << 23, 128 * KiB), ((1 << 22) + 1, 32 * KiB)):
         assert rt.apply(n, chunk) == pkg.UCCL_ELAUNCH and rt.fold(n, chunk) == pkg.UCCL_ELAUNCH, (n, chunk)

@@ -38,6 +38,7 @@ APPLY = [(57, 65536, True, "parts", few(256, 2, ALL, True), few(256, 2, ALL, Tru
          (800, 131072, True, "ordered", ordered(ALL), ordered(ALL))]
 # records, chunk bytes, name, kernel of SUM
 FOLD = [(400, 4096, "group", "gather_group_kernelI{op}Lb0EE"),
-        (3100, 4096, "tiles of eight", "chunk_gather_kernelILi1024ELi8ELi2E{op}E"),
-        (600, 65536, "one record a tile", "chunk_gather_kernelILi1024ELi1ELi2E{op}E"),
+        (3100, 4096, "tiles of eight", "chunk_gather_kernelILi1024ELi8ELi2E{op}LNS_5StoreE17EE"),
+        (8400, 9008, "large tiles off lines", "chunk_gather_kernelILi1024ELi4ELi2E{op}LNS_5StoreE0EE"),
+        (600, 65536, "one record a tile", "chunk_gather_kernelILi1024ELi1ELi2E{op}LNS_5StoreE17EE"),
         (800, 131072, "ordered", "gather_ordered_kernelI{op}E")]
