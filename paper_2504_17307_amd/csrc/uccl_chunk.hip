@@ -551,7 +551,8 @@ uint32_t group_gather_parts(uint32_t n_descs, const Tuning& tune) {
 //   decided 64 at a time: 8 x 1 MiB messages in 4 KiB chunks 27.9 / 24.9, 6 000 bytes 12 MiB 21.5 / 20.9, 30 000 bytes 22 MiB 34.3 / 35.4.  Of unknown
 //     size 3.6 MB 13.3 / 12.1 and 33 MB 35.5 / 34.6, but 60 MB in 98 256-byte chunks 41.1 / 44.3: not taken.
 //   in destination order, by record: 256 MiB bf16 262 / 256, 1 GiB 554 / 549, 100 MiB in 64 KiB 104 / 101, odd 256 MiB 260 / 260;
-//     not copies that forward nothing (all-to-all of 32 MiB in 64 KiB 38.9 / 39.5)
+//     not copies without staging (all-to-all of 32 MiB in 64 KiB 38.9 / 39.5, where runs differ by 0.5).  With staging those of two ranks, which forward nothing, lose too (200 MiB in 64 KiB
+//     70.0 / 71.2), but looking at each record for it costs the step of 256 MiB 254.8 / 256.2.  Records of unknown size are not written through: not measured
 bool in_lines(const Tuning& tune) { return tune.chunk_bytes != 0u && tune.chunk_bytes % 128u == 0u; }
 template <class KernelArgs>
 uint64_t payload(const KernelArgs& a, const Tuning& tune) { return static_cast<uint64_t>(a.n_descs) * tune.chunk_bytes; }

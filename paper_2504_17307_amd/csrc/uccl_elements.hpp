@@ -198,13 +198,14 @@ constexpr uint32_t cache_policy() {
 
 // Which stores of a chunk are written through: none (the masks above), both, or both but the combined accumulator.
 // Measured, us a pass of the whole ring step or call, as the masks say / through (three sets of buffers):
-//   1 GiB reduce-scatter 559 / 548, 256 MiB bf16 262 / 256, 100 MiB in 64 KiB chunks 104 / 101, 64 MiB in 32 KiB chunks 70.4 / 66.6,
+//   1 GiB reduce-scatter 559 / 548, 256 MiB bf16 262 / 256, 100 MiB in 64 KiB chunks 104 / 101,
 //   4 MiB in parts 10.9 / 10.6, 8 MiB 14.2 / 13.4; all-to-all of 20 MiB a peer 29.2 / 26.9; 14 MB in 4 KB chunks 17.0 / 16.0
 // Tiles of records (4 KiB chunks, 128 messages) lose by it where they combine, 56.5 / 58.5, and gain with the
 // accumulator as before, 55.7.  Reads change nothing (accumulator loaded non-temporally 0.5 % slower).  With the nt bit on the
 // accumulator too the step of 256 MiB takes 283: the copy phase no longer finds it in the last-level cache.
 // A line that two wavefronts write each a part of goes to memory twice, so where chunks do not begin on a line it does
-// not pay once they are no longer in the last-level cache (64 MiB in 8 944-byte chunks 78 / 87, 20 000 282 / 297).
+// not pay once they are no longer in the last-level cache (64 MiB in 8 944-byte chunks 78 / 87, 20 000 282 / 297).  Which
+// launch gets what: few_through, lines_or_small, launch_tiles' callers.
 enum Through {
   kNoThrough, kAllThrough, kAllButCombined,
   kByRecord,    // none or both, chosen in the kernel
