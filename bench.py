@@ -36,11 +36,11 @@ METRIC = "reduced payload GB/s (dedup+place+reduce+forward of one rank's chunk s
 # kernel source it was measured on, identified by the hash of the HIP source files.
 MEASURED_TRAFFIC = {
     # (workload, source_hash() of the files under csrc/): bytes per launch
-    ("config1", "7993dd2079021ab8"): 14883648,
-    ("config2", "7993dd2079021ab8"): 1008443070,
-    ("config3", "7993dd2079021ab8"): 3626221412,
-    ("config4", "7993dd2079021ab8"): 108167032,
-    ("direct-rs", "7993dd2079021ab8"): 1208730106,
+    ("config1", "49ee04448d0fdce9"): 14882216,
+    ("config2", "49ee04448d0fdce9"): 1008463086,
+    ("config3", "49ee04448d0fdce9"): 3626190236,
+    ("config4", "49ee04448d0fdce9"): 108158056,
+    ("direct-rs", "49ee04448d0fdce9"): 1208729184,
 }
 
 WORKLOADS = {

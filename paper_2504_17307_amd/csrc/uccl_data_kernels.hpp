@@ -919,7 +919,7 @@ __device__ __forceinline__ bool gather_sources_ok(const GatherArgs& g, const ucc
 // source j, the same in every lane.  ACC: how the result is stored.  Through, us a pass, default policy / this: tiles 60 MiB
 // in 4 KiB chunks from three sources 62.3 / 58.8, 64 MiB in 9 008-byte ones from two 53.9 / 52.3; decided 64 at a time 20 MiB in 64 KiB chunks from seven 36.8 / 35.5,
 // 30 MiB in 6 000-byte ones 63.3 / 60.7; in destination order 128 MiB in 128 KiB chunks from seven 206 / 197, 100 MiB in 20 000-byte ones from three 104.6 / 99.4.
-// Where a line is two chunks' it goes out twice: tiles of chunks that are no whole lines lose from one source once they have left the last-level cache, 100 MiB in 9 008-byte chunks
+// Where a line is two chunks' it goes out in parts: tiles of chunks that are no whole lines lose from one source once they have left the last-level cache, 100 MiB in 9 008-byte chunks
 // 68.8 / 72.3, 200 MiB 133.5 / 137.4, in 6 000 136.6 / 137.7, in 12 400 134.4 / 135.8, from three 217.7 / 218.2, from seven (100 MiB) 197.9 / 195.0; the host does not know how many there are, so above 72 MiB they keep the
 // default policy.  Of unknown size all is written through, which costs such calls from one source 3 % (200 MiB in 9 008 133.7 / 137.8, 250 MiB in 33 008 176 / 182; 70 MiB 42.9 / 42.0): choosing
 // by the tile's first record in the kernel costs those in whole lines 2 % (200 MiB in 4 KiB chunks 129.9 / 132.3, default 131.2), choosing at the store 12 %.

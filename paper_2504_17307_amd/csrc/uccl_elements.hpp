@@ -203,8 +203,9 @@ constexpr uint32_t cache_policy() {
 // Tiles of records (4 KiB chunks, 128 messages) lose by it where they combine, 56.5 / 58.5, and gain with the
 // accumulator as before, 55.7.  Reads change nothing (accumulator loaded non-temporally 0.5 % slower).  With the nt bit on the
 // accumulator too the step of 256 MiB takes 283: the copy phase no longer finds it in the last-level cache.
-// A line that two wavefronts write each a part of goes to memory twice, so where chunks do not begin on a line it does
-// not pay once they are no longer in the last-level cache (64 MiB in 8 944-byte chunks 78 / 87, 20 000 282 / 297).  Which
+// A line that two wavefronts write each a part of leaves the L2s in parts, so where chunks do not begin on a line it does
+// not pay once they are no longer in the last-level cache (64 MiB in 8 944-byte chunks 78 / 87, 20 000 282 / 297).  It is the time of those
+// partial writes and not their bytes: all-to-all of 200 MiB in 4 KiB chunks off a line 216.1 / 216.8 MB written (on lines 212.7), 85 / 97 us.  Which
 // launch gets what: few_through, lines_or_small, launch_tiles' callers.
 enum Through {
   kNoThrough, kAllThrough, kAllButCombined,
